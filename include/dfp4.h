@@ -169,11 +169,9 @@ int dfp4_dequantize(dfp4_tensor in, void* y, int y_dtype, int64_t ld_elems, void
  * sums run on the int8 matrix cores with int32 accumulation and are exact.
  * Where the block exponents of a tile span at most 12 binades per row the
  * outer sum is exact as well (exponent offsets folded into the int8 operands,
- * one conversion to fp32 at the end); otherwise it is accumulated in fp32,
- * one addition per block.  That slower per-block path also takes every product
- * with K > 16384 and, at its own pace, every product with M <= 64 (few rows);
- * 512 x 128 output tiles whose exponents spread further are computed that way by
- * the workgroup that finds them (dfp4_gemm_declined_tiles counts them).
+ * one conversion to fp32 at the end); output tiles whose exponents spread further,
+ * or whose exact sum could overflow int32, are accumulated in fp32, one addition
+ * per block, by the workgroup that finds them.
  *   A        quantized [M, K]; W quantized [N, K] (both blocked along K)
  *   out      device, [M, N] row-major, leading dimension ldc (elements, N <= ldc < 2^27);
  *            out_dtype DFP4_F32 or DFP4_BF16 (round to nearest even)
@@ -214,15 +212,16 @@ size_t dfp4_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  *                    a copy of the codes and three table words per block, both in the order
  *                    the kernels read them, about 0.9 bytes per element).  A size of 0
  *                    means nothing is prepared for this operand (K > 16384): NULL may be
- *                    passed then.
+ *                    passed then.  An activation of at most 256 rows is not expanded ahead
+ *                    (its products read it as it is); its buffer holds a counter only.
  * dfp4_gemm_prepared multiplies.  The quantized tensors are still passed: paths that do not
  * use the prepared form read them.  a_prepared is written to (arrival counters of tiles
  * whose K is split between workgroups), so one prepared A serves one product at a time:
  * products on one stream are ordered by the stream, products that may overlap in time need
- * their own prepared copy.  Results are bit-identical to dfp4_gemm, except possibly for
- * products with at most 64 rows of A: there both take the exact scheme (one rounding of the
- * exact sum) where the exponents allow it, but dfp4_gemm decides that per 32 x 32 output
- * tile from the tile's own rows, and a tile it cannot take gets one fp32 term per block.
+ * their own prepared copy.  Results are bit-identical to dfp4_gemm wherever both sum
+ * exactly (one rounding of the exact sum); which tiles' exponents spread too far for that is
+ * decided per 512 x 128 outputs here, and for at most 256 rows of A, as in dfp4_gemm, per
+ * tile of the kernel the product's size selects.
  *   workspace   at least dfp4_gemm_prepared_workspace_bytes(M, N, K) bytes (partial tiles
  *               where K is split; 0 for products with many output tiles), 256-byte aligned
  * Limits: ceil(rows / 512) * (K/32 + 1) * 49152 < 2^31 for A, rows * K / 2 < 2^31 for W
@@ -237,8 +236,8 @@ int dfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const voi
 int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const void* w_prepared, void* out,
                         int out_dtype, int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
 /*
- * Diagnostic: number of 512 x 128 output tiles that products on this prepared A ([M, K]) have
- * computed on the per-block fp32 path since it was prepared (exponent spread beyond what the
+ * Diagnostic: number of output tiles (512 x 128; smaller ones for at most 256 rows of A) that
+ * products on this prepared A ([M, K]) have computed on the per-block fp32 path since it was prepared (exponent spread beyond what the
  * exact path folds into its operands).  `count` is a HOST pointer.  Synchronizes with the device.
  */
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfp4.so")
 HELPERS = os.path.join(ROOT, "bench_helpers")
-SOURCES = ["api.hip", "quantize.hip", "dequantize.hip", "gemm.hip", "gemm_native.hip"]
+SOURCES = ["api.hip", "quantize.hip", "dequantize.hip", "gemm.hip", "gemm_direct.hip", "gemm_native.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-fconstexpr-steps=200000000",

@@ -47,14 +47,9 @@
 //                        exact int32 sums.  A tile whose exponents spread too far
 //                        (or whose int32 sum could overflow) is computed by the same
 //                        workgroup with one fp32 scale-and-add per block;
-//   gemm_rows_kernel     the same exact scheme for at most 64 rows of A on prepared
-//                        operands (decode shapes): 32 x 32 outputs per workgroup, its 16
-//                        (or 8) waves share K; no list of visits, the class pairs other
-//                        than (0, 0) are added with their weights afterwards;
-//   gemm_small_kernel    at most 64 rows of A, nothing prepared: the exact scheme with the tile's
-//                        own reference exponents found in the kernel; per-block fp32 flush
-//                        for a tile whose exponents spread too far;
-//   gemm_block_kernel    whole products with K > 16384: per-block fp32 flush;
+//   gemm_direct_kernel   (gemm_direct.hip) the same exact scheme with both operands expanded inside the
+//                        kernel, in tiles from 32 x 32 to 256 x 128: few rows, few tiles, long K, batches
+//                        whose expanded A would be read only once;
 //   gemm_block16_kernel  operands quantized in blocks of 16: per-block fp32 flush.
 //
 // The order of the elements inside an MFMA operand does not matter as long
@@ -63,75 +58,22 @@
 #include "common.h"
 #include "formatbook.h"
 #include "quant_pass.h"
+#include "gemm_common.h"
 #include "gemm_step_asm.inc"
 
 namespace dfp4 {
 
-// [dialect][shift] -> {magnitudes lo, hi, negated magnitudes lo, hi}, bytes u << shift
-struct ShiftedBook { uint32_t w[kDialects][4][4]; };
-constexpr ShiftedBook make_shifted_book() {
-    ShiftedBook b{};
-    for (int d = 0; d < kDialects; ++d)
-        for (int s = 0; s < 4; ++s)
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t u = (uint32_t)kBook[d][j] << s;
-                b.w[d][s][j / 4] |= u << (8 * (j % 4));
-                b.w[d][s][2 + j / 4] |= ((256u - u) & 0xffu) << (8 * (j % 4));
-            }
-    return b;
-}
-__device__ const ShiftedBook g_shifted_book = make_shifted_book();
-
 namespace {
-
-// Results leave the kernel once and are not read again by it: stored with the non-temporal hint so
-// that they do not push the operands other workgroups still need out of the caches.
-#if defined(DFP4_TIMING_NO_OUT_STORES)   // timing experiments only: results are computed and dropped
-__device__ int g_timing_store_results = 0;
-#define DFP4_OUT_STORE(PTR, VAL) do { if (g_timing_store_results) *(PTR) = (VAL); } while (0)
-#elif defined(DFP4_PLAIN_OUT_STORES)
-#define DFP4_OUT_STORE(PTR, VAL) (*(PTR) = (VAL))
-#else
-#define DFP4_OUT_STORE(PTR, VAL) __builtin_nontemporal_store((VAL), (PTR))
-#endif
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kTileM = 512, kTileN = 128;   // fast kernel: outputs per workgroup
 constexpr int kGroups = kTileM / 32;        // 32-row groups per tile
 constexpr int kMaxKB = 512;           // fast path: K <= 16384
-constexpr int kMaxClass = 2;          // classes 0..2, i.e. exponent offsets 0..11
-constexpr int kIntBound = 4660;       // n0 + 16 n1 + 256 n2 <= 2^31 / (32 * 120 * 120)
 constexpr int kBBufBytes = 8 * 1024;  // int8 W operands of one step: 4 column tiles x 2 x 1 KiB
 constexpr int kRqPitch = 136;         // bf16 per staged output row (128 + 8: rows stay 16-byte aligned)
 constexpr int kVisitPad = 12;         // padding visits after the last one (the loop looks 5 steps ahead)
 constexpr int kClassPairs = (kMaxClass + 1) * (kMaxClass + 2) / 2;   // (class of A, class of W) with sum <= kMaxClass
 constexpr int kVisitCap = kClassPairs * kMaxKB + 2 * (kMaxClass + 1) + kVisitPad + 4;
-constexpr uint32_t kZeroTab = kDialects * 4 * 16;   // byte offset of the all-zero table behind the shifted book in LDS
 constexpr int kMaxSplitTiles = 2048;  // arrival counters per prepared A: K is split only below this many tiles
-
-struct GemmParams {
-    const uint8_t *a_codes, *a_dial, *a_exp, *w_codes, *w_dial, *w_exp;
-    void* out;
-    int M, N, KB;
-    int64_t ldc, strideA_rows, strideW_rows, strideC;
-    // prepared operands (per batch entry: base + batch * stride) and their regions
-    uint8_t* a_prep;
-    uint8_t* w_prep;
-    int64_t a_prep_stride, w_prep_stride;
-    int64_t off_refa, off_mask, off_cnt, off_a8;      // inside a prepared A
-    int64_t off_refw, off_wmask, off_wmeta, off_wcodes;   // inside a prepared W
-    uint32_t wmeta_cls_stride;                        // bytes between the table dwords of two classes
-    // exact int32 partial tiles of workgroups that share an output tile (split K)
-    int* part;
-    int64_t part_stride;              // ints per batch entry
-    int tiles_m, tiles_n;             // 512 x 128 output tiles
-    int ksplit;                       // workgroups sharing one output tile (each takes a range of K)
-    // requantizing epilogue: the quantized [M, N] output (blocks of 32 along N)
-    uint32_t* q_codes;
-    uint8_t *q_dial, *q_exp;
-};
 
 __host__ __device__ inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
@@ -181,40 +123,26 @@ inline int64_t partial_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
     const int s = choose_ksplit(tiles * batch, KB);
     return s > 1 ? align256((int64_t)s * tiles * kTileM * kTileN * 4) : 0;
 }
-inline bool takes_small_kernel(int64_t M, int64_t KB) { return M <= 64 && KB > 0 && KB <= 512; }
-inline bool takes_fast_kernel(int64_t M, int64_t KB) { return !takes_small_kernel(M, KB) && KB > 0 && KB <= kMaxKB; }
-
-// 8 codes (one dword) -> 8 signed int8 through one dialect table:
-// returns the even-numbered elements in one dword and the odd ones in another.
-// Magnitudes and negated magnitudes are looked up with v_perm_b32 (selector =
-// 3-bit index); the per-byte choice between them uses v_perm_b32's
-// sign-replication selectors (8..11 = 0x00 / 0xff from bit 7 of bytes 1, 3, 5, 7
-// of the source pair), which turn the code's sign bits into byte masks.
-__device__ __forceinline__ void unpack8(uint32_t c, uint32_t plo, uint32_t phi, uint32_t nlo,
-                                        uint32_t nhi, uint32_t& even, uint32_t& odd) {
-    const uint32_t ie = c & 0x07070707u, io = (c >> 4) & 0x07070707u;
-    const uint32_t pe = __builtin_amdgcn_perm(phi, plo, ie), po = __builtin_amdgcn_perm(phi, plo, io);
-    const uint32_t ne = __builtin_amdgcn_perm(nhi, nlo, ie), no = __builtin_amdgcn_perm(nhi, nlo, io);
-    // result byte k <- sign of byte k of x: bytes 1, 3 come from x, bytes 0, 2 from x << 8
-    constexpr uint32_t kSignSel = 0x090b080au;
-    const uint32_t c4 = c << 4;                                   // index sign bit 3 -> bit 7
-    const uint32_t mo = __builtin_amdgcn_perm(c << 8, c, kSignSel);
-    const uint32_t me = __builtin_amdgcn_perm(c4 << 8, c4, kSignSel);
-    even = (ne & me) | (pe & ~me);
-    odd = (no & mo) | (po & ~mo);
+// Which kernel.  gemm_fast_kernel multiplies expanded operands; gemm_direct_kernel (gemm_direct.hip) expands in the
+// kernel and takes everything gemm_fast_kernel cannot (few rows, K beyond its visit list), and the products it is
+// estimated to finish sooner: those with few output tiles, where the large kernel's one wave per SIMD leaves most
+// of the chip idle (M x N x K = 100 x 1000 x 4096: 112 us with the prepass, 11 us direct; 1024 x 1024 x 4096:
+// 108 and 20; 2048 x 4096 x 4096: 74 and 66; 4096 x 4096 x 4096: 89 and 148), and batches whose expanded A would
+// be read only once or twice (P V of attention).
+constexpr int kPreparedMinRows = 257;       // an A operand of fewer rows is not expanded ahead: direct wins for any N
+inline bool fast_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
+// Estimated microseconds of gemm_fast_kernel, with its prepass unless the operands are prepared (launches and
+// prologue; half a microsecond per block of a tile; per round the exposed epilogue; the exchange of partial tiles)
+inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
+    const int64_t cu = device_cu_count(), tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN) * batch;
+    const int s = choose_ksplit(tiles, KB);
+    const float rounds = (float)((tiles * s + cu - 1) / cu);
+    const float prep = prepared ? 0.0f : 15.0f + 2.1f * (float)((M + N) * KB * kBlock) * (float)batch * 2.5e-7f;
+    return prep + 5.0f + rounds * (6.0f + 0.5f * (float)KB / (float)s) + (s > 1 ? 25.0f : 0.0f);
 }
-
-__device__ __forceinline__ v4i unpack16(uint32_t c0, uint32_t c1, uint4 tab) {
-    uint32_t a, b, e, f;
-    unpack8(c0, tab.x, tab.y, tab.z, tab.w, a, b);
-    unpack8(c1, tab.x, tab.y, tab.z, tab.w, e, f);
-    return v4i{(int)a, (int)b, (int)e, (int)f};
-}
-
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+inline bool takes_direct_kernel(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
+    return !fast_kernel_can(M, KB) || (prepared && M < kPreparedMinRows) ||
+           gemm_direct_cost(M, N, KB, batch) <= fast_cost(M, N, KB, batch, prepared);
 }
 
 // ---------------------------------------------------------------------------
@@ -233,12 +161,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // W rows: reference exponent, per class and block one table offset (dword), and the classes
 // present in each block among the 128 rows of a tile.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int min_bytes(uint32_t x) {
-    return min(min((int)(x & 0xffu), (int)((x >> 8) & 0xffu)), min((int)((x >> 16) & 0xffu), (int)(x >> 24)));
-}
-__device__ __forceinline__ int max_bytes(uint32_t x) {
-    return max(max((int)(x & 0xffu), (int)((x >> 8) & 0xffu)), max((int)((x >> 16) & 0xffu), (int)(x >> 24)));
-}
 // up to 8 bytes starting at q (the first n are read), little-endian in a 64-bit word
 __device__ __forceinline__ uint64_t load_bytes8(const uint8_t* q, int n) {
     if (n == 8) {
@@ -397,104 +319,6 @@ __global__ __launch_bounds__(1024) void gemm_prep_kernel(GemmParams p, int n_a, 
             if ((present >> (4 * k + cc)) & 1u)
                 *reinterpret_cast<v4i*>(dst + cc * cls_stride) = cls[k] == cc ? data : v4i{0, 0, 0, 0};
     }
-}
-
-// ---------------------------------------------------------------------------
-// Per-block flush (always correct): 128 x 128 outputs per workgroup of 256 threads,
-// operands straight from global memory, one fp32 scale-and-add per block as in the
-// paper's MAC (Section 3.3).  Used by gemm_block_kernel for products the single-
-// accumulator kernel does not take, and by that kernel itself for tiles it declines.
-// ---------------------------------------------------------------------------
-template <bool MX, bool BF16>
-__device__ __forceinline__ void block_flush_tile(const GemmParams& p, int64_t bz, int by, int bx,
-                                                 uint8_t (&s_exp)[2][256]) {
-    const int KB = p.KB;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = by * 128, n0 = bx * 128;
-    const int64_t a_row0 = bz * p.strideA_rows, w_row0 = bz * p.strideW_rows;
-    const int half = lane >> 5, l32 = lane & 31;
-
-    int64_t a_row[2], w_row[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        a_row[i] = a_row0 + min(m0 + wm * 64 + i * 32 + l32, p.M - 1);
-        w_row[i] = w_row0 + min(n0 + wn * 64 + i * 32 + l32, p.N - 1);
-    }
-    const int t = threadIdx.x;
-    const int64_t e_row = t < 128 ? a_row0 + min(m0 + t, p.M - 1) : w_row0 + min(n0 + t - 128, p.N - 1);
-    const uint8_t* e_src = (t < 128 ? p.a_exp : p.w_exp) + e_row * KB;
-
-    float acc[2][2][16];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int x = 0; x < 16; ++x) acc[i][j][x] = 0.0f;
-
-    // operands of one block, loaded one iteration ahead so that the memory latency of block kb + 1
-    // passes behind the arithmetic of block kb
-    struct BlockOperands { uint2 ca[2], cw[2]; uint32_t da[2], dw[2], e; };
-    auto load_block = [&](int kb) {
-        BlockOperands o;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            o.ca[i] = *reinterpret_cast<const uint2*>(p.a_codes + (a_row[i] * KB + kb) * 16 + half * 8);
-            o.cw[i] = *reinterpret_cast<const uint2*>(p.w_codes + (w_row[i] * KB + kb) * 16 + half * 8);
-            o.da[i] = MX ? 7u : ((uint32_t)p.a_dial[a_row[i] * KB + kb] & 15u);
-            o.dw[i] = MX ? 7u : ((uint32_t)p.w_dial[w_row[i] * KB + kb] & 15u);
-        }
-        o.e = e_src[kb];
-        return o;
-    };
-    BlockOperands nxt{};
-    if (KB > 0) nxt = load_block(0);              // K = 0: nothing to read, the outputs are zeros
-    for (int kb = 0; kb < KB; ++kb) {
-        const BlockOperands cur = nxt;
-        if (kb + 1 < KB) nxt = load_block(kb + 1);
-        uint8_t* se = s_exp[kb & 1];
-        se[t] = (uint8_t)cur.e;
-        v4i a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            a[i] = unpack16(cur.ca[i].x, cur.ca[i].y, *reinterpret_cast<const uint4*>(g_shifted_book.w[cur.da[i]][0]));
-            b[i] = unpack16(cur.cw[i].x, cur.cw[i].y, *reinterpret_cast<const uint4*>(g_shifted_book.w[cur.dw[i]][0]));
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                v16i pr = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                pr = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], pr, 0, 0, 0);
-                const int ew = se[128 + wn * 64 + j * 32 + l32];
-#pragma unroll
-                for (int x = 0; x < 16; ++x) {
-                    const int row = 8 * (x >> 2) + 4 * half + (x & 3);
-                    const int ea = se[wm * 64 + i * 32 + row];
-                    acc[i][j][x] += ldexpf((float)pr[x], ea + ew - 256);
-                }
-            }
-    }
-
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wn * 64 + j * 32 + l32;
-#pragma unroll
-            for (int x = 0; x < 16; ++x) {
-                const int m = m0 + wm * 64 + i * 32 + 8 * (x >> 2) + 4 * half + (x & 3);
-                if (m < p.M && n < p.N) {
-                    const int64_t o = bz * p.strideC + (int64_t)m * p.ldc + n;
-                    if constexpr (BF16)
-                        static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne(acc[i][j][x]);
-                    else
-                        static_cast<float*>(p.out)[o] = acc[i][j][x];
-                }
-            }
-        }
 }
 
 // Requantizing GEMM, tiles that went through the per-block flush: quantize the 128 x 128 bf16
@@ -1035,475 +859,9 @@ __global__ __launch_bounds__(256, 1) void gemm_fast_kernel(GemmParams p) {
 #undef DFP4_READ_ACC
 }
 
-// ---------------------------------------------------------------------------
-// Few rows of A (decode shapes, M <= 64): W is streamed once per 32 rows of A and
-// the time goes into expanding W, so the tile is 32 (A rows) x 32 (W rows) per
-// workgroup and the workgroup's 16 (or 8) waves share K: wave w takes a contiguous
-// range of blocks and multiplies block by block (one MFMA each); the partial tiles
-// are added in a fixed order through LDS.  No prepass and no workspace.
-// small_tile() applies the exponent pair per block in fp32 as the paper does;
-// small_exact_tile() (tried first) folds the exponents into the operands instead.
-// ---------------------------------------------------------------------------
-constexpr int kSmallWaves = 16;     // waves of a workgroup, at most (LDS is laid out for this many)
-constexpr int kSmallMaxKB = 512;      // LDS holds the 32 rows' exponent bytes of all blocks
-constexpr int kSmallMaxM = 64;
-static_assert(kSmallMaxM == 64 && kSmallMaxKB == 512, "takes_small_kernel() states these limits");
-
-struct SmallTileLds {
-    __attribute__((aligned(16))) uint32_t tab[kDialects * 4];   // shift-0 tables
-    __attribute__((aligned(4))) uint8_t ea[kSmallMaxKB * 32];   // [block][row] exponent bytes of A
-    float red[kSmallWaves / 2][16][64];
-};
-
-// One 32 x 32 output tile by a workgroup of 16 waves, one fp32 scale-and-add per block.
-template <bool MX, bool BF16, int NW>
-__device__ __forceinline__ void small_tile(const GemmParams& p, int64_t bz, int m0, int n0, SmallTileLds& lds) {
-    uint32_t (&s_tab)[kDialects * 4] = lds.tab;
-    uint8_t (&s_ea)[kSmallMaxKB * 32] = lds.ea;
-    float (&s_red)[kSmallWaves / 2][16][64] = lds.red;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, r = lane & 31;
-    const int KB = p.KB;
-    const int64_t a_row0 = bz * p.strideA_rows, w_row0 = bz * p.strideW_rows;
-
-    const int64_t arow = a_row0 + min(m0 + r, p.M - 1), wrow = w_row0 + min(n0 + r, p.N - 1);
-    const uint8_t* ac = p.a_codes + arow * KB * 16 + h * 8;
-    const uint8_t* wc = p.w_codes + wrow * KB * 16 + h * 8;
-    const uint8_t* ad = MX ? nullptr : p.a_dial + arow * KB;
-    const uint8_t* wd = MX ? nullptr : p.w_dial + wrow * KB;
-    const uint8_t* we = p.w_exp + wrow * KB;
-    const int per = (KB + NW - 1) / NW;
-    const int kb_lo = wave * per, kb_hi = min(KB, kb_lo + per);
-
-    for (int i = tid; i < kDialects * 4; i += NW * 64) s_tab[i] = g_shifted_book.w[i >> 2][0][i & 3];
-    for (int i = tid; i < 32 * KB; i += NW * 64) {
-        const int row = i / KB, kb = i - row * KB;
-        s_ea[kb * 32 + row] = p.a_exp[(a_row0 + min(m0 + row, p.M - 1)) * KB + kb];
-    }
-    __syncthreads();
-
-    float acc[16];
-#pragma unroll
-    for (int x = 0; x < 16; ++x) acc[x] = 0.0f;
-    constexpr int kU = 4;              // blocks whose loads are issued together
-    for (int kb0 = kb_lo; kb0 < kb_hi; kb0 += kU) {
-        uint2 ca[kU], cw[kU];
-        uint32_t da[kU], dw[kU], ew[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int kb = min(kb0 + u, kb_hi - 1);            // the tail repeats the last block (not used)
-            ca[u] = *reinterpret_cast<const uint2*>(ac + (int64_t)kb * 16);
-            cw[u] = *reinterpret_cast<const uint2*>(wc + (int64_t)kb * 16);
-            da[u] = MX ? 7u : ((uint32_t)ad[kb] & 15u);
-            dw[u] = MX ? 7u : ((uint32_t)wd[kb] & 15u);
-            ew[u] = we[kb];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int kb = kb0 + u;
-            if (kb >= kb_hi) break;                            // wave-uniform
-            const v4i a = unpack16(ca[u].x, ca[u].y, *reinterpret_cast<const uint4*>(&s_tab[da[u] * 4]));
-            const v4i b = unpack16(cw[u].x, cw[u].y, *reinterpret_cast<const uint4*>(&s_tab[dw[u] * 4]));
-            v16i pr = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-            pr = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, pr, 0, 0, 0);
-            const int ewc = (int)ew[u] - 256;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t e4 = *reinterpret_cast<const uint32_t*>(&s_ea[kb * 32 + 8 * q + 4 * h]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[4 * q + j] += ldexpf((float)pr[4 * q + j], (int)((e4 >> (8 * j)) & 0xffu) + ewc);
-            }
-        }
-    }
-    // the NW partial tiles, added in a fixed order: the upper half of the waves hands theirs to the lower
-    if (wave >= NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) s_red[wave - NW / 2][x][lane] = acc[x];
-    }
-    __syncthreads();
-    if (wave < NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) s_red[wave][x][lane] += acc[x];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16 / NW; ++i) {
-        const int x = wave + i * NW;                           // thread (x, lane) finishes one output
-        float sum = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW / 2; ++w) sum += s_red[w][x][lane];
-        const int m = m0 + 8 * (x >> 2) + 4 * h + (x & 3), n = n0 + r;
-        if (m < p.M && n < p.N) {
-            const int64_t o = bz * p.strideC + (int64_t)m * p.ldc + n;
-            if constexpr (BF16)
-                static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne(sum);
-            else
-                static_cast<float*>(p.out)[o] = sum;
-        }
-    }
-}
-
-// The same tile with the exact scheme of the large kernel, nothing prepared: the workgroup finds the
-// reference exponents of its 32 rows of A and 32 rows of W itself (both tiles' exponent bytes go to
-// LDS), folds each block's offset into the int8 operands (shift) and a class (weight 16^class sum),
-// and sums all of K in int32 -- no floating-point work per block, which is what bounds small_tile().
-// Blocks whose rows are all of class 0 on both sides (the common case) take one MFMA; others take one
-// per pair of classes present, rows of other classes zeroed, added with the pair's weight.  Returns
-// false, having stored nothing, when the exponents spread beyond what an int32 sum can hold (decided
-// from the largest offsets of the two tiles, the same for every thread): small_tile() computes the tile.
-struct SmallExactLds {
-    __attribute__((aligned(16))) uint32_t tab[kDialects * 16 + 4];     // [dialect][shift] tables
-    __attribute__((aligned(16))) uint8_t ea[kSmallMaxKB * 32];         // [block][row] exponent bytes of A
-    __attribute__((aligned(16))) uint8_t ew[kSmallMaxKB * 32];         // and of W; later the partial tiles
-    int mn[64], mx[64];                                                // per row of A (0..31) and of W (32..63)
-};
-static_assert(sizeof(int) * (kSmallWaves / 2) * 16 * 64 <= 2 * kSmallMaxKB * 32, "partial tiles reuse ea and ew");
-
-template <bool MX, bool BF16, int NW>
-__device__ __forceinline__ bool small_exact_tile(const GemmParams& p, int64_t bz, int m0, int n0, SmallExactLds& lds) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, r = lane & 31;
-    const int KB = p.KB;
-    const int64_t a_row0 = bz * p.strideA_rows, w_row0 = bz * p.strideW_rows;
-    const int64_t arow = a_row0 + min(m0 + r, p.M - 1), wrow = w_row0 + min(n0 + r, p.N - 1);
-    const uint8_t* ac = p.a_codes + arow * KB * 16 + h * 8;
-    const uint8_t* wc = p.w_codes + wrow * KB * 16 + h * 8;
-    const uint8_t* ad = MX ? nullptr : p.a_dial + arow * KB;
-    const uint8_t* wd = MX ? nullptr : p.w_dial + wrow * KB;
-    const int per = (KB + NW - 1) / NW;
-    const int kb_lo = wave * per, kb_hi = min(KB, kb_lo + per);
-
-    for (int i = tid; i < kDialects * 16 + 4; i += NW * 64) lds.tab[i] = i < kDialects * 16 ? (&g_shifted_book.w[0][0][0])[i] : 0u;
-    for (int i = tid; i < 32 * KB; i += NW * 64) {
-        const int row = i / KB, kb = i - row * KB;
-        lds.ea[kb * 32 + row] = p.a_exp[(a_row0 + min(m0 + row, p.M - 1)) * KB + kb];
-        lds.ew[kb * 32 + row] = p.w_exp[(w_row0 + min(n0 + row, p.N - 1)) * KB + kb];
-    }
-    if (tid < 64) {
-        lds.mn[tid] = 255;
-        lds.mx[tid] = 0;
-    }
-    __syncthreads();
-    {
-        // smallest and largest exponent byte of every row: thread (row, part) scans every (2 NW)-th block
-        const int row = tid & 31, part = tid >> 5;
-        int amn = 255, amx = 0, wmn = 255, wmx = 0;
-        for (int kb = part; kb < KB; kb += 2 * NW) {
-            const int a = lds.ea[kb * 32 + row], w = lds.ew[kb * 32 + row];
-            amn = min(amn, a); amx = max(amx, a);
-            wmn = min(wmn, w); wmx = max(wmx, w);
-        }
-        if (part < KB) {
-            atomicMin(&lds.mn[row], amn); atomicMax(&lds.mx[row], amx);
-            atomicMin(&lds.mn[32 + row], wmn); atomicMax(&lds.mx[32 + row], wmx);
-        }
-    }
-    __syncthreads();
-    {
-        // Can every class pair that may occur be taken, and the worst-case sum be held?  From the largest
-        // offsets only: classes up to ca_max and cw_max may meet in any block.
-        int da = 0, dw = 0;
-        for (int i = 0; i < 32; ++i) {
-            da = max(da, lds.mx[i] - lds.mn[i]);
-            dw = max(dw, lds.mx[32 + i] - lds.mn[32 + i]);
-        }
-        const int ca_max = da >> 2, cw_max = dw >> 2;
-        if (ca_max + cw_max > kMaxClass) return false;
-        int per_block = 0;
-        for (int ca = 0; ca <= ca_max; ++ca)
-            for (int cw = 0; cw <= cw_max; ++cw) per_block += 1 << (4 * (ca + cw));
-        if (per_block * KB > kIntBound) return false;
-    }
-    const int refa = lds.mn[r], refw = lds.mn[32 + r];
-
-    v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const v4i zero4 = {0, 0, 0, 0};
-    constexpr int kU = 4;              // blocks whose loads are issued together
-    for (int kb0 = kb_lo; kb0 < kb_hi; kb0 += kU) {
-        uint2 ca[kU], cw[kU];
-        uint32_t da[kU], dw[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int kb = min(kb0 + u, kb_hi - 1);            // the tail repeats the last block (not used)
-            ca[u] = *reinterpret_cast<const uint2*>(ac + (int64_t)kb * 16);
-            cw[u] = *reinterpret_cast<const uint2*>(wc + (int64_t)kb * 16);
-            da[u] = MX ? 7u : ((uint32_t)ad[kb] & 15u);
-            dw[u] = MX ? 7u : ((uint32_t)wd[kb] & 15u);
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int kb = kb0 + u;
-            if (kb >= kb_hi) break;                            // wave-uniform
-            const int oa = (int)lds.ea[kb * 32 + r] - refa, ow = (int)lds.ew[kb * 32 + r] - refw;   // offsets >= 0
-            const int cla = oa >> 2, clw = ow >> 2;
-            const uint4 ta = *reinterpret_cast<const uint4*>(&lds.tab[(da[u] * 4 + (oa & 3)) * 4]);
-            const uint4 tw = *reinterpret_cast<const uint4*>(&lds.tab[(dw[u] * 4 + (ow & 3)) * 4]);
-            const v4i a = unpack16(ca[u].x, ca[u].y, ta), b = unpack16(cw[u].x, cw[u].y, tw);
-            if (__ballot((cla | clw) != 0) == 0ull) {
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
-            } else {
-                for (int ct = 0; ct <= kMaxClass; ++ct) {
-                    for (int c1 = 0; c1 <= ct; ++c1) {
-                        const int c2 = ct - c1;
-                        if (__ballot(cla == c1) == 0ull || __ballot(clw == c2) == 0ull) continue;
-                        const v4i pa = cla == c1 ? a : zero4, pb = clw == c2 ? b : zero4;
-                        v16i t16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                        t16 = __builtin_amdgcn_mfma_i32_32x32x32_i8(pa, pb, t16, 0, 0, 0);
-#pragma unroll
-                        for (int x = 0; x < 16; ++x) acc[x] += t16[x] << (4 * ct);
-                    }
-                }
-            }
-        }
-    }
-    // the NW exact partial tiles, added through LDS (over the exponent bytes, which are no longer needed)
-    __syncthreads();
-    int (*red)[16][64] = reinterpret_cast<int (*)[16][64]>(lds.ea);
-    if (wave >= NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) red[wave - NW / 2][x][lane] = acc[x];
-    }
-    __syncthreads();
-    if (wave < NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) red[wave][x][lane] += acc[x];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16 / NW; ++i) {
-        const int x = wave + i * NW;                           // thread (x, lane) finishes one output
-        int sum = 0;
-#pragma unroll
-        for (int w = 0; w < NW / 2; ++w) sum += red[w][x][lane];
-        const int lr = 8 * (x >> 2) + 4 * h + (x & 3), m = m0 + lr, n = n0 + r;
-        if (m < p.M && n < p.N) {
-            const float f = ldexpf((float)sum, lds.mn[lr] + lds.mn[32 + r] - 256);
-            const int64_t o = bz * p.strideC + (int64_t)m * p.ldc + n;
-            if constexpr (BF16)
-                static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne(f);
-            else
-                static_cast<float*>(p.out)[o] = f;
-        }
-    }
-    return true;
-}
-
-template <bool MX, bool BF16, int NW>
-__global__ __launch_bounds__(NW * 64) void gemm_small_kernel(GemmParams p) {
-    __shared__ union {
-        SmallExactLds exact;
-        SmallTileLds flush;
-    } lds;
-    const int m0 = (int)blockIdx.y * 32, n0 = (int)blockIdx.x * 32;
-    if (small_exact_tile<MX, BF16, NW>(p, blockIdx.z, m0, n0, lds.exact)) return;
-    __syncthreads();
-    small_tile<MX, BF16, NW>(p, blockIdx.z, m0, n0, lds.flush);
-}
-
-// ---------------------------------------------------------------------------
-// Few rows of A on PREPARED operands (decode shapes with weights prepared offline): the exact
-// scheme of the large kernel -- exponent offsets folded into the int8 operands, classes weighted
-// by 16^(class of A + class of W), one conversion at the end -- in the shape of the few-rows
-// kernel: a workgroup of NW waves owns 32 rows of A x 32 rows of W and the waves share K in
-// contiguous ranges of block pairs.  The kernel is bound by latency, so it keeps the chain of
-// dependent memory accesses short: there is no list of visits.  A wave issues, before anything
-// else, the loads of its first pairs for the common case (class 0 of both operands): class masks,
-// codes and table offsets of W, expanded fragments of A.  The masks come back first; a block that
-// has other classes as well (rare: outlier channels) gets extra products, each computed into a
-// temporary tile and added with its weight 16^(class sum), which is exact in int32 under the same
-// bound the large kernel checks.  Whether the tile can be taken at all is decided by every wave
-// from the masks of all of K (same data, same decision).  The NW exact partial tiles are added
-// through LDS.  A tile the scheme cannot take is computed by small_tile().
-// ---------------------------------------------------------------------------
-template <bool MX, bool BF16, int NW>
-__global__ __launch_bounds__(NW * 64) void gemm_rows_kernel(GemmParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t s_tab[kDialects * 16 + 4];
-    __shared__ union {
-        int red[kSmallWaves / 2][16][64];
-        SmallTileLds small;
-    } u;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, r = lane & 31;
-    const int KB = p.KB;
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    const uint8_t* ap = p.a_prep;
-    const uint8_t* wp = p.w_prep;
-    const uint8_t* mask_a = ap + p.off_mask + (int64_t)(m0 / kTileM) * KB;      // classes of the 512-row tile of A
-    const uint8_t* mask_w = wp + p.off_wmask + (int64_t)(n0 / kTileN) * KB;     // and of the 128-row tile of W
-
-    const uint32_t grp_stride = (uint32_t)(KB + 1) * 1024u;
-    const uint64_t cls_stride = (uint64_t)p.tiles_m * kGroups * grp_stride;
-    const uint8_t* a8 = ap + p.off_a8 + (uint64_t)(m0 / 32) * grp_stride + (uint32_t)r * 16u;
-    const int ncol = n0 + r;                            // rows beyond N exist in the prepared W: all-zero tables
-    const uint64_t w_slot = (uint64_t)(ncol >> 5) * KB * 32u + (uint32_t)(ncol & 31);      // [group][block][row]
-    const uint8_t* wcodes = wp + p.off_wcodes + w_slot * 16u;
-    const uint8_t* wmeta = wp + p.off_wmeta + w_slot * 4u;
-
-    // this wave's range of block pairs (lane half h takes block 2 * pair + h)
-    const int P = (KB + 1) / 2, per = (P + NW - 1) / NW;
-    const int p_lo = min(P, wave * per), p_hi = min(P, p_lo + per);
-    constexpr int kU = 4;                              // pairs whose loads are issued together
-    uint32_t mA[kU], mW[kU], meta[kU];
-    uint4 wc[kU];
-    v4i af[kU][2];
-    auto issue = [&](int g0) {
-#pragma unroll
-        for (int q = 0; q < kU; ++q) {                 // the masks first: they are needed first
-            const int kb = 2 * min(g0 + q, p_hi - 1) + h;
-            mA[q] = kb < KB ? mask_a[kb] : 0u;
-            mW[q] = kb < KB ? mask_w[kb] : 0u;
-        }
-#pragma unroll
-        for (int q = 0; q < kU; ++q) {
-            const int kb = 2 * min(g0 + q, p_hi - 1) + h, kbw = min(kb, KB - 1);
-            wc[q] = *reinterpret_cast<const uint4*>(wcodes + (uint32_t)kbw * 512u);
-            meta[q] = *reinterpret_cast<const uint32_t*>(wmeta + (uint32_t)kbw * 128u);        // class 0 of W
-            const uint8_t* src = a8 + (uint32_t)min(kb, KB) * 1024u;                          // class 0 of A; KB = zeros
-            af[q][0] = *reinterpret_cast<const v4i*>(src);
-            af[q][1] = *reinterpret_cast<const v4i*>(src + 512);
-        }
-    };
-    // loads in the order their values are needed: the masks of all of K (the decision below), the
-    // table, then the first pairs' operands
-    uint32_t da[kMaxKB / 64], dw[kMaxKB / 64];
-#pragma unroll
-    for (int j = 0; j < kMaxKB / 64; ++j) {
-        const int kb = j * 64 + lane;
-        da[j] = kb < KB ? mask_a[kb] : 0u;
-        dw[j] = kb < KB ? mask_w[kb] : 0u;
-    }
-    const uint32_t tab_word = tid < kDialects * 16 ? (&g_shifted_book.w[0][0][0])[tid] : 0u;
-    if (p_lo < p_hi) issue(p_lo);
-
-    // reference exponents of the outputs this thread finishes (x = wave, wave + NW, ..): loaded now, used last
-    int ref_sum[16 / NW];
-#pragma unroll
-    for (int i = 0; i < 16 / NW; ++i) {
-        const int x = wave + i * NW;
-        const int m = min(m0 + 8 * (x >> 2) + 4 * h + (x & 3), p.M - 1);
-        ref_sum[i] = (int)ap[p.off_refa + m] + (int)wp[p.off_refw + ncol] - 256;
-    }
-    // Can the tile be taken?  Classes beyond those kept, or a sum of weights an int32 accumulator
-    // could not hold.  Every wave decides from the masks of all of K.
-    bool declined;
-    {
-        bool bad = false;
-        int weight = 0;
-#pragma unroll
-        for (int j = 0; j < kMaxKB / 64; ++j) {
-            if (j * 64 >= KB) break;                   // uniform
-            const uint32_t a = da[j], w = dw[j];
-            const int ha = 31 - __builtin_clz(a | 1u), hw = 31 - __builtin_clz(w | 1u);
-            bad |= ha + hw > kMaxClass;
-#pragma unroll
-            for (int ct = 0; ct <= kMaxClass; ++ct)
-#pragma unroll
-                for (int ca = 0; ca <= ct; ++ca)
-                    weight += __popcll(__ballot(((a >> ca) & 1u) && ((w >> (ct - ca)) & 1u))) << (4 * ct);
-        }
-        declined = __ballot(bad) != 0ull || weight > kIntBound;
-    }
-    if (tid < kDialects * 16 + 4) s_tab[tid] = tab_word;        // NW * 64 >= 512 > 260 entries
-    __syncthreads();
-    if (declined) {
-        if (tid == 0 && blockIdx.x % (kTileN / 32) == 0)   // counted once per 512 x 128 tile, like the large kernel
-            atomicAdd(reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(ap) + p.off_cnt) + kMaxSplitTiles, 1u);
-        small_tile<MX, BF16, NW>(p, 0, m0, n0, u.small);
-        return;
-    }
-
-    v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const v4i zero4 = {0, 0, 0, 0};
-    bool any_odd = false;                              // some block of this wave's range has other classes too
-    for (int g0 = p_lo; g0 < p_hi; g0 += kU) {
-        if (g0 != p_lo) issue(g0);
-        bool odd = false;
-#pragma unroll
-        for (int q = 0; q < kU; ++q) odd |= g0 + q < p_hi && 2 * (g0 + q) + h < KB && (mA[q] != 1u || mW[q] != 1u);
-        const bool mixed = __ballot(odd) != 0ull;      // uniform
-        any_odd |= mixed;
-#pragma unroll
-        for (int q = 0; q < kU; ++q) {
-            if (g0 + q >= p_hi) break;                 // wave-uniform
-            const uint4 tab = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(s_tab) + meta[q]);
-            const v4i b0 = unpack16(wc[q].x, wc[q].y, tab), b1 = unpack16(wc[q].z, wc[q].w, tab);
-            v4i a0 = af[q][0], a1 = af[q][1];
-            if (mixed) {                               // a class-0 fragment exists only where the tile has class 0
-                const bool have = (mA[q] & 1u) != 0u && 2 * (g0 + q) + h < KB;
-                a0 = have ? a0 : zero4;
-                a1 = have ? a1 : zero4;
-            }
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc, 0, 0, 0);
-        }
-    }
-    // The other class pairs (rare: blocks with outliers), pair by pair: lanes whose block has the
-    // class pair bring its operands, the others zeros; the product goes to a temporary tile and is
-    // added with its weight.
-    if (any_odd) {
-        for (int pr = p_lo; pr < p_hi; ++pr) {
-            const int kb = 2 * pr + h;
-            const uint32_t kbw = (uint32_t)min(kb, KB - 1);
-            const uint32_t ma = kb < KB ? mask_a[kb] : 0u, mw = kb < KB ? mask_w[kb] : 0u;
-            if (__ballot((ma | mw) > 1u) == 0ull) continue;
-            const uint4 codes = *reinterpret_cast<const uint4*>(wcodes + kbw * 512u);
-            for (int ct = 1; ct <= kMaxClass; ++ct) {
-                for (int ca = 0; ca <= ct; ++ca) {
-                    const int cw = ct - ca;
-                    const bool part = ((ma >> ca) & 1u) && ((mw >> cw) & 1u);
-                    if (__ballot(part) == 0ull) continue;
-                    const uint8_t* src = a8 + (uint64_t)ca * cls_stride + kbw * 1024u;
-                    const v4i x0 = part ? *reinterpret_cast<const v4i*>(src) : zero4;
-                    const v4i x1 = part ? *reinterpret_cast<const v4i*>(src + 512) : zero4;
-                    const uint32_t mt = *reinterpret_cast<const uint32_t*>(
-                        wmeta + (uint64_t)cw * p.wmeta_cls_stride + kbw * 128u);
-                    const uint4 tab = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(s_tab) + mt);
-                    const v4i b0 = unpack16(codes.x, codes.y, tab), b1 = unpack16(codes.z, codes.w, tab);
-                    v16i t16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                    t16 = __builtin_amdgcn_mfma_i32_32x32x32_i8(x0, b0, t16, 0, 0, 0);
-                    t16 = __builtin_amdgcn_mfma_i32_32x32x32_i8(x1, b1, t16, 0, 0, 0);
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) acc[x] += t16[x] << (4 * ct);
-                }
-            }
-        }
-    }
-    // the NW exact partial tiles: the upper half of the waves hands theirs to the lower, then thread
-    // (x, lane) finishes one output
-    if (wave >= NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) u.red[wave - NW / 2][x][lane] = acc[x];
-    }
-    __syncthreads();
-    if (wave < NW / 2) {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) u.red[wave][x][lane] += acc[x];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16 / NW; ++i) {
-        const int x = wave + i * NW;
-        int sum = 0;
-#pragma unroll
-        for (int w = 0; w < NW / 2; ++w) sum += u.red[w][x][lane];
-        const int m = m0 + 8 * (x >> 2) + 4 * h + (x & 3), n = n0 + r;
-        if (m < p.M && n < p.N) {
-            const float f = ldexpf((float)sum, ref_sum[i]);
-            const int64_t o = (int64_t)m * p.ldc + n;
-            if constexpr (BF16)
-                static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne(f);
-            else
-                static_cast<float*>(p.out)[o] = f;
-        }
-    }
-}
-
-// Whole product through the per-block flush (K beyond the single-accumulator kernel's limit).
-template <bool MX, bool BF16>
-__global__ __launch_bounds__(256) void gemm_block_kernel(GemmParams p) {
-    __shared__ uint8_t s_exp[2][256];
-    block_flush_tile<MX, BF16>(p, blockIdx.z, (int)blockIdx.y, (int)blockIdx.x, s_exp);
+// The whole prepared form of an A operand of few rows: the count of declined tiles.
+__global__ void clear_count_kernel(uint32_t* count) {
+    if (threadIdx.x == 0) *count = 0;
 }
 
 }  // namespace
@@ -1520,42 +878,43 @@ static int64_t max_rows_w(int64_t KB) { return ((((int64_t)1 << 31) - 1) / (KB *
 size_t gemm_prepared_bytes(int64_t rows, int64_t K, bool weight) {
     const int64_t KB = K / kBlock;
     if (rows <= 0 || KB <= 0 || KB > kMaxKB) return 0;
+    if (!weight && rows < kPreparedMinRows) return 256;    // the count of declined tiles
     return (size_t)(weight ? prep_w_layout(rows, KB).total : prep_a_layout(rows, KB).total);
 }
 
 // byte offset, inside a prepared A, of the dword that counts tiles declined since it was prepared
 size_t gemm_prepared_declined_offset(int64_t M, int64_t K) {
-    return (size_t)prep_a_layout(M, K / kBlock).off_cnt + (size_t)kMaxSplitTiles * 4;
+    return M < kPreparedMinRows ? 0 : (size_t)prep_a_layout(M, K / kBlock).off_cnt + (size_t)kMaxSplitTiles * 4;
 }
 
 size_t gemm_prepared_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t KB = K / kBlock;
-    if (M <= 0 || N <= 0 || !takes_fast_kernel(M, KB)) return 0;
+    if (M <= 0 || N <= 0 || takes_direct_kernel(M, N, KB, 1, true)) return 0;
     return (size_t)partial_bytes(M, N, KB, 1);
 }
 
-size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+// what gemm_fast_kernel and its prepass need
+size_t gemm_fast_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t KB = K / kBlock;
-    if (M <= 0 || N <= 0 || !takes_fast_kernel(M, KB)) return 0;
+    if (M <= 0 || N <= 0 || !fast_kernel_can(M, KB)) return 0;
     const int64_t Mc = M < max_rows_a(KB) ? M : max_rows_a(KB), Nc = N < max_rows_w(KB) ? N : max_rows_w(KB);
     return (size_t)(prep_a_layout(Mc, KB).total + prep_w_layout(Nc, KB).total + partial_bytes(Mc, Nc, KB, 1));
 }
 
+size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    const int64_t KB = K / kBlock;
+    if (M <= 0 || N <= 0 || !fast_kernel_can(M, KB)) return 0;
+    // nothing but a token where the direct kernel is taken whatever the batch
+    if (takes_direct_kernel(M, N, KB, 1, false) && takes_direct_kernel(M, N, KB, 65535, false)) return 256;
+    return gemm_fast_workspace_bytes(M, N, K);
+}
+
 size_t gemm_requant_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0) return 0;
-    return (size_t)align256((int64_t)gemm_workspace_bytes(M, N, K)) + (size_t)align256(M * N * 2);
+    return (size_t)align256((int64_t)gemm_fast_workspace_bytes(M, N, K)) + (size_t)align256(M * N * 2);
 }
 
 namespace {
-
-template <typename F>
-void dispatch_mx_bf16(bool mx, bool bf16, F&& f) {
-    if (mx) {
-        if (bf16) f(std::true_type{}, std::true_type{}); else f(std::true_type{}, std::false_type{});
-    } else {
-        if (bf16) f(std::false_type{}, std::true_type{}); else f(std::false_type{}, std::false_type{});
-    }
-}
 
 void fill_params(GemmParams& p, const dfp4_tensor& A, const dfp4_tensor& W, void* out, int64_t ldc,
                  int64_t strideA_rows, int64_t strideW_rows, int64_t strideC, const dfp4_tensor* rq) {
@@ -1619,34 +978,24 @@ int launch_fast(bool mx, bool bf16, GemmParams& p, int64_t batch, int* part, siz
     return check_launch();
 }
 
-// products the single-accumulator kernel does not take: few rows, or K beyond its limit
-int launch_other(bool mx, bool bf16, GemmParams& p, int64_t batch, const dfp4_tensor* rq, hipStream_t stream) {
-    if (batch > 65535) return DFP4_ERR_SHAPE;
-    if (takes_small_kernel(p.M, p.KB)) {
-        dim3 gs((unsigned)((p.N + 31) / 32), (unsigned)((p.M + 31) / 32), (unsigned)batch);
-        // 16 waves per tile while every tile finds a compute unit of its own; 8 beyond that, so that two
-        // workgroups share a unit (registers allow 16 waves per unit) instead of waiting for a second round
-        const bool narrow = (int64_t)gs.x * gs.y * gs.z > device_cu_count();
-        dispatch_mx_bf16(mx, bf16, [&](auto mxc, auto bc) {
-            if (narrow)
-                hipLaunchKernelGGL((gemm_small_kernel<decltype(mxc)::value, decltype(bc)::value, 8>), gs,
-                                   dim3(8 * 64), 0, stream, p);
-            else
-                hipLaunchKernelGGL((gemm_small_kernel<decltype(mxc)::value, decltype(bc)::value, kSmallWaves>), gs,
-                                   dim3(kSmallWaves * 64), 0, stream, p);
-        });
-    } else {
-        dim3 gb((unsigned)((p.N + 127) / 128), (unsigned)((p.M + 127) / 128), (unsigned)batch);
-        if (gb.y > 65535) return DFP4_ERR_SHAPE;
-        dispatch_mx_bf16(mx, bf16, [&](auto mxc, auto bc) {
-            hipLaunchKernelGGL((gemm_block_kernel<decltype(mxc)::value, decltype(bc)::value>), gb, dim3(256), 0,
-                               stream, p);
-        });
-    }
-    const int rc = check_launch();
-    if (rc != DFP4_OK || !rq) return rc;
-    // the bf16 temporary holds [batch * M, N]
-    return launch_quantize(mx, p.out, (int64_t)p.M * batch, p.N, p.ldc, *rq, stream);
+// direct kernel, in pieces of at most as many rows as it addresses
+int launch_direct(bool mx, bool bf16, dfp4_tensor A, dfp4_tensor W, void* out, int64_t ldc, int64_t batch,
+                  int64_t strideA_rows, int64_t strideW_rows, int64_t strideC, hipStream_t stream) {
+    const int64_t KB = A.K / kBlock, step = gemm_direct_max_rows(KB), M = A.rows, N = W.rows;
+    for (int64_t m0 = 0; m0 < M; m0 += step)
+        for (int64_t n0 = 0; n0 < N; n0 += step) {
+            dfp4_tensor a = A, w = W;
+            a.rows = M - m0 < step ? M - m0 : step;
+            w.rows = N - n0 < step ? N - n0 : step;
+            a.codes += m0 * KB * 16; a.exponent += m0 * KB; if (a.dialect) a.dialect += m0 * KB;
+            w.codes += n0 * KB * 16; w.exponent += n0 * KB; if (w.dialect) w.dialect += n0 * KB;
+            GemmParams p{};
+            fill_params(p, a, w, static_cast<uint8_t*>(out) + (size_t)(m0 * ldc + n0) * (bf16 ? 2 : 4), ldc, strideA_rows,
+                        strideW_rows, strideC, nullptr);
+            const int rc = launch_gemm_direct(mx, bf16, p, batch, stream);
+            if (rc != DFP4_OK) return rc;
+        }
+    return DFP4_OK;
 }
 
 bool shape_in_range(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t ldc) {
@@ -1660,9 +1009,8 @@ int gemm_shape_check(dfp4_tensor A, dfp4_tensor W, int64_t ldc, int64_t batch, b
     const int64_t M = A.rows, N = W.rows, KB = A.K / kBlock;
     if (M == 0 || N == 0 || batch == 0) return DFP4_OK;
     if (!shape_in_range(M, N, KB, batch, ldc)) return DFP4_ERR_SHAPE;
-    if (takes_fast_kernel(M, KB) && (rq || batch > 1) && (M > max_rows_a(KB) || N > max_rows_w(KB)))
+    if (fast_kernel_can(M, KB) && (rq || batch > 1) && (M > max_rows_a(KB) || N > max_rows_w(KB)))
         return DFP4_ERR_SHAPE;         // only the plain single product is cut into pieces
-    if (!takes_fast_kernel(M, KB) && !takes_small_kernel(M, KB) && (M + 127) / 128 > 65535) return DFP4_ERR_SHAPE;
     return DFP4_OK;
 }
 
@@ -1676,10 +1024,11 @@ int launch_gemm(bool mx, dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype,
     int rc = gemm_shape_check(A, W, ldc, batch, rq != nullptr);
     if (rc != DFP4_OK) return rc;
     const bool bf16 = out_dtype == DFP4_BF16;
-    if (!takes_fast_kernel(M, KB)) {
-        GemmParams p{};
-        fill_params(p, A, W, out, ldc, strideA_rows, strideW_rows, strideC, rq);
-        return launch_other(mx, bf16, p, batch, rq, stream);
+    const size_t fast_bytes = gemm_fast_workspace_bytes(M, N, A.K) * (size_t)batch;
+    if (!fast_kernel_can(M, KB) || (!rq && (takes_direct_kernel(M, N, KB, batch, false) || !workspace || workspace_bytes < fast_bytes))) {
+        rc = launch_direct(mx, bf16, A, W, out, ldc, batch, strideA_rows, strideW_rows, strideC, stream);
+        if (rc != DFP4_OK || !rq) return rc;
+        return launch_quantize(mx, out, M * batch, N, ldc, *rq, stream);       // `out` holds the bf16 [batch * M, N]
     }
     // pieces of at most mc x nc outputs (one piece for every product of ordinary size)
     const int64_t mc = M < max_rows_a(KB) ? M : max_rows_a(KB), nc = N < max_rows_w(KB) ? N : max_rows_w(KB);
@@ -1717,6 +1066,10 @@ int launch_gemm(bool mx, dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype,
 // products that consume it).
 int launch_gemm_prepare(bool mx, dfp4_tensor T, bool weight, void* prepared, hipStream_t stream) {
     const int64_t KB = T.K / kBlock;
+    if (!weight && T.rows < kPreparedMinRows) {
+        hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(64), 0, stream, static_cast<uint32_t*>(prepared));
+        return check_launch();
+    }
     GemmParams p{};
     dfp4_tensor none{};
     none.K = T.K;
@@ -1752,24 +1105,19 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     if (M == 0 || N == 0) return DFP4_OK;
     if (!shape_in_range(M, N, KB, 1, ldc)) return DFP4_ERR_SHAPE;
     const bool bf16 = out_dtype == DFP4_BF16;
+    if (KB == 0 || KB > kMaxKB) return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
     GemmParams p{};
     fill_params(p, A, W, out, ldc, 0, 0, 0, nullptr);
-    if (KB == 0 || KB > kMaxKB) return launch_other(mx, bf16, p, 1, nullptr, stream);
+    if (M < kPreparedMinRows) {
+        p.declined = static_cast<uint32_t*>(a_prepared);
+        if (N <= gemm_direct_max_rows(KB)) return launch_gemm_direct(mx, bf16, p, 1, stream);
+        return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
+    }
     if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     set_prepared(p, static_cast<uint8_t*>(a_prepared), 0, static_cast<uint8_t*>(const_cast<void*>(w_prepared)), 0);
-    if (takes_small_kernel(M, KB)) {
-        // few rows: the exact scheme in the shape of the few-rows kernel
-        dim3 gs((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32), 1);
-        const bool narrow = (int64_t)gs.x * gs.y > device_cu_count();     // as for gemm_small_kernel
-        dispatch_mx_bf16(mx, bf16, [&](auto mxc, auto bc) {
-            if (narrow)
-                hipLaunchKernelGGL((gemm_rows_kernel<decltype(mxc)::value, decltype(bc)::value, 8>), gs,
-                                   dim3(8 * 64), 0, stream, p);
-            else
-                hipLaunchKernelGGL((gemm_rows_kernel<decltype(mxc)::value, decltype(bc)::value, kSmallWaves>), gs,
-                                   dim3(kSmallWaves * 64), 0, stream, p);
-        });
-        return check_launch();
+    if (takes_direct_kernel(M, N, KB, 1, true) && N <= gemm_direct_max_rows(KB)) {
+        p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));
+        return launch_gemm_direct(mx, bf16, p, 1, stream);
     }
     return launch_fast(mx, bf16, p, 1, static_cast<int*>(workspace), workspace_bytes, false, stream);
 }

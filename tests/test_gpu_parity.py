@@ -1129,3 +1129,55 @@ def test_gemm_mixed_block_sizes(M, N, K, ba, bw):
         out = dfp4.gemm_blocks(qa, ba, qw, bw, dtype=dtype)
         torch.cuda.synchronize()
         _assert_gemm_close(out, ref, absdot, f"blocks {ba}x{bw} {dtype}", bf16=dtype == torch.bfloat16)
+
+
+# --------------------------------------------------------------------------
+# GEMM that expands both operands inside the kernel: every tile shape the size rule selects, at sizes that
+# end inside a tile, inside a group of 4 blocks and inside a wave's share of K
+# --------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,spread", [
+    (1, 33, 32, 0), (33, 31, 96, 0), (31, 1000, 4128, 0), (64, 65, 16384, 0),      # 32 x 32
+    (65, 2100, 1056, 0), (190, 2000, 512, 0),                                      # 64 x 64
+    (513, 3001, 2080, 0), (300, 2049, 16416, 0),                                   # 128 x 128, K in one and in two shares
+    (1500, 4000, 1120, 0),                                                         # 256 x 128
+    (40, 70, 512, 7), (130, 900, 512, 7), (777, 1300, 1024, 5),                    # classes on both operands
+    (40, 70, 1056, 30), (200, 1030, 544, 30), (513, 3001, 2080, 30)])              # tiles summed in fp32, block by block
+def test_gemm_direct_shapes(M, N, K, spread):
+    print(f"gemm direct: {M}x{N}x{K}, exponents over {spread} binades", flush=True)
+    g = torch.Generator().manual_seed(M + N + K)
+    def operand(rows, std):
+        x = torch.randn(rows, K // 32, 32, generator=g) * std
+        if spread:
+            x *= torch.exp2(torch.randint(0, spread + 1, (rows, K // 32, 1), generator=g).float())
+        return x.view(rows, K).to(torch.bfloat16)
+    a, w = operand(M, 1.0), operand(N, 0.02)
+    if not spread:
+        a[:, :: max(2, K // 8)] *= 50.0                          # outlier channels
+    qa, qw = dfp4.quantize(_dev(a)), dfp4.quantize(_dev(w))
+    ref, absdot = _gemm_ref(synth.to_f64(a), synth.to_f64(w))
+    out = dfp4.gemm(qa, qw)
+    torch.cuda.synchronize()
+    _assert_gemm_close(out, ref, absdot, "direct f32")
+    if not spread:
+        # one rounding of the exact sum (the float64 reference itself is exact at these sizes)
+        assert (np.abs(out.cpu().double().numpy() - ref) <= np.abs(ref) * 2.0 ** -24 + 1e-300).all()
+    out = dfp4.gemm(qa, qw, dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    _assert_gemm_close(out, ref, absdot, "direct bf16", bf16=True)
+    outm = dfp4.mxfp4_gemm(dfp4.mxfp4_quantize(_dev(a)), dfp4.mxfp4_quantize(_dev(w)))
+    torch.cuda.synchronize()
+    _assert_gemm_close(outm, *_gemm_ref(synth.to_f64(a), synth.to_f64(w), mx=True), "direct mxfp4")
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 300, 512), (257, 300, 512), (400, 2000, 1056), (1100, 1030, 2048)])
+def test_gemm_prepared_direct_shapes(M, N, K):
+    # prepared operands, few tiles: the references and masks of the prepared form, expansion in the kernel
+    a = synth.gaussian_outlier_channels(M, K, max(1, K // 100), 50.0, 1.0, seed=M)
+    w = synth.gaussian(N, K, 0.02, seed=N)
+    qa, qw = dfp4.quantize(_dev(a)), dfp4.quantize(_dev(w))
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    ref, _ = _gemm_ref(synth.to_f64(a), synth.to_f64(w))
+    out = dfp4.gemm_prepared(pa, pw)
+    torch.cuda.synchronize()
+    assert (np.abs(out.cpu().double().numpy() - ref) <= np.abs(ref) * 2.0 ** -24 + 1e-300).all()
+    assert dfp4.gemm_declined_tiles(pa) == 0
