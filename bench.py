@@ -532,7 +532,7 @@ def main():
             wps, ap1 = [dfp4.native_pack(q) for q in qws], dfp4.quantize_native(a1.to(dev))
             ms1n = median_ms(lambda: dfp4.gemm_native_packed(ap1, wps[0], out=o1), torch, 30, 5)
             ms1ns = stream_ms([(lambda w=w: dfp4.gemm_native_packed(ap1, w, out=o1)) for w in wps], torch)
-            b1n = (m1 + n1) * k1 * (1792 + 64) / 2048 + 4 * m1 * n1
+            b1n = (m1 + n1) * k1 * (1536 + 64) / 2048 + 4 * m1 * n1
             entry["native"] = {"ms": round(ms1n, 4), "stream_ms": round(ms1ns, 4),
                                "GBps": round(b1n / (ms1ns * 1e-3) / 1e9, 1),
                                "frac_hbm": round(b1n / (ms1ns * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),

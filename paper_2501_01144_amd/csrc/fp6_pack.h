@@ -32,9 +32,17 @@ __device__ __forceinline__ uint64_t pack6(uint32_t c, uint32_t tlo, uint32_t thi
     return (uint64_t)lo24 | ((uint64_t)hi24 << 24);
 }
 
-// Packed FP6 operand: per (32-row tile, step) 1792 bytes = 64 lanes x 16 bytes (registers 0..3) followed by
-// 64 lanes x 12 bytes (registers 4, 5, one unused dword); lane = 32 * (block % 2) + row % 32.
-constexpr int kFp6ChunkBytes = 1792;
+// Packed FP6 operand: per (pair of 32-row tiles, step) 3072 bytes = 64 lanes x 16 bytes (registers 0..3) of the even
+// tile, the same of the odd tile, then 64 lanes x 8 bytes (registers 4, 5) of the even and of the odd tile;
+// lane = 32 * (block % 2) + row % 32.  Every KiB is one direct load of a wave into LDS, and both parts are
+// read back at their own width (see gen_native_loop.py).
+constexpr int kFp6PairBytes = 3072;
+__host__ __device__ inline size_t fp6_lo(size_t tile, size_t step, size_t S) {
+    return ((tile >> 1) * S + step) * kFp6PairBytes + (tile & 1) * 1024;
+}
+__host__ __device__ inline size_t fp6_hi(size_t tile, size_t step, size_t S) {
+    return ((tile >> 1) * S + step) * kFp6PairBytes + 2048 + (tile & 1) * 512;
+}
 
 }  // namespace
 }  // namespace dfp4

@@ -19,14 +19,14 @@
 // register x of lane (h, c) is row 8 (x / 4) + 4 h + x % 4, column c.
 //
 // Kernels.  native_pack_kernel rewrites an operand in the order the matrix instruction
-// wants it (per 32-row tile and step, 64 lanes x 16 bytes, for FP6 followed by 64 lanes x 12
-// bytes of which 8 are used, plus one dword of four scale bytes per lane and group of four
+// wants it (per 32-row tile and step, 64 lanes x 16 bytes, for FP6 another 64 lanes x 8
+// bytes (fp6_pack.h), plus one dword of four scale bytes per lane and group of four
 // tiles), so that the multiply kernel's loads are whole lines; weights are packed once,
 // offline, and quantize_native_kernel (quantize.hip) writes an activation in this form
 // directly.  gemm_native_kernel: 256 x 256 outputs per workgroup, four waves as 2 x 2, each
 // 128 x 128 (16 accumulator tiles = 256 registers, one wave per SIMD), or 128 x 256 per
-// workgroup when there are few tiles; operands go global -> LDS by direct loads three (FP6)
-// or seven (FP4) steps ahead, LDS -> registers one step ahead, one barrier per step; the
+// workgroup when there are few tiles; operands go global -> LDS by direct loads five
+// or seven steps ahead, LDS -> registers one step ahead, one barrier per step; the
 // main loop is generated assembly (gen_native_loop.py).  With very few tiles K is split
 // between workgroups and native_reduce_kernel adds their fp32 partial tiles in a fixed order.
 #include <type_traits>
@@ -52,7 +52,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne_n(float f) {
 // Packed operands (written by native_pack_kernel): rows padded to a multiple of 256,
 // S = ceil(KB / 2) steps, a missing second block is all zeros.
 //   bits [row tile of 32][step][64 lanes x 16 bytes]                    FP4: registers 0..3 of the lane
-//        [row tile of 32][step][64 lanes x 16 bytes | 64 lanes x 12 bytes]   FP6: registers 0..3 | 4, 5, pad
+//        [pair of row tiles][step][3 KiB]                              FP6: see fp6_pack.h
 //   sc   [group of 4 row tiles][step][lane] dword: byte t = scale byte of row tile 4 g + t
 // Both arrays end with eight steps of slack: the loop loads up to seven steps ahead.
 struct PackedOperand {
@@ -92,22 +92,16 @@ __global__ __launch_bounds__(256) void native_pack_kernel(PackParams p) {
         eb = p.expo[blk];
         if constexpr (FMT == kFmtFp6) dl = p.dial ? ((uint32_t)p.dial[blk] & 15u) : 7u;
     }
-    const int64_t chunk = (int64_t)tile * p.S + s;
     if constexpr (FMT == kFmtFp4) {
-        reinterpret_cast<uint4*>(p.dst.bits)[chunk * 64 + lane] = codes;     // the MXFP4 code is the E2M1 bit pattern
+        reinterpret_cast<uint4*>(p.dst.bits)[((int64_t)tile * p.S + s) * 64 + lane] = codes;     // the MXFP4 code is the E2M1 bit pattern
     } else {
         const uint32_t tlo = g_fp6_book.w[dl][0], thi = g_fp6_book.w[dl][1];
         const uint64_t p0 = pack6(codes.x, tlo, thi), p1 = pack6(codes.y, tlo, thi);
         const uint64_t p2 = pack6(codes.z, tlo, thi), p3 = pack6(codes.w, tlo, thi);
-        uint32_t* d0 = reinterpret_cast<uint32_t*>(p.dst.bits + chunk * 1792 + lane * 16);
-        d0[0] = (uint32_t)p0;
-        d0[1] = (uint32_t)(p0 >> 32) | ((uint32_t)p1 << 16);
-        d0[2] = (uint32_t)(p1 >> 16);
-        d0[3] = (uint32_t)p2;
-        uint32_t* d1 = reinterpret_cast<uint32_t*>(p.dst.bits + chunk * 1792 + 1024 + lane * 12);
-        d1[0] = (uint32_t)(p2 >> 32) | ((uint32_t)p3 << 16);
-        d1[1] = (uint32_t)(p3 >> 16);
-        d1[2] = 0;
+        *reinterpret_cast<uint4*>(p.dst.bits + fp6_lo(tile, s, p.S) + lane * 16) =
+            make_uint4((uint32_t)p0, (uint32_t)(p0 >> 32) | ((uint32_t)p1 << 16), (uint32_t)(p1 >> 16), (uint32_t)p2);
+        *reinterpret_cast<uint2*>(p.dst.bits + fp6_hi(tile, s, p.S) + lane * 8) =
+            make_uint2((uint32_t)(p2 >> 32) | ((uint32_t)p3 << 16), (uint32_t)(p3 >> 16));
     }
     reinterpret_cast<uint8_t*>(p.dst.sc)[(((int64_t)(tile >> 2) * p.S + s) * 64 + lane) * 4 + (tile & 3)] = (uint8_t)eb;
 }
@@ -116,9 +110,10 @@ __global__ __launch_bounds__(256) void native_pack_kernel(PackParams p) {
 template <int FMT, bool BF16, int TA>
 __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
     constexpr bool kFp6 = FMT == kFmtFp6;
-    constexpr int kTileLds = kFp6 ? 2048 : 1024, kStage = (2 * TA + 8) * kTileLds + 1024, kStages = kFp6 ? 4 : 8;
+    constexpr int kTileLds = kFp6 ? 1536 : 1024, kStage = (2 * TA + 8) * kTileLds + 1024;
+    constexpr int kStages = kFp6 && TA == 4 ? 6 : 8;
     constexpr int kRowsWg = 64 * TA, kRowsWave = 32 * TA;
-    constexpr int kGStride = kFp6 ? 1792 : 1024;             // global bytes per (tile, step)
+    constexpr int kGStride = kFp6 ? kFp6PairBytes : 1024;    // global bytes per (pair of tiles, step) / (tile, step)
     __shared__ __attribute__((aligned(16))) uint8_t s_stage[kStages * kStage];
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
@@ -130,16 +125,18 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
     {
         const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(
             (int)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&s_stage[0]);
-        const uint32_t tstride = (uint32_t)p.S * (uint32_t)kGStride;      // bytes per tile
-        // this wave fetches A tiles 2w, 2w+1 and B tiles 2w, 2w+1 of the workgroup's 8 + 8, and scale chunk w
-        const uint64_t ab = reinterpret_cast<uint64_t>(p.a.bits) +
-                            ((uint64_t)blockIdx.y * (2 * TA) + (TA == 4 ? 2 * wave : wave)) * tstride;
-        const uint64_t bb = reinterpret_cast<uint64_t>(p.w.bits) + ((uint64_t)blockIdx.x * 8 + 2 * wave) * tstride;
+        const uint32_t tstride = (uint32_t)p.S * (uint32_t)kGStride;      // bytes per tile (FP4) / pair of tiles
+        // this wave fetches A tiles 2w, 2w+1 (128-row form: tile w) and B tiles 2w, 2w+1 of the workgroup's 8 + 8,
+        // and scale chunk w
+        const uint64_t a_tile = (uint64_t)blockIdx.y * (2 * TA) + (TA == 4 ? 2 * wave : wave);
+        const uint64_t b_tile = (uint64_t)blockIdx.x * 8 + 2 * wave;
+        const uint64_t ab = reinterpret_cast<uint64_t>(p.a.bits) + (kFp6 ? fp6_lo(a_tile, 0, p.S) : a_tile * tstride);
+        const uint64_t bb = reinterpret_cast<uint64_t>(p.w.bits) + (kFp6 ? fp6_lo(b_tile, 0, p.S) : b_tile * tstride);
         const uint64_t sb = wave < 2
             ? reinterpret_cast<uint64_t>(p.a.sc) + (TA == 4 ? (uint64_t)blockIdx.y * 2 + wave : (uint64_t)blockIdx.y) * (uint64_t)p.S * 256
             : reinterpret_cast<uint64_t>(p.w.sc) + ((uint64_t)blockIdx.x * 2 + (wave - 2)) * (uint64_t)p.S * 256;
-        const uint32_t l16 = (uint32_t)lane * 16u, l4 = (uint32_t)lane * 4u;
-        const uint32_t g16 = l16 + (uint32_t)s_lo * kGStride, g12 = (uint32_t)lane * 12u + (uint32_t)s_lo * kGStride;
+        const uint32_t l16 = (uint32_t)lane * 16u, l8 = (uint32_t)lane * 8u, l4 = (uint32_t)lane * 4u;
+        const uint32_t g16 = l16 + (uint32_t)s_lo * kGStride;
         const uint32_t g4 = l4 + (uint32_t)s_lo * 256u;
 #define DFP4_NATIVE_RUN(LOOP)                                                                                     \
         asm volatile(LOOP                                                                                           \
@@ -148,7 +145,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
                        [bhi] "s"((uint32_t)(bb >> 32)), [slo] "s"((uint32_t)sb), [shi] "s"((uint32_t)(sb >> 32)), \
                        [tstride] "s"(tstride), [wv] "s"(wave), [lds] "s"(lds),                                      \
                        [ldsend] "s"(lds + (uint32_t)(kStages * kStage)), [steps] "s"((uint32_t)S),                  \
-                       [l16] "v"(l16), [l4] "v"(l4), [g16] "v"(g16), [g12] "v"(g12), [g4] "v"(g4)                   \
+                       [l16] "v"(l16), [l8] "v"(l8), [l4] "v"(l4), [g16] "v"(g16), [g4] "v"(g4)                   \
                      : DFP4_NATIVE_VGPR_CLOBBERS, DFP4_NATIVE_ACC_CLOBBERS, DFP4_NATIVE_SGPR_CLOBBERS, "m0", "scc", \
                        "memory")
         if constexpr (kFp6 && TA == 4) DFP4_NATIVE_RUN(DFP4_NATIVE_LOOP_FP6);
@@ -245,20 +242,19 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
 template <int FMT, bool BF16>
 __global__ __launch_bounds__(1024) void gemm_native_small_kernel(NativeParams p) {
     constexpr bool kFp6 = FMT == kFmtFp6;
-    constexpr int kStride = kFp6 ? kFp6ChunkBytes : 1024;
     __shared__ float s_red[8][2][16][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kh = lane >> 5, c = lane & 31;
     const int S = p.S, t = blockIdx.x, mt = (p.M + 31) / 32;           // mt = 1 or 2 row tiles of A
     const int per = (S + 15) / 16, s_lo = wave * per, s_hi = min(S, s_lo + per);
     auto load = [&](const PackedOperand& src, int tile, int s, v8i& v, int& sc) {
-        const uint8_t* q = src.bits + ((int64_t)tile * S + s) * kStride;
-        const uint4 lo = *reinterpret_cast<const uint4*>(q + lane * 16);
+        const uint4 lo = *reinterpret_cast<const uint4*>(
+            src.bits + (kFp6 ? fp6_lo(tile, s, S) : ((size_t)tile * S + s) * 1024) + lane * 16);
         v = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, 0, 0, 0, 0};
         if constexpr (kFp6) {
-            const uint32_t* hi = reinterpret_cast<const uint32_t*>(q + 1024 + lane * 12);
-            v[4] = (int)hi[0];
-            v[5] = (int)hi[1];
+            const uint2 hi = *reinterpret_cast<const uint2*>(src.bits + fp6_hi(tile, s, S) + lane * 8);
+            v[4] = (int)hi.x;
+            v[5] = (int)hi.y;
         }
         sc = (int)(src.sc[((int64_t)(tile >> 2) * S + s) * 64 + lane] >> (8 * (tile & 3)));
     };
@@ -333,7 +329,7 @@ struct OperandLayout { int64_t sc, total; };
 inline OperandLayout operand_layout(int64_t rows, int64_t KB, bool fp6) {
     const int64_t S = (KB + 1) / 2, tiles = (rows + 255) / 256 * 8;
     OperandLayout l{};
-    l.sc = up256((tiles * S + 8) * (fp6 ? 1792 : 1024));
+    l.sc = up256(fp6 ? (tiles / 2 * S + 8) * kFp6PairBytes : (tiles * S + 8) * 1024);
     l.total = up256(l.sc + ((tiles / 4) * S + 8) * 256);
     return l;
 }

@@ -6,38 +6,43 @@ A workgroup computes 256 x 256 outputs with four waves as 2 x 2, each wave 128 x
 (4 x 4 tiles of 32 x 32, accumulator tile (i, j) in a[16 (4 i + j) : +15]).  One step =
 one pair of blocks (K = 64) = 16 MFMAs per wave.  A second form (suffix _H) halves the rows:
 128 x 256 per workgroup, 64 x 128 per wave, 8 MFMAs per step, for products with few tiles.  Both operands arrive pre-arranged in the
-instruction's register order (native_pack_kernel), so a (tile, step) chunk is 64 lanes x
-16 bytes (FP4), followed for FP6 by 64 lanes x 12 bytes (8 used: registers 4 and 5), and the loop only moves data:
+instruction's register order (native_pack_kernel): FP4 a (tile, step) chunk of 64 lanes x 16 bytes; FP6 a
+(pair of tiles, step) chunk of 3 KiB, 64 lanes x 16 bytes (registers 0..3) of either tile, then 64 lanes x 8 bytes
+(registers 4, 5) of either.  The loop only moves data:
 
-  global -> LDS  direct loads (global_load_lds_dwordx4 / dwordx3; a lane's 12 bytes land
-                 at a 16-byte lane stride), three (FP6) or seven (FP4) steps ahead, four or eight LDS
-                 stages in rotation;
-                 wave w fetches A tiles 2w, 2w+1, B tiles 2w, 2w+1 and scale chunk w;
+  global -> LDS  direct loads (global_load_lds_dwordx4, whole KiB), five or seven steps ahead, six or
+                 eight LDS stages in rotation;
+                 wave w fetches A tiles 2w, 2w+1, B tiles 2w, 2w+1 and scale chunk w; in the 128-row form
+                 A tile w, and of an FP6 pair's last KiB both waves of the pair write the same copy;
   LDS -> regs    the wave's 4 A and 4 B tiles and two scale dwords of step s + 1 are read
                  during step s (two register sets used alternately);
   one barrier per step, in the middle of the MFMA stream: after it every wave's loads of
   step s + 1 have landed and nobody reads the stage that this step's loads overwrite.
 
-LDS stage: 16 tiles x TILE bytes (A tiles 0..7, B tiles 0..7; TILE = 1 KiB for FP4, 2 KiB
-for FP6: two 1 KiB halves) + 4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).
+LDS stage: the chunks of A tiles 0..7 and B tiles 0..7 as in memory (1 KiB per tile for FP4, 3 KiB per pair
+for FP6) + 4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).  The loop of the FP6 form is bound by LDS: a step
+reads 8 tiles in each of 4 waves and writes 16.  With registers 4, 5 kept at 8 bytes per lane a tile costs
+12 + 12 cycles of the 128 byte/cycle pipe; at the 16-byte stride that 12-byte direct loads leave, the
+8-byte reads cost as much as 16-byte ones (16 + 16).  MLP pass of 2048 rows, 4096 x 14336
+(3 products + 2 quantizers): 290 us with the 16-byte stride and four stages, 260 us so.
 
 Registers (fixed): a[0:255] accumulators; v[40:87] / v[88:135] operand sets (A tile i at
 +6 i, B tile j at +24 + 6 j); v136..v139 scale dwords (A, B of set 0; A, B of set 1);
-v144 / v145 / v146 global offsets (operands, scales, second halves), v150.. LDS read bases
+v144 / v145 global offsets (operands, scales), v150.. LDS read bases
 (the loop is unrolled over the stages, so a stage is a base register plus an immediate);
-s[60:69] global bases of the wave's five chunks, s70 step, s74 / s75 scratch, s77..s83 the
-wave's LDS addresses inside stage 0 (reads: A, B, scales A, B; loads: A, B, scales).
+s[60:69] global bases of the wave's five chunks, s70 step, s74 / s75 scratch, s77..s84 the
+wave's LDS addresses inside stage 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the 128-row form).
 """
 import os
 
 FR = [40, 88]
 SA = [136, 138]
 SB = [137, 139]
-VOFF, VSOFF, VOFF2 = 144, 145, 146
-VBASE = 150                      # LDS read bases: group q at VBASE + 4 q: operands A, B, scales A, B
+VOFF, VSOFF = 144, 145
+VBASE = 150                      # LDS read bases: group q at VBASE + 6 q: operands A, B, scales A, B, registers 4, 5 of A, B
 S_BASE, S_VC = 60, 70
 S_T0, S_T1 = 74, 75
-S_RA, S_RB, S_RSA, S_RSB, S_DA, S_DB, S_DS = 77, 78, 79, 80, 81, 82, 83
+S_RA, S_RB, S_RSA, S_RSB, S_DA, S_DB, S_DS, S_DA2 = 77, 78, 79, 80, 81, 82, 83, 84
 
 
 def vr(n, cnt=1):
@@ -53,30 +58,33 @@ class Fmt:
         self.fp6 = fp6
         self.ta = ta                                 # A tiles (of 32 rows) per wave: 4 (256-row workgroup) or 2 (128)
         self.regs = 6 if fp6 else 4
-        self.tile = 2048 if fp6 else 1024            # LDS bytes per tile and stage
+        self.tile = 1536 if fp6 else 1024            # LDS bytes per tile and stage
         self.stage = (2 * ta + 8) * self.tile + 1024
-        self.gstride = 1792 if fp6 else 1024         # global bytes per (tile, step): 1024 + 768
+        self.gstride = 3072 if fp6 else 1024         # global bytes per (pair of tiles, step) / (tile, step)
         self.code = 2 if fp6 else 4                  # cbsz / blgp
-        a_tiles = ta // 2                            # A tiles this wave fetches per step (B: always 2)
-        self.per_step = (a_tiles + 2) * (2 if fp6 else 1) + 1     # direct loads per wave and step
-        self.nst = 4 if fp6 else 8                   # LDS stages (FP6: 4 x 33 KiB, FP4: 8 x 17 KiB)
+        # direct loads per wave and step: A, B, scales
+        self.per_step = (3 if ta == 4 else 2) + 3 + 1 if fp6 else ta // 2 + 2 + 1
+        self.nst = 6 if fp6 and ta == 4 else 8       # LDS stages (FP6: 6 x 25 KiB or 8 x 19 KiB, FP4: 8 x 17 or 13 KiB)
         self.dist = self.nst - 1                     # loads run this many steps ahead
         # LDS reads address a stage as (base register of its group) + immediate (< 64 KiB)
-        self.per_group = max(1, (65535 - (3 * self.tile + 1024 + 16)) // self.stage)
+        self.per_group = (65535 - 4 * self.tile) // self.stage
         self.groups = (self.nst + self.per_group - 1) // self.per_group
 
 
 def frag_reads(f, p, stage):
     """LDS reads of the operands held in `stage` into register set p."""
     q, off = stage // f.per_group, (stage % f.per_group) * f.stage
-    va, vb, vsa, vsb = (VBASE + 4 * q + i for i in range(4))
+    va, vb, vsa, vsb, va2, vb2 = (VBASE + 6 * q + i for i in range(6))
     o = []
-    for side, v in ((0, va), (1, vb)):
+    for side, v, v2 in ((0, va, va2), (1, vb, vb2)):
         for t in range(f.ta if side == 0 else 4):
             r = FR[p] + 24 * side + 6 * t
-            o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{off + t * f.tile}")
             if f.fp6:
-                o.append(f"ds_read_b64 {vr(r + 4, 2)}, {vr(v)} offset:{off + t * f.tile + 1024}")
+                pair = off + (t >> 1) * 3072
+                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{pair + (t & 1) * 1024}")
+                o.append(f"ds_read_b64 {vr(r + 4, 2)}, {vr(v2)} offset:{pair + 2048 + (t & 1) * 512}")
+            else:
+                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{off + t * f.tile}")
     o.append(f"ds_read_b32 {vr(SA[p])}, {vr(vsa)} offset:{off}")
     o.append(f"ds_read_b32 {vr(SB[p])}, {vr(vsb)} offset:{off}")
     return o
@@ -84,23 +92,33 @@ def frag_reads(f, p, stage):
 
 def dma_groups(f, stage):
     """Direct loads of one step of this wave into `stage`, as groups (m0 setup, [loads that use it]).
-    An instruction offset applies to the global and to the LDS address alike, and the second half of an
-    FP6 chunk sits 1024 bytes behind the first in both, so the two halves share one m0."""
+    An instruction offset applies to the global and to the LDS address alike, so the loads of one FP6
+    chunk share one m0."""
     o = []
-    for side, dst in ((0, S_DA), (1, S_DB)):
-        for k in range(f.ta // 2 if side == 0 else 2):
-            base = sr(S_BASE + 4 * side + 2 * k, 2)
-            loads = [f"global_load_lds_dwordx4 {vr(VOFF)}, {base}"]
-            if f.fp6:
-                loads.append(f"global_load_lds_dwordx3 {vr(VOFF2)}, {base} offset:1024")
-            o.append((f"s_add_u32 m0, {sr(dst)}, {stage * f.stage + k * f.tile}", loads))
+
+    def group(dst, base, offsets, disp=0):
+        at = f"{vr(VOFF)}, {sr(S_BASE + 2 * base, 2)}"
+        o.append((f"s_add_u32 m0, {sr(dst)}, {stage * f.stage + disp}",
+                  [f"global_load_lds_dwordx4 {at}" + (f" offset:{x}" if x else "") for x in offsets]))
+
+    if f.fp6:
+        if f.ta == 4:
+            group(S_DA, 0, (0, 1024, 2048))
+        else:
+            group(S_DA, 0, (0,))
+            group(S_DA2, 1, (2048,))
+        group(S_DB, 2, (0, 1024, 2048))
+    else:
+        for k in range(f.ta // 2):
+            group(S_DA, k, (0,), k * f.tile)
+        for k in range(2):
+            group(S_DB, 2 + k, (0,), k * f.tile)
     o.append((f"s_add_u32 m0, {sr(S_DS)}, {stage * f.stage}", [f"global_load_lds_dword {vr(VSOFF)}, {sr(S_BASE + 8, 2)}"]))
     return o
 
 
 def advance_global(f):
-    return [f"v_add_u32 {vr(VOFF)}, {f.gstride}, {vr(VOFF)}", f"v_add_u32 {vr(VSOFF)}, 0x100, {vr(VSOFF)}"] + (
-        [f"v_add_u32 {vr(VOFF2)}, {f.gstride}, {vr(VOFF2)}"] if f.fp6 else [])
+    return [f"v_add_u32 {vr(VOFF)}, {f.gstride}, {vr(VOFF)}", f"v_add_u32 {vr(VSOFF)}, 0x100, {vr(VSOFF)}"]
 
 
 def mfma(f, p, k):
@@ -122,7 +140,9 @@ def step(f, u):
     # after the barrier: every m0 setup is followed by an LDS read (m0 needs one instruction before its use)
     tail = []
     for m0, loads in dmas:
-        tail.append([m0] + ([reads.pop(0)] if reads else ["s_nop 0"]) + loads)
+        tail.append([m0] + ([reads.pop(0)] if reads else ["s_nop 0"]) + loads[:1])
+        for ld in loads[1:]:
+            tail.append([ld] + [reads.pop(0) for _ in range(min(2, len(reads)))])
     while reads:
         tail.append([reads.pop(0)] + ([reads.pop(0)] if reads else []))
     nm = 4 * f.ta                     # MFMAs per step
@@ -145,7 +165,8 @@ def step(f, u):
 
 def entry(f):
     o = [f"v_accvgpr_write_b32 a{n}, 0" for n in range(256)]
-    # global bases: A tiles 2w, 2w+1; B tiles 2w, 2w+1 (each tile holds `tstride` bytes); scale chunk
+    # global bases: FP4 A tiles 2w, 2w+1 and B tiles 2w, 2w+1 (each tile holds `tstride` bytes); FP6 A pair w and B
+    # pair w, or in the 128-row form A tile w and (second base) its pair; scale chunk
     o += [f"s_mov_b32 {sr(S_BASE)}, %[alo]", f"s_mov_b32 {sr(S_BASE + 1)}, %[ahi]",
           f"s_add_u32 {sr(S_BASE + 2)}, %[alo], %[tstride]", f"s_addc_u32 {sr(S_BASE + 3)}, %[ahi], 0",
           f"s_mov_b32 {sr(S_BASE + 4)}, %[blo]", f"s_mov_b32 {sr(S_BASE + 5)}, %[bhi]",
@@ -167,6 +188,12 @@ def entry(f):
           f"s_mul_i32 {sr(S_DA)}, %[wv], {(f.ta // 2) * f.tile}", f"s_add_u32 {sr(S_DA)}, {sr(S_DA)}, %[lds]",
           f"s_mul_i32 {sr(S_DB)}, %[wv], {2 * f.tile}", f"s_add_u32 {sr(S_DB)}, {sr(S_DB)}, {offb}",
           f"s_add_u32 {sr(S_DB)}, {sr(S_DB)}, %[lds]"]
+    if f.fp6 and f.ta == 2:           # A tile w inside pair w / 2: 1 KiB apart, in memory and in LDS
+        o += [f"s_lshl_b32 {sr(S_RSA)}, {sr(S_T1)}, 10",
+              f"s_sub_u32 {sr(S_BASE + 2)}, %[alo], {sr(S_RSA)}", f"s_subb_u32 {sr(S_BASE + 3)}, %[ahi], 0",
+              f"s_mul_i32 {sr(S_DA2)}, {sr(S_T0)}, 3072", f"s_add_u32 {sr(S_DA2)}, {sr(S_DA2)}, %[lds]",
+              f"s_add_u32 {sr(S_DA)}, {sr(S_DA2)}, {sr(S_RSA)}",
+              f"s_mov_b32 {sr(S_RSA)}, {offs}", f"s_add_u32 {sr(S_RSA)}, {sr(S_RSA)}, %[lds]"]
     if f.ta == 4:
         o += [f"s_lshl_b32 {sr(S_DS)}, %[wv], 8"]
     else:                             # scale chunks: wave 0 and 1 -> the A group (slot 0), waves 2, 3 -> B groups (slots 2, 3)
@@ -175,10 +202,13 @@ def entry(f):
           f"s_lshl_b32 {sr(S_T1)}, {sr(S_T0)}, 4"]              # S_T1 = 16 wm: shift of the A scale dword (128-row form)
     for q in range(f.groups):
         goff = q * f.per_group * f.stage
-        for i, (s, lane) in enumerate(((S_RA, "%[l16]"), (S_RB, "%[l16]"), (S_RSA, "%[l4]"), (S_RSB, "%[l4]"))):
-            o += [f"s_add_u32 {sr(S_T0)}, {sr(s)}, {goff}", f"v_add_u32 {vr(VBASE + 4 * q + i)}, {sr(S_T0)}, {lane}"]
+        bases = [(S_RA, "%[l16]"), (S_RB, "%[l16]"), (S_RSA, "%[l4]"), (S_RSB, "%[l4]")]
+        if f.fp6:
+            bases += [(S_RA, "%[l8]"), (S_RB, "%[l8]")]
+        for i, (s, lane) in enumerate(bases):
+            o += [f"s_add_u32 {sr(S_T0)}, {sr(s)}, {goff}", f"v_add_u32 {vr(VBASE + 6 * q + i)}, {sr(S_T0)}, {lane}"]
     o += [f"s_mov_b32 {sr(S_VC)}, 0",
-          f"v_mov_b32 {vr(VOFF)}, %[g16]", f"v_mov_b32 {vr(VSOFF)}, %[g4]", f"v_mov_b32 {vr(VOFF2)}, %[g12]"]
+          f"v_mov_b32 {vr(VOFF)}, %[g16]", f"v_mov_b32 {vr(VSOFF)}, %[g4]"]
     # pipeline fill: steps 0 .. dist-1 into stages 0 .. dist-1
     for st in range(f.dist):
         for m0, loads in dma_groups(f, st):
@@ -218,7 +248,7 @@ def main():
         parts.append(f"#define DFP4_NATIVE_ACC_READ_{g} \\\n" + c_string(rd) + "\n")
     vclob = ", ".join(f'"v{n}"' for n in range(40, 170))
     aclob = ", ".join(f'"a{n}"' for n in range(256))
-    sclob = ", ".join(f'"s{n}"' for n in range(S_BASE, S_DS + 1))
+    sclob = ", ".join(f'"s{n}"' for n in range(S_BASE, S_DA2 + 1))
     parts.append(f"#define DFP4_NATIVE_VGPR_CLOBBERS {vclob}\n")
     parts.append(f"#define DFP4_NATIVE_ACC_CLOBBERS {aclob}\n")
     parts.append(f"#define DFP4_NATIVE_SGPR_CLOBBERS {sclob}\n")

@@ -225,19 +225,17 @@ __global__ __launch_bounds__(kThreads) void quantize_native_kernel(
             const uint32_t next_mid = quad<0x39>(mid32);
             const uint32_t lo_of_2 = quad<0xAA>(lo32);                 // lane 2's low dword
             const uint32_t tile = row >> 5, slot = kh * 32u + (row & 31u);
-            uint8_t* chunk = bits + ((size_t)tile * S + step) * kFp6ChunkBytes;
             // a step past the last one of an odd-length group does not exist; a missing second block
             // (odd KB) is written as zeros with a finite scale so that it multiplies to zero
             const bool step_ok = row_ok && step < S;
             if (step_ok && sub == 0) {
                 const uint4 v = on[p] ? make_uint4(lo32, hi16 | (next_lo << 16), next_mid, lo_of_2) : make_uint4(0, 0, 0, 0);
-                *reinterpret_cast<uint4*>(chunk + slot * 16u) = v;
+                *reinterpret_cast<uint4*>(bits + fp6_lo(tile, step, S) + slot * 16u) = v;
                 scales[(((size_t)(tile >> 2) * S + step) * 64u + slot) * 4u + (tile & 3u)] = on[p] ? (uint8_t)eb : (uint8_t)0;
             }
             if (step_ok && sub == 2) {
-                uint32_t* d = reinterpret_cast<uint32_t*>(chunk + 1024u + slot * 12u);       // 4-byte aligned only
-                d[0] = on[p] ? (hi16 | (next_lo << 16)) : 0u;
-                d[1] = on[p] ? next_mid : 0u;
+                *reinterpret_cast<uint2*>(bits + fp6_hi(tile, step, S) + slot * 8u) =
+                    on[p] ? make_uint2(hi16 | (next_lo << 16), next_mid) : make_uint2(0, 0);
             }
         }
     }
