@@ -1181,3 +1181,19 @@ def test_gemm_prepared_direct_shapes(M, N, K):
     torch.cuda.synchronize()
     assert (np.abs(out.cpu().double().numpy() - ref) <= np.abs(ref) * 2.0 ** -24 + 1e-300).all()
     assert dfp4.gemm_declined_tiles(pa) == 0
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,K", [(1, 32), (1, 2016), (2, 1024), (5, 416), (257, 64)])
+def test_dequantize_around_64_blocks(rows, K, dtype):
+    # 1, 63, 64, 65 and 514 blocks: a wave takes 64; contiguous and strided outputs
+    x = synth.student_t(rows, K, 3.0, seed=rows + K)
+    q = dfp4.quantize(_dev(x))
+    ref = O.dfp4_dequantize(*O.dfp4_quantize(synth.to_f64(x)))
+    wide = torch.full((rows, K + 32), 7.0, dtype=dtype, device="cuda")
+    y = dfp4.dequantize(q, dtype)
+    dfp4.dequantize(q, out=wide[:, 16:16 + K])
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().double().numpy(), ref)
+    assert np.array_equal(wide[:, 16:16 + K].cpu().double().numpy(), ref)
+    assert bool((wide[:, :16] == 7).all()) and bool((wide[:, 16 + K:] == 7).all())
