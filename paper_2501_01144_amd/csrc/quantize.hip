@@ -249,25 +249,35 @@ __global__ __launch_bounds__(kThreads) void quantize_native_kernel(
 // but contracted over the sequence.  A workgroup loads a 128 x 64 tile (whole
 // 128-byte lines), transposes it through LDS and runs the same per-block
 // arithmetic as quantize_kernel: thread (column c, quarter sub) handles rows
-// 32 p + 8 sub .. + 7 of column c for p = 0..3.
+// 32 p + 8 sub .. + 7 of column c for p = 0..3.  A workgroup lives for one tile of 16 KiB, so what it does besides
+// counts: the 768-byte tables (the 24 KiB ones, filled by every workgroup, were more traffic than the input and
+// left room for 3 workgroups per compute unit) and 16-byte stores after an exchange within the quad.
+// P V of attention, 4 x 32 heads of 2048 (4 transposed quantizers of 2048 x 4096 among it): 503 -> 481 us a pass.
 // ---------------------------------------------------------------------------
 constexpr int kTRows = 128, kTCols = 64, kTPitch = 66;     // LDS row pitch in bf16 (33 dwords: no bank conflicts)
+
+// lanes of a quad a step apart (CTRL) exchange halves of a pair of registers: the lane with `odd` unset keeps a and
+// receives the other's a in b, the other keeps b and receives b in a
+template <int CTRL>
+__device__ __forceinline__ void exchange(uint32_t& a, uint32_t& b, uint32_t odd) {
+    const uint32_t recv = quad<CTRL>(odd ? a : b);
+    if (odd) a = recv;
+    else b = recv;
+}
 
 template <bool MX>
 __global__ __launch_bounds__(256) void quantize_t_kernel(
     const uint16_t* __restrict__ x, int64_t ld, uint32_t rows, uint32_t cols, uint32_t out_blocks, uint32_t block0,
-    uint32_t* __restrict__ codes, uint8_t* __restrict__ dialect, uint8_t* __restrict__ exponent) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds_q[MX ? 64 : kDialects * 1024];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_s[MX ? 16 : kPairs * 1024];
+    uint32_t wide /* `codes` is 16-byte aligned */, uint32_t* __restrict__ codes, uint8_t* __restrict__ dialect, uint8_t* __restrict__ exponent) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds_q[MX ? 64 : kDialects * 32];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_s[MX ? 16 : kPairs * 32];
     __shared__ __attribute__((aligned(4))) uint16_t s_x[kTRows * kTPitch];
     const uint32_t tid = threadIdx.x;
     if constexpr (MX) {
         if (tid < 64) lds_q[tid] = g_quant_tables.mx[tid];
     } else {
-        const uint4* gq = reinterpret_cast<const uint4*>(g_quant_tables.q);
-        const uint4* gs = reinterpret_cast<const uint4*>(g_quant_tables.s);
-        for (uint32_t i = tid; i < 1024u; i += 256u) reinterpret_cast<uint4*>(lds_q)[i] = gq[i];
-        for (uint32_t i = tid; i < 512u; i += 256u) reinterpret_cast<uint4*>(lds_s)[i] = gs[i];
+        if (tid < 32) reinterpret_cast<uint4*>(lds_q)[tid] = reinterpret_cast<const uint4*>(g_quant_tables.near_i)[tid];
+        else if (tid < 48) reinterpret_cast<uint4*>(lds_s)[tid - 32] = reinterpret_cast<const uint4*>(g_quant_tables.vote1)[tid - 32];
     }
     const uint32_t r0 = blockIdx.y * kTRows, c0 = blockIdx.x * kTCols;
     // load: 8 threads per row (8 bf16 = 16 bytes each), 32 rows per sweep
@@ -285,6 +295,7 @@ __global__ __launch_bounds__(256) void quantize_t_kernel(
     // rows of a longer sequence, written at block column block0)
     const uint32_t kb_in = rows / kBlock;
     const bool col_ok = c0 + c < cols;
+    uint32_t code[4], eb[4], dl[4] = {0, 0, 0, 0};
 #pragma unroll
     for (uint32_t p = 0; p < kTRows / kBlock; ++p) {
         const uint32_t rb = p * kBlock + sub * 8u;             // first of this lane's 8 rows
@@ -293,18 +304,27 @@ __global__ __launch_bounds__(256) void quantize_t_kernel(
         for (int j = 0; j < 4; ++j)
             w[j] = (uint32_t)s_x[(rb + 2 * j) * kTPitch + c] | ((uint32_t)s_x[(rb + 2 * j + 1) * kTPitch + c] << 16);
         const uint4 wv = make_uint4(w[0], w[1], w[2], w[3]);
-        uint32_t code, eb, dl = 0;
-        if constexpr (MX) mxfp4_pass(wv, lds_q, code, eb);
-        else dfp4_pass(wv, lds_s, lds_q, code, eb, dl);
-        const uint32_t blk_row = (r0 >> 5) + p;                // block index along the original rows
-        if (col_ok && blk_row < kb_in) {
-            const size_t blk = (size_t)(c0 + c) * out_blocks + block0 + blk_row;
-            codes[blk * 4u + sub] = code;
-            if (sub == 0) {
-                exponent[blk] = (uint8_t)eb;
-                if constexpr (!MX) dialect[blk] = (uint8_t)dl;
-            }
+        if constexpr (MX) mxfp4_pass(wv, lds_q, code[p], eb[p]);
+        else dfp4_pass_small(wv, lds_s, lds_q, code[p], eb[p], dl[p]);
+    }
+    // the quad's 4 x 4 code dwords transposed (lane `sub` had dword sub of blocks 0..3, gets the whole block sub),
+    // so that a lane stores 16 bytes and a quad the 64 of its column's four blocks
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) exchange<0xB1>(code[j], code[j + 1], sub & 1u);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) exchange<0x4E>(code[j], code[j + 2], sub & 2u);
+    const uint32_t blk_row = (r0 >> 5) + sub;                  // block index along the original rows
+    if (col_ok && blk_row < kb_in) {
+        const size_t blk = (size_t)(c0 + c) * out_blocks + block0 + blk_row;
+        uint32_t* dst = codes + blk * 4u;                      // `codes` is only as aligned as the caller's buffer: 4 bytes
+        if (wide) {
+            *reinterpret_cast<uint4*>(dst) = make_uint4(code[0], code[1], code[2], code[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dst[j] = code[j];
         }
+        exponent[blk] = (uint8_t)(sub == 0 ? eb[0] : sub == 1 ? eb[1] : sub == 2 ? eb[2] : eb[3]);
+        if constexpr (!MX) dialect[blk] = (uint8_t)(sub == 0 ? dl[0] : sub == 1 ? dl[1] : sub == 2 ? dl[2] : dl[3]);
     }
 }
 
@@ -448,12 +468,12 @@ int launch_quantize_t(bool mx, const void* x, int64_t rows, int64_t cols, int64_
     uint32_t* cp = reinterpret_cast<uint32_t*>(out.codes);
     if (mx)
         hipLaunchKernelGGL((quantize_t_kernel<true>), grid, dim3(256), 0, stream, xp, ld, (uint32_t)rows,
-                           (uint32_t)cols, (uint32_t)(out.K / kBlock), (uint32_t)(row_offset / kBlock), cp,
-                           out.dialect, out.exponent);
+                           (uint32_t)cols, (uint32_t)(out.K / kBlock), (uint32_t)(row_offset / kBlock),
+                           aligned(cp, 16) ? 1u : 0u, cp, out.dialect, out.exponent);
     else
         hipLaunchKernelGGL((quantize_t_kernel<false>), grid, dim3(256), 0, stream, xp, ld, (uint32_t)rows,
-                           (uint32_t)cols, (uint32_t)(out.K / kBlock), (uint32_t)(row_offset / kBlock), cp,
-                           out.dialect, out.exponent);
+                           (uint32_t)cols, (uint32_t)(out.K / kBlock), (uint32_t)(row_offset / kBlock),
+                           aligned(cp, 16) ? 1u : 0u, cp, out.dialect, out.exponent);
     return check_launch();
 }
 

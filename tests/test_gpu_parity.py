@@ -1183,6 +1183,19 @@ def test_gemm_prepared_direct_shapes(M, N, K):
     assert dfp4.gemm_declined_tiles(pa) == 0
 
 
+@pytest.mark.parametrize("rows,cols,skip", [(32, 8, 0), (96, 72, 4), (128, 64, 0), (160, 136, 12)])
+def test_quantize_t_tile_edges_and_code_alignment(rows, cols, skip):
+    # part tiles of 128 x 64, and codes that are only 4-byte aligned (16-byte stores are not taken)
+    x = synth.student_t(rows, cols, 3.0, seed=rows + cols)
+    n = cols * rows // 2
+    buf = torch.full((skip + n + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+    meta = [torch.empty((cols, rows // 32), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    q = dfp4.quantize_t(_dev(x), out=dfp4.QTensor(buf[skip:skip + n].view(cols, rows // 2), *meta, cols, rows))
+    torch.cuda.synchronize()
+    _assert_quant_equal(q, O.dfp4_quantize(synth.to_f64(x).T.copy()), f"quantize_t {rows}x{cols} + {skip}")
+    assert bool((buf[:skip] == 0xA5).all()) and bool((buf[skip + n:] == 0xA5).all())
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,K", [(1, 32), (1, 2016), (2, 1024), (5, 416), (257, 64)])
 def test_dequantize_around_64_blocks(rows, K, dtype):
