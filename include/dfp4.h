@@ -288,8 +288,8 @@ size_t dfp4_gemm_native_workspace_bytes(int64_t M, int64_t N, int64_t K);
  */
 size_t dfp4_native_packed_bytes(int64_t rows, int64_t K);
 /* Online DialectFP4 quantization (as dfp4_quantize) straight into the packed form: equal to
- * dfp4_quantize followed by dfp4_native_pack, except that the layout's padding rows are left
- * untouched (they only reach outputs that are never stored).  x as for dfp4_quantize. */
+ * dfp4_quantize followed by dfp4_native_pack; the whole of the dfp4_native_packed_bytes(rows, K) is
+ * written, the layout's padding as zeros.  x as for dfp4_quantize. */
 int dfp4_quantize_native(const void* x_bf16, int64_t rows, int64_t K, int64_t ld_elems, void* packed,
                          size_t bytes, void* stream);
 int dfp4_native_pack(dfp4_tensor T, void* packed, size_t bytes, void* stream);

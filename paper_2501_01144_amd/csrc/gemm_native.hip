@@ -329,8 +329,8 @@ struct OperandLayout { int64_t sc, total; };
 inline OperandLayout operand_layout(int64_t rows, int64_t KB, bool fp6) {
     const int64_t S = (KB + 1) / 2, tiles = (rows + 255) / 256 * 8;
     OperandLayout l{};
-    l.sc = up256(fp6 ? (tiles / 2 * S + 8) * kFp6PairBytes : (tiles * S + 8) * 1024);
-    l.total = up256(l.sc + ((tiles / 4) * S + 8) * 256);
+    l.sc = up256(fp6 ? (tiles / 2 * S + kSlackSteps) * kFp6PairBytes : (tiles * S + kSlackSteps) * 1024);
+    l.total = up256(l.sc + ((tiles / 4) * S + kSlackSteps) * 256);
     return l;
 }
 

@@ -443,7 +443,8 @@ def quantize_native(x, buf=None):
     rows, K = x.shape
     n = int(load().dfp4_native_packed_bytes(rows, K))
     if buf is None:
-        buf = torch.zeros(max(n, 256), dtype=torch.uint8, device=x.device)
+        buf = torch.empty(n, dtype=torch.uint8, device=x.device) if n else \
+            torch.zeros(256, dtype=torch.uint8, device=x.device)
     ld = x.stride(0) if rows > 1 else K
     _check(load().dfp4_quantize_native(_ptr(x), rows, K, ld, _ptr(buf), buf.numel(), _stream()), "dfp4_quantize_native")
     return PackedWeights(buf, rows, K, False)

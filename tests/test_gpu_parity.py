@@ -1183,6 +1183,18 @@ def test_gemm_prepared_direct_shapes(M, N, K):
     assert dfp4.gemm_declined_tiles(pa) == 0
 
 
+@pytest.mark.parametrize("rows,K", [(1, 32), (33, 96), (256, 64), (257, 320)])
+def test_quantize_native_writes_the_whole_buffer(rows, K):
+    # padding rows, the missing block of an odd K / 32 and the slack behind either array leave as zeros
+    x = synth.student_t(rows, K, 3.0, seed=rows + K).cuda()
+    n = int(dfp4.load().dfp4_native_packed_bytes(rows, K))
+    want = dfp4.native_pack(dfp4.quantize(x), buf=torch.zeros(n, dtype=torch.uint8, device="cuda"))
+    dirty = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    dfp4.quantize_native(x, buf=dirty)
+    torch.cuda.synchronize()
+    assert torch.equal(dirty[:n], want.buf) and bool((dirty[n:] == 0xA5).all())
+
+
 @pytest.mark.parametrize("rows,cols,skip", [(32, 8, 0), (96, 72, 4), (128, 64, 0), (160, 136, 12)])
 def test_quantize_t_tile_edges_and_code_alignment(rows, cols, skip):
     # part tiles of 128 x 64, and codes that are only 4-byte aligned (16-byte stores are not taken)
