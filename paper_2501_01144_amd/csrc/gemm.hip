@@ -1115,7 +1115,7 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     }
     if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     set_prepared(p, static_cast<uint8_t*>(a_prepared), 0, static_cast<uint8_t*>(const_cast<void*>(w_prepared)), 0);
-    if (takes_direct_kernel(M, N, KB, 1, true) && N <= gemm_direct_max_rows(KB)) {
+    if (takes_direct_kernel(M, N, KB, 1, true) && (M > N ? M : N) <= gemm_direct_max_rows(KB)) {
         p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));
         return launch_gemm_direct(mx, bf16, p, 1, stream);
     }

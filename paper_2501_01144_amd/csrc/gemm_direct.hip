@@ -543,8 +543,12 @@ float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch) {
     return us;
 }
 
-// The kernel addresses an operand with 32-bit byte offsets: at most this many rows in one launch
-int64_t gemm_direct_max_rows(int64_t KB) { return (((int64_t)1 << 28) / (KB > 0 ? KB : 1)) / 512 * 512; }
+// At most this many rows of an operand in one launch: the kernel addresses it with 32-bit byte offsets, and the rows
+// of A give at most 65535 tiles of the smallest shape along the grid's y
+int64_t gemm_direct_max_rows(int64_t KB) {
+    const int64_t offsets = ((int64_t)1 << 28) / (KB > 0 ? KB : 1), grid_y = (int64_t)65535 * 32;
+    return (offsets < grid_y ? offsets : grid_y) / 512 * 512;
+}
 
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
     float us;

@@ -1183,6 +1183,22 @@ def test_gemm_prepared_direct_shapes(M, N, K):
     assert dfp4.gemm_declined_tiles(pa) == 0
 
 
+def test_gemm_direct_rows_beyond_one_launch():
+    # more rows than 65535 tiles of 32: the product is cut into launches; every output is the exact sum
+    M, N, K = 65535 * 32 + 700, 5, 32
+    print(f"gemm direct: {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    qa = dfp4.quantize(torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16))
+    qw = dfp4.quantize(torch.randn(N, K, generator=g, device="cuda").to(torch.bfloat16))
+    a, w = dfp4.dequantize(qa, torch.float32).double(), dfp4.dequantize(qw, torch.float32).double()
+    want = torch.zeros(M, N, dtype=torch.float64, device="cuda")     # sums of at most 32 products: exact in float64
+    for k in range(K):
+        want += a[:, k:k + 1] * w[:, k]
+    assert torch.equal(dfp4.gemm(qa, qw), want.float())
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    assert torch.equal(dfp4.gemm_prepared(pa, pw), want.float())
+
+
 @pytest.mark.parametrize("rows,K", [(1, 32), (33, 96), (256, 64), (257, 320)])
 def test_quantize_native_writes_the_whole_buffer(rows, K):
     # padding rows, the missing block of an odd K / 32 and the slack behind either array leave as zeros
