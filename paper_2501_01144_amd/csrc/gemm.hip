@@ -128,7 +128,9 @@ inline int64_t partial_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
 // estimated to finish sooner: those with few output tiles, where the large kernel's one wave per SIMD leaves most
 // of the chip idle (M x N x K = 100 x 1000 x 4096: 112 us with the prepass, 11 us direct; 1024 x 1024 x 4096:
 // 108 and 20; 2048 x 4096 x 4096: 74 and 66; 4096 x 4096 x 4096: 89 and 148), and batches whose expanded A would
-// be read only once or twice (P V of attention).
+// be read only once or twice (P V of attention).  K of one iteration of the direct kernel (Q K^T) goes there unless
+// it is prepared already: an expanded A of 4 blocks costs more to fetch than to expand, and the large kernel's prologue and epilogue have
+// nothing to hide behind (128 heads of 2048 x 2048 x 128: 568 and 502 us; 1 x 4096 x 4096 x 128: 31 and 22).
 constexpr int kPreparedMinRows = 257;       // an A operand of fewer rows is not expanded ahead: direct wins for any N
 inline bool fast_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
 // Estimated microseconds of gemm_fast_kernel, with its prepass unless the operands are prepared (launches and
@@ -141,7 +143,7 @@ inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool pre
     return prep + 5.0f + rounds * (6.0f + 0.5f * (float)KB / (float)s) + (s > 1 ? 25.0f : 0.0f);
 }
 inline bool takes_direct_kernel(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
-    return !fast_kernel_can(M, KB) || (prepared && M < kPreparedMinRows) ||
+    return !fast_kernel_can(M, KB) || (prepared ? M < kPreparedMinRows : KB <= kDirectOnceBlocks) ||
            gemm_direct_cost(M, N, KB, batch) <= fast_cost(M, N, KB, batch, prepared);
 }
 

@@ -28,16 +28,26 @@
 namespace dfp4 {
 namespace {
 
-template <int TI_, int TJ_, int WM_, int WN_, int KG_>
+
+// ONCE: K is one iteration (attention scores: heads of 64 or 128).  Such a tile is all latency (exponents, codes, LDS,
+// stores), so what counts is tiles in flight: one operand buffer instead of two, and one set of accumulators (class
+// sums from the highest down, shifted in between), so that three workgroups share a compute unit instead of two.
+// Q K^T to fp32 (microseconds; before: gemm_fast_kernel with its prepass / the 128 x 128 shape with two buffers):
+//   128 heads, 2048 x 2048 x 128    568 / 566 -> 502      the same with heads of 64    545 / 540 -> 371 (6.0 TB/s)
+//    16 heads,  700 x 1312 x  64     45 /  28 ->  21       32 heads, 300 x 2048 x 128   54 /  32 ->  26
+// The write of the scores is 313 us of the first (a fill of the same size); classes on both operands, up to four
+// products per pair of blocks, are most of the rest.
+template <int TI_, int TJ_, int WM_, int WN_, int KG_, bool ONCE_ = false>
 struct DirectShape {
+    static constexpr bool kOnce = ONCE_;
     static constexpr int TI = TI_, TJ = TJ_, WM = WM_, WN = WN_, KG = KG_;
     static constexpr int kGroupThreads = 64 * WM * WN, kThreads = kGroupThreads * KG;
     static constexpr int kTm = 32 * TI * WM, kTn = 32 * TJ * WN, kRows = kTm + kTn, kRowGroups = kRows / 32;
     static constexpr int kItemRows = kGroupThreads / 4;                // rows of one item index
     static constexpr int kItems = kRows / kItemRows, kItemsA = kTm / kItemRows;
     static constexpr bool kPrivate = WM * WN == 1;                     // the group is one wave: no barrier in the loop
-    static constexpr int kBufs = kPrivate ? 1 : 2;
-    static constexpr int kWavesPerSimd = TI * TJ == 1 ? 4 : 2;         // what the registers allow
+    static constexpr int kBufs = kPrivate || kOnce ? 1 : 2;
+    static constexpr int kWavesPerSimd = TI * TJ == 1 ? 4 : kOnce ? 3 : 2;         // what the registers allow
     static constexpr int scan_parts() {                                // threads that look for a row's smallest exponent
         int p = 1;
         while (p * 2 * kRows <= kThreads && p < 16) p *= 2;
@@ -331,7 +341,52 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
                 for (int j = 0; j < TJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.a[i][t], o.b[j][t], acc[i][j], 0, 0, 0);
     };
-    if constexpr (S::kPrivate) {
+    if constexpr (S::kOnce) {
+        if (KB > 0) {
+#pragma unroll
+            for (int j = 0; j < S::kItems; ++j) expand(item[j], j, table(item[j], j, 0), 0);
+        }
+        __syncthreads();
+        const int top = ca_max + cw_max;
+#pragma unroll 1
+        for (int ct = top; ct >= 0; --ct) {
+            if (ct < top) {
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                        for (int x = 0; x < 16; ++x) acc[i][j][x] <<= 4;
+            }
+#pragma unroll 1
+            for (int c1 = max(0, ct - cw_max); c1 <= min(ct, ca_max); ++c1)
+#pragma unroll 1
+                for (int pr = 0; 2 * pr < KB; ++pr) {
+                    Operands o;
+                    read(o, 0, pr);
+                    bool any_a[TI], any_b[TJ];
+#pragma unroll
+                    for (int i = 0; i < TI; ++i) {
+                        any_a[i] = __ballot(o.ka[i] == c1) != 0ull;
+                        only(o.ka[i] == c1, o.a[i], o.a[i]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) {
+                        any_b[j] = __ballot(o.kw[j] == ct - c1) != 0ull;
+                        only(o.kw[j] == ct - c1, o.b[j], o.b[j]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < TI; ++i)
+#pragma unroll
+                        for (int j = 0; j < TJ; ++j)
+                            if (any_a[i] && any_b[j]) {
+#pragma unroll
+                                for (int t = 0; t < 2; ++t)
+                                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.a[i][t], o.b[j][t], acc[i][j], 0, 0, 0);
+                            }
+                }
+        }
+    } else if constexpr (S::kPrivate) {
         // one wave: LDS operations are in order, no barrier; 4 waves per SIMD hide the latencies
         for (int k = 0; k < per; k += 4) {
             const int kb0 = k_lo + k;
@@ -393,7 +448,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
             }
         }
     }
-    if (ca_max + cw_max > 0) {
+    if (!S::kOnce && ca_max + cw_max > 0) {
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -552,7 +607,10 @@ int64_t gemm_direct_max_rows(int64_t KB) {
 
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
     float us;
-    switch (choose_shape(p.M, p.N, p.KB, batch, &us)) {
+    const int shape = choose_shape(p.M, p.N, p.KB, batch, &us);
+    // the one-iteration form of the 128 x 128 tile was the fastest of the large tiles for every such K measured
+    if (shape >= 3 && p.KB <= kDirectOnceBlocks) return launch<DirectShape<2, 2, 2, 2, 1, true>>(mx, bf16, p, batch, stream);
+    switch (shape) {
         case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);
         case 1: return launch<DirectShape<1, 1, 2, 2, 4>>(mx, bf16, p, batch, stream);
         case 2: return launch<DirectShape<1, 1, 2, 2, 2>>(mx, bf16, p, batch, stream);

@@ -1183,6 +1183,38 @@ def test_gemm_prepared_direct_shapes(M, N, K):
     assert dfp4.gemm_declined_tiles(pa) == 0
 
 
+@pytest.mark.parametrize("batch,M,N,K,spread", [
+    (1, 129, 131, 32, 0), (1, 1000, 520, 96, 0), (2, 300, 1030, 64, 0), (3, 257, 129, 128, 0), (1, 2000, 2049, 128, 0),
+    (2, 300, 520, 128, 5), (1, 130, 1030, 96, 9), (2, 257, 260, 128, 30), (1, 200, 300, 160, 0)])
+def test_gemm_short_k(batch, M, N, K, spread):
+    # K of at most four blocks (one iteration of the direct kernel), and one block more; both operands have classes
+    print(f"gemm short K: {batch} x {M}x{N}x{K}, exponents over {spread} binades", flush=True)
+    g = torch.Generator().manual_seed(M + N + K)
+    def operand(rows, std):
+        x = torch.randn(rows, K // 32, 32, generator=g) * std
+        if spread:
+            x *= torch.exp2(torch.randint(0, spread + 1, (rows, K // 32, 1), generator=g).float())
+        else:
+            x[:, 0, 3] = torch.where(x[:, 0, 3] < 0, -40.0, 40.0) * std    # 3 to 6 binades above the others: class 1 at most
+        return x.view(rows, K).to(torch.bfloat16)
+    a, w = operand(batch * M, 1.0), operand(batch * N, 0.02)
+    qa, qw = dfp4.quantize(_dev(a)), dfp4.quantize(_dev(w))
+    for dtype in (torch.float32, torch.bfloat16):
+        out = dfp4.gemm_batched(qa, qw, batch, M, N, dtype=dtype)
+        torch.cuda.synchronize()
+        out = out.reshape(batch, M, N)
+        for b in range(batch):
+            ref, absdot = _gemm_ref(synth.to_f64(a[b * M:(b + 1) * M]), synth.to_f64(w[b * N:(b + 1) * N]))
+            _assert_gemm_close(out[b], ref, absdot, f"short K {dtype}", bf16=dtype == torch.bfloat16)
+            if not spread and dtype == torch.float32:         # one rounding of the exact sum
+                assert (np.abs(out[b].cpu().double().numpy() - ref) <= np.abs(ref) * 2.0 ** -24 + 1e-300).all()
+    if batch == 1:
+        pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+        _assert_gemm_close(dfp4.gemm_prepared(pa, pw), ref, absdot, "short K prepared")
+        outm = dfp4.mxfp4_gemm(dfp4.mxfp4_quantize(_dev(a)), dfp4.mxfp4_quantize(_dev(w)))
+        _assert_gemm_close(outm, *_gemm_ref(synth.to_f64(a), synth.to_f64(w), mx=True), "short K mxfp4")
+
+
 def test_gemm_direct_rows_beyond_one_launch():
     # more rows than 65535 tiles of 32: the product is cut into launches; every output is the exact sum
     M, N, K = 65535 * 32 + 700, 5, 32
