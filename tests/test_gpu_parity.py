@@ -1270,3 +1270,50 @@ def test_dequantize_around_64_blocks(rows, K, dtype):
     assert np.array_equal(y.cpu().double().numpy(), ref)
     assert np.array_equal(wide[:, 16:16 + K].cpu().double().numpy(), ref)
     assert bool((wide[:, :16] == 7).all()) and bool((wide[:, 16 + K:] == 7).all())
+
+
+# --------------------------------------------------------------------------
+# int32 sums are decided by the classes that meet in a block, not by the largest class of each operand
+# --------------------------------------------------------------------------
+def _lifted(rows, K, std, blocks, by, g, every=1):
+    """Positive values whose blocks share one exponent, except `blocks` of every `every`-th row, lifted by 2^by (sums of
+    products of lifted blocks pass 2^24 units: added one block at a time in fp32 they would be rounded)."""
+    x = 0.5 + 7.0 * torch.rand(rows, K // 32, 32, generator=g)
+    x[:, :, 3] = 7.0
+    x[::every, blocks] *= 2.0 ** by
+    return (x.view(rows, K) * std).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("M,N,K,n_a,n_w,meet,by_a,by_w", [
+    (16, 300, 4096, 20, 40, 10, 7, 7), (40, 70, 4192, 20, 40, 9, 6, 7),           # decode; K / 32 not a multiple of 4
+    (16, 300, 11008, 10, 6, 4, 7, 7), (200, 300, 14336, 8, 6, 3, 7, 7),
+    (128, 2049, 14336, 8, 6, 3, 7, 7), (700, 1030, 4096, 20, 30, 7, 7, 7),
+    (300, 2049, 16480, 9, 9, 6, 7, 7),                                            # K beyond the prepared form
+    (1500, 4000, 1120, 20, 22, 7, 7, 7), (652, 3397, 1184, 20, 22, 7, 7, 7),
+    (16, 300, 1024, 2, 4, 0, 11, 7), (200, 300, 1056, 2, 6, 0, 9, 6), (300, 520, 128, 1, 1, 0, 10, 9)])   # classes 2 and 1 that never meet
+def test_gemm_exact_where_few_high_blocks_meet(M, N, K, n_a, n_w, meet, by_a, by_w):
+    # A and W hold a few blocks far above the others, `meet` of them the same.  The exact sum fits int32 by the blocks that
+    # meet (asserted), although not by the largest class of either operand
+    print(f"gemm, few high blocks: {M}x{N}x{K}", flush=True)
+    KB, ca, cw = K // 32, by_a // 4, by_w // 4
+    g = torch.Generator().manual_seed(M + N + K)
+    order = torch.randperm(KB, generator=g)
+    in_a, in_w = order[:n_a], order[n_a - meet:n_a - meet + n_w]
+    a, w = _lifted(M, K, 1.0, in_a, by_a, g, every=2), _lifted(N, K, 0.0625, in_w, by_w, g)
+    both = 16 ** cw + 16 ** (ca + cw)                    # half the rows of A stay low
+    weight = KB - n_a - n_w + meet + (n_a - meet) * (1 + 16 ** ca) + (n_w - meet) * 16 ** cw + meet * both
+    assert weight <= (2 ** 31 - 1) // (32 * 120 * 120) and (ca + cw <= 2 or not meet)
+    assert ca + cw > 2 or min((KB - n_a + n_a * 16 ** ca) * 16 ** cw, (KB - n_w + n_w * 16 ** cw) * 16 ** ca) > 4660
+    qa, qw = dfp4.quantize(_dev(a)), dfp4.quantize(_dev(w))
+    ref, _ = _gemm_ref(synth.to_f64(a), synth.to_f64(w))
+
+    def assert_exact(out, what):                         # one rounding of the exact sum (float64 holds it)
+        torch.cuda.synchronize()
+        bad = np.abs(out.cpu().double().numpy() - ref) > np.abs(ref) * 2.0 ** -24
+        assert not bad.any(), f"{what}: {bad.sum()} of {bad.size} outputs are not one rounding of the exact sum"
+    assert_exact(dfp4.gemm(qa, qw), "plain")
+    assert_exact(dfp4.gemm_batched(qa, qw, 1, M, N)[0], "batched")
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    assert_exact(dfp4.gemm_prepared(pa, pw), "prepared")
+    if pa.buf is not None:
+        assert dfp4.gemm_declined_tiles(pa) == 0
