@@ -654,10 +654,12 @@ float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch) {
 }
 
 // At most this many rows of an operand in one launch: the kernel addresses it with 32-bit byte offsets, and the rows
-// of A give at most 65535 tiles of the smallest shape along the grid's y
+// of A give at most 65535 tiles of the smallest shape along the grid's y.  Whole tiles while that many rows fit; at
+// least 4 rows for any K / 32 < 2^26.
 int64_t gemm_direct_max_rows(int64_t KB) {
     const int64_t offsets = ((int64_t)1 << 28) / (KB > 0 ? KB : 1), grid_y = (int64_t)65535 * 32;
-    return (offsets < grid_y ? offsets : grid_y) / 512 * 512;
+    const int64_t rows = offsets < grid_y ? offsets : grid_y;
+    return rows >= 512 ? rows / 512 * 512 : rows;
 }
 
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {

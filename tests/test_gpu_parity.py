@@ -1231,6 +1231,21 @@ def test_gemm_direct_rows_beyond_one_launch():
     assert torch.equal(dfp4.gemm_prepared(pa, pw), want.float())
 
 
+def test_gemm_direct_k_beyond_2_to_24():
+    # fewer than 512 rows are addressed with 32-bit offsets; whole numbers whose sums fp32 holds: every output is exact
+    M, N, K = 3, 2, 2 ** 24 + 64
+    print(f"gemm direct: {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    def operand(rows):
+        x = torch.zeros(rows, K, device="cuda")
+        x[:, ::32 * 997] = torch.randint(-6, 7, x[:, ::32 * 997].shape, generator=g, device="cuda").float()
+        x[:, -1] = 3.0
+        return dfp4.quantize(x.to(torch.bfloat16))
+    qa, qw = operand(M), operand(N)
+    a, w = dfp4.dequantize(qa, torch.float32).double(), dfp4.dequantize(qw, torch.float32).double()
+    assert torch.equal(dfp4.gemm(qa, qw), torch.stack([(a * w[n]).sum(1) for n in range(N)], 1).float())
+
+
 @pytest.mark.parametrize("rows,K", [(1, 32), (33, 96), (256, 64), (257, 320)])
 def test_quantize_native_writes_the_whole_buffer(rows, K):
     # padding rows, the missing block of an odd K / 32 and the slack behind either array leave as zeros
