@@ -1110,12 +1110,12 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     if (KB == 0 || KB > kMaxKB) return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
     GemmParams p{};
     fill_params(p, A, W, out, ldc, 0, 0, 0, nullptr);
+    if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     if (M < kPreparedMinRows) {
         p.declined = static_cast<uint32_t*>(a_prepared);
         if (N <= gemm_direct_max_rows(KB)) return launch_gemm_direct(mx, bf16, p, 1, stream);
         return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
     }
-    if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     set_prepared(p, static_cast<uint8_t*>(a_prepared), 0, static_cast<uint8_t*>(const_cast<void*>(w_prepared)), 0);
     if (takes_direct_kernel(M, N, KB, 1, true) && (M > N ? M : N) <= gemm_direct_max_rows(KB)) {
         p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));

@@ -169,3 +169,13 @@ def test_gemm_requant_batched_argument_errors(lib):
     assert lib.dfp4_gemm_requant_batched(a, w, _t(16, 16, 16, 128, 64), 2, 64, 64, vp(0), sz(0), vp(0)) == -5
     assert lib.dfp4_gemm_requant_batched(a, w, _t(16, 16, 16, 128, 64), -1, 64, 64, vp(256), sz(1 << 30), vp(0)) == -2
     assert lib.dfp4_gemm_requant_batched(a, w, _t(16, 16, 16, 0, 64), 0, 64, 64, vp(0), sz(0), vp(0)) == 0
+
+
+def test_gemm_prepared_refuses_a_weight_beyond_its_limit(lib):
+    # rows * K / 2 < 2^31 for W (dfp4_gemm_prepare refuses such a W): also where A has few rows
+    vp, sz = ctypes.c_void_p, ctypes.c_size_t
+    big = _t(256, 256, 256, 1 << 18, 16384)
+    assert lib.dfp4_gemm_prepare(big, 1, vp(256), sz(1 << 62), vp(0)) == -2
+    for rows in (1, 64, 256, 300):
+        a = _t(256, 256, 256, rows, 16384)
+        assert lib.dfp4_gemm_prepared(a, vp(256), big, vp(256), vp(256), 0, 1 << 18, vp(256), sz(1 << 40), vp(0)) == -2
