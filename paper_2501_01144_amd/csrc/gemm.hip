@@ -983,12 +983,13 @@ int launch_fast(bool mx, bool bf16, GemmParams& p, int64_t batch, int* part, siz
 // direct kernel, in pieces of at most as many rows as it addresses
 int launch_direct(bool mx, bool bf16, dfp4_tensor A, dfp4_tensor W, void* out, int64_t ldc, int64_t batch,
                   int64_t strideA_rows, int64_t strideW_rows, int64_t strideC, hipStream_t stream) {
-    const int64_t KB = A.K / kBlock, step = gemm_direct_max_rows(KB), M = A.rows, N = W.rows;
-    for (int64_t m0 = 0; m0 < M; m0 += step)
-        for (int64_t n0 = 0; n0 < N; n0 += step) {
+    const int64_t KB = A.K / kBlock, M = A.rows, N = W.rows;
+    const int64_t mc = gemm_direct_max_rows(KB, false), nc = gemm_direct_max_rows(KB, true);
+    for (int64_t m0 = 0; m0 < M; m0 += mc)
+        for (int64_t n0 = 0; n0 < N; n0 += nc) {
             dfp4_tensor a = A, w = W;
-            a.rows = M - m0 < step ? M - m0 : step;
-            w.rows = N - n0 < step ? N - n0 : step;
+            a.rows = M - m0 < mc ? M - m0 : mc;
+            w.rows = N - n0 < nc ? N - n0 : nc;
             a.codes += m0 * KB * 16; a.exponent += m0 * KB; if (a.dialect) a.dialect += m0 * KB;
             w.codes += n0 * KB * 16; w.exponent += n0 * KB; if (w.dialect) w.dialect += n0 * KB;
             GemmParams p{};
@@ -1113,11 +1114,10 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     if (M < kPreparedMinRows) {
         p.declined = static_cast<uint32_t*>(a_prepared);
-        if (N <= gemm_direct_max_rows(KB)) return launch_gemm_direct(mx, bf16, p, 1, stream);
-        return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
+        return launch_gemm_direct(mx, bf16, p, 1, stream);     // one launch: max_rows_w is half of what it takes
     }
     set_prepared(p, static_cast<uint8_t*>(a_prepared), 0, static_cast<uint8_t*>(const_cast<void*>(w_prepared)), 0);
-    if (takes_direct_kernel(M, N, KB, 1, true) && (M > N ? M : N) <= gemm_direct_max_rows(KB)) {
+    if (takes_direct_kernel(M, N, KB, 1, true) && M <= gemm_direct_max_rows(KB, false) && N <= gemm_direct_max_rows(KB, true)) {
         p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));
         return launch_gemm_direct(mx, bf16, p, 1, stream);
     }

@@ -653,12 +653,12 @@ float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch) {
     return us;
 }
 
-// At most this many rows of an operand in one launch: the kernel addresses it with 32-bit byte offsets, and the rows
-// of A give at most 65535 tiles of the smallest shape along the grid's y.  Whole tiles while that many rows fit; at
-// least 4 rows for any K / 32 < 2^26.
-int64_t gemm_direct_max_rows(int64_t KB) {
-    const int64_t offsets = ((int64_t)1 << 28) / (KB > 0 ? KB : 1), grid_y = (int64_t)65535 * 32;
-    const int64_t rows = offsets < grid_y ? offsets : grid_y;
+// At most this many rows of A or of W in one launch: the kernel addresses an operand with 32-bit byte offsets, the rows
+// of A give at most 65535 tiles of the smallest shape along the grid's y, and those of W at most 2^22 along its x, of
+// 512 threads each.  Whole tiles while that many rows fit; at least 4 rows for any K / 32 < 2^26.
+int64_t gemm_direct_max_rows(int64_t KB, bool weight) {
+    const int64_t offsets = ((int64_t)1 << 28) / (KB > 0 ? KB : 1), grid = weight ? (int64_t)1 << 27 : (int64_t)65535 * 32;
+    const int64_t rows = offsets < grid ? offsets : grid;
     return rows >= 512 ? rows / 512 * 512 : rows;
 }
 

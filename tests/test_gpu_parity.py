@@ -1231,6 +1231,26 @@ def test_gemm_direct_rows_beyond_one_launch():
     assert torch.equal(dfp4.gemm_prepared(pa, pw), want.float())
 
 
+def test_gemm_prepared_few_rows_counts_declined_tiles_for_any_n():
+    # more columns than 65535 tiles of 32, in one launch; blocks 20 binades apart in a row of A decline every tile
+    M, N, K = 4, 65535 * 32 + 700, 64
+    print(f"gemm prepared: {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    a, w = torch.randn(M, K, generator=g, device="cuda"), torch.randn(N, K, generator=g, device="cuda")
+    a[1, :32] *= 2.0 ** 20
+    qa, qw = dfp4.quantize(a.to(torch.bfloat16)), dfp4.quantize(w.to(torch.bfloat16))
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    out = dfp4.gemm_prepared(pa, pw)
+    a, w = dfp4.dequantize(qa, torch.float32).double(), dfp4.dequantize(qw, torch.float32).double()
+    ref, absdot = torch.zeros_like(out, dtype=torch.float64), torch.zeros_like(out, dtype=torch.float64)
+    for k in range(K):
+        term = a[:, k:k + 1] * w[:, k]
+        ref += term
+        absdot += term.abs()
+    assert bool(((out.double() - ref).abs() <= GEMM_RTOL * absdot).all())
+    assert dfp4.gemm_declined_tiles(pa) in [(N + n - 1) // n for n in (32, 64, 128)]      # every tile of one row of tiles
+
+
 def test_gemm_direct_k_beyond_2_to_24():
     # fewer than 512 rows are addressed with 32-bit offsets; whole numbers whose sums fp32 holds: every output is exact
     M, N, K = 3, 2, 2 ** 24 + 64
