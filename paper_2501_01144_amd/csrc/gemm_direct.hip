@@ -442,7 +442,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
                 }
         }
     } else if constexpr (S::kPrivate) {
-        // one wave: LDS operations are in order, no barrier; 4 waves per SIMD hide the latencies
+        // one wave: its LDS operations execute in order, so lanes exchange operands without a barrier; the fences keep
+        // the compiler to that order (they cost no instruction).  4 waves per SIMD hide the latencies
+        auto in_order = [] {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
         for (int k = 0; k < per; k += 4) {
             const int kb0 = k_lo + k;
             if (kb0 >= KB) break;
@@ -451,12 +457,14 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
                 expand(item[j], j, table(item[j], j, kb0), 0);
                 load(item[j], j, kb0 + 4);
             }
+            in_order();
 #pragma unroll
             for (int pr = 0; pr < 2; ++pr) {
                 Operands o;
                 read(o, 0, pr);
                 multiply(o);
             }
+            in_order();
         }
     } else {
         // One iteration: multiply the 4 blocks from kb0 (buffer BUF), expand the next 4 into the other buffer,
