@@ -30,16 +30,19 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t as_u(float f) { return __builtin_bit_cast(uint32_t, f); }
 
-// 8 elements: one dword of codes with its dialect and exponent byte
+// The dword of codes c (8 elements) with its dialect and exponent byte.  bf16: all 8, one 16-byte store; fp32: the
+// elements 4 half .. 4 half + 3, one 16-byte store.
 template <bool BF16>
-__device__ __forceinline__ void expand_store(uint32_t c, uint32_t d, int byte, void* __restrict__ y, int64_t off) {
+__device__ __forceinline__ void expand_store(uint32_t c, uint32_t half, uint32_t d, int byte, void* __restrict__ y, int64_t off) {
+    constexpr int kElems = BF16 ? 8 : 4;
     const int e = byte - 128;                              // 0.5 u 2^(byte-127) = u 2^(byte-128)
+    if constexpr (!BF16) c >>= 16u * half;
     const uint32_t lo = g_book_words.w[d][0], hi = g_book_words.w[d][1];
     const uint32_t mag_even = __builtin_amdgcn_perm(hi, lo, c & 0x07070707u);
     const uint32_t mag_odd = __builtin_amdgcn_perm(hi, lo, (c >> 4) & 0x07070707u);
-    uint32_t v[8];
+    uint32_t v[kElems];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < kElems / 2; ++j) {
         const uint32_t ue = (mag_even >> (8 * j)) & 0xffu, uo = (mag_odd >> (8 * j)) & 0xffu;
         v[2 * j] = as_u(ldexpf((float)ue, e)) | ((c << (28 - 8 * j)) & 0x80000000u);
         v[2 * j + 1] = as_u(ldexpf((float)uo, e)) | ((c << (24 - 8 * j)) & 0x80000000u);
@@ -49,31 +52,32 @@ __device__ __forceinline__ void expand_store(uint32_t c, uint32_t d, int byte, v
                        (v[4] >> 16) | (v[5] & 0xffff0000u), (v[6] >> 16) | (v[7] & 0xffff0000u)};
         __builtin_nontemporal_store(o, reinterpret_cast<v4u*>(static_cast<uint16_t*>(y) + off));
     } else {
-        v4u* p = reinterpret_cast<v4u*>(static_cast<float*>(y) + off);
-        const v4u o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
-        __builtin_nontemporal_store(o0, p);
-        __builtin_nontemporal_store(o1, p + 1);
+        const v4u o = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(o, reinterpret_cast<v4u*>(static_cast<float*>(y) + off));
     }
 }
 
-// A wave takes 64 blocks as four passes of 16 (lane = dword of codes), the loads of all four first; the grid covers
-// the tensor and results bypass the caches (nobody reads them soon).  Bound by memory: 4096 x 14336 to bf16, operands
-// from HBM, 23.1 us = 6.5 TB/s.  One load, table look-up and store at a time in 4096 persistent workgroups was bound by
-// the latency of that chain: 38.8 us.  `narrow`: one exponent byte and dialect id per 16 elements.
+// A wave takes 64 blocks in passes, the loads of all passes first; the grid covers the tensor and results bypass the
+// caches (nobody reads them soon).  A lane stores 16 bytes and a pass whole lines: bf16 a dword of codes per lane, 16
+// blocks a pass; fp32 half a dword, 8 blocks a pass.  Bound by memory: 4096 x 14336 to bf16, operands from HBM, 23.1 us
+// = 6.5 TB/s; 8192 x 4096 to fp32, operands and results in turn from six sets, 24.6 us = 6.2 TB/s.  One load, table
+// look-up and store at a time in 4096 persistent workgroups was bound by the latency of that chain (38.8 and 43.9 us); a
+// whole dword per lane for fp32 stores half a line twice, which costs 56.7 us when it bypasses the caches and 44.3 when
+// it does not (whole lines through the caches: 42.4).  `narrow`: one exponent byte and dialect id per 16 elements.
 template <bool MX, bool BF16, bool CONTIG>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(
     const uint32_t* __restrict__ codes, const uint8_t* __restrict__ dialect,
     const uint8_t* __restrict__ exponent, void* __restrict__ y, int64_t ld, uint32_t blocks_per_row,
     uint32_t nblocks, uint32_t narrow) {
-    constexpr uint32_t kPasses = 4, kBlocksPerPass = 16;
-    const uint32_t lane = threadIdx.x & 63u, sub = lane & 3u;
+    constexpr uint32_t kLanes = BF16 ? 4 : 8, kBlocksPerPass = 64 / kLanes, kPasses = 64 / kBlocksPerPass, kElems = kBlock / kLanes;
+    const uint32_t lane = threadIdx.x & 63u, part = lane % kLanes, sub = part * 4u / kLanes;     // dword of the block
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t nsuper = (nblocks + 63u) / 64u, stride = gridDim.x * (kThreads / 64);
     for (uint32_t sc = blockIdx.x * (kThreads / 64) + wave; sc < nsuper; sc += stride) {
         uint32_t c[kPasses], e[kPasses], d[kPasses];
 #pragma unroll
         for (uint32_t p = 0; p < kPasses; ++p) {
-            const uint32_t b = min(sc * 64u + p * kBlocksPerPass + (lane >> 2), nblocks - 1u);
+            const uint32_t b = min(sc * 64u + p * kBlocksPerPass + lane / kLanes, nblocks - 1u);
             const size_t mb = narrow ? (size_t)b * 2u + (sub >> 1) : (size_t)b;
             c[p] = codes[(size_t)b * 4u + sub];
             e[p] = exponent[mb];
@@ -81,16 +85,16 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(
         }
 #pragma unroll
         for (uint32_t p = 0; p < kPasses; ++p) {
-            const uint32_t b = sc * 64u + p * kBlocksPerPass + (lane >> 2);
+            const uint32_t b = sc * 64u + p * kBlocksPerPass + lane / kLanes;
             if (b >= nblocks) break;
             int64_t off;
             if constexpr (CONTIG) {
-                off = (int64_t)b * kBlock + sub * 8;
+                off = (int64_t)b * kBlock + part * kElems;
             } else {
                 const uint32_t row = b / blocks_per_row;
-                off = (int64_t)row * ld + (int64_t)(b - row * blocks_per_row) * kBlock + sub * 8;
+                off = (int64_t)row * ld + (int64_t)(b - row * blocks_per_row) * kBlock + part * kElems;
             }
-            expand_store<BF16>(c[p], d[p], (int)e[p], y, off);
+            expand_store<BF16>(c[p], part & 1u, d[p], (int)e[p], y, off);
         }
     }
 }

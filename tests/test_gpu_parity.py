@@ -1352,3 +1352,24 @@ def test_gemm_exact_where_few_high_blocks_meet(M, N, K, n_a, n_w, meet, by_a, by
     assert_exact(dfp4.gemm_prepared(pa, pw), "prepared")
     if pa.buf is not None:
         assert dfp4.gemm_declined_tiles(pa) == 0
+
+
+def test_dequantize_fp32_stores_whole_lines():
+    # the same tensor to fp32 moves 1.8 times the bytes of bf16; stores of half lines that bypass the caches took 4.5 times
+    # as long, whole lines take 2.0 times
+    q = dfp4.quantize(synth.student_t(8192, 4096, 3.0, seed=0).cuda())
+
+    def us(dtype):
+        y, best = torch.empty(8192, 4096, dtype=dtype, device="cuda"), float("inf")
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                dfp4.dequantize(q, out=y)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 20 * 1e3)
+        return best
+    t32, t16 = us(torch.float32), us(torch.bfloat16)
+    print(f"dequantize 8192x4096: fp32 {t32:.1f} us, bf16 {t16:.1f} us", flush=True)
+    assert t32 < 3 * t16
