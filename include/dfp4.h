@@ -241,6 +241,13 @@ int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const vo
  * exact path folds into its operands).  `count` is a HOST pointer.  Synchronizes with the device.
  */
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);
+/*
+ * Diagnostic: the kernel that a product of these sizes takes (batch 1 unless dfp4_gemm_batched; prepared: with
+ * dfp4_gemm_prepared).  0: gemm_fast_kernel (512 x 128 output tiles, expanded operands).  1 to 7: gemm_direct_kernel
+ * (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
+ * two, 128 x 128, 256 x 128, and 128 x 128 for K of at most 128.  DFP4_ERR_SHAPE for sizes that are no product.
+ */
+int dfp4_gemm_path(int64_t M, int64_t N, int64_t K, int64_t batch, int prepared);
 
 /*
  * dfp4_gemm for callers that cannot allocate device memory or pass a workspace: code under

@@ -305,6 +305,11 @@ int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint3
     return DFP4_OK;
 }
 
+int dfp4_gemm_path(int64_t M, int64_t N, int64_t K, int64_t batch, int prepared) {
+    if (M <= 0 || N <= 0 || K < 0 || K % kBlock != 0 || batch <= 0) return DFP4_ERR_SHAPE;
+    return gemm_path(M, N, K / kBlock, batch, prepared != 0);
+}
+
 // Native block-scaled GEMM.  w_packed == nullptr: both operands are packed into the workspace
 // (A first, then W); otherwise only A is, and W comes packed (dfp4_native_pack / mxfp4_native_pack).
 static int gemm_native_common(bool fp6, dfp4_tensor A, const dfp4_tensor* W, const void* w_packed, int64_t N,

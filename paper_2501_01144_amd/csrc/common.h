@@ -36,6 +36,7 @@ int launch_gemm(bool mx, dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype,
                 int64_t batch, int64_t strideA_rows, int64_t strideW_rows, int64_t strideC,
                 void* workspace, size_t workspace_bytes, hipStream_t stream, const dfp4_tensor* rq = nullptr);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
+int gemm_path(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared);
 size_t gemm_fast_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int gemm_shape_check(dfp4_tensor A, dfp4_tensor W, int64_t ldc, int64_t batch, bool rq);
 size_t gemm_prepared_bytes(int64_t rows, int64_t K, bool weight);

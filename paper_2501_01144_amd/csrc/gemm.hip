@@ -126,21 +126,30 @@ inline int64_t partial_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
 // Which kernel.  gemm_fast_kernel multiplies expanded operands; gemm_direct_kernel (gemm_direct.hip) expands in the
 // kernel and takes everything gemm_fast_kernel cannot (few rows, K beyond its visit list), and the products it is
 // estimated to finish sooner: those with few output tiles, where the large kernel's one wave per SIMD leaves most
-// of the chip idle (M x N x K = 100 x 1000 x 4096: 112 us with the prepass, 11 us direct; 1024 x 1024 x 4096:
-// 108 and 20; 2048 x 4096 x 4096: 74 and 66; 4096 x 4096 x 4096: 89 and 148), and batches whose expanded A would
+// of the chip idle or the exchange of partial sums takes longer than the product (M x N x K = 1024 x 1024 x 4096: 108 us
+// with the prepass, 20 direct; 512 x 4096 x 4096: 112 and 34; 2048 x 4096 x 4096: 75 and 67; 4096 x 4096 x 4096: 90 and
+// 144; 2048 x 4096 x 14336: 171 and 262; 1024 x 14336 x 4096: 84 and 127), and batches whose expanded A would
 // be read only once or twice (P V of attention).  K of one iteration of the direct kernel (Q K^T) goes there unless
 // it is prepared already: an expanded A of 4 blocks costs more to fetch than to expand, and the large kernel's prologue and epilogue have
-// nothing to hide behind (128 heads of 2048 x 2048 x 128: 568 and 502 us; 1 x 4096 x 4096 x 128: 31 and 22).
-constexpr int kPreparedMinRows = 257;       // an A operand of fewer rows is not expanded ahead: direct wins for any N
+// nothing to hide behind (128 heads of 2048 x 2048 x 128: 504 and 400 us; 1 x 4096 x 4096 x 128: 31 and 22).
+// Against both kernels timed on 940 products not among those fitted (M 65..4096, N 64..14336, K 160..16384) the kernel and
+// shape taken are 2.7 % slower than the best on average, 10 % in 5 % of them, 14 % in 1 %; prepared (630) 1.2, 6 and 13 %.
+// An A operand of fewer rows than kPreparedMinRows is not expanded ahead: direct is faster by up to 3.5 times (65 x 1024 x
+// 16384), but for 200 to 256 rows and N x K of 2^26 or more, where it is up to 13 % slower (256 x 14336 x 14336).
+constexpr int kPreparedMinRows = 257;
 inline bool fast_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
-// Estimated microseconds of gemm_fast_kernel, with its prepass unless the operands are prepared (launches and
-// prologue; half a microsecond per block of a tile; per round the exposed epilogue; the exchange of partial tiles)
+// Estimated microseconds of gemm_fast_kernel, fitted like those of the direct shapes: per round of workgroups a fixed
+// part, and per block of a workgroup's share of K more where the chip is full, growing beyond 128 blocks; the results; the exchange of partial tiles between s workgroups; the prepass unless the operands are prepared
 inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
     const int64_t cu = device_cu_count(), tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN) * batch;
     const int s = choose_ksplit(tiles, KB);
-    const float rounds = (float)((tiles * s + cu - 1) / cu);
-    const float prep = prepared ? 0.0f : 15.0f + 2.1f * (float)((M + N) * KB * kBlock) * (float)batch * 2.5e-7f;
-    return prep + 5.0f + rounds * (6.0f + 0.5f * (float)KB / (float)s) + (s > 1 ? 25.0f : 0.0f);
+    const int64_t rounds = tiles * s / cu, rest = tiles * s - rounds * cu;
+    const float steps = (float)KB / (float)s, grow = 1.0f + 0.151f * (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
+    float t = (float)rounds * (12.8f + steps * 0.36f * grow) + (float)(M * N * batch) * 4e-6f * (N % 16 != 0 ? 0.406f : 0.012f);
+    if (rest > 0) t += 12.8f + steps * (0.284f + 0.0755f * (float)rest / (float)cu) * grow;
+    if (s > 1) t += 4.5f + 10.4f * (float)(s - 1);
+    if (!prepared) t += 7.7f + (0.601f * (float)M + 0.332f * (float)N) * (float)(KB * kBlock * batch) * 1e-6f;
+    return t;
 }
 inline bool takes_direct_kernel(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
     return !fast_kernel_can(M, KB) || (prepared ? M < kPreparedMinRows : KB <= kDirectOnceBlocks) ||
@@ -909,6 +918,11 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     // nothing but a token where the direct kernel is taken whatever the batch
     if (takes_direct_kernel(M, N, KB, 1, false) && takes_direct_kernel(M, N, KB, 65535, false)) return 256;
     return gemm_fast_workspace_bytes(M, N, K);
+}
+
+int gemm_path(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
+    prepared = prepared && KB > 0 && KB <= kMaxKB;         // otherwise nothing is prepared and the operands are read as they are
+    return takes_direct_kernel(M, N, KB, batch, prepared) ? 1 + gemm_direct_shape(M, N, KB, batch) : 0;
 }
 
 size_t gemm_requant_workspace_bytes(int64_t M, int64_t N, int64_t K) {

@@ -324,6 +324,7 @@ void dispatch_mx_bf16(bool mx, bool bf16, F&& f) {
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream);
 constexpr int kDirectOnceBlocks = 4;         // K, in blocks, that it takes in one iteration
 float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch);
+int gemm_direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch);
 int64_t gemm_direct_max_rows(int64_t KB, bool weight);
 
 }  // namespace dfp4

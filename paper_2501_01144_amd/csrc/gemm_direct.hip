@@ -207,7 +207,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
             // The classes that meet in every block: 8 lanes take 4 blocks, each an eighth of the rows of A and of W, and
             // OR the bits of the classes they find.  Few outlier channels on both operands end here (one block of
             // class 1 each is beyond the first bound from K = 608, beyond that of the rows from K = 8864).
-            // 700 x 4096 x 14336, 0.05 % of the channels of W x 20: 1600 us with every such tile declined, 166 so.
+            // 700 x 4096 x 4096, 0.5 % of the channels of W x 20: 465 us with every such tile declined, 65 so.
             const int n4 = (KB + 3) >> 2, part8 = tid & 7;
             int weight = 0;
             auto present = [&](const uint8_t* e0, const uint8_t* ref0, int n, int last, int left) {
@@ -614,40 +614,66 @@ int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t s
     return check_launch();
 }
 
-// The tile shapes, and what one takes per round of workgroups, in microseconds: `fixed` + `step` for every 4
-// blocks of a group's share of K, with one workgroup per compute unit and (`resident` 2) with two.  Fitted to
-// measured times of 60 products, M 1..2048, N 256..14336, K 256..14336 (within 15 % on 256 compute units).
-// Small tiles win while they fit the chip in a round or two, because every step of a workgroup is latency;
-// large tiles expand fewer items per output.  For example (M, N, K = 4096), 32 / 64 (KG 4) / 128 (KG 2) / 256 rows:
-//   32 x 4096     10.7   17.8   37.7   55.6 us
-//   256 x 4096    29.2   19.2   39.2   57.6
-//   777 x 3001    70.4   55.7   41.6   59.9
-//   2048 x 4096    208    141   86.0   66.1
-struct DirectCost { int tm, tn, kg, resident; bool any_k; float fixed1, step1, fixed2, step2; };
-constexpr DirectCost kDirectCost[] = {
-    {32, 32, 8, 2, false, 3.6f, 1.6f, 3.6f, 3.17f},
-    {64, 64, 4, 1, false, 5.2f, 1.55f, 0, 0},
-    {64, 64, 2, 2, false, 3.5f, 1.0f, 4.0f, 1.75f},
-    {128, 128, 2, 1, true, 5.0f, 2.1f, 0, 0},
-    {128, 128, 1, 2, true, 2.5f, 1.5f, 6.0f, 2.15f},
-    {256, 128, 1, 1, true, 4.5f, 1.7f, 0, 0},
+// The tile shapes and what a product takes with each, in microseconds: `base`; per round of workgroups `fixed`, and for
+// every 4 blocks of a group's share of K `step` + `fill` x the share of the chip that the round fills (the last round's
+// rest counts as much as it fills), growing with K beyond 128 blocks by `grow` per 384; `store` per 10^6 outputs of 4
+// bytes, where rows of outputs begin inside a line (N % 16) `ragged`.  1: one workgroup per compute unit, 2: two, which
+// shapes that fit take as soon as there are more tiles than compute units.
+// Fitted to 21000 products timed on 256 compute units, M 1..4096, N 64..14336, K 32..16384, 1 to 128 problems, each with
+// every shape: the estimates are within 10 % (rms).  Microseconds of 32 / 64 (KG 4) / 64 (KG 2) / 128 (KG 2) / 128 / 256 rows, and of gemm_fast_kernel
+// with its prepass:
+//   16 x 4096 x 4096       10.1   17.5   20.0   36.5   49.0      -      -
+//   512 x 4096 x 4096      60.6   40.1   33.8   39.6   50.3   57.0    112
+//   777 x 3001 x 2080      54.1   40.0   31.8   27.1   31.0   35.4     72
+//   2048 x 4096 x 4096        -    156    123   87.8   76.1   66.9   75.5
+//   2048 x 4096 x 14336       -    487    439    300    305    262    171
+struct DirectCost {
+    int tm, tn, kg, resident;
+    bool any_k;
+    float base, fixed1, step1, fill1, fixed2, step2, fill2, store, ragged, grow;
 };
+constexpr DirectCost kDirectCost[] = {
+    {32, 32, 8, 2, false, 2.63f, 0.53f, 1.67f, 0.27f, 0.0f, 3.07f, 0.61f, 0.351f, 0.378f, 0.0f},
+    {64, 64, 4, 1, false, 2.11f, 2.46f, 1.58f, 0.53f, 0, 0, 0, 0.221f, 0.235f, 0.0f},
+    {64, 64, 2, 2, false, 3.32f, 0.72f, 0.985f, 0.177f, 1.77f, 1.43f, 0.434f, 0.167f, 0.180f, 0.059f},
+    {128, 128, 2, 1, true, 3.02f, 3.32f, 1.93f, 0.404f, 0, 0, 0, 0.239f, 0.233f, 0.074f},
+    {128, 128, 1, 2, true, 2.90f, 2.31f, 1.38f, 0.162f, 3.11f, 1.76f, 0.335f, 0.047f, 0.262f, 0.152f},
+    {256, 128, 1, 1, true, 1.29f, 4.71f, 1.56f, 0.216f, 0, 0, 0, 0.065f, 0.322f, 0.188f},
+};
+constexpr int kOnceShape = 6;                          // the one-iteration form of the 128 x 128 tile
 
 int choose_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, float* us) {
     const int64_t cu = device_cu_count();
+    const float outputs = (float)(M * N * batch) * 4e-6f, beyond = (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
+    const bool ragged = N % 16 != 0;
     int best = 0;
     *us = 3e38f;
     for (int i = 0; i < (int)(sizeof(kDirectCost) / sizeof(kDirectCost[0])); ++i) {
         const DirectCost& c = kDirectCost[i];
-        if (KB > 512 && !c.any_k) continue;            // their declined tiles keep all exponents of A in LDS
+        if (KB > kSmallMaxKB && !c.any_k) continue;    // their declined tiles keep all exponents of A in LDS
+        if (KB <= kDirectOnceBlocks && c.any_k) continue;      // the large tiles take a K of one iteration in one form
         const int64_t tiles = ((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn) * batch;
-        const float steps = (float)(((KB + c.kg - 1) / c.kg + 3) / 4);
+        const float steps = (float)(((KB + c.kg - 1) / c.kg + 3) / 4), grow = 1.0f + c.grow * beyond;
         const bool two = c.resident == 2 && tiles > cu;
-        const float rounds = (float)((tiles + cu * (two ? 2 : 1) - 1) / (cu * (two ? 2 : 1)));
-        const float t = rounds * (two ? c.fixed2 + steps * c.step2 : c.fixed1 + steps * c.step1);
+        const int64_t slots = two ? 2 * cu : cu, rounds = tiles / slots, rest = tiles - rounds * slots;
+        auto round_us = [&](bool pair, float fill) {
+            return pair ? c.fixed2 + steps * (c.step2 + c.fill2 * fill) * grow : c.fixed1 + steps * (c.step1 + c.fill1 * fill) * grow;
+        };
+        float t = c.base + outputs * (ragged ? c.ragged : c.store) + (float)rounds * round_us(two, 1.0f);
+        if (rest > 0) t += two && rest > cu ? round_us(true, (float)rest / (float)slots) : round_us(false, (float)rest / (float)cu);
         if (t < *us) {
             *us = t;
             best = i;
+        }
+    }
+    if (KB <= kDirectOnceBlocks) {
+        // tiles of one iteration flow through the chip rather than in rounds: latency, then tiles and outputs.  (12 %
+        // below the fit: where it is close to the small tiles it wins more often than they do.)
+        const float tiles = (float)(((M + 127) / 128) * ((N + 127) / 128) * batch) / (float)cu, more = tiles > 1.61f ? tiles - 1.61f : 0.0f;
+        const float t = 5.1f + 0.34f * (float)KB + more * (1.30f + 0.147f * (float)KB) + outputs * (ragged ? 0.40f : 0.071f);
+        if (t < *us) {
+            *us = t;
+            best = kOnceShape;
         }
     }
     return best;
@@ -659,6 +685,11 @@ float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch) {
     float us;
     choose_shape(M, N, KB, batch, &us);
     return us;
+}
+
+int gemm_direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch) {
+    float us;
+    return choose_shape(M, N, KB, batch, &us);
 }
 
 // At most this many rows of A or of W in one launch: the kernel addresses an operand with 32-bit byte offsets, the rows
@@ -673,15 +704,14 @@ int64_t gemm_direct_max_rows(int64_t KB, bool weight) {
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
     float us;
     const int shape = choose_shape(p.M, p.N, p.KB, batch, &us);
-    // the one-iteration form of the 128 x 128 tile was the fastest of the large tiles for every such K measured
-    if (shape >= 3 && p.KB <= kDirectOnceBlocks) return launch<DirectShape<2, 2, 2, 2, 1, true>>(mx, bf16, p, batch, stream);
     switch (shape) {
         case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);
         case 1: return launch<DirectShape<1, 1, 2, 2, 4>>(mx, bf16, p, batch, stream);
         case 2: return launch<DirectShape<1, 1, 2, 2, 2>>(mx, bf16, p, batch, stream);
         case 3: return launch<DirectShape<2, 2, 2, 2, 2>>(mx, bf16, p, batch, stream);
         case 4: return launch<DirectShape<2, 2, 2, 2, 1>>(mx, bf16, p, batch, stream);
-        default: return launch<DirectShape<2, 2, 4, 2, 1>>(mx, bf16, p, batch, stream);
+        case 5: return launch<DirectShape<2, 2, 4, 2, 1>>(mx, bf16, p, batch, stream);
+        default: return launch<DirectShape<2, 2, 2, 2, 1, true>>(mx, bf16, p, batch, stream);
     }
 }
 

@@ -28,7 +28,7 @@ SYMBOLS = [
     "dfp4_quantize", "dfp4_quantize_b64", "dfp4_quantize_mse", "dfp4_quantize_t", "mxfp4_quantize_t", "dfp4_quantize_t_at", "dfp4_dequantize", "dfp4_gemm", "dfp4_gemm_batched", "dfp4_gemm_workspace_bytes", "dfp4_gemm_noalloc",
     "dfp4_quantize_block", "dfp4_dequantize_block", "dfp4_gemm_blocks",
     "dfp4_gemm_prepared_bytes", "dfp4_gemm_prepare", "mxfp4_gemm_prepare", "dfp4_gemm_prepared_workspace_bytes",
-    "dfp4_gemm_prepared", "mxfp4_gemm_prepared", "dfp4_gemm_declined_tiles",
+    "dfp4_gemm_prepared", "mxfp4_gemm_prepared", "dfp4_gemm_declined_tiles", "dfp4_gemm_path",
     "mxfp4_gemm_native", "dfp4_gemm_native", "dfp4_gemm_native_workspace_bytes", "dfp4_native_packed_bytes",
     "dfp4_quantize_native", "dfp4_native_pack", "mxfp4_native_pack", "dfp4_gemm_native_packed_w", "mxfp4_gemm_native_packed_w",
     "dfp4_gemm_native_packed", "mxfp4_gemm_native_packed", "dfp4_gemm_native_splitk_bytes",
@@ -82,6 +82,8 @@ def load():
         getattr(lib, name).restype = ci
     lib.dfp4_gemm_declined_tiles.argtypes = [vp, i64, i64, ctypes.POINTER(ctypes.c_uint32)]
     lib.dfp4_gemm_declined_tiles.restype = ci
+    lib.dfp4_gemm_path.argtypes = [i64, i64, i64, i64, ci]
+    lib.dfp4_gemm_path.restype = ci
     lib.dfp4_gemm_noalloc.argtypes = [_CTensor, _CTensor, vp, ci, i64, vp]
     lib.dfp4_gemm_noalloc.restype = ci
     lib.dfp4_gemm_workspace_bytes.argtypes = [i64, i64, i64]
@@ -342,6 +344,11 @@ def gemm_declined_tiles(a):
     n = ctypes.c_uint32(0)
     _check(load().dfp4_gemm_declined_tiles(_ptr(a.buf), a.q.rows, a.q.K, ctypes.byref(n)), "dfp4_gemm_declined_tiles")
     return int(n.value)
+
+
+def gemm_path(M, N, K, batch=1, prepared=False):
+    """dfp4_gemm_path: the kernel a product takes (0: gemm_fast_kernel, 1..7: a shape of gemm_direct_kernel)."""
+    return int(load().dfp4_gemm_path(M, N, K, batch, 1 if prepared else 0))
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20

@@ -179,3 +179,35 @@ def test_gemm_prepared_refuses_a_weight_beyond_its_limit(lib):
     for rows in (1, 64, 256, 300):
         a = _t(256, 256, 256, rows, 16384)
         assert lib.dfp4_gemm_prepared(a, vp(256), big, vp(256), vp(256), 0, 1 << 18, vp(256), sz(1 << 40), vp(0)) == -2
+
+
+@pytest.mark.parametrize("M,N,K,batch,prepared,large", [
+    # microseconds of gemm_fast_kernel (with its prepass unless prepared) and of the best shape of gemm_direct_kernel
+    (2048, 4096, 14336, 1, 0, True),       # 171, 262
+    (1536, 4096, 14336, 1, 0, True),       # 145, 237
+    (2048, 2048, 14336, 1, 0, True),       # 137, 164
+    (2048, 4096, 11008, 1, 0, True),       # 145, 176
+    (1024, 14336, 4096, 1, 0, True),       # 84, 127
+    (3067, 1281, 14464, 1, 0, True),       # 153, 240
+    (4096, 4096, 4096, 1, 0, True),        # 90, 144
+    (512, 14336, 4096, 1, 1, True),        # 53, 64
+    (2048, 4096, 4096, 1, 0, False),       # 75, 67
+    (777, 3001, 2080, 1, 0, False),        # 72, 27
+    (512, 4096, 14336, 1, 0, False),       # 153, 111
+    (1024, 1024, 4096, 1, 0, False),       # 108, 20
+    (2048, 128, 2048, 128, 0, False),      # 397, 183
+    (2048, 2048, 128, 128, 0, False),      # 504, 397
+    (400, 2759, 6592, 1, 1, False),        # 97, 46
+    (64, 28672, 16384, 1, 0, False), (1, 32, 32, 1, 0, False), (700, 700, 16416, 1, 1, False)])     # the only kernel
+def test_gemm_path_takes_the_faster_kernel(lib, M, N, K, batch, prepared, large):
+    path = lib.dfp4_gemm_path(M, N, K, batch, prepared)
+    assert 0 <= path <= 7 and (path == 0) == large
+
+
+def test_gemm_path_of_short_k_and_of_errors(lib):
+    # K of one iteration: small tiles while they are few (4.7 against 8 microseconds), the one-iteration form beyond
+    assert dfp4.gemm_path(1, 256, 128) == 1 and dfp4.gemm_path(60, 700, 64) == 1
+    assert dfp4.gemm_path(2048, 4096, 128) == 7 and dfp4.gemm_path(1, 2048, 128, batch=128) == 7
+    assert dfp4.gemm_path(2048, 4096, 160) != 7
+    for bad in ((0, 4, 32, 1), (4, 0, 32, 1), (4, 4, 33, 1), (4, 4, 32, 0), (4, 4, -32, 1)):
+        assert lib.dfp4_gemm_path(*bad, 0) == -2
