@@ -112,15 +112,14 @@ inline PrepWLayout prep_w_layout(int64_t N, int64_t KB) {
 }
 // Workgroups per output tile: when there are fewer tiles than compute units, K is split
 // between 2, 4 or 8 workgroups; the last of them to finish adds the others' exact int32 sums.
-inline int choose_ksplit(int64_t tiles, int64_t KB) {
-    const int64_t cu = device_cu_count();
+inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
     int s = 1;
     while (s < 8 && tiles * s * 2 <= cu && KB / (2 * s) >= 16) s *= 2;
     return tiles <= kMaxSplitTiles ? s : 1;
 }
-inline int64_t partial_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
+inline int64_t partial_bytes(int64_t M, int64_t N, int64_t KB, int64_t cu) {
     const int64_t tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN);
-    const int s = choose_ksplit(tiles * batch, KB);
+    const int s = choose_ksplit(tiles, KB, cu);
     return s > 1 ? align256((int64_t)s * tiles * kTileM * kTileN * 4) : 0;
 }
 // Which kernel.  gemm_fast_kernel multiplies expanded operands; gemm_direct_kernel (gemm_direct.hip) expands in the
@@ -140,20 +139,23 @@ constexpr int kPreparedMinRows = 257;
 inline bool fast_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
 // Estimated microseconds of gemm_fast_kernel, fitted like those of the direct shapes: per round of workgroups a fixed
 // part, and per block of a workgroup's share of K more where the chip is full, growing beyond 128 blocks; the results; the exchange of partial tiles between s workgroups; the prepass unless the operands are prepared
-inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
-    const int64_t cu = device_cu_count(), tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN) * batch;
-    const int s = choose_ksplit(tiles, KB);
+inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared, int64_t cu) {
+    const int64_t tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN) * batch;
+    const int s = choose_ksplit(tiles, KB, cu);
     const int64_t rounds = tiles * s / cu, rest = tiles * s - rounds * cu;
     const float steps = (float)KB / (float)s, grow = 1.0f + 0.151f * (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
-    float t = (float)rounds * (12.8f + steps * 0.36f * grow) + (float)(M * N * batch) * 4e-6f * (N % 16 != 0 ? 0.406f : 0.012f);
+    float t = (float)rounds * (12.8f + steps * 0.36f * grow) + (float)M * (float)N * (float)batch * 4e-6f * (N % 16 != 0 ? 0.406f : 0.012f);
     if (rest > 0) t += 12.8f + steps * (0.284f + 0.0755f * (float)rest / (float)cu) * grow;
     if (s > 1) t += 4.5f + 10.4f * (float)(s - 1);
     if (!prepared) t += 7.7f + (0.601f * (float)M + 0.332f * (float)N) * (float)(KB * kBlock * batch) * 1e-6f;
     return t;
 }
-inline bool takes_direct_kernel(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
-    return !fast_kernel_can(M, KB) || (prepared ? M < kPreparedMinRows : KB <= kDirectOnceBlocks) ||
-           gemm_direct_cost(M, N, KB, batch) <= fast_cost(M, N, KB, batch, prepared);
+// the shape of gemm_direct_kernel that is taken, -1: gemm_fast_kernel
+inline int direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared, int64_t cu) {
+    const DirectChoice d = choose_direct(M, N, KB, batch, cu);
+    const bool direct = !fast_kernel_can(M, KB) || (prepared ? M < kPreparedMinRows : KB <= kDirectOnceBlocks) ||
+                        d.us <= fast_cost(M, N, KB, batch, prepared, cu);
+    return direct ? d.shape : -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -900,29 +902,34 @@ size_t gemm_prepared_declined_offset(int64_t M, int64_t K) {
 
 size_t gemm_prepared_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t KB = K / kBlock;
-    if (M <= 0 || N <= 0 || takes_direct_kernel(M, N, KB, 1, true)) return 0;
-    return (size_t)partial_bytes(M, N, KB, 1);
+    if (M <= 0 || N <= 0 || !fast_kernel_can(M, KB) || M < kPreparedMinRows) return 0;
+    const int64_t cu = device_cu_count();
+    return direct_shape(M, N, KB, 1, true, cu) >= 0 ? 0 : (size_t)partial_bytes(M, N, KB, cu);
 }
 
 // what gemm_fast_kernel and its prepass need
+static size_t fast_workspace_bytes(int64_t M, int64_t N, int64_t KB, int64_t cu) {
+    const int64_t Mc = M < max_rows_a(KB) ? M : max_rows_a(KB), Nc = N < max_rows_w(KB) ? N : max_rows_w(KB);
+    return (size_t)(prep_a_layout(Mc, KB).total + prep_w_layout(Nc, KB).total + partial_bytes(Mc, Nc, KB, cu));
+}
+
 size_t gemm_fast_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t KB = K / kBlock;
-    if (M <= 0 || N <= 0 || !fast_kernel_can(M, KB)) return 0;
-    const int64_t Mc = M < max_rows_a(KB) ? M : max_rows_a(KB), Nc = N < max_rows_w(KB) ? N : max_rows_w(KB);
-    return (size_t)(prep_a_layout(Mc, KB).total + prep_w_layout(Nc, KB).total + partial_bytes(Mc, Nc, KB, 1));
+    return M <= 0 || N <= 0 || !fast_kernel_can(M, KB) ? 0 : fast_workspace_bytes(M, N, KB, device_cu_count());
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t KB = K / kBlock;
     if (M <= 0 || N <= 0 || !fast_kernel_can(M, KB)) return 0;
     // nothing but a token where the direct kernel is taken whatever the batch
-    if (takes_direct_kernel(M, N, KB, 1, false) && takes_direct_kernel(M, N, KB, 65535, false)) return 256;
-    return gemm_fast_workspace_bytes(M, N, K);
+    const int64_t cu = device_cu_count();
+    if (direct_shape(M, N, KB, 1, false, cu) >= 0 && direct_shape(M, N, KB, 65535, false, cu) >= 0) return 256;
+    return fast_workspace_bytes(M, N, KB, cu);
 }
 
 int gemm_path(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared) {
     prepared = prepared && KB > 0 && KB <= kMaxKB;         // otherwise nothing is prepared and the operands are read as they are
-    return takes_direct_kernel(M, N, KB, batch, prepared) ? 1 + gemm_direct_shape(M, N, KB, batch) : 0;
+    return 1 + direct_shape(M, N, KB, batch, prepared, device_cu_count());
 }
 
 size_t gemm_requant_workspace_bytes(int64_t M, int64_t N, int64_t K) {
@@ -975,7 +982,7 @@ int launch_prep(bool mx, const GemmParams& p, bool do_a, bool do_w, int64_t batc
 int launch_fast(bool mx, bool bf16, GemmParams& p, int64_t batch, int* part, size_t part_bytes, bool rq,
                 hipStream_t stream) {
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-    p.ksplit = choose_ksplit(tiles * batch, p.KB);
+    p.ksplit = choose_ksplit(tiles * batch, p.KB, device_cu_count());
     const size_t per_batch = (size_t)p.ksplit * tiles * kTileM * kTileN * 4;
     if (p.ksplit > 1 && (!part || per_batch * (size_t)batch > part_bytes)) p.ksplit = 1;   // no room: no split
     p.part = part;
@@ -997,7 +1004,7 @@ int launch_fast(bool mx, bool bf16, GemmParams& p, int64_t batch, int* part, siz
 // direct kernel, in pieces of at most as many rows as it addresses
 int launch_direct(bool mx, bool bf16, dfp4_tensor A, dfp4_tensor W, void* out, int64_t ldc, int64_t batch,
                   int64_t strideA_rows, int64_t strideW_rows, int64_t strideC, hipStream_t stream) {
-    const int64_t KB = A.K / kBlock, M = A.rows, N = W.rows;
+    const int64_t KB = A.K / kBlock, M = A.rows, N = W.rows, cu = device_cu_count();
     const int64_t mc = gemm_direct_max_rows(KB, false), nc = gemm_direct_max_rows(KB, true);
     for (int64_t m0 = 0; m0 < M; m0 += mc)
         for (int64_t n0 = 0; n0 < N; n0 += nc) {
@@ -1009,7 +1016,7 @@ int launch_direct(bool mx, bool bf16, dfp4_tensor A, dfp4_tensor W, void* out, i
             GemmParams p{};
             fill_params(p, a, w, static_cast<uint8_t*>(out) + (size_t)(m0 * ldc + n0) * (bf16 ? 2 : 4), ldc, strideA_rows,
                         strideW_rows, strideC, nullptr);
-            const int rc = launch_gemm_direct(mx, bf16, p, batch, stream);
+            const int rc = launch_gemm_direct(mx, bf16, p, batch, choose_direct(p.M, p.N, KB, batch, cu).shape, stream);
             if (rc != DFP4_OK) return rc;
         }
     return DFP4_OK;
@@ -1041,8 +1048,9 @@ int launch_gemm(bool mx, dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype,
     int rc = gemm_shape_check(A, W, ldc, batch, rq != nullptr);
     if (rc != DFP4_OK) return rc;
     const bool bf16 = out_dtype == DFP4_BF16;
-    const size_t fast_bytes = gemm_fast_workspace_bytes(M, N, A.K) * (size_t)batch;
-    if (!fast_kernel_can(M, KB) || (!rq && (takes_direct_kernel(M, N, KB, batch, false) || !workspace || workspace_bytes < fast_bytes))) {
+    const int64_t cu = device_cu_count();
+    if (!fast_kernel_can(M, KB) || (!rq && (!workspace || workspace_bytes < fast_workspace_bytes(M, N, KB, cu) * (size_t)batch ||
+                                            direct_shape(M, N, KB, batch, false, cu) >= 0))) {
         rc = launch_direct(mx, bf16, A, W, out, ldc, batch, strideA_rows, strideW_rows, strideC, stream);
         if (rc != DFP4_OK || !rq) return rc;
         return launch_quantize(mx, out, M * batch, N, ldc, *rq, stream);       // `out` holds the bf16 [batch * M, N]
@@ -1123,17 +1131,19 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     if (!shape_in_range(M, N, KB, 1, ldc)) return DFP4_ERR_SHAPE;
     const bool bf16 = out_dtype == DFP4_BF16;
     if (KB == 0 || KB > kMaxKB) return launch_direct(mx, bf16, A, W, out, ldc, 1, 0, 0, 0, stream);
+    const int64_t cu = device_cu_count();
     GemmParams p{};
     fill_params(p, A, W, out, ldc, 0, 0, 0, nullptr);
     if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     if (M < kPreparedMinRows) {
         p.declined = static_cast<uint32_t*>(a_prepared);
-        return launch_gemm_direct(mx, bf16, p, 1, stream);     // one launch: max_rows_w is half of what it takes
+        return launch_gemm_direct(mx, bf16, p, 1, choose_direct(M, N, KB, 1, cu).shape, stream);     // one launch: max_rows_w is half of what it takes
     }
     set_prepared(p, static_cast<uint8_t*>(a_prepared), 0, static_cast<uint8_t*>(const_cast<void*>(w_prepared)), 0);
-    if (takes_direct_kernel(M, N, KB, 1, true) && M <= gemm_direct_max_rows(KB, false) && N <= gemm_direct_max_rows(KB, true)) {
+    const int shape = direct_shape(M, N, KB, 1, true, cu);
+    if (shape >= 0 && M <= gemm_direct_max_rows(KB, false) && N <= gemm_direct_max_rows(KB, true)) {
         p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));
-        return launch_gemm_direct(mx, bf16, p, 1, stream);
+        return launch_gemm_direct(mx, bf16, p, 1, shape, stream);
     }
     return launch_fast(mx, bf16, p, 1, static_cast<int*>(workspace), workspace_bytes, false, stream);
 }

@@ -319,12 +319,12 @@ void dispatch_mx_bf16(bool mx, bool bf16, F&& f) {
 }  // namespace
 
 // gemm_direct.hip: any product of at most gemm_direct_max_rows(KB, false) rows of A and (KB, true) of W, with the operands as they
-// are or (p.a_prep, p.w_prep) with the references and class masks of prepared ones; the cost is an estimate in
-// microseconds
-int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream);
+// are or (p.a_prep, p.w_prep) with the references and class masks of prepared ones; a shape and the microseconds it is
+// estimated to take on `cu` compute units
+struct DirectChoice { int shape; float us; };
+int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
 constexpr int kDirectOnceBlocks = 4;         // K, in blocks, that it takes in one iteration
-float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch);
-int gemm_direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch);
+DirectChoice choose_direct(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu);
 int64_t gemm_direct_max_rows(int64_t KB, bool weight);
 
 }  // namespace dfp4

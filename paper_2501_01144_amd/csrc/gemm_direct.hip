@@ -616,8 +616,8 @@ int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t s
 
 // The tile shapes and what a product takes with each, in microseconds: `base`; per round of workgroups `fixed`, and for
 // every 4 blocks of a group's share of K `step` + `fill` x the share of the chip that the round fills (the last round's
-// rest counts as much as it fills), growing with K beyond 128 blocks by `grow` per 384; `store` per 10^6 outputs of 4
-// bytes, where rows of outputs begin inside a line (N % 16) `ragged`.  1: one workgroup per compute unit, 2: two, which
+// rest counts as much as it fills), growing with K beyond 128 blocks by `grow` per 384; `store` per MB of fp32
+// results, where their rows begin inside a line (N % 16) `ragged`.  1: one workgroup per compute unit, 2: two, which
 // shapes that fit take as soon as there are more tiles than compute units.
 // Fitted to 21000 products timed on 256 compute units, M 1..4096, N 64..14336, K 32..16384, 1 to 128 problems, each with
 // every shape: the estimates are within 10 % (rms).  Microseconds of 32 / 64 (KG 4) / 64 (KG 2) / 128 (KG 2) / 128 / 256 rows, and of gemm_fast_kernel
@@ -642,12 +642,13 @@ constexpr DirectCost kDirectCost[] = {
 };
 constexpr int kOnceShape = 6;                          // the one-iteration form of the 128 x 128 tile
 
-int choose_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, float* us) {
-    const int64_t cu = device_cu_count();
-    const float outputs = (float)(M * N * batch) * 4e-6f, beyond = (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
+}  // namespace
+
+DirectChoice choose_direct(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu) {
+    const float outputs = (float)M * (float)N * (float)batch * 4e-6f, beyond = (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
     const bool ragged = N % 16 != 0;
-    int best = 0;
-    *us = 3e38f;
+    DirectChoice best{0, 3e38f};
+#pragma unroll
     for (int i = 0; i < (int)(sizeof(kDirectCost) / sizeof(kDirectCost[0])); ++i) {
         const DirectCost& c = kDirectCost[i];
         if (KB > kSmallMaxKB && !c.any_k) continue;    // their declined tiles keep all exponents of A in LDS
@@ -661,35 +662,16 @@ int choose_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, float* us) {
         };
         float t = c.base + outputs * (ragged ? c.ragged : c.store) + (float)rounds * round_us(two, 1.0f);
         if (rest > 0) t += two && rest > cu ? round_us(true, (float)rest / (float)slots) : round_us(false, (float)rest / (float)cu);
-        if (t < *us) {
-            *us = t;
-            best = i;
-        }
+        if (t < best.us) best = {i, t};
     }
     if (KB <= kDirectOnceBlocks) {
         // tiles of one iteration flow through the chip rather than in rounds: latency, then tiles and outputs.  (12 %
         // below the fit: where it is close to the small tiles it wins more often than they do.)
         const float tiles = (float)(((M + 127) / 128) * ((N + 127) / 128) * batch) / (float)cu, more = tiles > 1.61f ? tiles - 1.61f : 0.0f;
         const float t = 5.1f + 0.34f * (float)KB + more * (1.30f + 0.147f * (float)KB) + outputs * (ragged ? 0.40f : 0.071f);
-        if (t < *us) {
-            *us = t;
-            best = kOnceShape;
-        }
+        if (t < best.us) best = {kOnceShape, t};
     }
     return best;
-}
-
-}  // namespace
-
-float gemm_direct_cost(int64_t M, int64_t N, int64_t KB, int64_t batch) {
-    float us;
-    choose_shape(M, N, KB, batch, &us);
-    return us;
-}
-
-int gemm_direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch) {
-    float us;
-    return choose_shape(M, N, KB, batch, &us);
 }
 
 // At most this many rows of A or of W in one launch: the kernel addresses an operand with 32-bit byte offsets, the rows
@@ -701,9 +683,7 @@ int64_t gemm_direct_max_rows(int64_t KB, bool weight) {
     return rows >= 512 ? rows / 512 * 512 : rows;
 }
 
-int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
-    float us;
-    const int shape = choose_shape(p.M, p.N, p.KB, batch, &us);
+int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream) {
     switch (shape) {
         case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);
         case 1: return launch<DirectShape<1, 1, 2, 2, 4>>(mx, bf16, p, batch, stream);
