@@ -1373,3 +1373,27 @@ def test_dequantize_fp32_stores_whole_lines():
     t32, t16 = us(torch.float32), us(torch.bfloat16)
     print(f"dequantize 8192x4096: fp32 {t32:.1f} us, bf16 {t16:.1f} us", flush=True)
     assert t32 < 3 * t16
+
+
+def test_calls_go_to_the_current_stream():
+    # the handle that a call gets is that of torch's current stream, also of a side stream and of a capturing one
+    assert (dfp4._stream().value or 0) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    a, w = synth.gaussian(33, 512, 1.0, seed=1).cuda(), synth.gaussian(65, 512, 0.02, seed=2).cuda()
+    want = dfp4.gemm(dfp4.quantize(a), dfp4.quantize(w))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        assert dfp4._stream().value == side.cuda_stream
+        out = dfp4.gemm(dfp4.quantize(a), dfp4.quantize(w))
+    side.synchronize()
+    assert torch.equal(out, want)
+    graph, qa, qw = torch.cuda.CUDAGraph(), dfp4.quantize(a), dfp4.quantize(w)
+    out.zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        dfp4.gemm(dfp4.quantize(a, out=qa), qw, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
