@@ -21,9 +21,10 @@
 // classes zeroed, into a second set of accumulators (class sum 1, weight 16; class sum 2 is added there
 // shifted).  Whether the tile can be summed in int32 is decided from the rows' exponents:
 // 32 * 120^2 * sum over blocks of 16^(class of A + class of W) must stay below 2^31 for every output.  Bounds of
-// rising cost: the largest classes of the tile in every block; the classes that meet in every block (the rule of
-// gemm_fast_kernel, on the tile's own rows); the blocks of every row against the largest class of the other operand.
-// A tile that passes none is computed with one fp32 scale-and-add per block.
+// rising cost: the largest classes of the tile in every block; the blocks of every row against the largest class of the
+// other operand (where that is 0 it is as good as the next; it also takes many rows whose high blocks lie in different
+// places); the classes that meet in every block (the rule of gemm_fast_kernel, on the tile's own rows).  A tile that
+// passes none is computed with one fp32 scale-and-add per block.
 #include <type_traits>
 #include "gemm_common.h"
 
@@ -203,51 +204,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
         cw_max = __builtin_amdgcn_readfirstlane(lds.spread[1]) >> 2;
         const bool can = max(ca_max, cw_max) <= kMaxClass && KB <= kIntBound;
         declined = !can || ca_max + cw_max > kMaxClass || (KB << (4 * (ca_max + cw_max))) > kIntBound;
-        if (can && declined && min(ca_max, cw_max) > 0) {
-            // The classes that meet in every block: 8 lanes take 4 blocks, each an eighth of the rows of A and of W, and
-            // OR the bits of the classes they find.  Few outlier channels on both operands end here (one block of
-            // class 1 each is beyond the first bound from K = 608, beyond that of the rows from K = 8864).
-            // 700 x 4096 x 4096, 0.5 % of the channels of W x 20: 465 us with every such tile declined, 65 so.
-            const int n4 = (KB + 3) >> 2, part8 = tid & 7;
-            int weight = 0;
-            auto present = [&](const uint8_t* e0, const uint8_t* ref0, int n, int last, int left) {
-                uint32_t mask = 0;
-#pragma unroll 4
-                for (int j = 0; j < n; ++j) {
-                    const uint8_t* e = e0 + (int64_t)min(j, last) * KB;
-                    uint32_t v = 0;
-                    if (left >= 4) {
-                        __builtin_memcpy(&v, e, 4);                    // no alignment assumed
-                    } else {                                           // the bytes beyond K are not looked at below
-                        for (int k = 0; k < left; ++k) v |= (uint32_t)e[k] << (8 * k);
-                    }
-                    // offset of every byte / 4 (no offset is beyond 11) -> its bit; a last row is repeated as it is
-                    mask |= __builtin_amdgcn_perm(0u, 0x00040201u, ((v - ref0[min(j, last)] * 0x01010101u) >> 2) & 0x03030303u);
-                }
-                return mask;
-            };
-            for (int i = tid; i < 8 * n4; i += S::kThreads) {
-                constexpr int kNa = S::kTm / 8, kNw = S::kTn / 8;
-                const int q = i >> 3, left = KB - 4 * q, ra = part8 * kNa, rw = part8 * kNw;
-                // rows beyond the operand: its last one, or none where this lane's share begins beyond it
-                const int la = p.M - 1 - (m0 + ra), lw = p.N - 1 - (n0 + rw);
-                uint32_t ma = 0, mw = 0;
-                if (la >= 0) ma = present(p.a_exp + (bz * p.strideA_rows + m0 + ra) * KB + 4 * q, &lds.mn[ra], kNa, la, left);
-                if (lw >= 0) mw = present(p.w_exp + (bz * p.strideW_rows + n0 + rw) * KB + 4 * q, &lds.mn[S::kTm + rw], kNw, lw, left);
-#pragma unroll
-                for (int o = 1; o < 8; o <<= 1) {
-                    ma |= (uint32_t)__shfl_xor((int)ma, o);
-                    mw |= (uint32_t)__shfl_xor((int)mw, o);
-                }
-                if (part8 < 4 && part8 < left) weight += block_weight((ma >> (8 * part8)) & 0xffu, (mw >> (8 * part8)) & 0xffu);
-            }
-            if (weight) atomicAdd(&lds.met, weight);
-            __syncthreads();
-            declined = lds.met > kIntBound;
-        }
-        if (can && declined && ca_max + cw_max <= kMaxClass) {
-            // the classes of every row's own blocks against the largest class of the other operand: where that is 0,
-            // and for many rows whose high blocks lie in different places
+        // a row with a single block of its operand's largest class, the least that can be found
+        const bool rows_may = can && ca_max + cw_max <= kMaxClass && min((KB - 1 + (1 << (4 * ca_max))) << (4 * cw_max),
+                                                                         (KB - 1 + (1 << (4 * cw_max))) << (4 * ca_max)) <= kIntBound;
+        // the classes of every row's own blocks against the largest class of the other operand
+        auto weigh_rows = [&] {
             if (is_row) {
                 int weight = 0;
                 for (int i = part; i < n16; i += kParts) {
@@ -264,11 +225,63 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
             }
             __syncthreads();
             declined = min(lds.weight[0], lds.weight[1]) > kIntBound;
+        };
+        auto weigh_met = [&] {
+            // The classes that meet in every block: 8 lanes take 4 blocks, each an eighth of the rows of A and of W, and
+            // OR the bits of the classes they find (A's in the low half of a block's byte).  Few outlier channels on both
+            // operands end here, all of them from K = 8864.  700 x 4096 x 4096, 0.5 % of the channels of W x 20: 465 us with
+            // every such tile declined, 65 so.  It is a chain of latencies: 16 x 4096 x 4096 13.7 us, 10.2 without classes on W.
+            int weight = 0;
+            if (KB >= 4) {
+                const int part8 = tid & 7;
+                for (int i = tid >> 3; 4 * i < KB; i += S::kThreads / 8) {
+                    const int left = min(KB - 4 * i, 4), at = min(4 * i, KB - 4);      // the last of K with those before them
+                    uint32_t met = 0;
+                    auto present = [&](const uint8_t* e, int64_t row0, int last, int r0, const uint8_t* ref, int n, int shift) {
+#pragma unroll 4
+                        for (int j = 0; j < n; ++j) {
+                            uint32_t v;
+                            __builtin_memcpy(&v, e + (row0 + min(r0 + j, last)) * KB + at, 4);     // no alignment assumed
+                            // offset of every byte / 4 (no offset is beyond 11) -> its bit
+                            met |= __builtin_amdgcn_perm(0u, 0x00040201u, ((v - ref[j] * 0x01010101u) >> 2) & 0x03030303u) << shift;
+                        }
+                    };
+                    constexpr int kNa = S::kTm / 8, kNw = S::kTn / 8;
+                    present(p.a_exp, bz * p.strideA_rows + m0, p.M - 1 - m0, part8 * kNa, &lds.mn[part8 * kNa], kNa, 0);
+                    present(p.w_exp, bz * p.strideW_rows + n0, p.N - 1 - n0, part8 * kNw, &lds.mn[S::kTm + part8 * kNw], kNw, 4);
+#pragma unroll
+                    for (int o = 1; o < 8; o <<= 1) met |= (uint32_t)__shfl_xor((int)met, o);
+                    met >>= 8 * (4 - left);
+                    if (part8 < left) weight += block_weight((met >> (8 * part8)) & 15u, (met >> (8 * part8 + 4)) & 15u);
+                }
+            } else {                                                   // up to 3 blocks: a bit per (block, class); the rows' weights are not in use
+                if (is_row && part == 0)
+                    for (int k = 0; k < KB; ++k) atomicOr(&lds.weight[is_a ? 0 : 1], 1 << (8 * k + ((erow[k] - mn) >> 2)));
+                __syncthreads();
+                if (tid < KB) weight = block_weight((lds.weight[0] >> (8 * tid)) & 15, (lds.weight[1] >> (8 * tid)) & 15);
+            }
+            if (weight) atomicAdd(&lds.met, weight);
+            __syncthreads();
+            declined = lds.met > kIntBound;
+        };
+        // With classes on both operands the rows are looked at first where K is short (24 x 2904 x 1600: 9.3 us, after the
+        // blocks 9.9), the blocks that meet first otherwise (16 x 4096 x 4096: 13.7, after the rows 14.4).  One copy of
+        // either, out of the way of the tiles that need neither.
+        if (can && declined) {
+            const bool both = min(ca_max, cw_max) > 0, rows_first = !both || KB <= 64;
+#pragma unroll 1
+            for (int pass = 0; pass < 2 && declined; ++pass) {
+                if ((pass == 0) == rows_first) {
+                    if (rows_may) weigh_rows();
+                } else if (both) {
+                    weigh_met();
+                }
+            }
         }
     }
 #pragma unroll
     for (int j = 0; j < S::kItems; ++j) ref[j] = lds.mn[j * S::kItemRows + r4];
-    if (declined) {                                                    // the same for every thread
+    if (declined) {                               // the same for every thread
         // counted once per 512 x 128 tile on prepared operands, once per tile otherwise
         if (p.declined && tid == 0 && (!p.a_prep || (m0 % 512 == 0 && n0 % 128 == 0))) atomicAdd(p.declined, 1u);
         __syncthreads();

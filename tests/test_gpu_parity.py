@@ -1325,7 +1325,8 @@ def _lifted(rows, K, std, blocks, by, g, every=1):
     (128, 2049, 14336, 8, 6, 3, 7, 7), (700, 1030, 4096, 20, 30, 7, 7, 7),
     (300, 2049, 16480, 9, 9, 6, 7, 7),                                            # K beyond the prepared form
     (1500, 4000, 1120, 20, 22, 7, 7, 7), (652, 3397, 1184, 20, 22, 7, 7, 7),
-    (16, 300, 1024, 2, 4, 0, 11, 7), (200, 300, 1056, 2, 6, 0, 9, 6), (300, 520, 128, 1, 1, 0, 10, 9)])   # classes 2 and 1 that never meet
+    (16, 300, 1024, 2, 4, 0, 11, 7), (200, 300, 1056, 2, 6, 0, 9, 6), (300, 520, 128, 1, 1, 0, 10, 9),
+    (300, 520, 96, 1, 1, 0, 10, 9), (40, 70, 64, 1, 1, 0, 9, 11)])                # classes 2 and 1 (and 2) that never meet
 def test_gemm_exact_where_few_high_blocks_meet(M, N, K, n_a, n_w, meet, by_a, by_w):
     # A and W hold a few blocks far above the others, `meet` of them the same.  The exact sum fits int32 by the blocks that
     # meet (asserted), although not by the largest class of either operand
