@@ -4,6 +4,8 @@
 // (8 elements); the dialect's 8 table bytes sit in two registers and
 // v_perm_b32 does four lookups per instruction.  Both output types hold the
 // values exactly (u has 4 significant bits).
+#include <type_traits>
+
 #include "common.h"
 #include "formatbook.h"
 
@@ -57,27 +59,29 @@ __device__ __forceinline__ void expand_store(uint32_t c, uint32_t half, uint32_t
     }
 }
 
-// A wave takes 64 blocks in passes, the loads of all passes first; the grid covers the tensor and results bypass the
-// caches (nobody reads them soon).  A lane stores 16 bytes and a pass whole lines: bf16 a dword of codes per lane, 16
-// blocks a pass; fp32 half a dword, 8 blocks a pass.  Bound by memory: 4096 x 14336 to bf16, operands from HBM, 23.1 us
-// = 6.5 TB/s; 8192 x 4096 to fp32, operands and results in turn from six sets, 24.6 us = 6.2 TB/s.  One load, table
-// look-up and store at a time in 4096 persistent workgroups was bound by the latency of that chain (38.8 and 43.9 us); a
-// whole dword per lane for fp32 stores half a line twice, which costs 56.7 us when it bypasses the caches and 44.3 when
-// it does not (whole lines through the caches: 42.4).  `narrow`: one exponent byte and dialect id per 16 elements.
-template <bool MX, bool BF16, bool CONTIG>
+// A wave takes PASSES times 16 blocks (bf16, a dword of codes per lane) or 8 (fp32, half a dword), the loads of all passes
+// first; a lane stores 16 bytes and a pass whole lines, past the caches (nobody reads the results soon).  Bound by memory:
+// 4096 x 14336 to bf16, operands from HBM, 23.1 us = 6.5 TB/s; 8192 x 4096 to fp32, operands and results in turn from six
+// sets, 23.5 us = 6.5 TB/s.  Four passes suit large bf16 tensors (4096 x 14336 in rows with gaps 23.5 us, one pass 27.1),
+// one pass everything else: small tensors are latency and want waves (1024 blocks to fp32 2.2 us, with eight passes 3.5;
+// to bf16 2.1, with four 2.7), and fp32 has twice the waves (8192 x 4096 again and again 20.8 us, with eight passes 24.6).
+// Before: one load, table look-up and store at a time in 4096 persistent workgroups (2.2, 2.1, 38.8 and 43.9 us); a whole
+// dword per lane for fp32 stores half a line twice, 56.7 us past the caches and 44.3 through them (whole lines through
+// them: 42.4).  `narrow`: one exponent byte and dialect id per 16 elements.
+template <bool MX, bool BF16, bool CONTIG, uint32_t PASSES>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(
     const uint32_t* __restrict__ codes, const uint8_t* __restrict__ dialect,
     const uint8_t* __restrict__ exponent, void* __restrict__ y, int64_t ld, uint32_t blocks_per_row,
     uint32_t nblocks, uint32_t narrow) {
-    constexpr uint32_t kLanes = BF16 ? 4 : 8, kBlocksPerPass = 64 / kLanes, kPasses = 64 / kBlocksPerPass, kElems = kBlock / kLanes;
+    constexpr uint32_t kLanes = BF16 ? 4 : 8, kBlocksPerPass = 64 / kLanes, kPasses = PASSES, kPerWave = kPasses * kBlocksPerPass, kElems = kBlock / kLanes;
     const uint32_t lane = threadIdx.x & 63u, part = lane % kLanes, sub = part * 4u / kLanes;     // dword of the block
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t nsuper = (nblocks + 63u) / 64u, stride = gridDim.x * (kThreads / 64);
+    const uint32_t nsuper = (nblocks + kPerWave - 1u) / kPerWave, stride = gridDim.x * (kThreads / 64);
     for (uint32_t sc = blockIdx.x * (kThreads / 64) + wave; sc < nsuper; sc += stride) {
         uint32_t c[kPasses], e[kPasses], d[kPasses];
 #pragma unroll
         for (uint32_t p = 0; p < kPasses; ++p) {
-            const uint32_t b = min(sc * 64u + p * kBlocksPerPass + lane / kLanes, nblocks - 1u);
+            const uint32_t b = min(sc * kPerWave + p * kBlocksPerPass + lane / kLanes, nblocks - 1u);
             const size_t mb = narrow ? (size_t)b * 2u + (sub >> 1) : (size_t)b;
             c[p] = codes[(size_t)b * 4u + sub];
             e[p] = exponent[mb];
@@ -85,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(
         }
 #pragma unroll
         for (uint32_t p = 0; p < kPasses; ++p) {
-            const uint32_t b = sc * 64u + p * kBlocksPerPass + lane / kLanes;
+            const uint32_t b = sc * kPerWave + p * kBlocksPerPass + lane / kLanes;
             if (b >= nblocks) break;
             int64_t off;
             if constexpr (CONTIG) {
@@ -106,25 +110,26 @@ int launch_dequantize(bool mx, dfp4_tensor in, void* y, int y_dtype, int64_t ld,
     if (nblocks64 == 0) return DFP4_OK;
     if (nblocks64 >= (int64_t)1 << 31) return DFP4_ERR_SHAPE;
     const uint32_t nblocks = (uint32_t)nblocks64;
-    const uint32_t nsuper = (nblocks + 63u) / 64u;
-    const uint32_t grid = (nsuper + kThreads / 64 - 1) / (kThreads / 64);
-    const bool contig = (ld == in.K);
+    const bool contig = (ld == in.K), bf16 = y_dtype == DFP4_BF16;
     const uint32_t kb = (uint32_t)(in.K / kBlock);
     const uint32_t* cp = reinterpret_cast<const uint32_t*>(in.codes);
-#define DFP4_LAUNCH(MXV, BV, CV)                                                                  \
-    hipLaunchKernelGGL((dequantize_kernel<MXV, BV, CV>), dim3(grid), dim3(kThreads), 0, stream, cp, \
-                       in.dialect, in.exponent, y, ld, kb, nblocks, narrow ? 1u : 0u)
-#define DFP4_PICK(MXV)                                                             \
-    do {                                                                           \
-        if (y_dtype == DFP4_BF16) {                                                \
-            if (contig) DFP4_LAUNCH(MXV, true, true); else DFP4_LAUNCH(MXV, true, false);   \
-        } else {                                                                   \
-            if (contig) DFP4_LAUNCH(MXV, false, true); else DFP4_LAUNCH(MXV, false, false); \
-        }                                                                          \
-    } while (0)
-    if (mx) DFP4_PICK(true); else DFP4_PICK(false);
-#undef DFP4_PICK
-#undef DFP4_LAUNCH
+    auto launch = [&](auto mx_c, auto bf16_c, auto contig_c, auto passes_c) {
+        constexpr bool kBf16 = decltype(bf16_c)::value;
+        constexpr uint32_t kPasses = decltype(passes_c)::value, kPerGroup = (kBf16 ? 16 : 8) * kPasses * (kThreads / 64);
+        const uint32_t want = (nblocks + kPerGroup - 1) / kPerGroup, grid = want < (1u << 23) ? want : 1u << 23;   // at most 2^31 threads
+        hipLaunchKernelGGL((dequantize_kernel<decltype(mx_c)::value, kBf16, decltype(contig_c)::value, kPasses>), dim3(grid), dim3(kThreads), 0,
+                           stream, cp, in.dialect, in.exponent, y, ld, kb, nblocks, narrow ? 1u : 0u);
+    };
+    auto pick = [](bool v, auto&& f) { if (v) f(std::true_type{}); else f(std::false_type{}); };
+    using One = std::integral_constant<uint32_t, 1>;
+    using Four = std::integral_constant<uint32_t, 4>;
+    pick(mx, [&](auto m) {
+        pick(contig, [&](auto c) {
+            if (!bf16) launch(m, std::false_type{}, c, One{});
+            else if (nblocks < (1u << 20)) launch(m, std::true_type{}, c, One{});
+            else launch(m, std::true_type{}, c, Four{});
+        });
+    });
     return check_launch();
 }
 

@@ -1292,9 +1292,9 @@ def test_quantize_t_tile_edges_and_code_alignment(rows, cols, skip):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("rows,K", [(1, 32), (1, 2016), (2, 1024), (5, 416), (257, 64)])
+@pytest.mark.parametrize("rows,K", [(1, 32), (1, 2016), (2, 1024), (5, 416), (257, 64), (1, 224), (3, 96), (1023, 32768), (1031, 32736)])
 def test_dequantize_around_64_blocks(rows, K, dtype):
-    # 1, 63, 64, 65 and 514 blocks: a wave takes 64; contiguous and strided outputs
+    # 1, 63, 64, 65 and 514 blocks, 7 and 9, and either side of 2^20: a wave takes 8 (fp32), 16 or 64; contiguous and strided
     x = synth.student_t(rows, K, 3.0, seed=rows + K)
     q = dfp4.quantize(_dev(x))
     ref = O.dfp4_dequantize(*O.dfp4_quantize(synth.to_f64(x)))
@@ -1398,3 +1398,29 @@ def test_calls_go_to_the_current_stream():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+def test_dequantize_small_tensors_take_waves():
+    # 1024 blocks are latency: with a wave for 64 of them they took 1.6 times (fp32) and 1.3 times as long as 32 blocks
+    # on top of a launch; with a wave for each 8 or 16 nearly as long
+    def us(rows, dtype):
+        q = dfp4.quantize(synth.gaussian(rows, 1024, 1.0, seed=rows).cuda())
+        y, stream, graph = torch.empty(rows, 1024, dtype=dtype, device="cuda"), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.stream(stream):
+            dfp4.dequantize(q, out=y)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(50):
+                dfp4.dequantize(q, out=y)
+        best = float("inf")
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 50 * 1e3)
+        return best
+    one, many = us(1, torch.float32), us(32, torch.float32)
+    print(f"dequantize to fp32: 32 blocks {one:.2f} us, 1024 blocks {many:.2f} us", flush=True)
+    assert many < 1.25 * one
