@@ -256,7 +256,8 @@ int dfp4_gemm_path(int64_t M, int64_t N, int64_t K, int64_t batch, int prepared)
  * DFP4_NOALLOC_SCRATCH_BYTES that is part of the library's device code (each GPU the
  * library runs on holds its own copy until the process ends).  The call allocates and
  * frees nothing.  Products with dfp4_gemm_workspace_bytes(M, N, K) above that size are
- * refused with DFP4_ERR_WORKSPACE (64 MiB covers M = 2048, N = 14336, K = 4096).
+ * refused with DFP4_ERR_WORKSPACE (64 MiB covers M = 2048, N = 14336, K = 4096), unless
+ * dfp4_gemm_path(M, N, K, 1, 0) is not 0: that kernel needs no workspace.
  * All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU
  * (different streams, different threads) race and must be ordered by the caller; calls on
  * one stream are ordered by the stream.  Every call initializes what it reads, so nothing

@@ -196,10 +196,11 @@ int dfp4_gemm(dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype, int64_t ld
 int dfp4_gemm_noalloc(dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype, int64_t ldc, void* stream) {
     if (A.rows < 0 || W.rows < 0 || A.K < 0) return DFP4_ERR_SHAPE;
     // the size check comes first: a product that does not fit is refused whatever else is wrong with it
-    if (gemm_workspace_bytes(A.rows, W.rows, A.K) > (size_t)DFP4_NOALLOC_SCRATCH_BYTES) return DFP4_ERR_WORKSPACE;
+    if (gemm_workspace_bytes(A.rows, W.rows, A.K) > (size_t)DFP4_NOALLOC_SCRATCH_BYTES &&
+        gemm_path(A.rows, W.rows, A.K / kBlock, 1, false) == 0)      // (a single product of another path needs none)
+        return DFP4_ERR_WORKSPACE;
     // argument checks first (with a stand-in for the workspace pointer), then the scratch array's address
-    int rc = check_gemm_args(A, W, out, out_dtype, ldc, true, reinterpret_cast<void*>(uintptr_t{256}),
-                             DFP4_NOALLOC_SCRATCH_BYTES);
+    int rc = check_gemm_args(A, W, out, out_dtype, ldc, true, reinterpret_cast<void*>(uintptr_t{256}), ~(size_t)0);
     if (rc != DFP4_OK) return rc;
     if (A.rows == 0 || W.rows == 0) return DFP4_OK;
     void* ws = nullptr;

@@ -141,6 +141,10 @@ def test_gemm_noalloc_argument_errors(lib):
     assert lib.dfp4_gemm_workspace_bytes(2048, 4096, 14336) > (64 << 20)
     assert lib.dfp4_gemm_noalloc(big_a, big_w, vp(16), 0, 4096, vp(0)) == -5
     assert b"workspace" in lib.dfp4_strerror(-5)
+    # more than the scratch array only as one of a batch: the single product needs none and is not refused for it (its null
+    # output is found next)
+    assert lib.dfp4_gemm_workspace_bytes(4141, 518, 12576) > (64 << 20) and lib.dfp4_gemm_path(4141, 518, 12576, 1, 0) > 0
+    assert lib.dfp4_gemm_noalloc(_t(16, 16, 16, 4141, 12576), _t(16, 16, 16, 518, 12576), vp(0), 0, 518, vp(0)) == -1
     # the other checks are those of dfp4_gemm
     assert lib.dfp4_gemm_noalloc(_t(16, 16, 16, 4, 64), _t(16, 16, 16, 4, 96), vp(16), 0, 4, vp(0)) == -2
     assert lib.dfp4_gemm_noalloc(_t(16, 16, 16, 4, 64), _t(16, 16, 16, 4, 64), vp(16), 9, 4, vp(0)) == -4
