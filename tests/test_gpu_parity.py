@@ -444,9 +444,8 @@ def test_gemm_few_rows_both_forms_of_the_tile(scale, K, exact):
         assert (err <= np.abs(ref) * 2.0 ** -24 + 1e-300).all(), "more than one rounding of the exact sum"
 
 
-def test_gemm_very_long_k_takes_block_flush_kernel():
-    # K beyond the single-accumulator kernel's range (more than 512 blocks): every tile is
-    # computed block by block with fp32 accumulation
+def test_gemm_very_long_k_is_summed_exactly():
+    # K beyond the large kernel's range (more than 512 blocks): gemm_direct_kernel, exact while the sum fits int32
     M, N, K = 70, 64, 32 * 520
     print(f"gemm parity: long K {M}x{N}x{K}", flush=True)
     a = synth.gaussian(M, K, 1.0, seed=71)
@@ -455,6 +454,7 @@ def test_gemm_very_long_k_takes_block_flush_kernel():
     torch.cuda.synchronize()
     ref, absdot = _gemm_ref(synth.to_f64(a), synth.to_f64(w))
     _assert_gemm_close(out, ref, absdot, "long K")
+    assert (np.abs(out.cpu().double().numpy() - ref) <= np.abs(ref) * 2.0 ** -24 + 1e-300).all()
 
 
 def test_gemm_batched_with_split_k():
@@ -1132,13 +1132,13 @@ def test_gemm_mixed_block_sizes(M, N, K, ba, bw):
 
 
 # --------------------------------------------------------------------------
-# GEMM that expands both operands inside the kernel: every tile shape the size rule selects, at sizes that
-# end inside a tile, inside a group of 4 blocks and inside a wave's share of K
+# GEMM that expands both operands inside the kernel, at sizes that end inside a tile, inside a group of 4 blocks and
+# inside a wave's share of K (every tile shape: test_gemm_direct_every_shape)
 # --------------------------------------------------------------------------
 @pytest.mark.parametrize("M,N,K,spread", [
     (1, 33, 32, 0), (33, 31, 96, 0), (31, 1000, 4128, 0), (64, 65, 16384, 0),      # 32 x 32
-    (65, 2100, 1056, 0), (190, 2000, 512, 0),                                      # 64 x 64
-    (513, 3001, 2080, 0), (300, 2049, 16416, 0),                                   # 128 x 128, K in one and in two shares
+    (65, 2100, 1056, 0), (190, 2000, 512, 0), (513, 3001, 2080, 0),                # 32 x 32 and 64 x 64
+    (300, 2049, 16416, 0),                                                         # 128 x 128, K in two shares
     (1500, 4000, 1120, 0),                                                         # 256 x 128
     (40, 70, 512, 7), (130, 900, 512, 7), (777, 1300, 1024, 5),                    # classes on both operands
     (40, 70, 1056, 30), (200, 1030, 544, 30), (513, 3001, 2080, 30)])              # tiles summed in fp32, block by block
@@ -1424,3 +1424,90 @@ def test_dequantize_small_tensors_take_waves():
     one, many = us(1, torch.float32), us(32, torch.float32)
     print(f"dequantize to fp32: 32 blocks {one:.2f} us, 1024 blocks {many:.2f} us", flush=True)
     assert many < 1.25 * one
+
+
+# --------------------------------------------------------------------------
+# Every kernel that the size rule selects, plain and prepared, exact and with declined tiles.  References: the dequantized
+# operands multiplied in float64 (the quantizers have tests of their own), which holds these sums exactly.
+# --------------------------------------------------------------------------
+def _path_operands(M, N, K, wide):
+    """Outlier channels on A, a few high blocks on both operands; `wide`: rows of A beyond what int32 sums can take."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    def operand(rows, std, high):
+        x = (torch.randn(rows, K // 32, 32, generator=g, device="cuda").clamp(-3.9, 3.9)) * std
+        x[:, :, 3] = 4.5 * std
+        x[:, :, 5] *= 0.1
+        if K >= 512:
+            x[:, high] *= 2.0 ** 5                                    # class 1
+        return x
+    a, w = operand(M, 1.0, 3), operand(N, 0.0625, 7)
+    if wide:
+        for r in (M // 3, M - 1):
+            a[r, -1] *= 2.0 ** 24 if K >= 64 else 1.0
+    qa, qw = (dfp4.quantize(x.view(x.shape[0], K).to(torch.bfloat16)) for x in (a, w))
+    da, dw = dfp4.dequantize(qa, torch.float32).double(), dfp4.dequantize(qw, torch.float32).double()
+    return qa, qw, da @ dw.T, da.abs() @ dw.abs().T
+
+
+def _check_outputs(out, ref, absdot, exact_rows, what):
+    torch.cuda.synchronize()
+    err = (out.double() - ref).abs()
+    if out.dtype == torch.bfloat16:
+        want = ref.to(torch.bfloat16).double()
+        ulp = torch.exp2(torch.floor(torch.log2(want.abs().clamp_min(1e-300))) - 7)
+        assert bool(((out.double() - want).abs() <= ulp + GEMM_RTOL * absdot).all()), what
+        return
+    assert bool((err <= GEMM_RTOL * absdot).all()), what
+    assert bool((err[exact_rows] <= ref[exact_rows].abs() * 2.0 ** -24).all()), what + ": not one rounding of the exact sum"
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("M,N,K,path", [
+    (31, 1000, 4128, 1), (36, 7898, 1344, 2), (190, 2000, 512, 3), (777, 3001, 2080, 4), (652, 3397, 544, 5),
+    (1500, 4000, 1120, 6), (1000, 2049, 96, 7), (300, 2049, 16416, 4)])
+def test_gemm_direct_every_shape(M, N, K, path, wide):
+    assert dfp4.gemm_path(M, N, K) == dfp4.gemm_path(M, N, K, prepared=True) == path
+    print(f"gemm_direct_kernel, path {path}: {M}x{N}x{K}, declined tiles {wide}", flush=True)
+    rows = [32, 64, 64, 128, 128, 256, 128][path - 1]
+    tile_rows = torch.arange(M, device="cuda") // rows
+    exact = (tile_rows != M // 3 // rows) & (tile_rows != (M - 1) // rows) if wide else torch.ones(M, dtype=torch.bool, device="cuda")
+    qa, qw, ref, absdot = _path_operands(M, N, K, wide)
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    # prepared operands of more than 256 rows are taken or declined by 512 x 128 outputs, as in gemm_fast_kernel
+    exact_p = exact if M <= 256 or K > 16384 or not wide else (torch.arange(M, device="cuda") // 512 != M // 3 // 512) & (torch.arange(M, device="cuda") // 512 != (M - 1) // 512)
+    for dtype in (torch.float32, torch.bfloat16):
+        _check_outputs(dfp4.gemm(qa, qw, dtype=dtype), ref, absdot, exact, f"plain {dtype}")
+        _check_outputs(dfp4.gemm_prepared(pa, pw, dtype=dtype), ref, absdot, exact_p, f"prepared {dtype}")
+    if pa.buf is not None:
+        assert (dfp4.gemm_declined_tiles(pa) > 0) == wide
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("M,N,K,prepared", [
+    (1552, 5664, 160, True), (518, 6686, 2848, True), (1188, 2211, 9472, True), (2338, 396, 16032, True),    # K whole, in 2, 4 and 8 shares
+    (2320, 5408, 448, False), (793, 4639, 4896, False), (845, 2333, 11104, False)])                          # K whole, in 2 and 4
+def test_gemm_fast_kernel_plain_outputs(M, N, K, prepared, wide):
+    # ragged results of the large kernel in both types, with classes on W and with declined tiles
+    assert dfp4.gemm_path(M, N, K, prepared=prepared) == 0
+    print(f"gemm_fast_kernel: {M}x{N}x{K}, prepared {prepared}, declined tiles {wide}", flush=True)
+    tile_rows = torch.arange(M, device="cuda") // 512
+    exact = (tile_rows != M // 3 // 512) & (tile_rows != (M - 1) // 512) if wide else torch.ones(M, dtype=torch.bool, device="cuda")
+    qa, qw, ref, absdot = _path_operands(M, N, K, wide)
+    if prepared:
+        pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    for dtype in (torch.float32, torch.bfloat16):
+        out = dfp4.gemm_prepared(pa, pw, dtype=dtype) if prepared else dfp4.gemm(qa, qw, dtype=dtype)
+        _check_outputs(out, ref, absdot, exact, f"{dtype}")
+    if prepared:
+        bad = len({M // 3 // 512, (M - 1) // 512}) * -(-N // 128)                  # tiles, counted by both products
+        assert dfp4.gemm_declined_tiles(pa) == (2 * bad if wide else 0)
+
+
+def test_gemm_prepared_and_plain_agree_across_kernels():
+    # equal sizes through different kernels: the same bits wherever both sum exactly
+    for M, N, K in ((1552, 5664, 160), (1188, 2211, 9472)):
+        assert dfp4.gemm_path(M, N, K) > 0 and dfp4.gemm_path(M, N, K, prepared=True) == 0
+        qa, qw, _, _ = _path_operands(M, N, K, False)
+        pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+        for dtype, bits in ((torch.float32, torch.int32), (torch.bfloat16, torch.int16)):
+            assert torch.equal(dfp4.gemm(qa, qw, dtype=dtype).view(bits), dfp4.gemm_prepared(pa, pw, dtype=dtype).view(bits)), (M, N, K)

@@ -45,6 +45,24 @@ def test_gemm_noalloc_matches_gemm_on_two_calls_in_a_row():
             first = False
 
 
+def test_gemm_noalloc_in_its_scratch_array():
+    # sizes of the kernel that expands its operands into the scratch array, the second within the first one's part of it
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    for (M, N, K, dtype) in [(3364, 2620, 1632, torch.float32), (2320, 5408, 448, torch.bfloat16)]:
+        assert dfp4.gemm_path(M, N, K) == 0 and (1 << 20) < dfp4.gemm_workspace_bytes(M, N, K) <= dfp4.NOALLOC_SCRATCH_BYTES
+        a, w = _case(M, N, K, 5 + M)
+        qa, qw = dfp4.quantize(a.to(dev)), dfp4.quantize(w.to(dev))
+        got = torch.full((M, N), float("nan"), dtype=dtype, device=dev)
+        dfp4.gemm_noalloc(qa, qw, got)
+        want = dfp4.gemm(qa, qw, dtype=dtype)
+        ref = (dfp4.dequantize(qa).double() @ dfp4.dequantize(qw).double().T).to(dtype)
+        torch.cuda.synchronize()
+        bits = torch.int32 if dtype == torch.float32 else torch.int16
+        assert torch.equal(got.view(bits), want.view(bits)) and torch.equal(got.view(bits), ref.view(bits)), (M, N, K)
+
+
 def test_gemm_noalloc_refuses_what_does_not_fit():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
