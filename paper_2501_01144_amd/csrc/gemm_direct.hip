@@ -204,9 +204,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
         cw_max = __builtin_amdgcn_readfirstlane(lds.spread[1]) >> 2;
         const bool can = max(ca_max, cw_max) <= kMaxClass && KB <= kIntBound;
         declined = !can || ca_max + cw_max > kMaxClass || (KB << (4 * (ca_max + cw_max))) > kIntBound;
-        // a row with a single block of its operand's largest class, the least that can be found
-        const bool rows_may = can && ca_max + cw_max <= kMaxClass && min((KB - 1 + (1 << (4 * ca_max))) << (4 * cw_max),
-                                                                         (KB - 1 + (1 << (4 * cw_max))) << (4 * ca_max)) <= kIntBound;
         // the classes of every row's own blocks against the largest class of the other operand
         auto weigh_rows = [&] {
             if (is_row) {
@@ -268,6 +265,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_direct_ker
         // blocks 9.9), the blocks that meet first otherwise (16 x 4096 x 4096: 13.7, after the rows 14.4).  One copy of
         // either, out of the way of the tiles that need neither.
         if (can && declined) {
+            // a row with a single block of its operand's largest class, the least that can be found
+            const bool rows_may = ca_max + cw_max <= kMaxClass && min((KB - 1 + (1 << (4 * ca_max))) << (4 * cw_max),
+                                                                      (KB - 1 + (1 << (4 * cw_max))) << (4 * ca_max)) <= kIntBound;
             const bool both = min(ca_max, cw_max) > 0, rows_first = !both || KB <= 64;
 #pragma unroll 1
             for (int pass = 0; pass < 2 && declined; ++pass) {
