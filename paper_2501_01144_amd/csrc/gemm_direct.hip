@@ -1,12 +1,13 @@
 // Block-scaled integer GEMM with nothing prepared: both operands are expanded from their 4-bit form inside
 // the kernel, all of K is summed exactly in int32 (scheme: gemm.hip).
 //
-// What bounds it.  Large products: the vector ALU (about 65 instructions per row and 32-element block
-// expanded), so the expansion is done once per workgroup and shared through LDS; the alternative is to
-// expand A in a pass of its own (gemm_prep_kernel) and multiply with gemm_fast_kernel, which pays where an
-// expanded byte is used by many column tiles and otherwise costs a round trip of 1 + 1 bytes per element
-// through memory.  Small products: latency, so the tile is cut down until the workgroups cover the chip
-// and the waves of a workgroup share K.
+// What bounds it.  Large products: the expansion (about 65 vector-ALU instructions per row and 32-element block)
+// and the waits between it and the multiply, so it is done once per workgroup and shared through LDS
+// (2048 x 4096 x 4096, two waves per SIMD: a wave has a vector-ALU instruction active 26 % of its cycles, waits 35 %, and
+// 28 % to issue; the matrix cores are busy 23 %).  The alternative is to expand A in a pass of its own
+// (gemm_prep_kernel) and multiply with gemm_fast_kernel, which pays where an expanded byte is used by many column
+// tiles and otherwise costs a round trip of 1 + 1 bytes per element through memory.  Small products: latency, so the
+// tile is cut down until the workgroups cover the chip and the waves of a workgroup share K.
 //
 // A workgroup has KG groups of WM x WN waves.  Every group computes the same tile of 32 TI WM x 32 TJ WN
 // outputs over its own contiguous range of K; the groups' exact partial sums are added through LDS.
@@ -36,7 +37,7 @@ namespace {
 // stores), so what counts is tiles in flight: one operand buffer instead of two, and one set of accumulators (class
 // sums from the highest down, shifted in between), so that three workgroups share a compute unit instead of two.
 // Q K^T to fp32 (microseconds; before: gemm_fast_kernel with its prepass / the 128 x 128 shape with two buffers):
-//   128 heads, 2048 x 2048 x 128    568 / 566 -> 502      the same with heads of 64    545 / 540 -> 371 (6.0 TB/s)
+//   128 heads, 2048 x 2048 x 128    568 / 566 -> 502      the same with heads of 64    545 / 540 -> 371 (5.9 TB/s)
 //    16 heads,  700 x 1312 x  64     45 /  28 ->  21       32 heads, 300 x 2048 x 128   54 /  32 ->  26
 // The write of the scores is 313 us of the first (a fill of the same size); classes on both operands, up to four
 // products per pair of blocks, are most of the rest.
