@@ -295,6 +295,7 @@ size_t dfp4_gemm_native_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * dfp4_gemm_native_splitk_bytes(M, N, K) bytes.
  */
 size_t dfp4_native_packed_bytes(int64_t rows, int64_t K);
+/* (Packed and prepared layouts are those of the library that wrote them: they are made again, not kept, across versions.) */
 /* Online DialectFP4 quantization (as dfp4_quantize) straight into the packed form: equal to
  * dfp4_quantize followed by dfp4_native_pack; the whole of the dfp4_native_packed_bytes(rows, K) is
  * written, the layout's padding as zeros.  x as for dfp4_quantize. */
