@@ -165,13 +165,13 @@ int dfp4_dequantize(dfp4_tensor in, void* y, int y_dtype, int64_t ld_elems, void
  * Block-scaled matrix multiply (Section 3.3): out = A * W^T,
  *   out[m, n] = sum over blocks kb of 2^(ea[m,kb] + ew[n,kb] - 2) *
  *               sum over k in kb of (+-ua[m,k]) * (+-uw[n,k])
- * with u the 4-bit unsigned integers (half-units) the codes index.  The inner
- * sums run on the int8 matrix cores with int32 accumulation and are exact.
- * Where the block exponents of a tile span at most 12 binades per row the
- * outer sum is exact as well (exponent offsets folded into the int8 operands,
- * one conversion to fp32 at the end); output tiles whose exponents spread further,
- * or whose exact sum could overflow int32, are accumulated in fp32, one addition
- * per block, by the workgroup that finds them.
+ * with u the 4-bit unsigned integers (half-units) the codes index.  The sum is exact,
+ * rounded once to the output type: large products run on the block-scaled matrix instruction
+ * where norms of the operands' rows show that no partial sum exceeds the 24 bits of fp32, all
+ * others on the int8 matrix cores with int32 accumulation (exponent offsets folded into the
+ * operands), where the block exponents of a tile span at most 12 binades per row.  Output
+ * tiles whose exponents spread further than either takes are accumulated in fp32, one
+ * addition per block, by the workgroup that finds them.
  *   A        quantized [M, K]; W quantized [N, K] (both blocked along K)
  *   out      device, [M, N] row-major, leading dimension ldc (elements, N <= ldc < 2^27);
  *            out_dtype DFP4_F32 or DFP4_BF16 (round to nearest even)
@@ -201,18 +201,17 @@ size_t dfp4_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * The same product with the per-operand work of dfp4_gemm done ahead (Section 3.3: the cost
  * of preparing a quantized activation block is amortized over the many weight blocks it is
  * multiplied with; weights are known in advance).  dfp4_gemm spends part of every call on
- * each operand alone: per-row reference exponents, per-block tables, and for A the 4-bit
- * codes expanded through the dialect tables to the int8 operands of the matrix cores.
+ * each operand alone: the codes rewritten as operands of the matrix instruction, and norms of
+ * the rows in units of their smallest block exponent.
  * dfp4_gemm_prepare does that once per tensor:
  *   is_weight != 0   T is a W operand [N, K] (offline, once per weight matrix)
  *   is_weight == 0   T is an A operand [M, K] (online, once per activation tensor, however
  *                    many products consume it: gate and up projections share one)
  *   prepared         device, 256-byte aligned, at least dfp4_gemm_prepared_bytes(rows, K,
- *                    is_weight) bytes; the layout is private to the library (for a weight:
- *                    a copy of the codes and three table words per block, both in the order
- *                    the kernels read them, about 0.9 bytes per element).  A size of 0
+ *                    is_weight) bytes; the layout is private to the library (about
+ *                    0.8 bytes per element).  A size of 0
  *                    means nothing is prepared for this operand (K > 16384): NULL may be
- *                    passed then.  An activation of at most 256 rows is not expanded ahead
+ *                    passed then.  An activation of at most 256 rows is not packed ahead
  *                    (its products read it as it is); its buffer holds a counter only.
  * dfp4_gemm_prepared multiplies.  The quantized tensors are still passed: paths that do not
  * use the prepared form read them.  a_prepared is written to (arrival counters of tiles
@@ -220,8 +219,8 @@ size_t dfp4_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * products on one stream are ordered by the stream, products that may overlap in time need
  * their own prepared copy.  Results are bit-identical to dfp4_gemm wherever both sum
  * exactly (one rounding of the exact sum); which tiles' exponents spread too far for that is
- * decided per 512 x 128 outputs here, and for at most 256 rows of A, as in dfp4_gemm, per
- * tile of the kernel the product's size selects.
+ * decided per tile of the kernel the product's size selects (dfp4_gemm_path), in gemm_direct_kernel
+ * on more than 256 rows of A per 512 x 128 outputs.
  *   workspace   at least dfp4_gemm_prepared_workspace_bytes(M, N, K) bytes (partial tiles
  *               where K is split; 0 for products with many output tiles), 256-byte aligned
  * Limits: ceil(rows / 512) * (K/32 + 1) * 49152 < 2^31 for A, rows * K / 2 < 2^31 for W
@@ -236,14 +235,14 @@ int dfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const voi
 int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const void* w_prepared, void* out,
                         int out_dtype, int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
 /*
- * Diagnostic: number of output tiles (512 x 128; smaller ones for at most 256 rows of A) that
- * products on this prepared A ([M, K]) have computed on the per-block fp32 path since it was prepared (exponent spread beyond what the
- * exact path folds into its operands).  `count` is a HOST pointer.  Synchronizes with the device.
+ * Diagnostic: number of output tiles (128 x 128 in the large kernel, 512 x 128 in gemm_direct_kernel, smaller ones
+ * for at most 256 rows of A) that products on this prepared A ([M, K]) have computed on the per-block fp32 path since it was
+ * prepared (exponent spread beyond what the exact paths take).  `count` is a HOST pointer.  Synchronizes with the device.
  */
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);
 /*
  * Diagnostic: the kernel that a product of these sizes takes (batch 1 unless dfp4_gemm_batched; prepared: with
- * dfp4_gemm_prepared).  0: gemm_fast_kernel (512 x 128 output tiles, expanded operands).  1 to 7: gemm_direct_kernel
+ * dfp4_gemm_prepared).  0: the large kernel (tiles of 256 or 128 x 256 on packed operands).  1 to 7: gemm_direct_kernel
  * (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
  * two, 128 x 128, 256 x 128, and 128 x 128 for K of at most 128.  DFP4_ERR_SHAPE for sizes that are no product.
  */

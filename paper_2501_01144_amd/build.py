@@ -29,48 +29,56 @@ _AGPR = re.compile(r"\ba(\d+|\[\d+:\d+\])(?![\w.])")
 
 
 def check_accumulators_untouched(asm_text):
-    """Guard for gemm_fast_kernel.  Its main loop is one inline-assembly statement that leaves
-    the 256 int32 accumulators in a0..a255; the epilogue reads them back with further
+    """Guard for gemm_native_kernel.  Its main loop is one inline-assembly statement that leaves
+    the 256 fp32 accumulators in a0..a255; the epilogue reads them back with further
     inline-assembly statements.  The compiler is told the loop clobbers those registers, so
     nothing in the language stops it from using an accumulation register for its own purposes
     (a spill, a copy) between the two.  This check makes that a build error instead of a silent
-    wrong result: in every gemm_fast_kernel, no compiler-generated instruction that can execute
-    after the main loop (followed through the kernel's branches) may name an accumulation
-    register, and the kernel must not use scratch memory."""
-    problems = []
+    wrong result: in every gemm_native_kernel, no compiler-generated instruction that can execute
+    after the main loop (followed through the kernel's branches, up to the statement that marks the
+    accumulators dead: a tile computed again) may name an accumulation register, and the
+    kernel must not use scratch memory."""
+    problems, kernels = [], 0
     lines = asm_text.splitlines()
     i, n = 0, len(lines)
     while i < n:
-        m = re.match(r"^(_ZN\S*gemm_fast_kernel\S*):", lines[i])
+        m = re.match(r"^(_ZN\S*gemm_native_kernel\S*):", lines[i])
         if not m:
             i += 1
             continue
         name = m.group(1)
+        kernels += 1
         j = i + 1
         while j < n and ".end_amdhsa_kernel" not in lines[j]:
             j += 1
         body = lines[i + 1:j]
         labels = {}
-        in_asm, asm_region, first_end = False, [], None
+        in_asm, is_loop, asm_region, loop_end, dead = False, False, [], None, set()
         for k, ln in enumerate(body):
             if ";;#ASMSTART" in ln:
-                in_asm = True
+                in_asm, is_loop = True, False
             elif ";;#ASMEND" in ln:
                 in_asm = False
-                if first_end is None:
-                    first_end = k
+                if is_loop:
+                    loop_end = k
+            elif in_asm and "v_mfma_scale" in ln:
+                is_loop = True
+            elif in_asm and "accumulators are dead" in ln:
+                dead.add(k)
             asm_region.append(in_asm)
             lm = re.match(r"^(\.LBB\w+):", ln)
             if lm and not in_asm:
                 labels[lm.group(1)] = k
-        if first_end is None:
+        if loop_end is None:
             problems.append(f"{name}: main loop not found")
         else:
-            seen, work = set(), [first_end + 1]
+            seen, work = set(), [loop_end + 1]
             while work:
                 k = work.pop()
                 while k < len(body) and k not in seen:
                     seen.add(k)
+                    if k in dead:
+                        break
                     code = body[k].split(";")[0].strip()
                     if not asm_region[k] and code and not code.startswith("."):
                         if _AGPR.search(code):
@@ -95,13 +103,13 @@ def check_accumulators_untouched(asm_text):
                 break
             k += 1
         i = j
+    if kernels == 0:
+        problems.append("gemm_native_kernel not found")
     return problems
 
 
 def build_library(verbose=True):
-    # the hand-scheduled GEMM loops are generated text (see csrc/gen_gemm_step.py, csrc/gen_native_loop.py)
-    subprocess.run([sys.executable, os.path.join(CSRC, "gen_gemm_step.py")], check=True,
-                   stdout=subprocess.DEVNULL)
+    # the hand-scheduled GEMM loops are generated text (see csrc/gen_native_loop.py)
     subprocess.run([sys.executable, os.path.join(CSRC, "gen_native_loop.py")], check=True,
                    stdout=subprocess.DEVNULL)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -117,9 +125,9 @@ def build_library(verbose=True):
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     # device assembly of the GEMM, for the accumulator guard
-    gemm_s = os.path.join(objdir, "gemm.s")
-    cmd = [hipcc, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "gemm.hip"), "-o", gemm_s]
-    procs.append(("gemm.hip (assembly)", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    gemm_s = os.path.join(objdir, "gemm_native.s")
+    cmd = [hipcc, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "gemm_native.hip"), "-o", gemm_s]
+    procs.append(("gemm_native.hip (assembly)", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     # measurement helpers used by bench.py: register-only int8 MFMA loops, plain streaming kernels
     for name in ("mfma_peak", "stream_peak", "mfma_shadow"):
         cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Wno-inline-asm", os.path.join(HELPERS, name + ".hip"),
@@ -140,7 +148,7 @@ def build_library(verbose=True):
         raise RuntimeError("libdfp4 build failed")
     problems = check_accumulators_untouched(open(gemm_s).read())
     if problems:
-        raise RuntimeError("gemm_fast_kernel accumulator guard:\n" + "\n".join(problems))
+        raise RuntimeError("gemm_native_kernel accumulator guard:\n" + "\n".join(problems))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -446,7 +446,7 @@ static int gemm_requant_common(bool mx, dfp4_tensor A, dfp4_tensor W, dfp4_tenso
     if (!out.codes || !out.exponent || (!mx && !out.dialect)) return DFP4_ERR_NULL;
     if (!aligned(out.codes, 4)) return DFP4_ERR_ALIGN;
     // per problem: the plain GEMM's workspace, then the bf16 [M, N] temporaries of all problems
-    const size_t gemm_ws = (size_t)((gemm_fast_workspace_bytes(A.rows, W.rows, A.K) + 255) & ~(size_t)255) * (size_t)batch;
+    const size_t gemm_ws = (size_t)((gemm_large_workspace_bytes(A.rows, W.rows, A.K) + 255) & ~(size_t)255) * (size_t)batch;
     const size_t temp_bytes = (size_t)(((A.rows * W.rows * 2) + 255) & ~(int64_t)255) * (size_t)batch;
     if (!workspace || workspace_bytes < gemm_ws + temp_bytes) return DFP4_ERR_WORKSPACE;
     void* temp = static_cast<uint8_t*>(workspace) + gemm_ws;

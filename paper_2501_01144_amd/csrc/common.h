@@ -37,7 +37,7 @@ int launch_gemm(bool mx, dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype,
                 void* workspace, size_t workspace_bytes, hipStream_t stream, const dfp4_tensor* rq = nullptr);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int gemm_path(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared);
-size_t gemm_fast_workspace_bytes(int64_t M, int64_t N, int64_t K);
+size_t gemm_large_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int gemm_shape_check(dfp4_tensor A, dfp4_tensor W, int64_t ldc, int64_t batch, bool rq);
 size_t gemm_prepared_bytes(int64_t rows, int64_t K, bool weight);
 size_t gemm_prepared_workspace_bytes(int64_t M, int64_t N, int64_t K);

@@ -22,14 +22,25 @@ constexpr Fp6Book make_fp6_book() {
 }
 static __device__ const Fp6Book g_fp6_book = make_fp6_book();
 
-// 8 codes (one dword) -> 48 bits: 8 six-bit values, element j in bits [6 j, 6 j + 6)
-__device__ __forceinline__ uint64_t pack6(uint32_t c, uint32_t tlo, uint32_t thi) {
-    const uint32_t ie = c & 0x07070707u, io = (c >> 4) & 0x07070707u;
-    const uint32_t e = __builtin_amdgcn_perm(thi, tlo, ie) | ((c << 2) & 0x20202020u);   // elements 0, 2, 4, 6
-    const uint32_t o = __builtin_amdgcn_perm(thi, tlo, io) | ((c >> 2) & 0x20202020u);   // elements 1, 3, 5, 7
-    const uint32_t lo24 = (e & 0x3fu) | ((o & 0x3fu) << 6) | (((e >> 8) & 0x3fu) << 12) | (((o >> 8) & 0x3fu) << 18);
-    const uint32_t hi24 = ((e >> 16) & 0x3fu) | (((o >> 16) & 0x3fu) << 6) | ((e >> 24) << 12) | ((o >> 24) << 18);
-    return (uint64_t)lo24 | ((uint64_t)hi24 << 24);
+// 32 codes -> the 192 bits of a lane's registers: 32 six-bit values, element j in bits [6 j, 6 j + 6).  Twelve-bit pairs in the
+// 16-bit halves of a dword first, 24 bits of four elements from those, no 64-bit shifts.
+struct Fp6Lane { uint32_t w[6]; };
+__device__ __forceinline__ void pack6_quarter(uint32_t c, uint32_t tlo, uint32_t thi, uint32_t& lo24, uint32_t& hi24) {
+    const uint32_t e = __builtin_amdgcn_perm(thi, tlo, c & 0x07070707u) | ((c << 2) & 0x20202020u);           // elements 0, 2, 4, 6
+    const uint32_t o = __builtin_amdgcn_perm(thi, tlo, (c >> 4) & 0x07070707u) | ((c >> 2) & 0x20202020u);    // elements 1, 3, 5, 7
+    const uint32_t p = (e & 0x003f003fu) | ((o & 0x003f003fu) << 6);                                         // 0 1 | 4 5
+    const uint32_t q = ((e >> 8) & 0x003f003fu) | (((o >> 8) & 0x003f003fu) << 6);                           // 2 3 | 6 7
+    lo24 = (p & 0xffffu) | ((q & 0xffffu) << 12);
+    hi24 = (p >> 16) | ((q >> 16) << 12);
+}
+__device__ __forceinline__ Fp6Lane pack6_lane(uint4 c, uint32_t tlo, uint32_t thi) {
+    uint32_t l0, h0, l1, h1, l2, h2, l3, h3;
+    pack6_quarter(c.x, tlo, thi, l0, h0);
+    pack6_quarter(c.y, tlo, thi, l1, h1);
+    pack6_quarter(c.z, tlo, thi, l2, h2);
+    pack6_quarter(c.w, tlo, thi, l3, h3);
+    return Fp6Lane{{l0 | (h0 << 24), (h0 >> 8) | (l1 << 16), (l1 >> 16) | (h1 << 8),
+                    l2 | (h2 << 24), (h2 >> 8) | (l3 << 16), (l3 >> 16) | (h3 << 8)}};
 }
 
 // Packed FP6 operand: per (pair of 32-row tiles, step) 3072 bytes = 64 lanes x 16 bytes (registers 0..3) of the even

@@ -27,19 +27,14 @@ struct GemmParams {
     void* out;
     int M, N, KB;
     int64_t ldc, strideA_rows, strideW_rows, strideC;
-    // prepared operands (per batch entry: base + batch * stride) and their regions
+    // prepared operands (per problem of a batch: base + problem * stride; gemm_native.hip)
     uint8_t* a_prep;
     uint8_t* w_prep;
     int64_t a_prep_stride, w_prep_stride;
-    int64_t off_refa, off_mask, off_cnt, off_a8;      // inside a prepared A
-    int64_t off_refw, off_wmask, off_wmeta, off_wcodes;   // inside a prepared W
-    uint32_t wmeta_cls_stride;                        // bytes between the table dwords of two classes
-    // exact int32 partial tiles of workgroups that share an output tile (split K)
-    int* part;
-    int64_t part_stride;              // ints per batch entry
-    int tiles_m, tiles_n;             // 512 x 128 output tiles
-    int ksplit;                       // workgroups sharing one output tile (each takes a range of K)
-    uint32_t* declined;               // counts tiles gemm_direct_kernel declines (may be null)
+    // prepared operands in gemm_direct_kernel (batch 1; otherwise null): smallest exponent of every row, and per (128 rows,
+    // block) the classes present
+    const uint8_t *ref_a, *mask_a, *ref_w, *mask_w;
+    uint32_t* declined;               // counts tiles computed with one fp32 scale-and-add per block (may be null)
     // requantizing epilogue: the quantized [M, N] output (blocks of 32 along N)
     uint32_t* q_codes;
     uint8_t *q_dial, *q_exp;
@@ -318,9 +313,17 @@ void dispatch_mx_bf16(bool mx, bool bf16, F&& f) {
 
 }  // namespace
 
-// gemm_direct.hip: any product of at most gemm_direct_max_rows(KB, false) rows of A and (KB, true) of W, with the operands as they
-// are or (p.a_prep, p.w_prep) with the references and class masks of prepared ones; a shape and the microseconds it is
-// estimated to take on `cu` compute units
+// gemm_native.hip: products whose operands are packed beforehand (exact_operand_bytes each; A with the counters)
+constexpr int kExactSplitTiles = 2048;        // K is split only below this many tiles
+constexpr int kExactCounters = kExactSplitTiles + 1;      // arrivals at every such tile, and the count of declined tiles
+int64_t exact_operand_bytes(int64_t rows, int64_t KB, bool fp6, bool counters);
+int64_t exact_split_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch);
+int launch_exact_prep(bool mx, const GemmParams& p, int64_t batch, bool classes, hipStream_t stream);
+void set_prepared_classes(bool mx, GemmParams& p, const uint8_t* a_prep, const uint8_t* w_prep);
+int launch_exact(bool mx, bool bf16, const GemmParams& g, int64_t batch, float* part, size_t part_bytes, bool rq, hipStream_t stream);
+
+// gemm_direct.hip: any product of at most gemm_direct_max_rows(KB, false) rows of A and (KB, true) of W, with the operands as
+// they are; a shape and the microseconds it is estimated to take on `cu` compute units
 struct DirectChoice { int shape; float us; };
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
 constexpr int kDirectOnceBlocks = 4;         // K, in blocks, that it takes in one iteration

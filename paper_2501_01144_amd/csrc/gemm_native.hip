@@ -29,10 +29,24 @@
 // or seven steps ahead, LDS -> registers one step ahead, one barrier per step; the
 // main loop is generated assembly (gen_native_loop.py).  With very few tiles K is split
 // between workgroups and native_reduce_kernel adds their fp32 partial tiles in a fixed order.
+//
+// Exact products (dfp4_gemm and its prepared, batched and requantizing forms; gemm.hip).  Their sums are defined as
+// exact, rounded once, and the same kernel gives that where it can be shown that no partial sum rounds.  A row's unit is
+// 2^(smallest exponent of its nonzero blocks - 1): every element is a whole number of units, every product a whole
+// number of (unit of A's row x unit of W's row), and as long as the absolute products of an output add up to no more
+// than 2^24 of these every partial sum, in any order, is a whole number that fp32 holds.  The matrix instruction adds
+// such terms exactly (3.2 million outputs of single instructions with sums of absolute terms below 2^24 units, block
+// offsets up to 16 binades and addends up to 2^23.9 checked: none off; its alignment keeps 24 bits).
+// exact_prep_kernel therefore computes, beside the packed form, norms of the rows in units (ExactStat), and a workgroup
+// compares three bounds of sum |a||w| with 2^24 after its main loop.  A tile that passes none is computed again in
+// int32 from the 4-bit operands by the same workgroup (gemm_int8_tile.h).  On activations with 0.5 % outlier channels
+// x 50 and Gaussian weights the bound is 2^20.3 at K = 4096 and 2^22.1 at K = 14336.
 #include <type_traits>
 #include "common.h"
 #include "formatbook.h"
 #include "fp6_pack.h"
+#include "quant_pass.h"
+#include "gemm_int8_tile.h"
 #include "gemm_native_asm.inc"
 
 namespace dfp4 {
@@ -42,12 +56,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kFmtFp6 = 2, kFmtFp4 = 4;      // format codes of the instruction (E2M3, E2M1)
-
-__device__ __forceinline__ uint16_t f32_to_bf16_rne_n(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
 
 // Packed operands (written by native_pack_kernel): rows padded to a multiple of 256,
 // S = ceil(KB / 2) steps, a missing second block is all zeros.
@@ -96,32 +104,393 @@ __global__ __launch_bounds__(256) void native_pack_kernel(PackParams p) {
         reinterpret_cast<uint4*>(p.dst.bits)[((int64_t)tile * p.S + s) * 64 + lane] = codes;     // the MXFP4 code is the E2M1 bit pattern
     } else {
         const uint32_t tlo = g_fp6_book.w[dl][0], thi = g_fp6_book.w[dl][1];
-        const uint64_t p0 = pack6(codes.x, tlo, thi), p1 = pack6(codes.y, tlo, thi);
-        const uint64_t p2 = pack6(codes.z, tlo, thi), p3 = pack6(codes.w, tlo, thi);
-        *reinterpret_cast<uint4*>(p.dst.bits + fp6_lo(tile, s, p.S) + lane * 16) =
-            make_uint4((uint32_t)p0, (uint32_t)(p0 >> 32) | ((uint32_t)p1 << 16), (uint32_t)(p1 >> 16), (uint32_t)p2);
-        *reinterpret_cast<uint2*>(p.dst.bits + fp6_hi(tile, s, p.S) + lane * 8) =
-            make_uint2((uint32_t)(p2 >> 32) | ((uint32_t)p3 << 16), (uint32_t)(p3 >> 16));
+        const Fp6Lane v = pack6_lane(codes, tlo, thi);
+        *reinterpret_cast<uint4*>(p.dst.bits + fp6_lo(tile, s, p.S) + lane * 16) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+        *reinterpret_cast<uint2*>(p.dst.bits + fp6_hi(tile, s, p.S) + lane * 8) = make_uint2(v.w[4], v.w[5]);
     }
     reinterpret_cast<uint8_t*>(p.dst.sc)[(((int64_t)(tile >> 2) * p.S + s) * 64 + lane) * 4 + (tile & 3)] = (uint8_t)eb;
 }
 
+// ---- exact products: the norms of packed rows
+// Of the rows of a 32-row tile over a chunk of K, in units of the row (its reference: the smallest exponent of its
+// nonzero blocks); every entry the largest over the rows, so that sums over chunks and maxima over tiles bound every row.
+struct alignas(16) ExactStat {
+    float sq;          // sum of squares
+    float sq_low;      // sum of squares over blocks less than 4 binades above the reference
+    float sum_high;    // sum of magnitudes over the other blocks
+    float top;         // largest magnitude, at most
+};
+constexpr int kStatChunks = 32;                       // chunks of a row, at most: [row tile][32]
+constexpr int kMaxChunkBlocks = 64;
+constexpr float kExactUnits = 16777216.0f * 0.9998f;  // the bounds' own rounding stays below 1e-4
+// Rows whose reference lies outside these exponent bytes take the int32 path: a product of two units is then at least 2^-126
+// (no partial sum is subnormal) and a sum of 2^24 of them below 2^127.
+constexpr int kMinRef = 66, kMaxRef = 178;
+
+struct ExactOperand {
+    const uint8_t *codes, *dial, *expo;
+    int64_t src_rows;                 // rows between two problems of a batch
+    uint8_t* dst;                     // packed operand, then scales, then norms (ExactLayout)
+    int64_t off_sc, off_stat, stride; // bytes
+    uint8_t *ref, *mask;              // of gemm_direct_kernel on prepared operands (may be null): [row] and [128 rows][block]
+    int rows, groups;                 // groups of 128 rows, an even number
+};
+
+struct ExactPrepParams {
+    ExactOperand a, w;
+    uint32_t* count;                  // cleared: arrival counters of tiles whose K is split, and the count of declined tiles
+    int64_t count_stride;             // dwords between two problems; 0 dwords: none
+    int counters;
+    int KB, S, chunks, chunk_blocks, wgs_a;
+};
+
+__device__ __forceinline__ float quad_pair_sum(float v) {     // over 8 neighbouring lanes, in all of them
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true));
+    return v;
+}
+
+// Tables of a dialect: magnitudes u of its 8 indices, and their E2M3 bit patterns
+struct ExactBook { uint32_t w[kDialects][4]; };
+constexpr ExactBook make_exact_book() {
+    ExactBook b{};
+    for (int d = 0; d < kDialects; ++d)
+        for (int j = 0; j < 8; ++j) {
+            b.w[d][j / 4] |= (uint32_t)kBook[d][j] << (8 * (j % 4));
+            b.w[d][2 + j / 4] |= (uint32_t)e2m3_of_half_units(kBook[d][j]) << (8 * (j % 4));
+        }
+    return b;
+}
+__device__ const ExactBook g_exact_book = make_exact_book();
+
+// Packs operands and computes the norms of their rows.  A workgroup = 128 rows x `chunk_blocks` (8 or 16) blocks of K; wave
+// (q, tile) takes rows 8 q .. of row tile `tile` of the four, a lane one block at a time.  Bound by latency: exponents of
+// the whole rows (which every chunk reads again, 1/16 of the codes' bytes each time), then codes, tables, stores; so there are 16
+// waves to a workgroup, 8 threads look through a row's exponents, and the codes are on their way meanwhile (with 4 waves of 4
+// blocks per lane: 2048 x 4096 10.0 us, 2048 x 14336 21.7; so 8.3 and 15.5).  8 lanes read the 128 bytes of 8 blocks of a
+// row, so that loads are whole lines, and the 8 rows of a wave are 128 contiguous bytes of a step's 16-byte parts.
+template <int FMT>
+__global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_book[kDialects][4];
+    __shared__ uint8_t s_ref[128], s_low[128];                         // smallest exponent of the nonzero blocks; of all blocks
+    __shared__ uint32_t s_mask[kMaxChunkBlocks];
+    __shared__ __attribute__((aligned(4))) uint8_t s_sc[8][32][4];     // scale bytes: [block][row][tile of the group]
+    __shared__ ExactStat s_stat[4][4];
+    // packed lanes, [tile of the group][block][row]; a block's rows are followed by a gap, so that the 8 blocks of a row that
+    // neighbouring lanes write fall on different banks
+    constexpr int kLoPitch = 32 * 16 + 16, kHiPitch = 32 * 8 + 8;
+    __shared__ __attribute__((aligned(16))) uint8_t s_lo[32 * kLoPitch], s_hi[FMT == kFmtFp6 ? 32 * kHiPitch : 16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool is_w = (int)blockIdx.x >= p.wgs_a;
+    const ExactOperand o = is_w ? p.w : p.a;
+    const int wg = (int)blockIdx.x - (is_w ? p.wgs_a : 0), group = wg / p.chunks, chunk = wg % p.chunks;
+    const int64_t bz = blockIdx.z;
+    const int KB = p.KB;
+    const int64_t src0 = bz * o.src_rows;
+    uint8_t* dst = o.dst + bz * o.stride;
+    const int k8 = lane & 7, t4 = wave & 3, r = (wave >> 2) * 8 + (lane >> 3);
+    const int tile = group * 4 + t4, row = tile * 32 + r;
+    // (no branch around a load: a block outside the operand reads the last and is cleared where it is used)
+    struct Block { uint4 c; uint32_t e, d; };
+    const uint32_t blk_row = (uint32_t)min(row, o.rows - 1) * (uint32_t)KB;
+    const uint8_t *codes = o.codes + src0 * KB * 16, *expo = o.expo + src0 * KB, *dial = FMT == kFmtFp6 ? o.dial + src0 * KB : nullptr;
+    auto load = [&](int sub) {
+        Block b;
+        const uint32_t blk = blk_row + (uint32_t)min(chunk * p.chunk_blocks + sub + k8, KB - 1);
+        b.c = *reinterpret_cast<const uint4*>(codes + (uint64_t)blk * 16);
+        b.e = expo[blk];
+        b.d = FMT == kFmtFp6 ? dial[blk] : 7;
+        return b;
+    };
+    Block cur = load(0);
+    if (tid < kDialects * 4) (&s_book[0][0])[tid] = (&g_exact_book.w[0][0])[tid];
+    if (tid < kMaxChunkBlocks) s_mask[tid] = 0;
+    if (blockIdx.x == 0)
+        for (int i = tid; i < p.counters; i += 1024) p.count[bz * p.count_stride + i] = 0;
+    {
+        // references: 8 threads per row
+        const int srow = group * 128 + (tid >> 3), part = tid & 7;
+        // pairs of bytes minus 1 as 16-bit numbers: a zero byte (an all-zero block) becomes 0xffff and is passed over
+        typedef uint16_t v2u __attribute__((ext_vector_type(2)));
+        v2u mn2 = {0xffff, 0xffff}, any2 = {0, 0};
+        auto scan = [&](uint32_t w) {
+            const v2u one = {1, 1}, lo = __builtin_bit_cast(v2u, w & 0x00ff00ffu) - one, hi = __builtin_bit_cast(v2u, (w >> 8) & 0x00ff00ffu) - one;
+            mn2 = __builtin_elementwise_min(mn2, __builtin_elementwise_min(lo, hi));
+            any2 |= lo | hi;
+        };
+        if (srow < o.rows) {
+            const uint8_t* e = o.expo + (src0 + srow) * KB;
+            const int n16 = KB >> 4;
+            for (int i0 = part; i0 < n16; i0 += 32) {
+                uint4 v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], e + 16 * min(i0 + 8 * q, n16 - 1), 16);   // no alignment assumed
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { scan(v[q].x); scan(v[q].y); scan(v[q].z); scan(v[q].w); }
+            }
+            for (int i = n16 * 16 + part; i < KB; i += 8) scan(e[i] * 0x01010101u);
+        }
+        int mn = min((int)mn2.x, (int)mn2.y);
+        mn = mn == 0xffff ? 255 : mn;
+        int all = ((uint32_t)(any2.x | any2.y) & 0x8000u) ? 0 : mn + 1;
+#pragma unroll
+        for (int x = 1; x < 8; x <<= 1) {
+            mn = min(mn, __shfl_xor(mn, x));
+            all = min(all, __shfl_xor(all, x));
+        }
+        all = min(all, 255);
+        if (part == 0) {
+            s_ref[tid >> 3] = (uint8_t)(mn + 1);                       // 0: no nonzero block
+            s_low[tid >> 3] = (uint8_t)all;
+            if (o.ref && chunk == 0 && srow < o.rows) o.ref[srow] = (uint8_t)all;
+        }
+    }
+    __syncthreads();
+    const int ref = s_ref[t4 * 32 + r], lowest = s_low[t4 * 32 + r];
+    ExactStat m{0, 0, 0, 0};                          // of this lane's blocks
+    for (int sub = 0; sub < p.chunk_blocks; sub += 8) {
+        const bool on = row < o.rows && chunk * p.chunk_blocks + sub + k8 < KB;
+        const uint4 c = on ? cur.c : make_uint4(0, 0, 0, 0);
+        const uint32_t e = on ? cur.e : 0;
+        const uint4 tab = *reinterpret_cast<const uint4*>(&s_book[cur.d & 15u][0]);
+        if (sub + 8 < p.chunk_blocks) cur = load(sub + 8);
+        const uint32_t c4[4] = {c.x, c.y, c.z, c.w};
+        uint32_t s1 = 0, s2 = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t ue = __builtin_amdgcn_perm(tab.y, tab.x, c4[k] & 0x07070707u);
+            const uint32_t uo = __builtin_amdgcn_perm(tab.y, tab.x, (c4[k] >> 4) & 0x07070707u);
+            s2 = __builtin_amdgcn_udot4(ue, ue, __builtin_amdgcn_udot4(uo, uo, s2, false), false);
+            s1 = __builtin_amdgcn_udot4(ue, 0x01010101u, __builtin_amdgcn_udot4(uo, 0x01010101u, s1, false), false);
+        }
+        const int delta = (int)e - ref;
+        // not for the fp32 path: a reference out of range, a nonzero block with byte 0 (passed over above), byte 255 (no scale)
+        const bool off = e == 255 || (s1 != 0 && (e == 0 || ref < kMinRef || ref > kMaxRef));
+        if (s1 != 0 || off) {
+            const float inf = __builtin_inff(), v2 = off ? inf : ldexpf((float)s2, 2 * delta);
+            m.sq += v2;
+            if (off || delta < 4) m.sq_low += v2;
+            if (off || delta >= 4) m.sum_high += off ? inf : ldexpf((float)s1, delta);
+            m.top = off ? inf : fmaxf(m.top, ldexpf((float)(tab.y >> 24), delta));
+        }
+        s_sc[k8][r][t4] = (uint8_t)e;
+        if constexpr (FMT == kFmtFp4) {
+            *reinterpret_cast<uint4*>(s_lo + (t4 * 8 + k8) * kLoPitch + r * 16) = c;
+        } else {
+            const Fp6Lane v = pack6_lane(c, tab.z, tab.w);
+            *reinterpret_cast<uint4*>(s_lo + (t4 * 8 + k8) * kLoPitch + r * 16) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+            *reinterpret_cast<uint2*>(s_hi + (t4 * 8 + k8) * kHiPitch + r * 8) = make_uint2(v.w[4], v.w[5]);
+        }
+        if (o.mask) {
+            uint32_t cls = on ? 1u << min(((int)e - lowest) >> 2, kMaxClass + 1) : 0u;
+#pragma unroll
+            for (int x = 8; x < 64; x <<= 1) cls |= (uint32_t)__shfl_xor((int)cls, x);
+            if (lane < 8) atomicOr(&s_mask[sub + k8], cls);
+        }
+        __syncthreads();
+        {
+            // wave (q, tile) writes step q of the tile: whole lines
+            const int q = wave >> 2, half = t4 * 8 + 2 * q + (lane >> 5), st = (chunk * p.chunk_blocks + sub) / 2 + q;
+            if (st < p.S) {
+                const uint4 lo = *reinterpret_cast<const uint4*>(s_lo + half * kLoPitch + (lane & 31) * 16);
+                if constexpr (FMT == kFmtFp4) {
+                    reinterpret_cast<uint4*>(dst)[((int64_t)tile * p.S + st) * 64 + lane] = lo;
+                } else {
+                    *reinterpret_cast<uint4*>(dst + fp6_lo(tile, st, p.S) + lane * 16) = lo;
+                    *reinterpret_cast<uint2*>(dst + fp6_hi(tile, st, p.S) + lane * 8) =
+                        *reinterpret_cast<const uint2*>(s_hi + half * kHiPitch + (lane & 31) * 8);
+                }
+            }
+        }
+        if (tid < 256) {
+            // scale dwords of the group's four tiles: 8 blocks x 32 rows
+            const int blk = tid >> 5, sr = tid & 31, kbs = chunk * p.chunk_blocks + sub + blk;
+            if ((kbs >> 1) < p.S)
+                reinterpret_cast<uint32_t*>(dst + o.off_sc)[((int64_t)group * p.S + (kbs >> 1)) * 64 + 32 * (kbs & 1) + sr] =
+                    *reinterpret_cast<const uint32_t*>(&s_sc[blk][sr][0]);
+        }
+        if (sub + 8 < p.chunk_blocks) __syncthreads();
+    }
+    if (o.mask && tid < p.chunk_blocks && chunk * p.chunk_blocks + tid < KB)
+        o.mask[(int64_t)group * KB + chunk * p.chunk_blocks + tid] = (uint8_t)s_mask[tid];
+    // over the 8 lanes of a row, then the largest of the wave's 8 rows, of the tile's 32
+    m.sq = quad_pair_sum(m.sq);
+    m.sq_low = quad_pair_sum(m.sq_low);
+    m.sum_high = quad_pair_sum(m.sum_high);
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+        m.top = fmaxf(m.top, __shfl_xor(m.top, x));
+        if (x < 8) continue;
+        m.sq = fmaxf(m.sq, __shfl_xor(m.sq, x));
+        m.sq_low = fmaxf(m.sq_low, __shfl_xor(m.sq_low, x));
+        m.sum_high = fmaxf(m.sum_high, __shfl_xor(m.sum_high, x));
+    }
+    if (lane == 0) s_stat[wave >> 2][t4] = m;
+    __syncthreads();
+    if (wave < 4) {
+        ExactStat* stat = reinterpret_cast<ExactStat*>(dst + o.off_stat) + (int64_t)(group * 4 + wave) * kStatChunks;
+        if (lane == 0) {
+            ExactStat t = s_stat[0][wave];
+#pragma unroll
+            for (int q = 1; q < 4; ++q) {
+                const ExactStat v = s_stat[q][wave];
+                t.sq = fmaxf(t.sq, v.sq);
+                t.sq_low = fmaxf(t.sq_low, v.sq_low);
+                t.sum_high = fmaxf(t.sum_high, v.sum_high);
+                t.top = fmaxf(t.top, v.top);
+            }
+            stat[chunk] = t;
+        }
+        if (chunk == 0 && lane >= p.chunks && lane < kStatChunks) stat[lane] = ExactStat{0, 0, 0, 0};
+    }
+}
+
+struct ExactParams : NativeParams {
+    GemmParams g;                     // the operands in their 4-bit form, results, requantized results
+    const ExactStat *a_stat, *w_stat;
+    int64_t a_stride, w_stride;       // bytes between the prepared operands of two problems
+    uint32_t* cnt;                    // arrival counters (split K), one per tile
+    int64_t cnt_stride;               // dwords
+};
+
+// the value DPP control CTRL brings to a lane
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+// the larger of the sums over lanes 0..31 and 32..63; the largest value of 64 lanes (no LDS: a chain of cross-lane reads there
+// costs a workgroup a microsecond)
+__device__ __forceinline__ float half_sum_max(float v) {
+    v = quad_pair_sum(v);
+    v += dpp<0x140>(v);                               // mirrored within 16 lanes
+    return fmaxf(lane_value(v, 0) + lane_value(v, 16), lane_value(v, 32) + lane_value(v, 48));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp<0xB1>(v));
+    v = fmaxf(v, dpp<0x4E>(v));
+    v = fmaxf(v, dpp<0x141>(v));
+    v = fmaxf(v, dpp<0x140>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// The largest norms of a wave's rows (lane: chunk lane % 32 of tile lane / 32 of each pair of tiles), in all lanes
+template <int N>
+__device__ __forceinline__ ExactStat reduce_stat(ExactStat (&v)[N]) {
+    ExactStat m{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        m.sq = fmaxf(m.sq, half_sum_max(v[i].sq));
+        m.sq_low = fmaxf(m.sq_low, half_sum_max(v[i].sq_low));
+        m.sum_high = fmaxf(m.sum_high, half_sum_max(v[i].sum_high));
+        m.top = fmaxf(m.top, v[i].top);
+    }
+    m.top = wave_max(m.top);
+    return m;
+}
+
+// Whether sum |a||w| is at most 2^24 units for all of them: Cauchy-Schwarz over all blocks; or over the low blocks of one
+// operand, and its high blocks (outlier channels) by their sum of magnitudes times the other's largest.  (Infinite norms and
+// 0 times infinity fail every comparison.)
+__device__ __forceinline__ bool sums_exactly(const ExactStat& a, const ExactStat& w) {
+    return sqrtf(a.sq) * sqrtf(w.sq) <= kExactUnits || sqrtf(a.sq_low) * sqrtf(w.sq) + a.sum_high * w.top <= kExactUnits ||
+           sqrtf(a.sq) * sqrtf(w.sq_low) + a.top * w.sum_high <= kExactUnits;
+}
+
+constexpr int kRqPitch = 136;         // bf16 per staged output row (128 + 8: rows stay 16-byte aligned)
+// requantizing epilogue: quantizer tables and, per wave, 64 rows x 128 columns of bf16 results, where the operands were
+struct RequantLds {
+    __attribute__((aligned(16))) uint8_t q[kDialects * 1024], s[kPairs * 1024];
+    __attribute__((aligned(16))) uint16_t st[4 * 64 * kRqPitch];
+};
+
+// the quantizer's tables, by a workgroup of 256 threads
+template <bool MX>
+__device__ __forceinline__ void load_requant_tables(RequantLds& l) {
+    if constexpr (MX) {
+        if (threadIdx.x < 64) l.q[threadIdx.x] = g_quant_tables.mx[threadIdx.x];
+    } else {
+        const uint4* gq = reinterpret_cast<const uint4*>(g_quant_tables.q);
+        const uint4* gs = reinterpret_cast<const uint4*>(g_quant_tables.s);
+        for (int i = threadIdx.x; i < 1024; i += 256) reinterpret_cast<uint4*>(l.q)[i] = gq[i];
+        for (int i = threadIdx.x; i < 512; i += 256) reinterpret_cast<uint4*>(l.s)[i] = gs[i];
+    }
+}
+
+// Requantizing GEMM, tiles that went through the per-block flush: quantize the 128 x 128 bf16
+// results the workgroup has just written to the temporary `p.out` (16 rows x 4 blocks per sweep,
+// 4 lanes per block).  lds_s / lds_q: the quantizer's tables.
+template <bool MX>
+__device__ __forceinline__ void quantize_flushed_piece(const GemmParams& p, int64_t bz, int by, int bx,
+                                                       const uint8_t* lds_s, const uint8_t* lds_q) {
+    __threadfence_block();
+    __syncthreads();
+    const int tid = threadIdx.x;
+    const int nb_row = p.N / kBlock;
+    const uint16_t* src = static_cast<const uint16_t*>(p.out) + bz * p.strideC;
+    for (int sweep = 0; sweep < 8; ++sweep) {
+        const int q = tid >> 2, sub = tid & 3;
+        const int m = by * 128 + sweep * 16 + (q >> 2), nb = bx * 4 + (q & 3);
+        const bool valid = m < p.M && nb < nb_row;      // the same for the 4 lanes of a block
+        uint4 wv = make_uint4(0, 0, 0, 0);
+        if (valid) wv = *reinterpret_cast<const uint4*>(src + (int64_t)m * p.ldc + nb * kBlock + sub * 8);
+        uint32_t code, eb, dl = 0;
+        if constexpr (MX) mxfp4_pass(wv, lds_q, code, eb);
+        else dfp4_pass(wv, lds_s, lds_q, code, eb, dl);
+        if (valid) {
+            const size_t blk = (size_t)(bz * p.M + m) * nb_row + nb;
+            p.q_codes[blk * 4 + sub] = code;
+            if (sub == 0) {
+                p.q_exp[blk] = (uint8_t)eb;
+                if constexpr (!MX) p.q_dial[blk] = (uint8_t)dl;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 // TA = 32-row tiles per wave: 4 (256 x 256 per workgroup) or 2 (128 x 256, for products with few tiles)
-template <int FMT, bool BF16, int TA>
-__global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
+// MODE: what is made of the sums.  kPlain: dfp4_gemm_native.  kExact: the exact products.  kRequant: those, quantized.
+constexpr int kPlain = 0, kExact = 1, kRequant = 2;
+template <int FMT, bool BF16, int TA, int MODE>
+__global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<MODE == kPlain, NativeParams, ExactParams> p) {
     constexpr bool kFp6 = FMT == kFmtFp6;
+    using PieceShape = DirectShape<2, 2, 2, 2, 1>;           // 128 x 128 by 256 threads
     constexpr int kTileLds = kFp6 ? 1536 : 1024, kStage = (2 * TA + 8) * kTileLds + 1024;
     constexpr int kStages = kFp6 && TA == 4 ? 6 : 8;
     constexpr int kRowsWg = 64 * TA, kRowsWave = 32 * TA;
     constexpr int kGStride = kFp6 ? kFp6PairBytes : 1024;    // global bytes per (pair of tiles, step) / (tile, step)
     __shared__ __attribute__((aligned(16))) uint8_t s_stage[kStages * kStage];
+    constexpr int kPieceAt = MODE == kRequant ? offsetof(RequantLds, st) : 0;      // behind the quantizer's tables
+    static_assert(MODE == kPlain || (kPieceAt + sizeof(TileLds<PieceShape>) <= sizeof(s_stage) && kPieceAt % 16 == 0));
+    static_assert(MODE != kRequant || sizeof(RequantLds) <= sizeof(s_stage));
+    __shared__ int s_ctl[5];                                 // exact: per wave, whether its sums are exact; arrivals (split K)
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = lane >> 5, c = lane & 31;
     const int wm = (int)wave >> 1, wn = (int)wave & 1;
-    // this workgroup's range of steps (split K: blockIdx.z)
+    // this workgroup's range of steps (split K: blockIdx.z, in exact products below the problem of a batch)
     const int per = (p.S + p.ksplit - 1) / p.ksplit;
-    const int s_lo = (int)blockIdx.z * per, S = min(p.S, s_lo + per) - s_lo;
+    const int sidx = MODE == kPlain ? (int)blockIdx.z : (int)(blockIdx.z % (unsigned)p.ksplit);
+    const int64_t bz = MODE == kPlain ? 0 : blockIdx.z / (unsigned)p.ksplit;
+    const int s_lo = sidx * per, S = min(p.S, s_lo + per) - s_lo;
+    // norms of the wave's rows of A and of W: used after the main loop, on their way during it
+    ExactStat stat_a[TA / 2], stat_w[2];
+    if constexpr (MODE != kPlain) {
+        p.a.bits += bz * p.a_stride;
+        p.w.bits += bz * p.w_stride;
+        p.a.sc += bz * (p.a_stride / 4);
+        p.w.sc += bz * (p.w_stride / 4);
+        const uint8_t* sa = reinterpret_cast<const uint8_t*>(p.a_stat + ((int64_t)blockIdx.y * (2 * TA) + wm * TA) * kStatChunks) + bz * p.a_stride;
+        const uint8_t* sw = reinterpret_cast<const uint8_t*>(p.w_stat + ((int64_t)blockIdx.x * 8 + wn * 4) * kStatChunks) + bz * p.w_stride;
+#pragma unroll
+        for (int i = 0; i < TA / 2; ++i) stat_a[i] = reinterpret_cast<const ExactStat*>(sa)[i * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) stat_w[i] = reinterpret_cast<const ExactStat*>(sw)[i * 64 + lane];
+    }
     {
         const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(
             (int)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&s_stage[0]);
@@ -159,13 +528,146 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
     // Register x of lane (kh, c) is row 32 i + 8 (x / 4) + 4 kh + x % 4, column 32 j + c.  Row
     // addresses are wave-uniform (scalar registers); the lane adds a constant byte offset.
     const int m0 = blockIdx.y * kRowsWg + wm * kRowsWave, n0 = blockIdx.x * 256 + wn * 128;
+#define DFP4_NATIVE_READ(G, V)                                                                      \
+    asm volatile(DFP4_NATIVE_ACC_READ_##G                                                           \
+                 : "=v"(V[0]), "=v"(V[1]), "=v"(V[2]), "=v"(V[3]), "=v"(V[4]), "=v"(V[5]),          \
+                   "=v"(V[6]), "=v"(V[7]), "=v"(V[8]), "=v"(V[9]), "=v"(V[10]), "=v"(V[11]),        \
+                   "=v"(V[12]), "=v"(V[13]), "=v"(V[14]), "=v"(V[15]))
+#define DFP4_NATIVE_TILES(F)                                                                        \
+    F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)                                                         \
+    if constexpr (TA == 4) { F(8) F(9) F(10) F(11) F(12) F(13) F(14) F(15) }
+    // exact products, split K: the tile's partial sums, [range][(16 tile + x) * 256 + thread]
+    constexpr int kPartTile = TA * 4 * 16 * 256;
+    const float* parts = nullptr;
+    if constexpr (MODE != kPlain) {
+        // (nothing of this before the loop: the norms are still on their way there)
+#pragma unroll
+        for (int i = 0; i < TA / 2; ++i) asm volatile("" : "+v"(stat_a[i].sq), "+v"(stat_a[i].sq_low), "+v"(stat_a[i].sum_high), "+v"(stat_a[i].top));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(stat_w[i].sq), "+v"(stat_w[i].sq_low), "+v"(stat_w[i].sum_high), "+v"(stat_w[i].top));
+        const bool exact = sums_exactly(reduce_stat(stat_a), reduce_stat(stat_w));
+        if (lane == 0) s_ctl[wave] = exact ? 1 : 0;
+        __syncthreads();                                     // and the operands in LDS are done with
+        if (__builtin_amdgcn_readfirstlane(s_ctl[0] & s_ctl[1] & s_ctl[2] & s_ctl[3]) == 0) {
+            asm volatile("; accumulators are dead from here");
+            if (sidx != 0) return;                           // all that share the tile find the same
+            TileLds<PieceShape>& lds = *reinterpret_cast<TileLds<PieceShape>*>(s_stage + kPieceAt);
+            if constexpr (MODE == kRequant) load_requant_tables<!kFp6>(*reinterpret_cast<RequantLds*>(s_stage));
+#pragma unroll 1
+            for (int i = 0; i < TA; ++i) {
+                int piece = i;
+                asm volatile("" : "+s"(piece));              // nothing of a piece is kept in registers for the next
+                const int by = (int)blockIdx.y * (TA / 2) + (piece >> 1), bx = (int)blockIdx.x * 2 + (piece & 1);
+                if (by * 128 >= p.M || bx * 128 >= p.N) continue;
+                int8_tile<!kFp6, BF16, PieceShape>(p.g, lds, bz, by, bx);
+                __syncthreads();
+                if constexpr (MODE == kRequant) {
+                    const RequantLds& rq = *reinterpret_cast<const RequantLds*>(s_stage);
+                    quantize_flushed_piece<!kFp6>(p.g, bz, by, bx, rq.s, rq.q);
+                }
+            }
+            return;
+        }
+        if (p.ksplit > 1) {
+            // Every range's workgroup publishes its partial sums and counts itself in; the last adds the others' to its own (exact,
+            // so in any order) and finishes the tile.  The sums travel as device-scope relaxed atomics: they pass the per-XCD L2,
+            // which a fence would write back as a whole.  "All my stores have completed" is the wait before the barrier.
+            const int tile_id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+            const int64_t tiles = (int64_t)gridDim.x * gridDim.y;
+            float* range0 = p.part + ((bz * tiles + tile_id) * p.ksplit) * (int64_t)kPartTile;
+            parts = range0;
+            if (m0 < p.M && n0 < p.N) {
+                float* mine = range0 + (int64_t)sidx * kPartTile;
+#define DFP4_NATIVE_PUBLISH(G)                                                                      \
+                {                                                                                   \
+                    int v[16];                                                                      \
+                    DFP4_NATIVE_READ(G, v);                                                         \
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x)                                  \
+                        __hip_atomic_store(reinterpret_cast<int*>(mine) + (G * 16 + x) * 256 + tid, v[x], __ATOMIC_RELAXED, \
+                                           __HIP_MEMORY_SCOPE_AGENT);                               \
+                }
+                DFP4_NATIVE_TILES(DFP4_NATIVE_PUBLISH)
+#undef DFP4_NATIVE_PUBLISH
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) {
+                uint32_t* cnt = p.cnt + bz * p.cnt_stride + tile_id;
+                const uint32_t arrived = atomicAdd(cnt, 1u);
+                if (arrived == (uint32_t)p.ksplit - 1u) atomicExch(cnt, 0u);      // ready for the next product
+                s_ctl[4] = (int)arrived;
+            }
+            __syncthreads();
+            if (s_ctl[4] != p.ksplit - 1) return;
+        }
+        if constexpr (MODE == kRequant) {
+            load_requant_tables<!kFp6>(*reinterpret_cast<RequantLds*>(s_stage));
+            __syncthreads();
+        }
+    }
     if (m0 >= p.M || n0 >= p.N) return;
+    // accumulator tile G, with the other ranges' partial sums in exact products
+    auto finish = [&](auto g_c, int (&v)[16]) {
+        if constexpr (MODE != kPlain) {
+            if (p.ksplit > 1) {
+                for (int r = 0; r < p.ksplit; ++r) {
+                    if (r == sidx) continue;
+                    const float* other = parts + (int64_t)r * kPartTile;
+#pragma unroll
+                    for (int x = 0; x < 16; ++x)
+                        v[x] = __builtin_bit_cast(int, __builtin_bit_cast(float, v[x]) +
+                                  __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const int*>(other) + (decltype(g_c)::value * 16 + x) * 256 + tid,
+                                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+                }
+            }
+        }
+    };
+    if constexpr (MODE == kRequant) {
+        // Section 3.3: results are quantized again for the next multiplication.  Each value is rounded to bf16 as the bf16 output
+        // would be; the wave stages 64 rows x 128 columns in LDS and re-reads them in the quantizer's layout (4 lanes per
+        // block of 32 consecutive columns).
+        RequantLds& rq = *reinterpret_cast<RequantLds*>(s_stage);
+        uint16_t* st = &rq.st[wave * 64 * kRqPitch];
+        const int nb_row = p.N / kBlock;
+#pragma unroll
+        for (int half = 0; half < TA / 2; ++half) {
+#define DFP4_NATIVE_STAGE(G)                                                                        \
+            if ((G >> 3) == half) {                                                                 \
+                int v[16];                                                                          \
+                DFP4_NATIVE_READ(G, v);                                                             \
+                finish(std::integral_constant<int, G>{}, v);                                        \
+                _Pragma("unroll") for (int x = 0; x < 16; ++x)                                      \
+                    st[(((G >> 2) & 1) * 32 + 8 * (x >> 2) + 4 * kh + (x & 3)) * kRqPitch + (G & 3) * 32 + c] = \
+                        f32_to_bf16_rne(__builtin_bit_cast(float, v[x]));                           \
+            }
+            DFP4_NATIVE_TILES(DFP4_NATIVE_STAGE)
+#undef DFP4_NATIVE_STAGE
+            for (int pass = 0; pass < 16; ++pass) {
+                const int b = pass * 16 + (lane >> 2), row = b >> 2, cb = b & 3, sub = lane & 3;
+                const uint4 wv = *reinterpret_cast<const uint4*>(&st[row * kRqPitch + cb * 32 + sub * 8]);
+                uint32_t code, eb, dl = 0;
+                if constexpr (!kFp6) mxfp4_pass(wv, rq.q, code, eb);
+                else dfp4_pass(wv, rq.s, rq.q, code, eb, dl);
+                const int m = m0 + half * 64 + row, nb = (n0 >> 5) + cb;
+                if (m < p.M && nb < nb_row) {
+                    const size_t blk = (size_t)(bz * p.M + m) * nb_row + nb;
+                    p.g.q_codes[blk * 4 + sub] = code;
+                    if (sub == 0) {
+                        p.g.q_exp[blk] = (uint8_t)eb;
+                        if constexpr (kFp6) p.g.q_dial[blk] = (uint8_t)dl;
+                    }
+                }
+            }
+        }
+        return;
+    }
     constexpr int kEsz = BF16 ? 2 : 4;
-    // split K: the fp32 partial tile of this range goes to part[blockIdx.z] (the kernel is then the fp32 one)
-    const bool partial = p.ksplit > 1;
+    // native products, split K: the fp32 partial tile of this range goes to part[blockIdx.z] (the kernel is then the fp32 one)
+    const bool partial = MODE == kPlain && p.ksplit > 1;
     const int64_t ld = partial ? p.N : p.ldc;
     uint8_t* base = partial ? reinterpret_cast<uint8_t*>(p.part + (int64_t)blockIdx.z * p.M * p.N)
                             : static_cast<uint8_t*>(p.out);
+    if constexpr (MODE != kPlain) base += bz * p.g.strideC * kEsz;
     uint8_t* wave_out = base + ((int64_t)m0 * ld + n0) * kEsz;                                 // uniform
     const int64_t row_bytes = ld * kEsz;                                                       // uniform
     const bool full = m0 + kRowsWave <= p.M && n0 + 128 <= p.N;                                // uniform
@@ -184,8 +686,8 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
             if constexpr (BF16 && kPairs) {
 #pragma unroll
                 for (int jj = 0; jj < 4; jj += 2) {
-                    const uint32_t b0 = f32_to_bf16_rne_n(__builtin_bit_cast(float, v[4 * q + jj]));
-                    const uint32_t b1 = f32_to_bf16_rne_n(__builtin_bit_cast(float, v[4 * q + jj + 1]));
+                    const uint32_t b0 = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj]));
+                    const uint32_t b1 = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj + 1]));
                     const uint32_t send = (c & 1) ? b0 : b1;
                     const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xf, 0xf, true);
                     const uint32_t word = (c & 1) ? (recv | (b1 << 16)) : (b0 | (recv << 16));
@@ -197,7 +699,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
                     if (kFull || (m0 + i * 32 + 8 * q + 4 * kh + jj < p.M && n0 + j * 32 + c < p.N)) {
                         uint8_t* dst = rowp + (int64_t)jj * row_bytes + lane_off;
                         if constexpr (BF16)
-                            *reinterpret_cast<uint16_t*>(dst) = f32_to_bf16_rne_n(__builtin_bit_cast(float, v[4 * q + jj]));
+                            *reinterpret_cast<uint16_t*>(dst) = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj]));
                         else
                             *reinterpret_cast<int*>(dst) = v[4 * q + jj];
                     }
@@ -208,32 +710,24 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(NativeParams p) {
 #define DFP4_NATIVE_STORE(G)                                                                        \
     {                                                                                               \
         int v[16];                                                                                  \
-        asm volatile(DFP4_NATIVE_ACC_READ_##G                                                       \
-                     : "=v"(v[0]), "=v"(v[1]), "=v"(v[2]), "=v"(v[3]), "=v"(v[4]), "=v"(v[5]),      \
-                       "=v"(v[6]), "=v"(v[7]), "=v"(v[8]), "=v"(v[9]), "=v"(v[10]), "=v"(v[11]),    \
-                       "=v"(v[12]), "=v"(v[13]), "=v"(v[14]), "=v"(v[15]));                         \
+        DFP4_NATIVE_READ(G, v);                                                                     \
+        finish(std::integral_constant<int, G>{}, v);                                                \
         store_tile(kFullC, kPairsC, G, v);                                                          \
-    }
-#define DFP4_NATIVE_ALL                                                                             \
-    DFP4_NATIVE_STORE(0) DFP4_NATIVE_STORE(1) DFP4_NATIVE_STORE(2) DFP4_NATIVE_STORE(3)             \
-    DFP4_NATIVE_STORE(4) DFP4_NATIVE_STORE(5) DFP4_NATIVE_STORE(6) DFP4_NATIVE_STORE(7)             \
-    if constexpr (TA == 4) {                                                                        \
-        DFP4_NATIVE_STORE(8) DFP4_NATIVE_STORE(9) DFP4_NATIVE_STORE(10) DFP4_NATIVE_STORE(11)       \
-        DFP4_NATIVE_STORE(12) DFP4_NATIVE_STORE(13) DFP4_NATIVE_STORE(14) DFP4_NATIVE_STORE(15)     \
     }
     if (pairs) {
         constexpr std::true_type kFullC{}, kPairsC{};
-        DFP4_NATIVE_ALL
+        DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
     } else if (full) {
         constexpr std::true_type kFullC{};
         constexpr std::false_type kPairsC{};
-        DFP4_NATIVE_ALL
+        DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
     } else {
         constexpr std::false_type kFullC{}, kPairsC{};
-        DFP4_NATIVE_ALL
+        DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
     }
-#undef DFP4_NATIVE_ALL
 #undef DFP4_NATIVE_STORE
+#undef DFP4_NATIVE_TILES
+#undef DFP4_NATIVE_READ
 }
 
 // Few rows of A (decode shapes, M <= 64): 32 W rows per workgroup, its 16 waves share K (wave w
@@ -296,7 +790,7 @@ __global__ __launch_bounds__(1024) void gemm_native_small_kernel(NativeParams p)
         const int m = i * 32 + 8 * (x >> 2) + 4 * kh + (x & 3);
         if (m < p.M && n < p.N) {
             const int64_t o = (int64_t)m * p.ldc + n;
-            if constexpr (BF16) static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne_n(sum);
+            if constexpr (BF16) static_cast<uint16_t*>(p.out)[o] = f32_to_bf16_rne(sum);
             else static_cast<float*>(p.out)[o] = sum;
         }
     }
@@ -311,7 +805,7 @@ __global__ __launch_bounds__(256) void native_reduce_kernel(const float* __restr
     float s = part[i];
     for (int z = 1; z < ksplit; ++z) s += part[(int64_t)z * total + i];
     const int64_t m = i / N, o = m * ldc + (i - m * N);
-    if constexpr (BF16) static_cast<uint16_t*>(out)[o] = f32_to_bf16_rne_n(s);
+    if constexpr (BF16) static_cast<uint16_t*>(out)[o] = f32_to_bf16_rne(s);
     else static_cast<float*>(out)[o] = s;
 }
 
@@ -413,8 +907,8 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
     const bool bf16 = out_dtype == DFP4_BF16 && p.ksplit == 1;     // partial tiles are fp32
 #define DFP4_NATIVE_LAUNCH(F, B)                                                                         \
     do {                                                                                                 \
-        if (half) hipLaunchKernelGGL((gemm_native_kernel<F, B, 2>), grid, dim3(256), 0, stream, p);      \
-        else hipLaunchKernelGGL((gemm_native_kernel<F, B, 4>), grid, dim3(256), 0, stream, p);           \
+        if (half) hipLaunchKernelGGL((gemm_native_kernel<F, B, 2, kPlain>), grid, dim3(256), 0, stream, p);      \
+        else hipLaunchKernelGGL((gemm_native_kernel<F, B, 4, kPlain>), grid, dim3(256), 0, stream, p);           \
     } while (0)
     if (fp6) {
         if (bf16) DFP4_NATIVE_LAUNCH(kFmtFp6, true); else DFP4_NATIVE_LAUNCH(kFmtFp6, false);
@@ -429,6 +923,134 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
         else
             hipLaunchKernelGGL((native_reduce_kernel<false>), dim3(gr), dim3(256), 0, stream, p.part, out, p.M, p.N, ldc, p.ksplit);
     }
+    return check_launch();
+}
+
+// ---- exact products
+namespace {
+
+// A prepared operand: [counters (A only) | bits | scales | norms | references | class masks]; rows padded to 256
+struct ExactLayout { int64_t bits, sc, stat, ref, mask, total; };
+inline ExactLayout exact_layout(int64_t rows, int64_t KB, bool fp6, bool counters) {
+    const OperandLayout o = operand_layout(rows, KB, fp6);
+    ExactLayout l{};
+    l.bits = counters ? up256((kExactCounters) * 4) : 0;
+    l.sc = l.bits + o.sc;
+    l.stat = l.bits + o.total;
+    l.ref = l.stat + (rows + 255) / 256 * 8 * kStatChunks * (int64_t)sizeof(ExactStat);
+    l.mask = l.ref + up256(rows);
+    l.total = up256(l.mask + (rows + 255) / 256 * 2 * KB);
+    return l;
+}
+
+// Tile height (128 or 256 rows by 256 columns) and the workgroups that share a tile's K
+struct ExactShape { bool half; int ksplit; };
+inline ExactShape exact_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu) {
+    const int64_t S = (KB + 1) / 2, cols = (N + 255) / 256 * batch;
+    const bool half = (M + 255) / 256 * cols * 2 <= cu && M > 128;
+    const int64_t tiles = (M + (half ? 127 : 255)) / (half ? 128 : 256) * cols;
+    int s = 1;
+    while (s < 8 && tiles * s * 2 <= cu && S / (2 * s) >= 8) s *= 2;
+    return {half, tiles <= kExactSplitTiles ? s : 1};
+}
+inline int64_t exact_part_bytes(int64_t M, int64_t N, ExactShape x, int64_t batch) {
+    if (x.ksplit == 1) return 0;
+    return (M + (x.half ? 127 : 255)) / (x.half ? 128 : 256) * ((N + 255) / 256) * batch * x.ksplit * (x.half ? 128 : 256) * 256 * 4;
+}
+
+}  // namespace
+
+int64_t exact_operand_bytes(int64_t rows, int64_t KB, bool fp6, bool counters) { return exact_layout(rows, KB, fp6, counters).total; }
+
+void set_prepared_classes(bool mx, GemmParams& p, const uint8_t* a_prep, const uint8_t* w_prep) {
+    const ExactLayout la = exact_layout(p.M, p.KB, !mx, true), lw = exact_layout(p.N, p.KB, !mx, false);
+    p.ref_a = a_prep + la.ref; p.mask_a = a_prep + la.mask;
+    p.ref_w = w_prep + lw.ref; p.mask_w = w_prep + lw.mask;
+}
+
+int64_t exact_split_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
+    return exact_part_bytes(M, N, exact_shape(M, N, KB, batch, device_cu_count()), batch);
+}
+
+// Packs A (p.a_prep, unless null) and W (p.w_prep, unless null) of `batch` problems; `classes` (batch 1): with what
+// gemm_direct_kernel reads of prepared operands
+int launch_exact_prep(bool mx, const GemmParams& p, int64_t batch, bool classes, hipStream_t stream) {
+    const int64_t KB = p.KB, S = (KB + 1) / 2;
+    ExactPrepParams q{};
+    q.KB = p.KB;
+    q.S = (int)S;
+    // 8 blocks at a time: as many times as leave two workgroups for every compute unit (they read the exponents of whole rows:
+    // fewer and longer chunks read less; 14336 x 4096 with 8 blocks each 36 us, so 28), at most 32 chunks
+    const int64_t groups = ((p.a_prep ? (p.M + 255) / 256 * 2 : 0) + (p.w_prep ? (p.N + 255) / 256 * 2 : 0)) * batch, eights = (KB + 7) / 8;
+    int64_t times = groups * eights / (2 * device_cu_count());
+    if (times > kMaxChunkBlocks / 8) times = kMaxChunkBlocks / 8;
+    if (times < (eights + kStatChunks - 1) / kStatChunks) times = (eights + kStatChunks - 1) / kStatChunks;
+    q.chunk_blocks = (int)(8 * times);
+    q.chunks = (int)((eights + times - 1) / times);
+    if (q.chunks > kStatChunks) return DFP4_ERR_SHAPE;
+    int64_t wgs = 0;
+    if (p.a_prep) {
+        const ExactLayout l = exact_layout(p.M, KB, !mx, true);
+        q.a = ExactOperand{p.a_codes, mx ? nullptr : p.a_dial, p.a_exp, p.strideA_rows, p.a_prep + l.bits, l.sc - l.bits, l.stat - l.bits,
+                           p.a_prep_stride, classes ? p.a_prep + l.ref : nullptr, classes ? p.a_prep + l.mask : nullptr, p.M, (p.M + 255) / 256 * 2};
+        q.count = reinterpret_cast<uint32_t*>(p.a_prep);
+        q.count_stride = p.a_prep_stride / 4;
+        q.counters = kExactCounters;
+        wgs = (int64_t)q.a.groups * q.chunks;
+        q.wgs_a = (int)wgs;
+    }
+    if (p.w_prep) {
+        const ExactLayout l = exact_layout(p.N, KB, !mx, false);
+        q.w = ExactOperand{p.w_codes, mx ? nullptr : p.w_dial, p.w_exp, p.strideW_rows, p.w_prep, l.sc, l.stat,
+                           p.w_prep_stride, classes ? p.w_prep + l.ref : nullptr, classes ? p.w_prep + l.mask : nullptr, p.N, (p.N + 255) / 256 * 2};
+        wgs += (int64_t)q.w.groups * q.chunks;
+    }
+    if (wgs == 0) return DFP4_OK;
+    if (wgs > 0x7fffffff || batch > 65535) return DFP4_ERR_SHAPE;
+    dim3 g((unsigned)wgs, 1, (unsigned)batch);
+    if (mx) hipLaunchKernelGGL((exact_prep_kernel<kFmtFp4>), g, dim3(1024), 0, stream, q);
+    else hipLaunchKernelGGL((exact_prep_kernel<kFmtFp6>), g, dim3(1024), 0, stream, q);
+    return check_launch();
+}
+
+// The product of prepared operands (p.a_prep, p.w_prep); `part`: room for the partial tiles where K is split
+int launch_exact(bool mx, bool bf16, const GemmParams& g, int64_t batch, float* part, size_t part_bytes, bool rq, hipStream_t stream) {
+    const int64_t KB = g.KB;
+    ExactShape x = exact_shape(g.M, g.N, KB, batch, device_cu_count());
+    if (x.ksplit > 1 && (!part || (size_t)exact_part_bytes(g.M, g.N, x, batch) > part_bytes)) x.ksplit = 1;      // no room: no split
+    const ExactLayout la = exact_layout(g.M, KB, !mx, true), lw = exact_layout(g.N, KB, !mx, false);
+    ExactParams p{};
+    p.a = PackedOperand{g.a_prep + la.bits, reinterpret_cast<uint32_t*>(g.a_prep + la.sc)};
+    p.w = PackedOperand{g.w_prep, reinterpret_cast<uint32_t*>(g.w_prep + lw.sc)};
+    p.out = g.out; p.M = g.M; p.N = g.N; p.S = (int)((KB + 1) / 2); p.ldc = g.ldc;
+    p.ksplit = x.ksplit;
+    p.part = part;
+    p.g = g;
+    p.a_stat = reinterpret_cast<const ExactStat*>(g.a_prep + la.stat);
+    p.w_stat = reinterpret_cast<const ExactStat*>(g.w_prep + lw.stat);
+    p.a_stride = g.a_prep_stride; p.w_stride = g.w_prep_stride;
+    p.cnt = reinterpret_cast<uint32_t*>(g.a_prep);
+    p.cnt_stride = g.a_prep_stride / 4;
+    dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)((g.M + (x.half ? 127 : 255)) / (x.half ? 128 : 256)), (unsigned)(batch * x.ksplit));
+    if (grid.y > 65535 || batch * x.ksplit > 65535) return DFP4_ERR_SHAPE;
+    dispatch_mx_bf16(mx, bf16, [&](auto mxc, auto bc) {
+        constexpr int kFmt = decltype(mxc)::value ? kFmtFp4 : kFmtFp6;
+        constexpr bool kBf16 = decltype(bc)::value;
+        auto run = [&](auto ta_c, auto mode_c) {
+            hipLaunchKernelGGL((gemm_native_kernel<kFmt, kBf16, decltype(ta_c)::value, decltype(mode_c)::value>), grid, dim3(256), 0, stream, p);
+        };
+        using Ta2 = std::integral_constant<int, 2>;
+        using Ta4 = std::integral_constant<int, 4>;
+        if constexpr (kBf16) {
+            if (rq) {
+                if (x.half) run(Ta2{}, std::integral_constant<int, kRequant>{});
+                else run(Ta4{}, std::integral_constant<int, kRequant>{});
+                return;
+            }
+        }
+        if (x.half) run(Ta2{}, std::integral_constant<int, kExact>{});
+        else run(Ta4{}, std::integral_constant<int, kExact>{});
+    });
     return check_launch();
 }
 

@@ -222,8 +222,9 @@ __global__ __launch_bounds__(kThreads) void quantize_native_kernel(
             uint32_t code, eb, dl;
             dfp4_pass_small(w[p], lds_s, lds_q, code, eb, dl);
             const uint32_t step = sg * 4u + p;
-            const uint64_t p48 = pack6(code, s_fp6[dl * 2], s_fp6[dl * 2 + 1]);
-            const uint32_t lo32 = (uint32_t)p48, mid32 = (uint32_t)(p48 >> 16), hi16 = (uint32_t)(p48 >> 32);
+            uint32_t lo24, hi24;                                       // 48 bits: low 32, those from bit 16, the upper 16
+            pack6_quarter(code, s_fp6[dl * 2], s_fp6[dl * 2 + 1], lo24, hi24);
+            const uint32_t lo32 = lo24 | (hi24 << 24), mid32 = (lo24 >> 16) | (hi24 << 8), hi16 = hi24 >> 8;
             // lane 0: {p0 lo, p0 hi16 | p1 lo16 << 16, p1 mid, p2 lo};  lane 2: {p2 hi16 | p3 lo16 << 16, p3 mid}
             const uint32_t next_lo = quad<0x39>(lo32);                 // low dword of the lane after this one
             const uint32_t next_mid = quad<0x39>(mid32);

@@ -1511,3 +1511,47 @@ def test_gemm_prepared_and_plain_agree_across_kernels():
         pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
         for dtype, bits in ((torch.float32, torch.int32), (torch.bfloat16, torch.int16)):
             assert torch.equal(dfp4.gemm(qa, qw, dtype=dtype).view(bits), dfp4.gemm_prepared(pa, pw, dtype=dtype).view(bits)), (M, N, K)
+
+
+# --------------------------------------------------------------------------
+# Large products sum in fp32 where norms of the rows show that no partial sum rounds, in int32 elsewhere: inputs on either side
+# of that rule.  Both are exact, so the bound is one rounding of the float64 product (2^-24; 2^-149 where that is subnormal).
+# --------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,prepared", [(1552, 5664, 160, True), (518, 6686, 2848, True), (2320, 5408, 448, False),
+                                            (845, 2333, 11104, False)])
+@pytest.mark.parametrize("kind", ["plain", "outliers", "massive", "zero blocks", "tiny", "huge", "spread rows", "all zero"])
+def test_gemm_large_exact_sums(M, N, K, prepared, kind):
+    assert dfp4.gemm_path(M, N, K, prepared=prepared) == 0
+    print(f"gemm large, exact sums: {M}x{N}x{K}, prepared {prepared}, {kind}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K + len(kind))
+    a, w = torch.randn(M, K, generator=g, device="cuda"), torch.randn(N, K, generator=g, device="cuda") * 0.02
+    if kind == "outliers":                                            # channels on both operands
+        a[:, torch.randperm(K, generator=g, device="cuda")[:max(1, K // 200)]] *= 50
+        w[:, torch.randperm(K, generator=g, device="cuda")[:2]] *= 20
+    elif kind == "massive":                                           # single elements: past 2^24 units in some tiles, not in others
+        for i, r in enumerate(range(3, M, 97)):
+            a[r, (r * 37) % K] = 2.0 ** (4 + i % 6)
+    elif kind == "zero blocks":
+        a[::3, :64] = 0
+        a[M // 2] = 0
+        w[:, 96:128] = 0
+    elif kind == "tiny":                                              # references below what the fp32 sums take, in some tiles
+        a[: M // 2] *= 2.0 ** -70
+        w[N // 2:] *= 2.0 ** -40
+    elif kind == "huge":
+        a[: M // 2] *= 2.0 ** 60
+        w[N // 2:] *= 2.0 ** 55
+    elif kind == "spread rows":                                       # every row its own power of two
+        a *= torch.exp2(torch.randint(-20, 20, (M, 1), generator=g, device="cuda").float())
+    elif kind == "all zero":
+        a.zero_()
+    qa, qw = dfp4.quantize(a.to(torch.bfloat16)), dfp4.quantize(w.to(torch.bfloat16))
+    ref = dfp4.dequantize(qa).double() @ dfp4.dequantize(qw).double().T
+    if prepared:
+        out = dfp4.gemm_prepared(dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True))
+    else:
+        out = dfp4.gemm(qa, qw)
+    torch.cuda.synchronize()
+    assert bool(((out.double() - ref).abs() <= (ref.abs() * 2.0 ** -24).clamp_min(2.0 ** -149)).all())
+    if kind == "all zero":
+        assert not bool(out.view(torch.int32).any())                  # +0
