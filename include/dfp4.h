@@ -242,8 +242,8 @@ int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const vo
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);
 /*
  * Diagnostic: the kernel that a product of these sizes takes (batch 1 unless dfp4_gemm_batched; prepared: with
- * dfp4_gemm_prepared).  0: the large kernel (tiles of 256 or 128 x 256 on packed operands).  1 to 7: gemm_direct_kernel
- * (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
+ * dfp4_gemm_prepared).  0: the large kernel (tiles of 256 or 128 x 256 on packed operands).  1 to 7: gemm_f8_kernel, with
+ * prepared operands of more than 256 rows gemm_direct_kernel (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
  * two, 128 x 128, 256 x 128, and 128 x 128 for K of at most 128.  DFP4_ERR_SHAPE for sizes that are no product.
  */
 int dfp4_gemm_path(int64_t M, int64_t N, int64_t K, int64_t batch, int prepared);

@@ -33,9 +33,11 @@
 //                        (It replaced a kernel that ran the scheme above on operands expanded to int8 beforehand:
 //                        2048 x 14336 x 4096 prepared 142 -> 83 us, 2048 x 4096 x 14336 125 -> 75, 4096 x 12288 x 4096
 //                        202 -> 117; with the prepass 150 -> 100, 162 -> 108, 220 -> 144.)
-//   gemm_direct_kernel   (gemm_direct.hip) the same exact scheme with both operands expanded inside the
-//                        kernel, in tiles from 32 x 32 to 256 x 128: few rows, few tiles, long K, batches
-//                        whose expanded A would be read only once;
+//   gemm_f8_kernel       (gemm_f8.hip) both operands expanded inside the kernel to FP8 for the block-scaled instruction, under the
+//                        same proof, in tiles from 32 x 32 to 256 x 128: few rows, few tiles, long K, batches whose packed A
+//                        would be read only once;
+//   gemm_direct_kernel   (gemm_direct.hip) the same tiles on the int8 matrix cores by the scheme above: small products of prepared
+//                        operands of more than 256 rows;
 //   gemm_block16_kernel  operands quantized in blocks of 16: per-block fp32 flush.
 //
 // The order of the elements inside an MFMA operand does not matter as long
@@ -60,8 +62,8 @@ inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
     while (s < 8 && tiles * s * 2 <= cu && KB / (2 * s) >= 16) s *= 2;
     return tiles <= kExactSplitTiles ? s : 1;
 }
-// Which kernel.  The large kernel multiplies packed operands; gemm_direct_kernel (gemm_direct.hip) expands in the kernel and
-// takes everything the large one is not for (few rows, K beyond 16384), and the products it is estimated to finish sooner:
+// Which kernel.  The large kernel multiplies packed operands; gemm_f8_kernel and gemm_direct_kernel ("direct") expand in the kernel and
+// take everything the large one is not for (few rows, K beyond 16384), and the products they are estimated to finish sooner:
 // those with few output tiles, and batches whose packed A would be read only once or twice (P V of attention).  K of one
 // iteration of the direct kernel (Q K^T) goes there unless it is prepared already.  fast_cost is of the int8 kernel that
 // the large one replaced, which is faster everywhere: the line lies where it lay, so that no product changed to a slower

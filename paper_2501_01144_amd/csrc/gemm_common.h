@@ -40,6 +40,8 @@ struct GemmParams {
     uint8_t *q_dial, *q_exp;
 };
 
+constexpr int kDirectOnceBlocks = 4;         // K, in blocks, that the direct kernels take in one iteration
+
 namespace {
 
 // Results leave the kernel once and are not read again by it: stored with the non-temporal hint so
@@ -200,24 +202,24 @@ __device__ __forceinline__ void block_flush_tile(const GemmParams& p, int64_t bz
 }
 
 // ---------------------------------------------------------------------------
-// A 32 x 32 output tile by a workgroup of NW (8 or 16) waves that share K in contiguous ranges, one fp32
+// A 32 x 32 output tile by a workgroup of NW (4, 8 or 16) waves that share K in contiguous ranges, one fp32
 // scale-and-add per block as in the paper's MAC; the partial tiles are added in a fixed order through LDS.
 // Small tiles that gemm_direct_kernel declines.
 // ---------------------------------------------------------------------------
-constexpr int kSmallWaves = 16;     // waves of a workgroup, at most (LDS is laid out for this many)
 constexpr int kSmallMaxKB = 512;      // LDS holds the 32 rows' exponent bytes of all blocks
 
+template <int NW, int MAX_KB>
 struct SmallTileLds {
     __attribute__((aligned(16))) uint32_t tab[kDialects * 4];   // shift-0 tables
-    __attribute__((aligned(4))) uint8_t ea[kSmallMaxKB * 32];   // [block][row] exponent bytes of A
-    float red[kSmallWaves / 2][16][64];
+    __attribute__((aligned(4))) uint8_t ea[MAX_KB * 32];        // [block][row] exponent bytes of A (a longer K: read where they are)
+    float red[NW / 2][16][64];
 };
 
-template <bool MX, bool BF16, int NW>
-__device__ __forceinline__ void small_tile(const GemmParams& p, int64_t bz, int m0, int n0, SmallTileLds& lds) {
+template <bool MX, bool BF16, int NW, int MAX_KB>
+__device__ __forceinline__ void small_tile(const GemmParams& p, int64_t bz, int m0, int n0, SmallTileLds<NW, MAX_KB>& lds) {
     uint32_t (&s_tab)[kDialects * 4] = lds.tab;
-    uint8_t (&s_ea)[kSmallMaxKB * 32] = lds.ea;
-    float (&s_red)[kSmallWaves / 2][16][64] = lds.red;
+    uint8_t (&s_ea)[MAX_KB * 32] = lds.ea;
+    float (&s_red)[NW / 2][16][64] = lds.red;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, r = lane & 31;
     const int KB = p.KB;
@@ -233,9 +235,12 @@ __device__ __forceinline__ void small_tile(const GemmParams& p, int64_t bz, int 
     const int kb_lo = wave * per, kb_hi = min(KB, kb_lo + per);
 
     for (int i = tid; i < kDialects * 4; i += NW * 64) s_tab[i] = g_shifted_book.w[i >> 2][0][i & 3];
-    for (int i = tid; i < 32 * KB; i += NW * 64) {
-        const int row = i / KB, kb = i - row * KB;
-        s_ea[kb * 32 + row] = p.a_exp[(a_row0 + min(m0 + row, p.M - 1)) * KB + kb];
+    const bool staged = KB <= MAX_KB;
+    if (staged) {
+        for (int i = tid; i < 32 * KB; i += NW * 64) {
+            const int row = i / KB, kb = i - row * KB;
+            s_ea[kb * 32 + row] = p.a_exp[(a_row0 + min(m0 + row, p.M - 1)) * KB + kb];
+        }
     }
     __syncthreads();
 
@@ -266,7 +271,14 @@ __device__ __forceinline__ void small_tile(const GemmParams& p, int64_t bz, int 
             const int ewc = (int)ew[u] - 256;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t e4 = *reinterpret_cast<const uint32_t*>(&s_ea[kb * 32 + 8 * q + 4 * h]);
+                uint32_t e4 = 0;
+                if (staged) {
+                    e4 = *reinterpret_cast<const uint32_t*>(&s_ea[kb * 32 + 8 * q + 4 * h]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        e4 |= (uint32_t)p.a_exp[(a_row0 + min(m0 + 8 * q + 4 * h + j, p.M - 1)) * KB + kb] << (8 * j);
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     acc[4 * q + j] += ldexpf((float)pr[4 * q + j], (int)((e4 >> (8 * j)) & 0xffu) + ewc);
@@ -326,7 +338,7 @@ int launch_exact(bool mx, bool bf16, const GemmParams& g, int64_t batch, float* 
 // they are; a shape and the microseconds it is estimated to take on `cu` compute units
 struct DirectChoice { int shape; float us; };
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
-constexpr int kDirectOnceBlocks = 4;         // K, in blocks, that it takes in one iteration
+int launch_gemm_f8(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
 DirectChoice choose_direct(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu);
 int64_t gemm_direct_max_rows(int64_t KB, bool weight);
 

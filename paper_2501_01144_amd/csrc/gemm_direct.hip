@@ -1,12 +1,7 @@
-// Block-scaled integer GEMM with nothing prepared: both operands are expanded from their 4-bit form inside
-// the kernel, all of K is summed exactly in int32 (scheme: gemm.hip).
-//
-// What bounds it.  Large products: the expansion (about 65 vector-ALU instructions per row and 32-element block)
-// and the waits between it and the multiply, so it is done once per workgroup and shared through LDS
-// (2048 x 4096 x 4096, two waves per SIMD: a wave has a vector-ALU instruction active 26 % of its cycles, waits 35 %, and
-// 28 % to issue; the matrix cores are busy 23 %).  The alternative is to pack both operands in a pass of their
-// own and multiply with the large kernel (gemm_native.hip), which pays where a packed byte is used by many tiles.  Small products: latency, so the
-// tile is cut down until the workgroups cover the chip and the waves of a workgroup share K.
+// Products of prepared operands of more than 256 rows that are too small for the large kernel, on the int8 matrix cores (the
+// tile: gemm_int8_tile.h), and the choice of a tile shape for these and for gemm_f8_kernel (gemm_f8.hip), which takes the
+// same shapes.  Here whether a tile is summed exactly in int32 or block by block is decided, and counted, from masks that were prepared with
+// the operands.
 #include "gemm_int8_tile.h"
 
 namespace dfp4 {
@@ -32,7 +27,8 @@ int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t s
 // rest counts as much as it fills), growing with K beyond 128 blocks by `grow` per 384; `store` per MB of fp32
 // results, where their rows begin inside a line (N % 16) `ragged`.  1: one workgroup per compute unit, 2: two, which
 // shapes that fit take as soon as there are more tiles than compute units.
-// Fitted to 21000 products timed on 256 compute units, M 1..4096, N 64..14336, K 32..16384, 1 to 128 problems, each with
+// Fitted to 21000 products timed with int8 operands on 256 compute units (gemm_f8_kernel is 0 to 20 % faster in all shapes, which
+// leaves the order of the shapes as it is), M 1..4096, N 64..14336, K 32..16384, 1 to 128 problems, each with
 // every shape: the estimates are within 10 % (rms).  Microseconds of 32 / 64 (KG 4) / 64 (KG 2) / 128 (KG 2) / 128 / 256 rows, and of the int8
 // kernel that the large one replaced, with its prepass:
 //   16 x 4096 x 4096       10.1   17.5   20.0   36.5   49.0      -      -
@@ -97,6 +93,7 @@ int64_t gemm_direct_max_rows(int64_t KB, bool weight) {
 }
 
 int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream) {
+    if (!p.ref_a) return launch_gemm_f8(mx, bf16, p, batch, shape, stream);
     switch (shape) {
         case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);
         case 1: return launch<DirectShape<1, 1, 2, 2, 4>>(mx, bf16, p, batch, stream);

@@ -1,0 +1,499 @@
+// Exact products of few rows, few tiles, short or very long K, and thin batches, with both operands in their 4-bit form: the
+// block-scaled matrix instruction on operands expanded to FP8 inside the kernel.
+//
+// Every DialectFP4 magnitude 0.5 u (u <= 15) is an FP8 E4M3 number, and the exponent byte is the instruction's scale, so an item
+// (row, block of 32 codes) is expanded by two table lookups and a sign bit per byte, with no reference exponent, no shift and
+// no class, and a pair of blocks is one instruction per 32 x 32 outputs.  Sums are fp32 and exact under the rule of
+// gemm_native.hip: with the norms of the rows in units of their smallest block exponent, sum |a||w| <= ||a|| ||w|| <= 2^24 units means that no
+// partial sum rounds (3.2 million outputs of single FP8 instructions below that bound checked: none off).  The norms are
+// taken while the items are expanded: of A from its codes, of W, which has most of the rows where A has few, from its
+// exponents alone (||w||^2 <= sum over blocks of 32 15^2 4^offset, which is about twice the norm of Gaussian data).  A tile
+// that does not pass is computed again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the
+// kernel's register count.
+//
+// This took the place of int8 operands with classes (gemm_int8_tile.h) for everything but prepared operands of more than 256
+// rows, whose tiles are taken or declined by prepared masks.  There a pass over the exponents came first, and classes on
+// both operands cost up to four products per pair of blocks.  Microseconds of a call with int8 / with FP8 operands (A with 0.5 %
+// outlier channels x 50, scores with two outlier dimensions on both):
+//   16 x 4096 x 4096      10.7 /  9.5     777 x 3001 x 2080     28.6 / 24.1     2048 x 4096 x 4096            78.7 / 65.7
+//   16 x 14336 x 4096     17.2 / 14.6     512 x 4096 x 4096     37.2 / 30.7     scores, 128 x 2048 x 2048 x 128  487 / 382
+//   36 x 7898 x 1344      10.9 /  9.0     512 x 4096 x 14336     110 / 100      P V, 128 x 2048 x 2048 x 128     210 / 195
+// What bounds it: as before nothing alone.  An item is about 60 vector-ALU instructions, and the expansion, the LDS traffic and the
+// products of a workgroup's few waves overlap only in part.  Tried: one operand buffer and three or four waves per SIMD for the
+// 128 x 128 and 256 x 128 tiles (3 to 18 % slower); four waves per SIMD for the tiles of one iteration (scores above 369, but 16 x 700 x 1312 x
+// 64 18.6 instead of 16.7 us).  The exponents' ends are kept as one packed maximum per row: as two values they cost registers, and
+// the last shape above 15 % of its time.
+//
+// Tiles, groups and the loop are those of gemm_int8_tile.h: KG groups of WM x WN waves, each with its contiguous range of K, 4
+// blocks per iteration, expanded operands in LDS as [32-row group][pair of blocks][half of a block][block of the pair][row][16
+// bytes], the row slot rotated by twice the block number.  The instruction wants in lane (h, r) half h of both blocks of row r, and the
+// scale of block h.
+#include "gemm_int8_tile.h"
+
+namespace dfp4 {
+namespace {
+
+// Tables of a dialect: FP8 E4M3 bit patterns of its 8 magnitudes, and the magnitudes u themselves
+constexpr uint8_t e4m3_of_half_units(int u) {
+    int e = -1;                                                        // floor(log2(0.5 u))
+    for (int v = u; v > 1; v >>= 1) ++e;
+    return u == 0 ? 0 : (uint8_t)(((e + 7) << 3) | (((u << 3) >> (e + 1)) & 7));
+}
+struct F8Book { uint32_t w[kDialects + 1][4]; };                       // the last: all zeros
+constexpr F8Book make_f8_book() {
+    F8Book b{};
+    for (int d = 0; d < kDialects; ++d)
+        for (int j = 0; j < 8; ++j) {
+            b.w[d][j / 4] |= (uint32_t)e4m3_of_half_units(kBook[d][j]) << (8 * (j % 4));
+            b.w[d][2 + j / 4] |= (uint32_t)kBook[d][j] << (8 * (j % 4));
+        }
+    return b;
+}
+__device__ const F8Book g_f8_book = make_f8_book();
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// References (exponent bytes of nonzero blocks) outside this range are left to int32: see gemm_native.hip
+constexpr int kMinRef = 66, kMaxRef = 178;
+constexpr float kExactUnits = 16777216.0f * 0.9998f;
+
+template <class S>
+struct F8Lds {
+    __attribute__((aligned(16))) uint8_t x[S::KG][S::kF8Bufs][S::kRowGroups * 4096];   // expanded operands: groups of A, of W
+    __attribute__((aligned(16))) uint32_t tab[kDialects + 1][4];
+    __attribute__((aligned(4))) uint8_t sc[S::KG][S::kF8Bufs][S::kRows][4];            // exponent bytes of the 4 blocks of a row
+    float sq[S::KG][S::kRows];                                         // per row: sum of squares in units of 2^-127 ...
+    uint8_t lo[S::KG][S::kRows];                                       // ... smallest exponent byte (255: all zero) ...
+    uint8_t ok[S::KG][S::kRows];                                       // ... and whether all are in range
+    int norm[2];                                                       // largest squared norm of A's, of W's rows in their units (bits)
+};
+
+template <int CTRL>
+__device__ __forceinline__ int quad_dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+
+// S: tile; F: the shape a tile is computed again with, of as many threads
+template <bool MX, bool BF16, class S, class F>
+__global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmParams p) {
+    static_assert(S::kThreads == F::kThreads && S::kTm % F::kTm == 0 && S::kTn % F::kTn == 0);
+    constexpr int TI = S::TI, TJ = S::TJ;
+    __shared__ union {
+        F8Lds<S> d;
+        TileLds<F> again;
+    } u;
+    F8Lds<S>& lds = u.d;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % (S::WM * S::WN);
+    const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) / (S::WM * S::WN);
+    const int gt = tid % S::kGroupThreads;
+    const int KB = p.KB;
+    const int64_t bz = blockIdx.z;
+    const int m0 = (int)blockIdx.y * S::kTm, n0 = (int)blockIdx.x * S::kTn;
+
+    // ---- items of this thread: rows kItemRows j + r4 (the first kItemsA of A), block b4 of the iteration
+    const int b4 = gt & 3, r4 = gt >> 2;
+    const int per = ((KB + S::KG - 1) / S::KG + 3) & ~3;               // blocks per group
+    const int k_lo = kg * per;
+    const int64_t a_blk0 = bz * p.strideA_rows * KB, w_blk0 = bz * p.strideW_rows * KB;
+    const uint8_t *ac = p.a_codes + a_blk0 * 16, *wc = p.w_codes + w_blk0 * 16;              // uniform bases,
+    const uint8_t *ae = p.a_exp + a_blk0, *we = p.w_exp + w_blk0;                            // 32-bit offsets
+    const uint8_t *ad = MX ? nullptr : p.a_dial + a_blk0, *wd = MX ? nullptr : p.w_dial + w_blk0;
+    uint32_t blk[S::kItems];                                           // first block of item j's row
+#pragma unroll
+    for (int j = 0; j < S::kItems; ++j) {
+        const int row = j * S::kItemRows + r4;
+        blk[j] = (uint32_t)(j < S::kItemsA ? min(m0 + row, p.M - 1) : min(n0 + row - S::kTm, p.N - 1)) * (uint32_t)KB;
+    }
+    struct Item { uint4 c; uint32_t e, d; };
+    Item item[S::kItems];                                              // of the next iteration
+    float sq[S::kItems];                                               // of the items expanded so far
+    typedef uint16_t v2u __attribute__((ext_vector_type(2)));
+    v2u ends[S::kItems];                                               // 255 - smallest exponent of nonzero blocks (0: none), largest exponent
+    auto load = [&](Item& it, int j, int kb0) {
+        const uint32_t i = blk[j] + (uint32_t)min(kb0 + b4, KB - 1);   // blocks beyond K read the row's last
+        it.c = *reinterpret_cast<const uint4*>((j < S::kItemsA ? ac : wc) + (uint64_t)(i * 16u));
+        it.e = (j < S::kItemsA ? ae : we)[i];
+        it.d = MX ? 7u : (uint32_t)(j < S::kItemsA ? ad : wd)[i];
+    };
+#pragma unroll
+    for (int j = 0; j < S::kItems; ++j) {
+        if (KB > 0) load(item[j], j, k_lo);
+        sq[j] = 0.0f;
+        ends[j] = v2u{0, 0};
+    }
+    for (int i = tid; i < (kDialects + 1) * 4; i += S::kThreads) (&lds.tab[0][0])[i] = (&g_f8_book.w[0][0])[i];
+    if (tid < 2) lds.norm[tid] = 0;
+    __syncthreads();
+
+    const int wm = wave / S::WN, wn = wave % S::WN, h = lane >> 5, r = lane & 31;
+    v16f acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) acc[i][j][x] = 0.0f;
+    // Item j of the iteration at kb0: the table of its dialect, then the expansion into a buffer, and its part of the row's norm
+    auto table = [&](const Item& it, int kb0) {
+        return *reinterpret_cast<const uint4*>(&lds.tab[kb0 + b4 < KB ? (it.d & 15u) : (uint32_t)kDialects][0]);
+    };
+    // of W the norm is taken from its codes only where K is long: with 0.5 % outlier channels x 50 on A the looser one is 2^22.5 units at
+    // K = 4096 and too much at 14336
+    const bool w_codes = KB > 192;
+    uint8_t* slot = &lds.x[kg][0][0] + (b4 >> 1) * 2048 + (b4 & 1) * 512;
+    auto expand = [&](const Item& it, int j, uint4 tab, int buf, int kb0) {
+        const int row = j * S::kItemRows + r4;
+        const uint32_t c4[4] = {it.c.x, it.c.y, it.c.z, it.c.w};
+        uint32_t v[8], s2 = 32 * 15 * 15;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[2 * k] = __builtin_amdgcn_perm(tab.y, tab.x, c4[k] & 0x07070707u) | ((c4[k] << 4) & 0x80808080u);
+            v[2 * k + 1] = __builtin_amdgcn_perm(tab.y, tab.x, (c4[k] >> 4) & 0x07070707u) | (c4[k] & 0x80808080u);
+        }
+        if (j < S::kItemsA || w_codes) {
+            s2 = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t ue = __builtin_amdgcn_perm(tab.w, tab.z, c4[k] & 0x07070707u), uo = __builtin_amdgcn_perm(tab.w, tab.z, (c4[k] >> 4) & 0x07070707u);
+                s2 = __builtin_amdgcn_udot4(ue, ue, __builtin_amdgcn_udot4(uo, uo, s2, false), false);
+            }
+        }
+        uint8_t* dst = slot + buf * (S::kRowGroups * 4096) + (row >> 5) * 4096 + ((row + 2 * b4) & 31) * 16;
+        *reinterpret_cast<uint4*>(dst) = make_uint4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(v[4], v[5], v[6], v[7]);
+        lds.sc[kg][buf][row][b4] = (uint8_t)it.e;
+        // 4^(e - 127) while e is in range (otherwise the tile is refused)
+        const bool some = kb0 + b4 < KB && ((it.c.x | it.c.y | it.c.z | it.c.w) & 0x77777777u) != 0;      // not an all-zero block
+        const float unit2 = __builtin_bit_cast(float, ((it.e << 1) - 127u) << 23);
+        sq[j] += some ? (float)s2 * unit2 : 0.0f;
+        ends[j] = __builtin_elementwise_max(ends[j], __builtin_bit_cast(v2u, (it.e << 16) | (some ? 255u - it.e : 0u)));
+    };
+    // the rows' norms over the 4 blocks' lanes; over the groups once all are there
+    auto row_norm = [&](float s, uint32_t lo, bool ok) {
+        const float v = lo == 255 ? 0.0f : ldexpf(s, 2 * (127 - (int)lo));
+        return ok ? v : __builtin_inff();
+    };
+    auto take_norm = [&](float v, int side) {
+        // (not negative: ordered like their bits)
+        int b = __builtin_bit_cast(int, v);
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) b = max(b, __shfl_xor(b, o));
+        if (lane == 0) atomicMax(&lds.norm[side], b);
+    };
+    auto finish_norms = [&] {
+#pragma unroll
+        for (int j = 0; j < S::kItems; ++j) {
+            float s = sq[j];
+            s += __builtin_bit_cast(float, quad_dpp<0xB1>(__builtin_bit_cast(int, s)));
+            s += __builtin_bit_cast(float, quad_dpp<0x4E>(__builtin_bit_cast(int, s)));
+            v2u e = ends[j];
+            e = __builtin_elementwise_max(e, __builtin_bit_cast(v2u, quad_dpp<0xB1>(__builtin_bit_cast(int, e))));
+            e = __builtin_elementwise_max(e, __builtin_bit_cast(v2u, quad_dpp<0x4E>(__builtin_bit_cast(int, e))));
+            const uint32_t lo = 255u - e.x, hi = e.y;
+            const bool ok = lo >= (uint32_t)kMinRef && (lo == 255 || lo <= (uint32_t)kMaxRef) && hi <= (uint32_t)kMaxRef + 20;
+            if constexpr (S::KG == 1) {
+                take_norm(row_norm(s, lo, ok), j < S::kItemsA ? 0 : 1);
+            } else {
+                const int row = j * S::kItemRows + r4;
+                if (b4 == 0) {
+                    lds.sq[kg][row] = s;
+                    lds.lo[kg][row] = (uint8_t)lo;
+                    lds.ok[kg][row] = ok ? 1 : 0;
+                }
+            }
+        }
+    };
+    struct Operands { v8i a[TI], b[TJ]; };                             // of a pair of blocks
+    struct Scales { int a[TI], b[TJ]; };                               // byte 0: of block h of the first pair, byte 2: of the second
+    auto read_scales = [&](Scales& o, int buf) {
+        const uint32_t* sc = reinterpret_cast<const uint32_t*>(&lds.sc[kg][buf][0][0]) + r;
+#pragma unroll
+        for (int i = 0; i < TI; ++i) o.a[i] = (int)(sc[(TI * wm + i) * 32] >> (8 * h));
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) o.b[j] = (int)(sc[S::kTm + (TJ * wn + j) * 32] >> (8 * h));
+    };
+    auto read = [&](Operands& o, int buf, int pr) {
+        const uint8_t* src = &lds.x[kg][buf][0] + pr * 2048 + h * 1024;
+        const int s0 = ((r + 4 * pr) & 31) * 16, s1 = 512 + ((r + 4 * pr + 2) & 31) * 16;
+        auto both = [&](int group) {
+            const v4i x = *reinterpret_cast<const v4i*>(src + group * 4096 + s0), y = *reinterpret_cast<const v4i*>(src + group * 4096 + s1);
+            return v8i{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+        };
+#pragma unroll
+        for (int i = 0; i < TI; ++i) o.a[i] = both(TI * wm + i);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) o.b[j] = both(S::kTm / 32 + TJ * wn + j);
+    };
+    auto multiply = [&](const Operands& o, const Scales& s, auto pr_c) {
+        constexpr int kByte = 2 * decltype(pr_c)::value;
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o.a[i], o.b[j], acc[i][j], 0, 0, kByte, s.a[i], kByte, s.b[j]);
+        // The operands are in use until here.  Where the sums change registers the compiler has let the result overlap an operand
+        // that it saw no further use of, which the instruction overwrites before it has read it for the last rows (the build checks).
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) asm volatile("" : "+v"(acc[i][j]) : "v"(o.a[i]), "v"(o.b[j]));
+    };
+    using First = std::integral_constant<int, 0>;
+    using Second = std::integral_constant<int, 1>;
+    if constexpr (S::kOnce) {
+        if (KB > 0) {
+#pragma unroll
+            for (int j = 0; j < S::kItems; ++j) expand(item[j], j, table(item[j], 0), 0, 0);
+        }
+        finish_norms();
+        __syncthreads();
+        if (KB > 0) {
+            Scales s;
+            read_scales(s, 0);
+            Operands o;
+            read(o, 0, 0);
+            multiply(o, s, First{});
+            if (KB > 2) {
+                read(o, 0, 1);
+                multiply(o, s, Second{});
+            }
+        }
+    } else if constexpr (S::kPrivate) {
+        // one wave: its LDS operations execute in order, so lanes exchange operands without a barrier; the fences keep
+        // the compiler to that order (they cost no instruction).  4 waves per SIMD hide the latencies
+        auto in_order = [] {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        for (int k = 0; k < per; k += 4) {
+            const int kb0 = k_lo + k;
+            if (kb0 >= KB) break;
+#pragma unroll
+            for (int j = 0; j < S::kItems; ++j) {
+                expand(item[j], j, table(item[j], kb0), 0, kb0);
+                load(item[j], j, kb0 + 4);
+            }
+            in_order();
+            Scales s;
+            read_scales(s, 0);
+            Operands o;
+            read(o, 0, 0);
+            multiply(o, s, First{});
+            read(o, 0, 1);
+            multiply(o, s, Second{});
+            in_order();
+        }
+        finish_norms();
+    } else if constexpr (S::kF8Bufs == 1) {
+        if (KB > 0) {
+            for (int k = 0; k < per; k += 4) {
+#pragma unroll
+                for (int j = 0; j < S::kItems; ++j) expand(item[j], j, table(item[j], k_lo + k), 0, k_lo + k);
+#pragma unroll
+                for (int j = 0; j < S::kItems; ++j) load(item[j], j, k_lo + k + 4);
+                __syncthreads();
+                Scales s;
+                read_scales(s, 0);
+                Operands o;
+                read(o, 0, 0);
+                multiply(o, s, First{});
+                read(o, 0, 1);
+                multiply(o, s, Second{});
+                __syncthreads();
+            }
+        }
+        finish_norms();
+    } else {
+        // One iteration: multiply the 4 blocks from kb0 (buffer BUF), expand the next 4 into the other buffer,
+        // load the 4 after those.  A wave issues the LDS reads of a pair's operands, expands while they are on
+        // their way, then multiplies.
+        auto iteration = [&](auto buf_c, int k) {
+            constexpr int kBuf = decltype(buf_c)::value, kNxt = 1 - kBuf, kHalf = S::kItems / 2;
+            const bool more = k + 4 < per;
+            Scales s;
+            read_scales(s, kBuf);
+            auto pair = [&](auto pr_c) {
+                constexpr int kPr = decltype(pr_c)::value;
+                constexpr int j_lo = kPr == 0 ? 0 : kHalf, j_hi = kPr == 0 ? kHalf : S::kItems;
+                uint4 tab[S::kItems];
+                if (more) {
+#pragma unroll
+                    for (int j = j_lo; j < j_hi; ++j) tab[j] = table(item[j], k_lo + k + 4);
+                }
+                Operands o;
+                read(o, kBuf, kPr);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) {
+#pragma unroll
+                    for (int j = j_lo; j < j_hi; ++j) {
+                        expand(item[j], j, tab[j], kNxt, k_lo + k + 4);
+                        load(item[j], j, k_lo + k + 8);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(o, s, pr_c);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            pair(First{});
+            pair(Second{});
+            __syncthreads();
+        };
+        if (KB > 0) {
+#pragma unroll
+            for (int j = 0; j < S::kItems; ++j) {
+                expand(item[j], j, table(item[j], k_lo), 0, k_lo);
+                load(item[j], j, k_lo + 4);
+            }
+            __syncthreads();
+            for (int k = 0; k < per; k += 8) {
+                iteration(std::integral_constant<int, 0>{}, k);
+                if (k + 4 >= per) break;
+                iteration(std::integral_constant<int, 1>{}, k + 4);
+            }
+        }
+        finish_norms();
+    }
+    if constexpr (!S::kOnce) __syncthreads();
+    if constexpr (S::KG > 1) {
+        for (int row = tid; row < (S::kRows + 63) / 64 * 64; row += S::kThreads) {       // whole waves
+            float v = 0.0f;
+            if (row < S::kRows) {
+                uint32_t lo = 255;
+                bool ok = true;
+#pragma unroll
+                for (int g = 0; g < S::KG; ++g) {
+                    lo = min(lo, (uint32_t)lds.lo[g][row]);
+                    ok = ok && lds.ok[g][row] != 0;
+                }
+                float s = 0.0f;
+#pragma unroll
+                for (int g = 0; g < S::KG; ++g) s += lds.sq[g][row];
+                v = row_norm(s, lo, ok);
+            }
+            static_assert(S::kTm % 32 == 0 && S::kTn % 32 == 0, "half a wave holds rows of one operand");
+            int b = __builtin_bit_cast(int, v);
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) b = max(b, __shfl_xor(b, o));
+            if ((lane & 31) == 0 && row < S::kRows) atomicMax(&lds.norm[row < S::kTm ? 0 : 1], b);
+        }
+        __syncthreads();
+    }
+    // the same for every thread
+    if (!(sqrtf(__builtin_bit_cast(float, lds.norm[0])) * sqrtf(__builtin_bit_cast(float, lds.norm[1])) <= kExactUnits)) {
+        __syncthreads();
+#pragma unroll 1
+        for (int i = 0; i < (S::kTm / F::kTm) * (S::kTn / F::kTn); ++i) {
+            int piece = i;
+            asm volatile("" : "+s"(piece));                            // nothing of a piece is kept in registers for the next
+            const int by = (int)blockIdx.y * (S::kTm / F::kTm) + piece / (S::kTn / F::kTn);
+            const int bx = (int)blockIdx.x * (S::kTn / F::kTn) + piece % (S::kTn / F::kTn);
+            if (by * F::kTm >= p.M || bx * F::kTn >= p.N) continue;
+            int8_tile<MX, BF16, F>(p, u.again, bz, by, bx);
+            __syncthreads();
+        }
+        return;
+    }
+
+    // ---- results
+    constexpr int kEsz = BF16 ? 2 : 4;
+    const int row0 = m0 + wm * 32 * TI, col0 = n0 + wn * 32 * TJ;      // of this wave
+    if constexpr (S::KG > 1) {
+        // the groups' exact partial sums, added through LDS; group kg finishes its share of the tile's outputs
+        constexpr int kOut = TI * TJ * 16, kShare = kOut / S::KG;
+        static_assert(sizeof(float) * S::KG * S::WM * S::WN * kOut * 64 <= sizeof(lds.x), "partial tiles reuse the operands");
+        float* red = reinterpret_cast<float*>(&lds.x[0][0][0]);
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int x = 0; x < 16; ++x)
+                    red[((kg * S::WM * S::WN + wave) * kOut + (i * TJ + j) * 16 + x) * 64 + lane] = acc[i][j][x];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kShare; ++q) {
+            const int o = kg * kShare + q, i = o / (16 * TJ), j = o / 16 % TJ, x = o % 16;
+            float sum = 0.0f;
+#pragma unroll
+            for (int g = 0; g < S::KG; ++g) sum += red[((g * S::WM * S::WN + wave) * kOut + o) * 64 + lane];
+            const int lr = 32 * i + 8 * (x >> 2) + 4 * h + (x & 3), lc = 32 * j + r;
+            if (row0 + lr < p.M && col0 + lc < p.N) {
+                const int64_t at = bz * p.strideC + (int64_t)(row0 + lr) * p.ldc + col0 + lc;
+                if constexpr (BF16) static_cast<uint16_t*>(p.out)[at] = f32_to_bf16_rne(sum);
+                else static_cast<float*>(p.out)[at] = sum;
+            }
+        }
+    } else {
+        if (row0 >= p.M || col0 >= p.N) return;
+        uint8_t* wave_out = static_cast<uint8_t*>(p.out) + (bz * p.strideC + (int64_t)row0 * p.ldc + col0) * kEsz;
+        const int64_t row_bytes = p.ldc * kEsz;
+        const bool full = row0 + 32 * TI <= p.M && col0 + 32 * TJ <= p.N;
+        // bf16: every lane stores two adjacent columns of one row (as in gemm_native_kernel)
+        const bool pairs = BF16 && full && (p.ldc & 1) == 0 && ((p.strideC * kEsz) & 3) == 0 &&
+                           (reinterpret_cast<uintptr_t>(p.out) & 3) == 0;
+        const uint32_t lane_off = pairs ? (uint32_t)((4 * h + (r & 1)) * row_bytes + (r & ~1) * kEsz)
+                                        : (uint32_t)(4 * h * row_bytes + r * kEsz);
+        auto store = [&](auto full_c, auto pairs_c) {
+            constexpr bool kFull = decltype(full_c)::value, kPairs = decltype(pairs_c)::value;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) {
+                    uint8_t* tile_out = wave_out + (int64_t)i * 32 * row_bytes + j * 32 * kEsz;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        uint8_t* rowp = tile_out + (int64_t)(8 * q) * row_bytes;
+                        if constexpr (kPairs) {
+#pragma unroll
+                            for (int x = 0; x < 4; x += 2) {
+                                const uint32_t b0 = f32_to_bf16_rne(acc[i][j][4 * q + x]), b1 = f32_to_bf16_rne(acc[i][j][4 * q + x + 1]);
+                                const uint32_t send = (r & 1) ? b0 : b1;
+                                const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xf, 0xf, true);
+                                const uint32_t word = (r & 1) ? (recv | (b1 << 16)) : (b0 | (recv << 16));
+                                DFP4_OUT_STORE(reinterpret_cast<uint32_t*>(rowp + (int64_t)x * row_bytes + lane_off), word);
+                            }
+                        } else {
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) {
+                                if (kFull || (row0 + i * 32 + 8 * q + 4 * h + x < p.M && col0 + j * 32 + r < p.N)) {
+                                    uint8_t* dst = rowp + (int64_t)x * row_bytes + lane_off;
+                                    if constexpr (BF16) DFP4_OUT_STORE(reinterpret_cast<uint16_t*>(dst), f32_to_bf16_rne(acc[i][j][4 * q + x]));
+                                    else DFP4_OUT_STORE(reinterpret_cast<float*>(dst), acc[i][j][4 * q + x]);
+                                }
+                            }
+                        }
+                    }
+                }
+        };
+        if (BF16 && pairs) store(std::true_type{}, std::integral_constant<bool, BF16>{});
+        else if (full) store(std::true_type{}, std::false_type{});
+        else store(std::false_type{}, std::false_type{});
+    }
+}
+
+template <class S, class F = S>
+int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
+    dim3 g((unsigned)((p.N + S::kTn - 1) / S::kTn), (unsigned)((p.M + S::kTm - 1) / S::kTm), (unsigned)batch);
+    dispatch_mx_bf16(mx, bf16, [&](auto mxc, auto bc) {
+        hipLaunchKernelGGL((gemm_f8_kernel<decltype(mxc)::value, decltype(bc)::value, S, F>), g, dim3(S::kThreads), 0, stream, p);
+    });
+    return check_launch();
+}
+
+}  // namespace
+
+// shapes: those of gemm_direct_kernel
+int launch_gemm_f8(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream) {
+    switch (shape) {
+        case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);
+        case 1: return launch<DirectShape<1, 1, 2, 2, 4>>(mx, bf16, p, batch, stream);
+        case 2: return launch<DirectShape<1, 1, 2, 2, 2>>(mx, bf16, p, batch, stream);
+        case 3: return launch<DirectShape<2, 2, 2, 2, 2>, DirectShape<1, 1, 2, 2, 2>>(mx, bf16, p, batch, stream);
+        case 4: return launch<DirectShape<2, 2, 2, 2, 1>, DirectShape<1, 1, 2, 2, 1>>(mx, bf16, p, batch, stream);
+        case 5: return launch<DirectShape<2, 2, 4, 2, 1>, DirectShape<1, 1, 2, 2, 2>>(mx, bf16, p, batch, stream);
+        default: return launch<DirectShape<2, 2, 2, 2, 1, true>, DirectShape<1, 1, 2, 2, 1, true>>(mx, bf16, p, batch, stream);
+    }
+}
+
+}  // namespace dfp4

@@ -46,6 +46,9 @@ struct DirectShape {
     static constexpr bool kPrivate = WM * WN == 1;                     // the group is one wave: no barrier in the loop
     static constexpr int kBufs = kPrivate || kOnce ? 1 : 2;
     static constexpr int kWavesPerSimd = TI * TJ == 1 ? 4 : kOnce ? 3 : 2;         // what the registers allow
+    // of gemm_f8_kernel
+    static constexpr int kF8Bufs = kBufs;
+    static constexpr int kF8Waves = TI * TJ == 1 ? 4 : kOnce ? 3 : 2;
     static constexpr int scan_parts() {                                // threads that look for a row's smallest exponent
         int p = 1;
         while (p * 2 * kRows <= kThreads && p < 16) p *= 2;
@@ -82,7 +85,7 @@ __device__ __forceinline__ int block_weight(uint32_t ma, uint32_t mw) {
 template <class S>
 union TileLds {
     DirectLds<S> d;
-    SmallTileLds small;                                                // declined tiles
+    SmallTileLds<S::kThreads / 64, S::kOnce ? kDirectOnceBlocks : kSmallMaxKB> small;      // declined tiles
 };
 
 // The tile (by, bx) of problem bz, by the S::kThreads threads of a workgroup; `u` is theirs alone, and a barrier lies between two calls
@@ -293,7 +296,7 @@ __device__ __forceinline__ void int8_tile(const GemmParams& p, TileLds<S>& u, in
             for (int i = 0; i < S::kTm / 32; ++i)
                 for (int j = 0; j < S::kTn / 32; ++j) {
                     if (m0 + 32 * i >= p.M || n0 + 32 * j >= p.N) continue;
-                    small_tile<MX, BF16, S::kThreads / 64>(p, bz, m0 + 32 * i, n0 + 32 * j, u.small);
+                    small_tile<MX, BF16>(p, bz, m0 + 32 * i, n0 + 32 * j, u.small);
                     __syncthreads();
                 }
         }
