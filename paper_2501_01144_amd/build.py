@@ -1,4 +1,5 @@
-"""Build libdfp4.so (HIP kernels + C ABI) in-tree with hipcc for gfx950, and the two
+"""Build libdfp4.so (HIP kernels + C ABI) in-tree with hipcc for gfx950, the native module of the Python binding
+(_binding.so, against the installed torch), and the
 measurement helpers of bench.py (bench_helpers/ at the repository root).
 
     python -m paper_2501_01144_amd.build
@@ -10,11 +11,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfp4.so")
+BINDING = os.path.join(HERE, "_binding.so")
 HELPERS = os.path.join(ROOT, "bench_helpers")
 SOURCES = ["api.hip", "quantize.hip", "dequantize.hip", "gemm.hip", "gemm_direct.hip", "gemm_f8.hip", "gemm_native.hip"]
 FLAGS = [
@@ -149,6 +152,19 @@ def build_library(verbose=True):
     f8_s = os.path.join(objdir, "gemm_f8.s")
     cmd = [hipcc, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "gemm_f8.hip"), "-o", f8_s]
     procs.append(("gemm_f8.hip (assembly)", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    # native module of the Python binding: host code only
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc)))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-unused-result", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{d}" for d in (os.path.join(troot, "include"), os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+                                      sysconfig.get_paths()["include"], os.path.join(rocm, "include"))),
+           os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + os.path.join(troot, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ldl"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append(("binding.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     # measurement helpers used by bench.py: register-only int8 MFMA loops, plain streaming kernels
     for name in ("mfma_peak", "stream_peak", "mfma_shadow"):
         cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Wno-inline-asm", os.path.join(HELPERS, name + ".hip"),

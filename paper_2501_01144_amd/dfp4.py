@@ -1,7 +1,9 @@
-"""ctypes binding of libdfp4.so: the same calls as include/dfp4.h, taking torch
-tensors for device memory and the current torch stream.  Argument marshalling
-only: every step of the path runs in the HIP kernels.  There is no fallback;
-if the library is missing or a call fails, an exception is raised.
+"""Binding of libdfp4.so: the same calls as include/dfp4.h, taking torch tensors for device
+memory and the current torch stream.  Argument marshalling only: every step of the path runs in
+the HIP kernels.  Calls that allocate their result go through the native module _binding
+(csrc/binding.cpp), which allocates and calls at once; calls into buffers of the caller's and the
+rarer entry points go through ctypes.  There is no fallback; if a library is missing or a call
+fails, an exception is raised.
 """
 import ctypes
 import os
@@ -13,6 +15,7 @@ BLOCK = 32
 F32, BF16 = 0, 1
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdfp4.so")
 _lib = None
+_native = None                   # the module _binding, bound to the library
 
 
 class Dfp4Error(RuntimeError):
@@ -43,7 +46,7 @@ def lib_path():
 
 def load():
     """Load libdfp4.so (built by `python -m paper_2501_01144_amd.build`)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -123,8 +126,28 @@ def load():
     for name in ("dfp4_quantize", "dfp4_quantize_b64", "dfp4_quantize_mse", "dfp4_quantize_t", "mxfp4_quantize_t", "mxfp4_quantize", "dfp4_dequantize", "mxfp4_dequantize", "dfp4_gemm",
                  "mxfp4_gemm", "dfp4_gemm_batched", "dfp4_formatbook"):
         getattr(lib, name).restype = ci
-    _lib = lib
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise Dfp4Error("paper_2501_01144_amd/_binding.so not found: build it with `python -m paper_2501_01144_amd.build`") from e
+    _binding.bind(_LIB_PATH, Dfp4Error)
+    _lib, _native = lib, _binding
     return lib
+
+
+def _calls():
+    if _native is None:
+        load()
+    return _native
+
+
+def _is_bf16(dtype):
+    assert dtype in (torch.float32, torch.bfloat16)
+    return dtype is torch.bfloat16
+
+
+def _five(q):
+    return q.codes, q.dialect, q.exponent, q.rows, q.K
 
 
 def strerror(code):
@@ -178,6 +201,8 @@ def _quantize(fn, what, x, out, mx):
 
 def quantize(x, out=None):
     """dfp4_quantize: bf16 [rows, K] (row stride allowed) -> QTensor."""
+    if out is None:
+        return QTensor(*_calls().quantize(x, 32, False))
     return _quantize(load().dfp4_quantize, "dfp4_quantize", x, out, False)
 
 
@@ -188,13 +213,10 @@ def quantize_b64(x, out=None):
 
 def quantize_block(x, block, out=None):
     """dfp4_quantize_block: block size 16, 32 or 64.  Blocks of 16 carry dialect / exponent arrays [rows, K/16]."""
+    if out is None:
+        return QTensor(*_calls().quantize(x, block, False))
     assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda and x.stride(1) == 1
     rows, K = x.shape
-    if out is None:
-        out = empty_qtensor(rows, K, x.device)
-        if block == 16:
-            out.dialect = torch.empty((rows, K // 16), dtype=torch.uint8, device=x.device)
-            out.exponent = torch.empty((rows, K // 16), dtype=torch.uint8, device=x.device)
     ld = x.stride(0) if rows > 1 else K
     _check(load().dfp4_quantize_block(_ptr(x), rows, K, ld, block, out.c(), _stream()), "dfp4_quantize_block")
     return out
@@ -256,6 +278,8 @@ def mxfp4_quantize_t(x, out=None):
 
 
 def mxfp4_quantize(x, out=None):
+    if out is None:
+        return QTensor(*_calls().quantize(x, 32, True))
     return _quantize(load().mxfp4_quantize, "mxfp4_quantize", x, out, True)
 
 
@@ -269,10 +293,14 @@ def _dequantize(fn, what, q, dtype, out):
 
 
 def dequantize(q, dtype=torch.float32, out=None):
+    if out is None:
+        return _calls().dequantize(*_five(q), _is_bf16(dtype), False)
     return _dequantize(load().dfp4_dequantize, "dfp4_dequantize", q, dtype, out)
 
 
 def mxfp4_dequantize(q, dtype=torch.float32, out=None):
+    if out is None:
+        return _calls().dequantize(*_five(q), _is_bf16(dtype), True)
     return _dequantize(load().mxfp4_dequantize, "mxfp4_dequantize", q, dtype, out)
 
 
@@ -300,6 +328,8 @@ def _gemm(fn, what, a, w, dtype, out, workspace):
 
 def gemm(a, w, dtype=torch.float32, out=None, workspace=None):
     """dfp4_gemm: out[M, N] = A[M, K] * W[N, K]^T on quantized operands."""
+    if out is None and workspace is None:
+        return _calls().gemm(*_five(a), *_five(w), _is_bf16(dtype), False)
     return _gemm(load().dfp4_gemm, "dfp4_gemm", a, w, dtype, out, workspace)
 
 
@@ -314,11 +344,11 @@ class PreparedOperand:
 
 def gemm_prepare(q, weight, mx=False, buf=None):
     """dfp4_gemm_prepare / mxfp4_gemm_prepare: the per-operand work of the GEMM, done once."""
+    if buf is None:
+        return PreparedOperand(q, _calls().gemm_prepare(*_five(q), bool(weight), bool(mx)), weight, mx)
     need = int(load().dfp4_gemm_prepared_bytes(q.rows, q.K, 1 if weight else 0))
     if need == 0:
         return PreparedOperand(q, None, weight, mx)
-    if buf is None:
-        buf = torch.empty(need, dtype=torch.uint8, device=q.codes.device)
     fn = load().mxfp4_gemm_prepare if mx else load().dfp4_gemm_prepare
     _check(fn(q.c(), 1 if weight else 0, _ptr(buf), buf.numel(), _stream()), "gemm_prepare")
     return PreparedOperand(q, buf, weight, mx)
@@ -327,6 +357,8 @@ def gemm_prepare(q, weight, mx=False, buf=None):
 def gemm_prepared(a, w, dtype=torch.float32, out=None, workspace=None):
     """dfp4_gemm_prepared / mxfp4_gemm_prepared: a, w are PreparedOperands."""
     assert not a.weight and w.weight and a.mx == w.mx
+    if out is None and workspace is None:
+        return _calls().gemm_prepared(*_five(a.q), a.buf, *_five(w.q), w.buf, _is_bf16(dtype), bool(a.mx))
     if out is None:
         out = torch.empty((a.q.rows, w.q.rows), dtype=dtype, device=a.q.codes.device)
     assert out.dtype in (torch.float32, torch.bfloat16) and out.stride(1) == 1
@@ -366,6 +398,8 @@ def gemm_noalloc(a, w, out):
 
 
 def mxfp4_gemm(a, w, dtype=torch.float32, out=None, workspace=None):
+    if out is None and workspace is None:
+        return _calls().gemm(*_five(a), *_five(w), _is_bf16(dtype), True)
     return _gemm(load().mxfp4_gemm, "mxfp4_gemm", a, w, dtype, out, workspace)
 
 
@@ -437,9 +471,8 @@ class PackedWeights:
 
 def native_pack(w, mx=False, buf=None):
     """dfp4_native_pack / mxfp4_native_pack: pack a quantized tensor (weights: once)."""
-    n = int(load().dfp4_native_packed_bytes(w.rows, w.K))
     if buf is None:
-        buf = torch.empty(max(n, 256), dtype=torch.uint8, device=w.codes.device)
+        return PackedWeights(_calls().native_pack(*_five(w), bool(mx)), w.rows, w.K, mx)
     fn = load().mxfp4_native_pack if mx else load().dfp4_native_pack
     _check(fn(w.c(), _ptr(buf), buf.numel(), _stream()), "native_pack")
     return PackedWeights(buf, w.rows, w.K, mx)
@@ -447,12 +480,12 @@ def native_pack(w, mx=False, buf=None):
 
 def quantize_native(x, buf=None):
     """dfp4_quantize_native: bf16 [rows, K] -> packed FP6 operand of the block-scaled matrix instruction."""
+    if buf is None and x.numel() > 0:
+        return PackedWeights(_calls().quantize_native(x), *x.shape, False)
     assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda and x.stride(1) == 1
     rows, K = x.shape
-    n = int(load().dfp4_native_packed_bytes(rows, K))
     if buf is None:
-        buf = torch.empty(n, dtype=torch.uint8, device=x.device) if n else \
-            torch.zeros(256, dtype=torch.uint8, device=x.device)
+        buf = torch.zeros(256, dtype=torch.uint8, device=x.device)
     ld = x.stride(0) if rows > 1 else K
     _check(load().dfp4_quantize_native(_ptr(x), rows, K, ld, _ptr(buf), buf.numel(), _stream()), "dfp4_quantize_native")
     return PackedWeights(buf, rows, K, False)
@@ -476,6 +509,9 @@ def gemm_native_packed_w(a, wp, dtype=torch.float32, out=None, workspace=None):
 
 def gemm_native_packed(ap, wp, dtype=torch.float32, out=None, workspace=None):
     """dfp4_gemm_native_packed / mxfp4_gemm_native_packed: both operands packed beforehand."""
+    if out is None and workspace is None:
+        assert ap.K == wp.K and ap.mx == wp.mx
+        return _calls().gemm_native_packed(ap.buf, ap.rows, wp.buf, wp.rows, ap.K, _is_bf16(dtype), bool(wp.mx))
     if out is None:
         out = torch.empty((ap.rows, wp.rows), dtype=dtype, device=ap.buf.device)
     need = int(load().dfp4_gemm_native_splitk_bytes(ap.rows, wp.rows, ap.K))
@@ -493,6 +529,8 @@ def gemm_native_packed(ap, wp, dtype=torch.float32, out=None, workspace=None):
 def gemm_batched(a, w, batch, M, N, dtype=torch.float32, out=None, workspace=None):
     """dfp4_gemm_batched: a holds batch*M rows, w batch*N rows (problem after problem);
     out [batch, M, N]."""
+    if out is None and workspace is None:
+        return _calls().gemm_batched(*_five(a), *_five(w), batch, M, N, _is_bf16(dtype))
     if out is None:
         out = torch.empty((batch, M, N), dtype=dtype, device=a.codes.device)
     assert out.is_contiguous()
