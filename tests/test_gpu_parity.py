@@ -1555,3 +1555,19 @@ def test_gemm_large_exact_sums(M, N, K, prepared, kind):
     assert bool(((out.double() - ref).abs() <= (ref.abs() * 2.0 ** -24).clamp_min(2.0 ** -149)).all())
     if kind == "all zero":
         assert not bool(out.view(torch.int32).any())                  # +0
+
+
+@pytest.mark.parametrize("rows,K", [(32768, 4096), (32767, 4096), (4101, 32736)])     # 2^22 blocks, below, and more in a ragged shape
+@pytest.mark.parametrize("mx", [False, True])
+def test_quantize_large_tensors_like_their_parts(rows, K, mx):
+    # tensors larger than the last cache are streamed past the caches; their parts, quantized alone, are not
+    print(f"quantize streamed: {rows}x{K}, mx {mx}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn(rows, K, generator=g, device="cuda", dtype=torch.bfloat16)
+    quant = dfp4.mxfp4_quantize if mx else dfp4.quantize
+    q = quant(x)
+    for lo in list(range(0, rows, rows // 7)) + [rows - 5]:
+        hi = min(rows, lo + 512)
+        part = quant(x[lo:hi])
+        assert torch.equal(q.codes[lo:hi], part.codes) and torch.equal(q.exponent[lo:hi], part.exponent)
+        assert mx or torch.equal(q.dialect[lo:hi], part.dialect)
