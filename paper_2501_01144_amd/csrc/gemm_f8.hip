@@ -56,6 +56,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 // References (exponent bytes of nonzero blocks) outside this range are left to int32: see gemm_native.hip
 constexpr int kMinRef = 66, kMaxRef = 178;
+constexpr int kMaxExp = 190;          // of any block: 4^(e - 127) is built as a float, and 2 e - 127 is its exponent byte
 constexpr float kExactUnits = 16777216.0f * 0.9998f;
 
 template <class S>
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
             e = __builtin_elementwise_max(e, __builtin_bit_cast(v2u, quad_dpp<0xB1>(__builtin_bit_cast(int, e))));
             e = __builtin_elementwise_max(e, __builtin_bit_cast(v2u, quad_dpp<0x4E>(__builtin_bit_cast(int, e))));
             const uint32_t lo = 255u - e.x, hi = e.y;
-            const bool ok = lo >= (uint32_t)kMinRef && (lo == 255 || lo <= (uint32_t)kMaxRef) && hi <= (uint32_t)kMaxRef + 20;
+            const bool ok = lo >= (uint32_t)kMinRef && (lo == 255 || lo <= (uint32_t)kMaxRef) && hi <= (uint32_t)kMaxExp;
             if constexpr (S::KG == 1) {
                 take_norm(row_norm(s, lo, ok), j < S::kItemsA ? 0 : 1);
             } else {

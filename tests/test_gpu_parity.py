@@ -1514,15 +1514,17 @@ def test_gemm_prepared_and_plain_agree_across_kernels():
 
 
 # --------------------------------------------------------------------------
-# Large products sum in fp32 where norms of the rows show that no partial sum rounds, in int32 elsewhere: inputs on either side
-# of that rule.  Both are exact, so the bound is one rounding of the float64 product (2^-24; 2^-149 where that is subnormal).
+# Products sum in fp32 where norms of the rows show that no partial sum rounds, in int32 elsewhere: inputs on either side
+# of that rule, in the large kernel and in every shape of the one that expands its operands.  Both are exact, so the bound is one rounding of the float64 product (2^-24; 2^-149 where that is subnormal).
 # --------------------------------------------------------------------------
-@pytest.mark.parametrize("M,N,K,prepared", [(1552, 5664, 160, True), (518, 6686, 2848, True), (2320, 5408, 448, False),
-                                            (845, 2333, 11104, False)])
+@pytest.mark.parametrize("M,N,K,prepared,path", [
+    (1552, 5664, 160, True, 0), (518, 6686, 2848, True, 0), (2320, 5408, 448, False, 0), (845, 2333, 11104, False, 0),
+    (31, 1000, 4128, False, 1), (36, 7898, 1344, True, 2), (190, 2000, 512, True, 3), (777, 3001, 2080, False, 4),
+    (652, 3397, 544, False, 5), (1500, 4000, 1120, False, 6), (1000, 2049, 96, False, 7)])
 @pytest.mark.parametrize("kind", ["plain", "outliers", "massive", "zero blocks", "tiny", "huge", "spread rows", "all zero"])
-def test_gemm_large_exact_sums(M, N, K, prepared, kind):
-    assert dfp4.gemm_path(M, N, K, prepared=prepared) == 0
-    print(f"gemm large, exact sums: {M}x{N}x{K}, prepared {prepared}, {kind}", flush=True)
+def test_gemm_exact_sums(M, N, K, prepared, path, kind):
+    assert dfp4.gemm_path(M, N, K, prepared=prepared) == path
+    print(f"gemm, exact sums: {M}x{N}x{K}, prepared {prepared}, {kind}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(K + len(kind))
     a, w = torch.randn(M, K, generator=g, device="cuda"), torch.randn(N, K, generator=g, device="cuda") * 0.02
     if kind == "outliers":                                            # channels on both operands
@@ -1555,6 +1557,28 @@ def test_gemm_large_exact_sums(M, N, K, prepared, kind):
     assert bool(((out.double() - ref).abs() <= (ref.abs() * 2.0 ** -24).clamp_min(2.0 ** -149)).all())
     if kind == "all zero":
         assert not bool(out.view(torch.int32).any())                  # +0
+
+
+@pytest.mark.parametrize("top", [190, 191, 193, 198, 199])
+def test_gemm_few_rows_high_exponents(top):
+    # One block 18 binades or more above the rest of its row: too far for fp32 sums and for int32, whatever its exponent byte
+    # (from 191 on its square is no float), so the tiles are counted as declined.
+    M, N, K = 40, 200, 512
+    print(f"few rows, exponent byte {top}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(top)
+    a = torch.randn(M, K // 32, 32, generator=g, device="cuda").clamp(-3.9, 3.9)
+    a[:, :, 3] = 4.5                                                  # exponent byte 127
+    a[7] *= 2.0 ** 45                                                 # 172
+    a[7, 5] *= 2.0 ** (top - 172)
+    w = torch.randn(N, K, generator=g, device="cuda") * 0.02
+    qa, qw = dfp4.quantize(a.view(M, K).to(torch.bfloat16)), dfp4.quantize(w.to(torch.bfloat16))
+    assert qa.exponent[7, 5] == top and qa.exponent[7, 4] == 172
+    pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
+    da, dw = dfp4.dequantize(qa).double(), dfp4.dequantize(qw).double()
+    out = dfp4.gemm_prepared(pa, pw)
+    torch.cuda.synchronize()
+    assert bool(((out.double() - da @ dw.T).abs() <= GEMM_RTOL * (da.abs() @ dw.abs().T)).all())
+    assert dfp4.gemm_declined_tiles(pa) > 0
 
 
 @pytest.mark.parametrize("rows,K", [(32768, 4096), (32767, 4096), (4101, 32736)])     # 2^22 blocks, below, and more in a ragged shape
