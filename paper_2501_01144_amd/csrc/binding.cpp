@@ -32,7 +32,20 @@ struct Failure {};                    // a Python exception is set
     throw Failure{};
 }
 
-void check(int rc, const char* what) {
+// Other Python threads run while memory is allocated (which may wait for the GPU) and while kernels are enqueued (a full queue waits)
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// an entry point of the library
+template <class F, class... A>
+void enqueue(const char* what, F* entry, A... a) {
+    int rc;
+    {
+        Unlocked u;
+        rc = entry(a...);
+    }
     if (rc == DFP4_OK) return;
     PyErr_Format(g_error, "%s failed: %s (%d)", what, p_dfp4_strerror(rc), rc);
     throw Failure{};
@@ -51,11 +64,15 @@ uint8_t* data(const at::Tensor& t) { return t.numel() > 0 ? static_cast<uint8_t*
 uint8_t* data(PyObject* o) { return o == Py_None ? nullptr : data(tensor(o)); }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-at::Tensor bytes(int64_t n, const at::Device& dev) { return at::empty({n}, at::TensorOptions().dtype(at::kByte).device(dev)); }
-at::Tensor bytes(int64_t r, int64_t c, const at::Device& dev) { return at::empty({r, c}, at::TensorOptions().dtype(at::kByte).device(dev)); }
-at::Tensor result(at::IntArrayRef shape, bool bf16, const at::Device& dev) {
-    return at::empty(shape, at::TensorOptions().dtype(bf16 ? at::kBFloat16 : at::kFloat).device(dev));
+at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Device& dev) {
+    Unlocked u;
+    return at::empty(shape, at::TensorOptions().dtype(type).device(dev));
 }
+at::Tensor bytes(int64_t n, const at::Device& dev) { return empty({n}, at::kByte, dev); }
+at::Tensor bytes(int64_t r, int64_t c, const at::Device& dev) { return empty({r, c}, at::kByte, dev); }
+at::Tensor result(at::IntArrayRef shape, bool bf16, const at::Device& dev) { return empty(shape, bf16 ? at::kBFloat16 : at::kFloat, dev); }
+
+int dtype(bool bf16) { return bf16 ? DFP4_BF16 : DFP4_F32; }
 
 // codes, dialect, exponent, rows, K
 dfp4_tensor quantized(PyObject* const* a) {
@@ -95,9 +112,9 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (!mx) dialect = bytes(rows, K / per, dev);
         const dfp4_tensor q{data(codes), mx ? nullptr : data(dialect), data(exponent), rows, K};
         const int64_t ld = rows > 1 ? x.stride(0) : K;
-        if (mx) check(p_mxfp4_quantize(data(x), rows, K, ld, q, stream()), "mxfp4_quantize");
-        else if (block == 32) check(p_dfp4_quantize(data(x), rows, K, ld, q, stream()), "dfp4_quantize");
-        else check(p_dfp4_quantize_block(data(x), rows, K, ld, (int)block, q, stream()), "dfp4_quantize_block");
+        if (mx) enqueue("mxfp4_quantize", p_mxfp4_quantize, data(x), rows, K, ld, q, stream());
+        else if (block == 32) enqueue("dfp4_quantize", p_dfp4_quantize, data(x), rows, K, ld, q, stream());
+        else enqueue("dfp4_quantize_block", p_dfp4_quantize_block, data(x), rows, K, ld, (int)block, q, stream());
         PyObject* d = mx ? Py_NewRef(Py_None) : THPVariable_Wrap(std::move(dialect));
         return Py_BuildValue("NNNLL", THPVariable_Wrap(std::move(codes)), d, THPVariable_Wrap(std::move(exponent)), (long long)rows, (long long)K);
     });
@@ -109,8 +126,7 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const dfp4_tensor q = quantized(a);
         const bool bf16 = a[5] == Py_True, mx = a[6] == Py_True;
         at::Tensor y = result({q.rows, q.K}, bf16, tensor(a[0]).device());
-        check((mx ? p_mxfp4_dequantize : p_dfp4_dequantize)(q, data(y), bf16 ? DFP4_BF16 : DFP4_F32, q.K, stream()),
-              mx ? "mxfp4_dequantize" : "dfp4_dequantize");
+        enqueue(mx ? "mxfp4_dequantize" : "dfp4_dequantize", mx ? p_mxfp4_dequantize : p_dfp4_dequantize, q, data(y), dtype(bf16), q.K, stream());
         return THPVariable_Wrap(std::move(y));
     });
 }
@@ -124,8 +140,8 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor out = result({A.rows, W.rows}, bf16, dev), ws;
         const size_t need = p_dfp4_gemm_workspace_bytes(A.rows, W.rows, A.K);
         if (need > 0) ws = bytes((int64_t)need, dev);
-        check((mx ? p_mxfp4_gemm : p_dfp4_gemm)(A, W, data(out), bf16 ? DFP4_BF16 : DFP4_F32, W.rows, need > 0 ? data(ws) : nullptr, need, stream()),
-              mx ? "mxfp4_gemm" : "dfp4_gemm");
+        enqueue(mx ? "mxfp4_gemm" : "dfp4_gemm", mx ? p_mxfp4_gemm : p_dfp4_gemm, A, W, data(out), dtype(bf16), W.rows, need > 0 ? data(ws) : nullptr, need,
+                stream());
         return THPVariable_Wrap(std::move(out));
     });
 }
@@ -142,8 +158,8 @@ PyObject* gemm_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor out = result({batch, M, N}, bf16, dev), ws;
         const size_t need = p_dfp4_gemm_workspace_bytes(M, N, A.K) * (size_t)batch;
         if (need > 0) ws = bytes((int64_t)need, dev);
-        check(p_dfp4_gemm_batched(A, W, data(out), bf16 ? DFP4_BF16 : DFP4_F32, N, batch, M, N, M * N, need > 0 ? data(ws) : nullptr, need, stream()),
-              "dfp4_gemm_batched");
+        enqueue("dfp4_gemm_batched", p_dfp4_gemm_batched, A, W, data(out), dtype(bf16), N, batch, M, N, M * N, need > 0 ? data(ws) : nullptr, need,
+                stream());
         return THPVariable_Wrap(std::move(out));
     });
 }
@@ -156,7 +172,7 @@ PyObject* gemm_prepare(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const size_t need = p_dfp4_gemm_prepared_bytes(q.rows, q.K, weight);
         if (need == 0) Py_RETURN_NONE;
         at::Tensor buf = bytes((int64_t)need, tensor(a[0]).device());
-        check((a[6] == Py_True ? p_mxfp4_gemm_prepare : p_dfp4_gemm_prepare)(q, weight, data(buf), need, stream()), "gemm_prepare");
+        enqueue("gemm_prepare", a[6] == Py_True ? p_mxfp4_gemm_prepare : p_dfp4_gemm_prepare, q, weight, data(buf), need, stream());
         return THPVariable_Wrap(std::move(buf));
     });
 }
@@ -170,8 +186,8 @@ PyObject* gemm_prepared(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor out = result({A.rows, W.rows}, bf16, dev), ws;
         const size_t need = p_dfp4_gemm_prepared_workspace_bytes(A.rows, W.rows, A.K);
         if (need > 0) ws = bytes((int64_t)need, dev);
-        check((mx ? p_mxfp4_gemm_prepared : p_dfp4_gemm_prepared)(A, data(a[5]), W, data(a[11]), data(out), bf16 ? DFP4_BF16 : DFP4_F32, W.rows,
-                                                                  need > 0 ? data(ws) : nullptr, need, stream()), "gemm_prepared");
+        enqueue("gemm_prepared", mx ? p_mxfp4_gemm_prepared : p_dfp4_gemm_prepared, A, data(a[5]), W, data(a[11]), data(out), dtype(bf16), W.rows,
+                need > 0 ? data(ws) : nullptr, need, stream());
         return THPVariable_Wrap(std::move(out));
     });
 }
@@ -182,7 +198,7 @@ PyObject* quantize_native(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& x = dense(a[0]);
         const int64_t rows = x.size(0), K = x.size(1);
         at::Tensor buf = bytes((int64_t)p_dfp4_native_packed_bytes(rows, K), x.device());
-        check(p_dfp4_quantize_native(data(x), rows, K, rows > 1 ? x.stride(0) : K, data(buf), (size_t)buf.numel(), stream()), "dfp4_quantize_native");
+        enqueue("dfp4_quantize_native", p_dfp4_quantize_native, data(x), rows, K, rows > 1 ? x.stride(0) : K, data(buf), (size_t)buf.numel(), stream());
         return THPVariable_Wrap(std::move(buf));
     });
 }
@@ -193,7 +209,7 @@ PyObject* native_pack(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const dfp4_tensor q = quantized(a);
         const int64_t need = (int64_t)p_dfp4_native_packed_bytes(q.rows, q.K);
         at::Tensor buf = bytes(need > 256 ? need : 256, tensor(a[0]).device());
-        check((a[5] == Py_True ? p_mxfp4_native_pack : p_dfp4_native_pack)(q, data(buf), (size_t)buf.numel(), stream()), "native_pack");
+        enqueue("native_pack", a[5] == Py_True ? p_mxfp4_native_pack : p_dfp4_native_pack, q, data(buf), (size_t)buf.numel(), stream());
         return THPVariable_Wrap(std::move(buf));
     });
 }
@@ -207,8 +223,8 @@ PyObject* gemm_native_packed(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor out = result({M, N}, bf16, dev), ws;
         const size_t need = p_dfp4_gemm_native_splitk_bytes(M, N, K);
         if (need > 0) ws = bytes((int64_t)need, dev);
-        check((mx ? p_mxfp4_gemm_native_packed : p_dfp4_gemm_native_packed)(data(a[0]), M, data(a[2]), N, K, data(out), bf16 ? DFP4_BF16 : DFP4_F32, N,
-                                                                            need > 0 ? data(ws) : nullptr, need, stream()), "gemm_native_packed");
+        enqueue("gemm_native_packed", mx ? p_mxfp4_gemm_native_packed : p_dfp4_gemm_native_packed, data(a[0]), M, data(a[2]), N, K, data(out), dtype(bf16), N,
+                need > 0 ? data(ws) : nullptr, need, stream());
         return THPVariable_Wrap(std::move(out));
     });
 }
