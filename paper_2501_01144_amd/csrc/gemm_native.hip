@@ -730,59 +730,83 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
 #undef DFP4_NATIVE_READ
 }
 
-// Few rows of A (decode shapes, M <= 64): 32 W rows per workgroup, its 16 waves share K (wave w
+// Few rows of A (decode shapes, M <= 64, MT tiles of 32): 32 W rows per workgroup, its 16 waves share K (wave w
 // takes a contiguous range of steps), one or two MFMAs per step; the 16 partial tiles are added in
 // a fixed order through LDS.  No vector-ALU work: both operands arrive packed.
-template <int FMT, bool BF16>
-__global__ __launch_bounds__(1024) void gemm_native_small_kernel(NativeParams p) {
+// Bound by the latency of the packed weights' stream.  STEPS: steps whose loads are on their way at once, 2 for FP6 operands where a wave
+// has four or more (K > 3072), with registers for two workgroups per compute unit where MT is 1.  Microseconds over rotating
+// weights, with one step at a time in registers for two tiles of A whatever M / so:
+//   FP6  16 x 14336 x 4096  15.3 / 12.4    64 x 14336 x 4096  19.0 / 17.0    FP4  16 x 14336 x 4096  10.7 / 10.1
+//        16 x  4096 x 4096   7.9 /  7.0     8 x 4096 x 14336  19.1 / 17.9         16 x  4096 x 4096   6.0 /  5.4
+// Three and four steps at once: 15.3 and 13.8 us for the first (one workgroup per compute unit).  Two steps of FP4: 64 x 14336 x 4096
+// 12.8 instead of 11.9; of FP6 with three steps to a wave, 48 x 1024 x 2080, 5.2 instead of 4.6.
+template <int FMT, bool BF16, int MT, int STEPS>
+__global__ __launch_bounds__(1024, MT == 1 ? 8 : 4) void gemm_native_small_kernel(NativeParams p) {
     constexpr bool kFp6 = FMT == kFmtFp6;
-    __shared__ float s_red[8][2][16][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_red[8][MT][16][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = lane >> 5, c = lane & 31;
-    const int S = p.S, t = blockIdx.x, mt = (p.M + 31) / 32;           // mt = 1 or 2 row tiles of A
+    const int S = p.S, t = blockIdx.x;
     const int per = (S + 15) / 16, s_lo = wave * per, s_hi = min(S, s_lo + per);
-    auto load = [&](const PackedOperand& src, int tile, int s, v8i& v, int& sc) {
-        const uint4 lo = *reinterpret_cast<const uint4*>(
-            src.bits + (kFp6 ? fp6_lo(tile, s, S) : ((size_t)tile * S + s) * 1024) + lane * 16);
-        v = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, 0, 0, 0, 0};
-        if constexpr (kFp6) {
-            const uint2 hi = *reinterpret_cast<const uint2*>(src.bits + fp6_hi(tile, s, S) + lane * 8);
-            v[4] = (int)hi.x;
-            v[5] = (int)hi.y;
-        }
-        sc = (int)(src.sc[((int64_t)(tile >> 2) * S + s) * 64 + lane] >> (8 * (tile & 3)));
+    struct Operand { uint4 lo; uint2 hi; uint32_t sc; };
+    auto load = [&](const PackedOperand& src, int tile, int s) {
+        Operand o;
+        o.lo = *reinterpret_cast<const uint4*>(src.bits + (kFp6 ? fp6_lo(tile, s, S) : ((size_t)tile * S + s) * 1024) + lane * 16);
+        if constexpr (kFp6) o.hi = *reinterpret_cast<const uint2*>(src.bits + fp6_hi(tile, s, S) + lane * 8);
+        o.sc = src.sc[((int64_t)(tile >> 2) * S + s) * 64 + lane];
+        return o;
     };
-    v16f acc[2];
+    auto bits = [&](const Operand& o) {
+        v8i v = {(int)o.lo.x, (int)o.lo.y, (int)o.lo.z, (int)o.lo.w, 0, 0, 0, 0};
+        if constexpr (kFp6) {
+            v[4] = (int)o.hi.x;
+            v[5] = (int)o.hi.y;
+        }
+        return v;
+    };
+    v16f acc[MT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int x = 0; x < 16; ++x) acc[i][x] = 0.0f;
-    for (int s = s_lo; s < s_hi; ++s) {
-        v8i w, a0, a1 = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-        int sw, s0, s1 = 0;
-        load(p.w, t, s, w, sw);
-        load(p.a, 0, s, a0, s0);
-        if (mt > 1) load(p.a, 1, s, a1, s1);
-        acc[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, w, acc[0], FMT, FMT, 0, s0, 0, sw);
-        if (mt > 1) acc[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, w, acc[1], FMT, FMT, 0, s1, 0, sw);
+    for (int s = s_lo; s < s_hi; s += STEPS) {
+        Operand w[STEPS], a[STEPS][MT];
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            const int sq = min(s + q, s_hi - 1);                       // (no branch around a load)
+            w[q] = load(p.w, t, sq);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[q][i] = load(p.a, i, sq);
+        }
+        __builtin_amdgcn_sched_barrier(0);                             // all loads before the first wait
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            if (s + q >= s_hi) break;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bits(a[q][i]), bits(w[q]), acc[i], FMT, FMT, 0, (int)(a[q][i].sc >> (8 * i)),
+                                                                         0, (int)(w[q].sc >> (8 * (t & 3))));
+        }
     }
     // the 16 partial tiles, added in a fixed order: waves 8..15 hand theirs to waves 0..7
     if (wave >= 8) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int x = 0; x < 16; ++x) s_red[wave - 8][i][x][lane] = acc[i][x];
     }
     __syncthreads();
     if (wave < 8) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int x = 0; x < 16; ++x) s_red[wave][i][x][lane] += acc[i][x];
     }
     __syncthreads();
     const int n = t * 32 + c;
-    for (int i = 0; i < mt; ++i) {
+    #pragma unroll
+    for (int i = 0; i < MT; ++i) {
         const int x = wave;                                    // thread (x, lane) finishes one output per row tile
         float sum = 0.0f;
 #pragma unroll
@@ -886,14 +910,15 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
         // decode shapes: one workgroup per 32 W rows (A occupies the first one or two row tiles of its layout)
         p.ksplit = 1;
         dim3 gs((unsigned)((N + 31) / 32));
-        const bool b16 = out_dtype == DFP4_BF16;
-        if (fp6) {
-            if (b16) hipLaunchKernelGGL((gemm_native_small_kernel<kFmtFp6, true>), gs, dim3(1024), 0, stream, p);
-            else hipLaunchKernelGGL((gemm_native_small_kernel<kFmtFp6, false>), gs, dim3(1024), 0, stream, p);
-        } else {
-            if (b16) hipLaunchKernelGGL((gemm_native_small_kernel<kFmtFp4, true>), gs, dim3(1024), 0, stream, p);
-            else hipLaunchKernelGGL((gemm_native_small_kernel<kFmtFp4, false>), gs, dim3(1024), 0, stream, p);
-        }
+        dispatch_mx_bf16(!fp6, out_dtype == DFP4_BF16, [&](auto mxc, auto bc) {
+            constexpr int kFmt = decltype(mxc)::value ? kFmtFp4 : kFmtFp6, kSteps = decltype(mxc)::value ? 1 : 2;
+            constexpr bool kBf16 = decltype(bc)::value;
+            const bool few = p.S <= 48;                                // at most three steps to a wave
+            if (M <= 32 && few) hipLaunchKernelGGL((gemm_native_small_kernel<kFmt, kBf16, 1, 1>), gs, dim3(1024), 0, stream, p);
+            else if (M <= 32) hipLaunchKernelGGL((gemm_native_small_kernel<kFmt, kBf16, 1, kSteps>), gs, dim3(1024), 0, stream, p);
+            else if (few) hipLaunchKernelGGL((gemm_native_small_kernel<kFmt, kBf16, 2, 1>), gs, dim3(1024), 0, stream, p);
+            else hipLaunchKernelGGL((gemm_native_small_kernel<kFmt, kBf16, 2, kSteps>), gs, dim3(1024), 0, stream, p);
+        });
         return check_launch();
     }
     p.ksplit = native_ksplit(M, N, KB);

@@ -1078,6 +1078,21 @@ def test_gemm_native_few_rows(M, N, K):
     _assert_gemm_close(outm, refm, absm, "native few rows mxfp4")
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 33, 3072), (32, 64, 3104), (33, 31, 3104), (32, 40, 4128), (64, 65, 4128), (7, 20, 16416)])
+def test_gemm_native_few_rows_steps_of_a_wave(M, N, K):
+    # three, four and five steps to a wave and many, waves without any, one and two row tiles, both formats
+    print(f"native few rows, steps of a wave: {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    x = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    for mx, quant, back in ((False, dfp4.quantize, dfp4.dequantize), (True, dfp4.mxfp4_quantize, dfp4.mxfp4_dequantize)):
+        qa, qw = quant(x), quant(w)
+        da, dw = back(qa).double(), back(qw).double()
+        out = dfp4.gemm_native_packed(dfp4.native_pack(qa, mx=mx), dfp4.native_pack(qw, mx=mx))
+        torch.cuda.synchronize()
+        assert bool(((out.double() - da @ dw.T).abs() <= GEMM_RTOL * (da.abs() @ dw.abs().T)).all())
+
+
 # --------------------------------------------------------------------------
 # blocks of 16 and mixed block sizes (Section 4.2, Table 3)
 # --------------------------------------------------------------------------
