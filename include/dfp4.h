@@ -219,8 +219,7 @@ size_t dfp4_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * products on one stream are ordered by the stream, products that may overlap in time need
  * their own prepared copy.  Results are bit-identical to dfp4_gemm wherever both sum
  * exactly (one rounding of the exact sum); which tiles' exponents spread too far for that is
- * decided per tile of the kernel the product's size selects (dfp4_gemm_path), in gemm_direct_kernel
- * on more than 256 rows of A per 512 x 128 outputs.
+ * decided per tile of the kernel the product's size selects (dfp4_gemm_path).
  *   workspace   at least dfp4_gemm_prepared_workspace_bytes(M, N, K) bytes (partial tiles
  *               where K is split; 0 for products with many output tiles), 256-byte aligned
  * Limits: ceil(rows / 512) * (K/32 + 1) * 49152 < 2^31 for A, rows * K / 2 < 2^31 for W
@@ -235,15 +234,15 @@ int dfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const voi
 int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const void* w_prepared, void* out,
                         int out_dtype, int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
 /*
- * Diagnostic: number of output tiles (128 x 128 in the large kernel, 512 x 128 in gemm_direct_kernel, smaller ones
- * for at most 256 rows of A) that products on this prepared A ([M, K]) have computed on the per-block fp32 path since it was
- * prepared (exponent spread beyond what the exact paths take).  `count` is a HOST pointer.  Synchronizes with the device.
+ * Diagnostic: number of output tiles whose exponents spread beyond what int32 sums take in products on this prepared A
+ * ([M, K]) since it was prepared (128 x 128 in the large kernel, 512 x 128 in gemm_f8_kernel, smaller ones for at most 256
+ * rows of A).  Of these the parts without a proof that their fp32 sums are exact went the per-block fp32 path.  `count` is a HOST pointer.  Synchronizes with the device.
  */
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);
 /*
  * Diagnostic: the kernel that a product of these sizes takes (batch 1 unless dfp4_gemm_batched; prepared: with
- * dfp4_gemm_prepared).  0: the large kernel (tiles of 256 or 128 x 256 on packed operands).  1 to 7: gemm_f8_kernel, with
- * prepared operands of more than 256 rows gemm_direct_kernel (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
+ * dfp4_gemm_prepared).  0: the large kernel (tiles of 256 or 128 x 256 on packed operands).  1 to 7: gemm_f8_kernel
+ * (operands expanded in the kernel) with tiles of 32 x 32, 64 x 64 with K in four shares, 64 x 64 in two, 128 x 128 in
  * two, 128 x 128, 256 x 128, and 128 x 128 for K of at most 128.  DFP4_ERR_SHAPE for sizes that are no product.
  */
 int dfp4_gemm_path(int64_t M, int64_t N, int64_t K, int64_t batch, int prepared);

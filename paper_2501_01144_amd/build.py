@@ -5,7 +5,7 @@ measurement helpers of bench.py (bench_helpers/ at the repository root).
     python -m paper_2501_01144_amd.build
 
 hipcc cross-compiles without a GPU.  The shared library is written next to
-this file; the ctypes binding loads it from there.
+this file; the binding loads it from there.
 """
 import os
 import re
@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfp4.so")
 BINDING = os.path.join(HERE, "_binding.so")
 HELPERS = os.path.join(ROOT, "bench_helpers")
-SOURCES = ["api.hip", "quantize.hip", "dequantize.hip", "gemm.hip", "gemm_direct.hip", "gemm_f8.hip", "gemm_native.hip"]
+SOURCES = ["api.hip", "quantize.hip", "dequantize.hip", "gemm.hip", "gemm_f8.hip", "gemm_native.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-fconstexpr-steps=200000000",

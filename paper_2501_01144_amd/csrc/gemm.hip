@@ -35,9 +35,8 @@
 //                        202 -> 117; with the prepass 150 -> 100, 162 -> 108, 220 -> 144.)
 //   gemm_f8_kernel       (gemm_f8.hip) both operands expanded inside the kernel to FP8 for the block-scaled instruction, under the
 //                        same proof, in tiles from 32 x 32 to 256 x 128: few rows, few tiles, long K, batches whose packed A
-//                        would be read only once;
-//   gemm_direct_kernel   (gemm_direct.hip) the same tiles on the int8 matrix cores by the scheme above: small products of prepared
-//                        operands of more than 256 rows;
+//                        would be read only once.  Products of prepared operands of more than 256 rows that are too small for
+//                        the large kernel take it too;
 //   gemm_block16_kernel  operands quantized in blocks of 16: per-block fp32 flush.
 //
 // The order of the elements inside an MFMA operand does not matter as long
@@ -62,8 +61,8 @@ inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
     while (s < 8 && tiles * s * 2 <= cu && KB / (2 * s) >= 16) s *= 2;
     return tiles <= kExactSplitTiles ? s : 1;
 }
-// Which kernel.  The large kernel multiplies packed operands; gemm_f8_kernel and gemm_direct_kernel ("direct") expand in the kernel and
-// take everything the large one is not for (few rows, K beyond 16384), and the products they are estimated to finish sooner:
+// Which kernel.  The large kernel multiplies packed operands; gemm_f8_kernel ("direct") expands in the kernel and
+// takes everything the large one is not for (few rows, K beyond 16384), and the products it is estimated to finish sooner:
 // those with few output tiles, and batches whose packed A would be read only once or twice (P V of attention).  K of one
 // iteration of the direct kernel (Q K^T) goes there unless it is prepared already.  fast_cost is of the int8 kernel that
 // the large one replaced, which is faster everywhere: the line lies where it lay, so that no product changed to a slower
@@ -85,7 +84,7 @@ inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool pre
     if (!prepared) t += 7.7f + (0.601f * (float)M + 0.332f * (float)N) * (float)(KB * kBlock * batch) * 1e-6f;
     return t;
 }
-// the shape of gemm_direct_kernel that is taken, -1: the large kernel
+// the shape of gemm_f8_kernel that is taken, -1: the large kernel
 inline int direct_shape(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared, int64_t cu) {
     const DirectChoice d = choose_direct(M, N, KB, batch, cu);
     const bool direct = !large_kernel_can(M, KB) || (prepared ? M < kPreparedMinRows : KB <= kDirectOnceBlocks) ||
@@ -293,7 +292,7 @@ int launch_direct(bool mx, bool bf16, dfp4_tensor A, dfp4_tensor W, void* out, i
             GemmParams p{};
             fill_params(p, a, w, static_cast<uint8_t*>(out) + (size_t)(m0 * ldc + n0) * (bf16 ? 2 : 4), ldc, strideA_rows,
                         strideW_rows, strideC, nullptr);
-            const int rc = launch_gemm_direct(mx, bf16, p, batch, choose_direct(p.M, p.N, KB, batch, cu).shape, stream);
+            const int rc = launch_gemm_f8(mx, bf16, p, batch, choose_direct(p.M, p.N, KB, batch, cu).shape, stream);
             if (rc != DFP4_OK) return rc;
         }
     return DFP4_OK;
@@ -413,13 +412,13 @@ int launch_gemm_prepared(bool mx, dfp4_tensor A, void* a_prepared, dfp4_tensor W
     if (M > max_rows_a(KB) || N > max_rows_w(KB)) return DFP4_ERR_SHAPE;
     if (M < kPreparedMinRows) {
         p.declined = static_cast<uint32_t*>(a_prepared);
-        return launch_gemm_direct(mx, bf16, p, 1, choose_direct(M, N, KB, 1, cu).shape, stream);     // one launch: max_rows_w is half of what it takes
+        return launch_gemm_f8(mx, bf16, p, 1, choose_direct(M, N, KB, 1, cu).shape, stream);     // one launch: max_rows_w is half of what it takes
     }
     p.declined = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a_prepared) + gemm_prepared_declined_offset(M, A.K));
     const int shape = direct_shape(M, N, KB, 1, true, cu);
     if (shape >= 0 && M <= gemm_direct_max_rows(KB, false) && N <= gemm_direct_max_rows(KB, true)) {
         set_prepared_classes(mx, p, static_cast<const uint8_t*>(a_prepared), static_cast<const uint8_t*>(w_prepared));
-        return launch_gemm_direct(mx, bf16, p, 1, shape, stream);
+        return launch_gemm_f8(mx, bf16, p, 1, shape, stream);
     }
     p.a_prep = static_cast<uint8_t*>(a_prepared);
     p.w_prep = static_cast<uint8_t*>(const_cast<void*>(w_prepared));

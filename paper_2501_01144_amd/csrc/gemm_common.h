@@ -1,4 +1,4 @@
-// Shared by the GEMM kernels (gemm.hip, gemm_direct.hip): operand tables, the expansion of 4-bit codes
+// Shared by the GEMM kernels (gemm.hip, gemm_f8.hip, gemm_native.hip): operand tables, the expansion of 4-bit codes
 // to int8, launch parameters, and the tiles computed with one fp32 scale-and-add per block.
 #pragma once
 #include <type_traits>
@@ -31,7 +31,7 @@ struct GemmParams {
     uint8_t* a_prep;
     uint8_t* w_prep;
     int64_t a_prep_stride, w_prep_stride;
-    // prepared operands in gemm_direct_kernel (batch 1; otherwise null): smallest exponent of every row, and per (128 rows,
+    // prepared operands in gemm_f8_kernel (batch 1; otherwise null): smallest exponent of every row, and per (128 rows,
     // block) the classes present
     const uint8_t *ref_a, *mask_a, *ref_w, *mask_w;
     uint32_t* declined;               // counts tiles computed with one fp32 scale-and-add per block (may be null)
@@ -204,7 +204,7 @@ __device__ __forceinline__ void block_flush_tile(const GemmParams& p, int64_t bz
 // ---------------------------------------------------------------------------
 // A 32 x 32 output tile by a workgroup of NW (4, 8 or 16) waves that share K in contiguous ranges, one fp32
 // scale-and-add per block as in the paper's MAC; the partial tiles are added in a fixed order through LDS.
-// Small tiles that gemm_direct_kernel declines.
+// Small tiles that int8_tile declines.
 // ---------------------------------------------------------------------------
 constexpr int kSmallMaxKB = 512;      // LDS holds the 32 rows' exponent bytes of all blocks
 
@@ -334,10 +334,9 @@ int launch_exact_prep(bool mx, const GemmParams& p, int64_t batch, bool classes,
 void set_prepared_classes(bool mx, GemmParams& p, const uint8_t* a_prep, const uint8_t* w_prep);
 int launch_exact(bool mx, bool bf16, const GemmParams& g, int64_t batch, float* part, size_t part_bytes, bool rq, hipStream_t stream);
 
-// gemm_direct.hip: any product of at most gemm_direct_max_rows(KB, false) rows of A and (KB, true) of W, with the operands as
+// gemm_f8.hip: any product of at most gemm_direct_max_rows(KB, false) rows of A and (KB, true) of W, with the operands as
 // they are; a shape and the microseconds it is estimated to take on `cu` compute units
 struct DirectChoice { int shape; float us; };
-int launch_gemm_direct(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
 int launch_gemm_f8(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream);
 DirectChoice choose_direct(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu);
 int64_t gemm_direct_max_rows(int64_t KB, bool weight);

@@ -11,13 +11,14 @@
 // that does not pass is computed again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the
 // kernel's register count.
 //
-// This took the place of int8 operands with classes (gemm_int8_tile.h) for everything but prepared operands of more than 256
-// rows, whose tiles are taken or declined by prepared masks.  There a pass over the exponents came first, and classes on
+// This took the place of int8 operands with classes (gemm_int8_tile.h).  There a pass over the exponents came first, and classes on
 // both operands cost up to four products per pair of blocks.  Microseconds of a call with int8 / with FP8 operands (A with 0.5 %
 // outlier channels x 50, scores with two outlier dimensions on both):
 //   16 x 4096 x 4096      10.7 /  9.5     777 x 3001 x 2080     28.6 / 24.1     2048 x 4096 x 4096            78.7 / 65.7
 //   16 x 14336 x 4096     17.2 / 14.6     512 x 4096 x 4096     37.2 / 30.7     scores, 128 x 2048 x 2048 x 128  487 / 382
 //   36 x 7898 x 1344      10.9 /  9.0     512 x 4096 x 14336     110 / 100      P V, 128 x 2048 x 2048 x 128     210 / 195
+// and, on prepared operands of more than 256 rows (where the references and classes were there already),
+//   300 x 4096 x 4096     32.7 / 26.9     777 x 3001 x 2080     30.1 / 25.4     1500 x 4000 x 1120            23.5 / 21.3
 // What bounds it: as before nothing alone.  An item is about 60 vector-ALU instructions, and the expansion, the LDS traffic and the
 // products of a workgroup's few waves overlap only in part.  Tried: one operand buffer and three or four waves per SIMD for the
 // 128 x 128 and 256 x 128 tiles (3 to 18 % slower); four waves per SIMD for the tiles of one iteration (scores above 369, but 16 x 700 x 1312 x
@@ -61,9 +62,9 @@ constexpr float kExactUnits = 16777216.0f * 0.9998f;
 
 template <class S>
 struct F8Lds {
-    __attribute__((aligned(16))) uint8_t x[S::KG][S::kF8Bufs][S::kRowGroups * 4096];   // expanded operands: groups of A, of W
+    __attribute__((aligned(16))) uint8_t x[S::KG][S::kBufs][S::kRowGroups * 4096];     // expanded operands: groups of A, of W
     __attribute__((aligned(16))) uint32_t tab[kDialects + 1][4];
-    __attribute__((aligned(4))) uint8_t sc[S::KG][S::kF8Bufs][S::kRows][4];            // exponent bytes of the 4 blocks of a row
+    __attribute__((aligned(4))) uint8_t sc[S::KG][S::kBufs][S::kRows][4];              // exponent bytes of the 4 blocks of a row
     float sq[S::KG][S::kRows];                                         // per row: sum of squares in units of 2^-127 ...
     uint8_t lo[S::KG][S::kRows];                                       // ... smallest exponent byte (255: all zero) ...
     uint8_t ok[S::KG][S::kRows];                                       // ... and whether all are in range
@@ -75,7 +76,7 @@ __device__ __forceinline__ int quad_dpp(int v) { return __builtin_amdgcn_update_
 
 // S: tile; F: the shape a tile is computed again with, of as many threads
 template <bool MX, bool BF16, class S, class F>
-__global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmParams p) {
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(GemmParams p) {
     static_assert(S::kThreads == F::kThreads && S::kTm % F::kTm == 0 && S::kTn % F::kTn == 0);
     constexpr int TI = S::TI, TJ = S::TJ;
     __shared__ union {
@@ -174,14 +175,16 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
         const float v = lo == 255 ? 0.0f : ldexpf(s, 2 * (127 - (int)lo));
         return ok ? v : __builtin_inff();
     };
-    auto take_norm = [&](float v, int side) {
-        // (not negative: ordered like their bits)
-        int b = __builtin_bit_cast(int, v);
-#pragma unroll
-        for (int o = 4; o < 64; o <<= 1) b = max(b, __shfl_xor(b, o));
-        if (lane == 0) atomicMax(&lds.norm[side], b);
+    // the largest of a wave's values, whose quads hold equal ones (not negative: ordered like their bits); no LDS
+    auto take_norm = [&](int v, int side) {
+        v = max(v, quad_dpp<0x141>(v));
+        v = max(v, quad_dpp<0x140>(v));
+        v = max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+        if (lane == 0) atomicMax(&lds.norm[side], v);
     };
     auto finish_norms = [&] {
+        int most[2] = {0, 0};
 #pragma unroll
         for (int j = 0; j < S::kItems; ++j) {
             float s = sq[j];
@@ -193,7 +196,8 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
             const uint32_t lo = 255u - e.x, hi = e.y;
             const bool ok = lo >= (uint32_t)kMinRef && (lo == 255 || lo <= (uint32_t)kMaxRef) && hi <= (uint32_t)kMaxExp;
             if constexpr (S::KG == 1) {
-                take_norm(row_norm(s, lo, ok), j < S::kItemsA ? 0 : 1);
+                int& m = most[j < S::kItemsA ? 0 : 1];
+                m = max(m, __builtin_bit_cast(int, row_norm(s, lo, ok)));
             } else {
                 const int row = j * S::kItemRows + r4;
                 if (b4 == 0) {
@@ -202,6 +206,10 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
                     lds.ok[kg][row] = ok ? 1 : 0;
                 }
             }
+        }
+        if constexpr (S::KG == 1) {
+            take_norm(most[0], 0);
+            take_norm(most[1], 1);
         }
     };
     struct Operands { v8i a[TI], b[TJ]; };                             // of a pair of blocks
@@ -284,25 +292,6 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
             read(o, 0, 1);
             multiply(o, s, Second{});
             in_order();
-        }
-        finish_norms();
-    } else if constexpr (S::kF8Bufs == 1) {
-        if (KB > 0) {
-            for (int k = 0; k < per; k += 4) {
-#pragma unroll
-                for (int j = 0; j < S::kItems; ++j) expand(item[j], j, table(item[j], k_lo + k), 0, k_lo + k);
-#pragma unroll
-                for (int j = 0; j < S::kItems; ++j) load(item[j], j, k_lo + k + 4);
-                __syncthreads();
-                Scales s;
-                read_scales(s, 0);
-                Operands o;
-                read(o, 0, 0);
-                multiply(o, s, First{});
-                read(o, 0, 1);
-                multiply(o, s, Second{});
-                __syncthreads();
-            }
         }
         finish_norms();
     } else {
@@ -471,7 +460,46 @@ __global__ __launch_bounds__(S::kThreads, S::kF8Waves) void gemm_f8_kernel(GemmP
         else if (full) store(std::true_type{}, std::false_type{});
         else store(std::false_type{}, std::false_type{});
     }
+    // Prepared operands of more than 256 rows: 512 x 128 outputs that the masks decline are counted once, by the first wave of their
+    // first tile (where that tile is computed again in int32: there).  Behind the stores, where it delays nobody: before the
+    // products 598 x 6742 x 288 took 15.6 us instead of 15.1.
+    if (p.ref_a && p.declined && m0 % 512 == 0 && n0 % 128 == 0 && tid < 64) {
+        int ha = 0, hw = 0, weight = 0;
+        mask_weights<64>(p, m0, n0, ha, hw, weight);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) weight += __shfl_xor(weight, o);
+        if (tid == 0 && weight > kIntBound) atomicAdd(p.declined, 1u);
+    }
 }
+
+// The tile shapes and what a product takes with each, in microseconds: `base`; per round of workgroups `fixed`, and for
+// every 4 blocks of a group's share of K `step` + `fill` x the share of the chip that the round fills (the last round's
+// rest counts as much as it fills), growing with K beyond 128 blocks by `grow` per 384; `store` per MB of fp32
+// results, where their rows begin inside a line (N % 16) `ragged`.  1: one workgroup per compute unit, 2: two, which
+// shapes that fit take as soon as there are more tiles than compute units.
+// Fitted to 21000 products timed with int8 operands on 256 compute units (gemm_f8_kernel is 0 to 20 % faster in all shapes, which
+// leaves the order of the shapes as it is), M 1..4096, N 64..14336, K 32..16384, 1 to 128 problems, each with
+// every shape: the estimates are within 10 % (rms).  Microseconds of 32 / 64 (KG 4) / 64 (KG 2) / 128 (KG 2) / 128 / 256 rows, and of the int8
+// kernel that the large one replaced, with its prepass:
+//   16 x 4096 x 4096       10.1   17.5   20.0   36.5   49.0      -      -
+//   512 x 4096 x 4096      60.6   40.1   33.8   39.6   50.3   57.0    112
+//   777 x 3001 x 2080      54.1   40.0   31.8   27.1   31.0   35.4     72
+//   2048 x 4096 x 4096        -    156    123   87.8   76.1   66.9   75.5
+//   2048 x 4096 x 14336       -    487    439    300    305    262    171
+struct DirectCost {
+    int tm, tn, kg, resident;
+    bool any_k;
+    float base, fixed1, step1, fill1, fixed2, step2, fill2, store, ragged, grow;
+};
+constexpr DirectCost kDirectCost[] = {
+    {32, 32, 8, 2, false, 2.63f, 0.53f, 1.67f, 0.27f, 0.0f, 3.07f, 0.61f, 0.351f, 0.378f, 0.0f},
+    {64, 64, 4, 1, false, 2.11f, 2.46f, 1.58f, 0.53f, 0, 0, 0, 0.221f, 0.235f, 0.0f},
+    {64, 64, 2, 2, false, 3.32f, 0.72f, 0.985f, 0.177f, 1.77f, 1.43f, 0.434f, 0.167f, 0.180f, 0.059f},
+    {128, 128, 2, 1, true, 3.02f, 3.32f, 1.93f, 0.404f, 0, 0, 0, 0.239f, 0.233f, 0.074f},
+    {128, 128, 1, 2, true, 2.90f, 2.31f, 1.38f, 0.162f, 3.11f, 1.76f, 0.335f, 0.047f, 0.262f, 0.152f},
+    {256, 128, 1, 1, true, 1.29f, 4.71f, 1.56f, 0.216f, 0, 0, 0, 0.065f, 0.322f, 0.188f},
+};
+constexpr int kOnceShape = 6;                          // the one-iteration form of the 128 x 128 tile
 
 template <class S, class F = S>
 int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t stream) {
@@ -484,7 +512,45 @@ int launch(bool mx, bool bf16, const GemmParams& p, int64_t batch, hipStream_t s
 
 }  // namespace
 
-// shapes: those of gemm_direct_kernel
+DirectChoice choose_direct(int64_t M, int64_t N, int64_t KB, int64_t batch, int64_t cu) {
+    const float outputs = (float)M * (float)N * (float)batch * 4e-6f, beyond = (float)(KB > 128 ? KB - 128 : 0) / 384.0f;
+    const bool ragged = N % 16 != 0;
+    DirectChoice best{0, 3e38f};
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(kDirectCost) / sizeof(kDirectCost[0])); ++i) {
+        const DirectCost& c = kDirectCost[i];
+        if (KB > kSmallMaxKB && !c.any_k) continue;    // their declined tiles keep all exponents of A in LDS
+        if (KB <= kDirectOnceBlocks && c.any_k) continue;      // the large tiles take a K of one iteration in one form
+        const int64_t tiles = ((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn) * batch;
+        const float steps = (float)(((KB + c.kg - 1) / c.kg + 3) / 4), grow = 1.0f + c.grow * beyond;
+        const bool two = c.resident == 2 && tiles > cu;
+        const int64_t slots = two ? 2 * cu : cu, rounds = tiles / slots, rest = tiles - rounds * slots;
+        auto round_us = [&](bool pair, float fill) {
+            return pair ? c.fixed2 + steps * (c.step2 + c.fill2 * fill) * grow : c.fixed1 + steps * (c.step1 + c.fill1 * fill) * grow;
+        };
+        float t = c.base + outputs * (ragged ? c.ragged : c.store) + (float)rounds * round_us(two, 1.0f);
+        if (rest > 0) t += two && rest > cu ? round_us(true, (float)rest / (float)slots) : round_us(false, (float)rest / (float)cu);
+        if (t < best.us) best = {i, t};
+    }
+    if (KB <= kDirectOnceBlocks) {
+        // tiles of one iteration flow through the chip rather than in rounds: latency, then tiles and outputs.  (12 %
+        // below the fit: where it is close to the small tiles it wins more often than they do.)
+        const float tiles = (float)(((M + 127) / 128) * ((N + 127) / 128) * batch) / (float)cu, more = tiles > 1.61f ? tiles - 1.61f : 0.0f;
+        const float t = 5.1f + 0.34f * (float)KB + more * (1.30f + 0.147f * (float)KB) + outputs * (ragged ? 0.40f : 0.071f);
+        if (t < best.us) best = {kOnceShape, t};
+    }
+    return best;
+}
+
+// At most this many rows of A or of W in one launch: the kernel addresses an operand with 32-bit byte offsets, the rows
+// of A give at most 65535 tiles of the smallest shape along the grid's y, and those of W at most 2^22 along its x, of
+// 512 threads each.  Whole tiles while that many rows fit; at least 4 rows for any K / 32 < 2^26.
+int64_t gemm_direct_max_rows(int64_t KB, bool weight) {
+    const int64_t offsets = ((int64_t)1 << 28) / (KB > 0 ? KB : 1), grid = weight ? (int64_t)1 << 27 : (int64_t)65535 * 32;
+    const int64_t rows = offsets < grid ? offsets : grid;
+    return rows >= 512 ? rows / 512 * 512 : rows;
+}
+
 int launch_gemm_f8(bool mx, bool bf16, const GemmParams& p, int64_t batch, int shape, hipStream_t stream) {
     switch (shape) {
         case 0: return launch<DirectShape<1, 1, 1, 1, 8>>(mx, bf16, p, batch, stream);

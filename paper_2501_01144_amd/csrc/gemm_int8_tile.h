@@ -1,6 +1,6 @@
 // A tile of A * W^T on operands in their 4-bit form, summed exactly in int32 on the int8 matrix cores (scheme: gemm.hip), or with
 // one fp32 scale-and-add per block where its exponents spread too far.  One workgroup computes a tile of
-// 32 TI WM x 32 TJ WN outputs: gemm_direct_kernel's, and 128 x 128 pieces of the tiles that gemm_native.hip cannot sum exactly in fp32.
+// 32 TI WM x 32 TJ WN outputs: a piece of a tile that gemm_f8.hip or gemm_native.hip cannot sum exactly in fp32.
 //
 // A workgroup has KG groups of WM x WN waves.  Every group computes the same tile of 32 TI WM x 32 TJ WN
 // outputs over its own contiguous range of K; the groups' exact partial sums are added through LDS.
@@ -46,9 +46,6 @@ struct DirectShape {
     static constexpr bool kPrivate = WM * WN == 1;                     // the group is one wave: no barrier in the loop
     static constexpr int kBufs = kPrivate || kOnce ? 1 : 2;
     static constexpr int kWavesPerSimd = TI * TJ == 1 ? 4 : kOnce ? 3 : 2;         // what the registers allow
-    // of gemm_f8_kernel
-    static constexpr int kF8Bufs = kBufs;
-    static constexpr int kF8Waves = TI * TJ == 1 ? 4 : kOnce ? 3 : 2;
     static constexpr int scan_parts() {                                // threads that look for a row's smallest exponent
         int p = 1;
         while (p * 2 * kRows <= kThreads && p < 16) p *= 2;
@@ -80,6 +77,22 @@ __device__ __forceinline__ int block_weight(uint32_t ma, uint32_t mw) {
         for (int c = 0; c <= ct; ++c)
             if (((ma >> c) & 1u) && ((mw >> (ct - c)) & 1u)) weight += 1 << (4 * ct);
     return weight;
+}
+
+// Of prepared operands: the classes of the 512 x 128 outputs that contain (m0, n0), from their masks; of this thread's blocks of K
+// the highest class of A and of W, and their weight
+template <int THREADS>
+__device__ __forceinline__ void mask_weights(const GemmParams& p, int m0, int n0, int& ha, int& hw, int& weight) {
+    const int KB = p.KB, group = m0 / 512 * 4, groups = min(4, (p.M + 127) / 128 - group);
+    const uint8_t *mask_a = p.mask_a + (int64_t)group * KB, *mask_w = p.mask_w + (int64_t)(n0 / 128) * KB;
+    for (int kb = threadIdx.x; kb < KB; kb += THREADS) {
+        uint32_t ma = 0;
+        for (int i = 0; i < groups; ++i) ma |= mask_a[(int64_t)i * KB + kb];
+        const uint32_t mw = mask_w[kb];
+        ha = max(ha, 31 - __builtin_clz(ma | 1u));
+        hw = max(hw, 31 - __builtin_clz(mw | 1u));
+        weight += block_weight(ma, mw);
+    }
 }
 
 template <class S>
@@ -141,18 +154,9 @@ __device__ __forceinline__ void int8_tile(const GemmParams& p, TileLds<S>& u, in
         // the prepared masks
         for (int i = tid; i < S::kRows; i += S::kThreads)
             lds.mn[i] = i < S::kTm ? p.ref_a[min(m0 + i, p.M - 1)] : p.ref_w[min(n0 + i - S::kTm, p.N - 1)];
-        const int group = m0 / 512 * 4, groups = min(4, (p.M + 127) / 128 - group);
-        const uint8_t *mask_a = p.mask_a + (int64_t)group * KB, *mask_w = p.mask_w + (int64_t)(n0 / 128) * KB;
-        __syncthreads();
         int ha = 0, hw = 0, weight = 0;
-        for (int kb = tid; kb < KB; kb += S::kThreads) {
-            uint32_t ma = 0;
-            for (int i = 0; i < groups; ++i) ma |= mask_a[(int64_t)i * KB + kb];
-            const uint32_t mw = mask_w[kb];
-            ha = max(ha, 31 - __builtin_clz(ma | 1u));
-            hw = max(hw, 31 - __builtin_clz(mw | 1u));
-            weight += block_weight(ma, mw);
-        }
+        __syncthreads();
+        mask_weights<S::kThreads>(p, m0, n0, ha, hw, weight);
         if (ha) atomicMax(&lds.spread[0], 4 * ha);
         if (hw) atomicMax(&lds.spread[1], 4 * hw);
         if (weight) atomicAdd(&lds.met, weight);

@@ -132,7 +132,7 @@ struct ExactOperand {
     int64_t src_rows;                 // rows between two problems of a batch
     uint8_t* dst;                     // packed operand, then scales, then norms (ExactLayout)
     int64_t off_sc, off_stat, stride; // bytes
-    uint8_t *ref, *mask;              // of gemm_direct_kernel on prepared operands (may be null): [row] and [128 rows][block]
+    uint8_t *ref, *mask;              // of gemm_f8_kernel on prepared operands (may be null): [row] and [128 rows][block]
     int rows, groups;                 // groups of 128 rows, an even number
 };
 
@@ -998,7 +998,7 @@ int64_t exact_split_bytes(int64_t M, int64_t N, int64_t KB, int64_t batch) {
 }
 
 // Packs A (p.a_prep, unless null) and W (p.w_prep, unless null) of `batch` problems; `classes` (batch 1): with what
-// gemm_direct_kernel reads of prepared operands
+// gemm_f8_kernel reads of prepared operands
 int launch_exact_prep(bool mx, const GemmParams& p, int64_t batch, bool classes, hipStream_t stream) {
     const int64_t KB = p.KB, S = (KB + 1) / 2;
     ExactPrepParams q{};

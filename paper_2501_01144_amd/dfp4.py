@@ -380,7 +380,7 @@ def gemm_declined_tiles(a):
 
 
 def gemm_path(M, N, K, batch=1, prepared=False):
-    """dfp4_gemm_path: the kernel a product takes (0: the large kernel, 1..7: a shape of gemm_direct_kernel)."""
+    """dfp4_gemm_path: the kernel a product takes (0: the large kernel, 1..7: a shape of gemm_f8_kernel)."""
     return int(load().dfp4_gemm_path(M, N, K, batch, 1 if prepared else 0))
 
 
