@@ -10,7 +10,7 @@ synthetic tensors already resident in HBM.
 
 Prints ONE JSON line.  `value` is the step's integer-op throughput (2*M*N*K summed
 over the three GEMMs, divided by the whole step time including both quantizer and
-both prepare launches).  `roofline` is the GEMM call against the int8 MFMA peak,
+both prepare launches).  `roofline` is the GEMM call against the FP6 MFMA peak,
 `roofline_quantizer` the quantizer against HBM on the two streaming tensors,
 `cpu_baseline` the NumPy oracle on a sample of the same workload.  Further keys
 hold the other configurations: the MXFP4 and block-scaled-instruction steps, the
@@ -129,8 +129,8 @@ def run_helper(name, args=(), timeout=120):
 
 
 def sampled_operand_bytes(qx, qw, torch, dfp4):
-    """32 KiB of the int8 operands the GEMM's matrix instructions really see, for the register-only
-    MFMA loop: signed dialect magnitudes u shifted left by the block's exponent offset modulo 4
+    """32 KiB of operands as the GEMM multiplies them where it takes the int8 matrix cores (tiles whose fp32 sums are
+    not proven exact), for the register-only MFMA loop: signed dialect magnitudes u shifted left by the block's exponent offset modulo 4
     (A blocks of a higher class appear as zeros in the class-0 pass, as in the kernel).  Built from
     the library's own dequantizer output: value = 0.5 u 2^e, so u << d = value * 2^(1 - e + d)."""
     def operand(q, rows, blocks):
@@ -285,7 +285,7 @@ def main():
         "metric": "DialectFP4 quant GB/s + quantized GEMM TOPS (% int8 MFMA peak), LLaMA-3-8B shapes",
         "value": None, "unit": "TOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": None, "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "int8", "data": "synthetic",
+        "vs_baseline": None, "dtype": "fp6 (exact sums)", "data": "synthetic",
         "config": {"workload": "LLaMA-3-8B MLP prefill, M=2048: quantize x[2048x4096] -> prepare -> gate/up GEMM "
                                "(K=4096,N=14336) -> quantize h[2048x14336] -> prepare -> down GEMM (K=14336,N=4096); "
                                "activations N(0,1) + 0.5% outlier channels x50, weights N(0,0.02), "
@@ -349,11 +349,11 @@ def main():
             "pct_int8_peak_step": round(100.0 * value / INT8_PEAK_TOPS, 2),
             "quantize_in_step_GBps": round(q_bytes / (q_ms * 1e-3) / 1e9, 1),
             "roofline": {"bound": "mfma",
-                         "kernel": "dfp4_gemm_prepared call = gemm_fast_kernel (3 calls per step, HIP events around each "
+                         "kernel": "dfp4_gemm_prepared call = gemm_native_kernel (3 calls per step, HIP events around each "
                                    "call on the launch stream)",
-                         "achieved": round(gemm_tops, 3), "peak": INT8_PEAK_TOPS, "unit": "TOP/s",
-                         "frac": round(gemm_tops / INT8_PEAK_TOPS, 4),
-                         "traffic": measured_traffic("gemm_fast_kernel_avg_MB_per_launch"),
+                         "achieved": round(gemm_tops, 3), "peak": FP6_PEAK_TOPS, "unit": "TOP/s",
+                         "frac": round(gemm_tops / FP6_PEAK_TOPS, 4), "frac_of_int8_peak": round(gemm_tops / INT8_PEAK_TOPS, 4),
+                         "traffic": measured_traffic("gemm_native_kernel_exact_avg_MB_per_launch"),
                          "traffic_source": "not measured by this run: the rocprofv3 --pmc figure kept in " + TRAFFIC_FILE,
                          "algorithmic_bytes_per_launch": round((2 * gemm_bytes(M, I, H, osz) + gemm_bytes(M, H, I, osz)) / 3),
                          "declined_tiles_last_step": declined},
@@ -362,10 +362,10 @@ def main():
         plain = {"gemm_gate": median_ms(lambda: dfp4.gemm(qx, wq["w_gate"], out=gate, workspace=ws), torch, 12, 3),
                  "gemm_down": median_ms(lambda: dfp4.gemm(qh, wq["w_down"], out=down, workspace=ws), torch, 12, 3)}
         plain_ms = 2 * plain["gemm_gate"] + plain["gemm_down"]
-        out["gemm_unprepared"] = {"what": "dfp4_gemm (nothing prepared ahead); at these sizes gemm_prep_kernel + gemm_fast_kernel",
+        out["gemm_unprepared"] = {"what": "dfp4_gemm (nothing prepared ahead); at these sizes exact_prep_kernel + gemm_native_kernel",
                                   "ms": {k: round(v, 4) for k, v in plain.items()},
                                   "TOPs": round(total_ops / (plain_ms * 1e-3) / 1e12, 1),
-                                  "frac": round(total_ops / (plain_ms * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)}
+                                  "frac": round(total_ops / (plain_ms * 1e-3) / 1e12 / FP6_PEAK_TOPS, 4)}
         if peak is not None:
             # the same matrix cores with nothing but MFMAs: the sustained clock, and with it the
             # attainable rate, depends on how many operand bits toggle
@@ -380,11 +380,6 @@ def main():
             out["roofline"]["measured_mfma_loop"] = peak
             if shadow is not None:
                 out["roofline"]["measured_mfma_shadow"] = shadow
-            out["roofline"]["frac_of_measured_random_int8_loop"] = round(
-                gemm_tops / peak["random_int8_operands"]["TOPs"], 4)
-            if "sampled_gemm_operands" in peak:
-                out["roofline"]["frac_of_measured_sampled_operand_loop"] = round(
-                    gemm_tops / peak["sampled_gemm_operands"]["TOPs"], 4)
 
     nside = max(10, args.steps // 2)
     if "mx" in sections:
@@ -514,7 +509,7 @@ def main():
             entry = {"ms": round(ms1, 4), "stream_ms": round(ms1s, 4), "weight_copies": ncopy,
                      "GBps": round(b1 / (ms1s * 1e-3) / 1e9, 1), "algorithmic_bytes": int(b1),
                      "frac_hbm": round(b1 / (ms1s * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
-                     "kernel": "gemm_direct_kernel (dfp4_gemm, nothing prepared)"}
+                     "kernel": "gemm_f8_kernel (dfp4_gemm, nothing prepared)"}
             # weights prepared offline, the activation prepared once: exact sums, no per-block floating point
             pa1 = dfp4.gemm_prepare(qa1, weight=False)
             pws = [dfp4.gemm_prepare(q, weight=True) for q in qws]
@@ -526,7 +521,7 @@ def main():
                                  "GBps": round(b1p / (ms1ps * 1e-3) / 1e9, 1),
                                  "frac_hbm": round(b1p / (ms1ps * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                                  "bytes": int(b1p), "prepare_a_ms": round(ms1a, 4),
-                                 "kernel": "gemm_direct_kernel (dfp4_gemm_prepared)"}
+                                 "kernel": "gemm_f8_kernel (dfp4_gemm_prepared)"}
             del pa1, pws
             # the same on the block-scaled instruction (weights packed beforehand: 6.25 bits per element instead of 4.5)
             wps, ap1 = [dfp4.native_pack(q) for q in qws], dfp4.quantize_native(a1.to(dev))
@@ -696,7 +691,7 @@ def main():
                     "pct_int8_peak_step": round(100.0 * n["TOPs"] / INT8_PEAK_TOPS, 2)})
         out["config"]["gemm"] = "native (v_mfma_scale_f32_32x32x64_f8f6f4, FP6 E2M3 operands)"
     else:
-        out["config"]["gemm"] = "int8 (v_mfma_i32_32x32x32_i8, exact int32 accumulation)"
+        out["config"]["gemm"] = "exact (v_mfma_scale_f32_32x32x64_f8f6f4, FP6 E2M3 operands; tiles whose fp32 sums are not proven exact: v_mfma_i32_32x32x32_i8)"
     print(json.dumps(out))
 
 
