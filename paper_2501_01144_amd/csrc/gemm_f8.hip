@@ -22,7 +22,9 @@
 // What bounds it: as before nothing alone.  An item is about 60 vector-ALU instructions, and the expansion, the LDS traffic and the
 // products of a workgroup's few waves overlap only in part.  Tried: one operand buffer and three or four waves per SIMD for the
 // 128 x 128 and 256 x 128 tiles (3 to 18 % slower); four waves per SIMD for the tiles of one iteration (scores above 369, but 16 x 700 x 1312 x
-// 64 18.6 instead of 16.7 us).  The exponents' ends are kept as one packed maximum per row: as two values they cost registers, and
+// 64 18.6 instead of 16.7 us).  A second look at W's codes where the bound
+// from its exponents fails (outlier channels on both operands, 1500 x 4000 x 1120: 116 us, of which 94 are the second, int32 product; 21 so), behind
+// the products: the compiler spilled the sums of three shapes (scores 399 -> 1086 us).  The exponents' ends are kept as one packed maximum per row: as two values they cost registers, and
 // the last shape above 15 % of its time.
 //
 // Tiles, groups and the loop are those of gemm_int8_tile.h: KG groups of WM x WN waves, each with its contiguous range of K, 4
