@@ -1610,3 +1610,69 @@ def test_quantize_large_tensors_like_their_parts(rows, K, mx):
         part = quant(x[lo:hi])
         assert torch.equal(q.codes[lo:hi], part.codes) and torch.equal(q.exponent[lo:hi], part.exponent)
         assert mx or torch.equal(q.dialect[lo:hi], part.dialect)
+
+
+# --------------------------------------------------------------------------
+# The rule for fp32 sums at its limit: absolute products of an output that add up to 2^24 units all but a few thousandths, most of it
+# one product (of two blocks 8 binades above the rest) beside products of one unit in the same pair of blocks, in other steps and in
+# other shares of K.  Every output is a whole number of units, so there is one right answer, bit for bit.  `over`: sums beyond 2^24 units
+# that int32 holds, rounded once.
+# --------------------------------------------------------------------------
+def _limit_operand(rows, K, mx, over, weight, g):
+    """Quantized operand, and its elements as whole numbers of units.  Rows whose numbers agree modulo 5 have their high blocks in the
+    same places."""
+    KB, dev = K // 32, "cuda"
+    book = torch.tensor(dfp4.formatbook(), device=dev)
+    r = torch.arange(rows, device=dev)
+    sign = torch.randint(0, 2, (rows, KB, 32), generator=g, device=dev)
+    idx = torch.ones(rows, KB, 32, dtype=torch.long, device=dev)                  # u = 1
+    dial = torch.full((rows, KB), 7, device=dev) if mx else torch.randint(0, 16, (rows, KB), generator=g, device=dev)
+    delta = torch.zeros(rows, KB, dtype=torch.long, device=dev)
+    if not weight:
+        idx[torch.randint(0, 16, (rows, KB, 32), generator=g, device=dev) == 0] = 0          # odd and even sums
+    if over:
+        n = min(KB - 1, 16)
+        for i in range(n):                                                        # A 8 binades up, W not: products of 15 * 15 * 2^8
+            kb = i * KB // n
+            idx[:, kb], sign[:, kb] = 7, 0
+            dial[:, kb] = 7 if mx else i % 2                                      # largest magnitude 15, or 12
+            delta[:, kb] = 0 if weight else 8
+    else:
+        p = torch.tensor([0, KB // 2, KB - 1, 1, 2 * KB // 3], device=dev)[r % 5]
+        for kb, up, elements, d in ((p, 8, (3,), 1), ((p + 1) % KB, 7, (0, 17, 31), 8)):
+            idx[r, kb] = 0
+            delta[r, kb] = up
+            dial[r, kb] = 7 if mx else d                                          # largest magnitude 15, 11 or 12
+            for e in elements if mx else elements[-1:]:
+                idx[r, kb, e] = 7
+                sign[r, kb, e] = (r % 2 if weight and up == 7 else 0)             # the second product taken away in every other column
+    u = book[dial].gather(2, idx)
+    whole = u * (1 - 2 * sign) << delta.unsqueeze(-1)
+    code = ((sign << 3) | idx).view(rows, K // 2, 2)
+    return dfp4.QTensor((code[..., 0] | (code[..., 1] << 4)).to(torch.uint8), None if mx else dial.to(torch.uint8),
+                        (delta + (118 if weight else 121)).to(torch.uint8), rows, K), whole.view(rows, K).double()
+
+
+@pytest.mark.parametrize("M,N,K,prepared,path", [
+    (1552, 5664, 160, True, 0), (518, 6686, 2848, True, 0), (2338, 396, 16032, True, 0), (845, 2333, 11104, False, 0),     # K whole, in 2, 8 and 4 shares
+    (31, 1000, 4128, False, 1), (36, 7898, 1344, True, 2), (190, 2000, 512, True, 3), (777, 3001, 2080, False, 4),
+    (300, 2049, 16416, False, 4), (652, 3397, 544, False, 5), (1500, 4000, 1120, True, 6), (1500, 4000, 1120, False, 6), (1000, 2049, 96, False, 7)])
+@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("over", [False, True])
+def test_gemm_exact_sums_at_the_limit(M, N, K, prepared, path, mx, over):
+    assert dfp4.gemm_path(M, N, K, prepared=prepared) == path
+    print(f"gemm, sums at the limit: {M}x{N}x{K}, prepared {prepared}, mx {mx}, over {over}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    (qa, a), (qw, w) = _limit_operand(M, K, mx, over, False, g), _limit_operand(N, K, mx, over, True, g)
+    units, most = a @ w.T, float((a.abs() @ w.abs().T).max())
+    if over:
+        assert K < 512 or most > 2.0 ** 24
+    else:
+        assert 0.98 * 2 ** 24 < most and float(a.square().sum(1).max()) < 0.9998 * 2 ** 24
+        assert K < 512 or float(units.abs().min()) < 2 ** 23 and bool((units[units.abs() > 2 ** 23].long() & 1).any())
+    if prepared:
+        out = dfp4.gemm_prepared(dfp4.gemm_prepare(qa, weight=False, mx=mx), dfp4.gemm_prepare(qw, weight=True, mx=mx))
+    else:
+        out = (dfp4.mxfp4_gemm if mx else dfp4.gemm)(qa, qw)
+    torch.cuda.synchronize()
+    assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
