@@ -7,6 +7,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/dfp4.h"
@@ -92,13 +93,14 @@ PyObject* call(Py_ssize_t given, Py_ssize_t wanted, F&& f) {
         PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
         return nullptr;
     }
+    // torch's own exceptions (an exhausted device: torch.OutOfMemoryError) as torch.empty raises them
+    HANDLE_TH_ERRORS
     try {
         return f();
     } catch (const Failure&) {
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
     }
-    return nullptr;
+    END_HANDLE_TH_ERRORS
 }
 
 // quantize(x, block, mx) -> codes, dialect, exponent, rows, K

@@ -1676,3 +1676,18 @@ def test_gemm_exact_sums_at_the_limit(M, N, K, prepared, path, mx, over):
         out = (dfp4.mxfp4_gemm if mx else dfp4.gemm)(qa, qw)
     torch.cuda.synchronize()
     assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
+
+
+# --------------------------------------------------------------------------
+# Calls that allocate their result raise what torch.empty raises.
+# --------------------------------------------------------------------------
+def test_calls_that_allocate_raise_out_of_memory():
+    rows = 1 << 20
+    print("results of 4 TiB", flush=True)
+    q = dfp4.quantize(torch.ones(rows, 32, dtype=torch.bfloat16, device="cuda"))
+    assert 4 * rows * rows > torch.cuda.get_device_properties(0).total_memory
+    a, w, packed = dfp4.gemm_prepare(q, weight=False), dfp4.gemm_prepare(q, weight=True), dfp4.native_pack(q)
+    for call in (lambda: dfp4.gemm(q, q), lambda: dfp4.gemm_prepared(a, w), lambda: dfp4.gemm_native_packed(packed, packed),
+                 lambda: dfp4.gemm_batched(q, q, 1, rows, rows), lambda: dfp4.gemm_native_packed_w(q, packed)):
+        with pytest.raises(torch.OutOfMemoryError):
+            call()
