@@ -129,7 +129,7 @@ def load():
     try:
         from . import _binding
     except ImportError as e:
-        raise Dfp4Error("paper_2501_01144_amd/_binding.so not found: build it with `python -m paper_2501_01144_amd.build`") from e
+        raise Dfp4Error(f"paper_2501_01144_amd/_binding.so: {e} (built by `python -m paper_2501_01144_amd.build`)") from e
     _binding.bind(_LIB_PATH, Dfp4Error)
     _lib, _native = lib, _binding
     return lib

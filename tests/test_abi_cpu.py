@@ -215,3 +215,14 @@ def test_gemm_path_of_short_k_and_of_errors(lib):
     assert dfp4.gemm_path(2048, 4096, 160) != 7
     for bad in ((0, 4, 32, 1), (4, 0, 32, 1), (4, 4, 33, 1), (4, 4, 32, 0), (4, 4, -32, 1)):
         assert lib.dfp4_gemm_path(*bad, 0) == -2
+
+
+def test_a_native_module_that_does_not_load_says_why(monkeypatch):
+    import sys
+    import paper_2501_01144_amd as package
+    monkeypatch.setattr(dfp4, "_lib", None)
+    monkeypatch.setattr(dfp4, "_native", None)
+    monkeypatch.delattr(package, "_binding", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2501_01144_amd._binding", None)
+    with pytest.raises(dfp4.Dfp4Error, match="halted"):                # the import system's own words
+        dfp4.load()
