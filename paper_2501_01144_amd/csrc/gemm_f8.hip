@@ -6,10 +6,16 @@
 // no class, and a pair of blocks is one instruction per 32 x 32 outputs.  Sums are fp32 and exact under the rule of
 // gemm_native.hip: with the norms of the rows in units of their smallest block exponent, sum |a||w| <= ||a|| ||w|| <= 2^24 units means that no
 // partial sum rounds (3.2 million outputs of single FP8 instructions below that bound checked: none off).  The norms are
-// taken while the items are expanded: of A from its codes, of W, which has most of the rows where A has few, from its
-// exponents alone (||w||^2 <= sum over blocks of 32 15^2 4^offset, which is about twice the norm of Gaussian data).  A tile
-// that does not pass is computed again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the
-// kernel's register count.
+// taken while the items are expanded: of A from its codes, of W, which has most of the rows where A has few, up to K = 6144 from its
+// exponents alone (||w||^2 <= sum over blocks of 32 15^2 4^offset: about three times the norm of Gaussian data, more with outliers) and
+// beyond from its codes.  A tile without a proof looks at the codes a second time, first W's, then A's, for the three bounds of
+// gemm_native.hip; one that passes none is computed again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the
+// kernel's register count.  Microseconds of a call, plain inputs / outlier channels on A (x 50) and W (x 20), or A alone (x 200), without a second look,
+// so that such tiles were multiplied twice / with it:
+//   32 x 4096 x 4096  9.2 / 21.2, 20.6 / 12.9, 12.8      1500 x 4000 x 1120                20.3 / 113 / 24
+//   777 x 3001 x 2080  24 /   91,   85 / 30, 30          P V, 128 x 2048 x 2048 x 128       160 / 637 / 181
+// The second look is vector-ALU work (a third of a product's time for either operand) and lost where it finds no proof: channels x 1000 on A at
+// K = 14336, 16 rows 84 -> 104, 512 rows 616 -> 694.
 //
 // This took the place of int8 operands with classes (gemm_int8_tile.h).  There a pass over the exponents came first, and classes on
 // both operands cost up to four products per pair of blocks.  Microseconds of a call with int8 / with FP8 operands (A with 0.5 %
@@ -22,15 +28,15 @@
 // What bounds it: as before nothing alone.  An item is about 60 vector-ALU instructions, and the expansion, the LDS traffic and the
 // products of a workgroup's few waves overlap only in part.  Tried: one operand buffer and three or four waves per SIMD for the
 // 128 x 128 and 256 x 128 tiles (3 to 18 % slower); four waves per SIMD for the tiles of one iteration (scores above 369, but 16 x 700 x 1312 x
-// 64 18.6 instead of 16.7 us).  A second look at W's codes where the bound
-// from its exponents fails (outlier channels on both operands, 1500 x 4000 x 1120: 116 us, of which 94 are the second, int32 product; 21 so), behind
-// the products: the compiler spilled the sums of three shapes (scores 399 -> 1086 us).  The exponents' ends are kept as one packed maximum per row: as two values they cost registers, and
-// the last shape above 15 % of its time.
+// 64 18.6 instead of 16.7 us); the second look with the sums in registers, which the compiler then spilled (scores 399 -> 1086 us): they are in LDS
+// meanwhile, and what follows the products takes the thread's place anew.  The exponents' ends are kept as one packed maximum per row: as two values
+// they cost registers, and the last shape above 15 % of its time.
 //
 // Tiles, groups and the loop are those of gemm_int8_tile.h: KG groups of WM x WN waves, each with its contiguous range of K, 4
 // blocks per iteration, expanded operands in LDS as [32-row group][pair of blocks][half of a block][block of the pair][row][16
 // bytes], the row slot rotated by twice the block number.  The instruction wants in lane (h, r) half h of both blocks of row r, and the
 // scale of block h.
+#include "exact_norms.h"
 #include "gemm_int8_tile.h"
 
 namespace dfp4 {
@@ -57,20 +63,21 @@ __device__ const F8Book g_f8_book = make_f8_book();
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// References (exponent bytes of nonzero blocks) outside this range are left to int32: see gemm_native.hip
-constexpr int kMinRef = 66, kMaxRef = 178;
 constexpr int kMaxExp = 190;          // of any block: 4^(e - 127) is built as a float, and 2 e - 127 is its exponent byte
-constexpr float kExactUnits = 16777216.0f * 0.9998f;
 
 template <class S>
 struct F8Lds {
-    __attribute__((aligned(16))) uint8_t x[S::KG][S::kBufs][S::kRowGroups * 4096];     // expanded operands: groups of A, of W
+    union {
+        __attribute__((aligned(16))) uint8_t x[S::KG][S::kBufs][S::kRowGroups * 4096]; // expanded operands: groups of A, of W
+        float sums[S::kOnce ? 1 : S::KG * S::kTm * S::kTn];            // of the groups, [group][wave][register][lane], once the operands are done with
+    };
     __attribute__((aligned(16))) uint32_t tab[kDialects + 1][4];
     __attribute__((aligned(4))) uint8_t sc[S::KG][S::kBufs][S::kRows][4];              // exponent bytes of the 4 blocks of a row
     float sq[S::KG][S::kRows];                                         // per row: sum of squares in units of 2^-127 ...
     uint8_t lo[S::KG][S::kRows];                                       // ... smallest exponent byte (255: all zero) ...
     uint8_t ok[S::KG][S::kRows];                                       // ... and whether all are in range
-    int norm[2];                                                       // largest squared norm of A's, of W's rows in their units (bits)
+    ExactStat part[S::KG > 1 ? S::KG : 1][S::KG > 1 ? S::kRows : 1];   // of the groups, second look
+    int norm[2][5];                                                    // of A's, of W's rows in their units, the largest (bits): squared norm; ExactStat
 };
 
 template <int CTRL>
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         ends[j] = v2u{0, 0};
     }
     for (int i = tid; i < (kDialects + 1) * 4; i += S::kThreads) (&lds.tab[0][0])[i] = (&g_f8_book.w[0][0])[i];
-    if (tid < 2) lds.norm[tid] = 0;
+    if (tid < 10) lds.norm[tid / 5][tid % 5] = 0;
     __syncthreads();
 
     const int wm = wave / S::WN, wn = wave % S::WN, h = lane >> 5, r = lane & 31;
@@ -141,8 +148,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     auto table = [&](const Item& it, int kb0) {
         return *reinterpret_cast<const uint4*>(&lds.tab[kb0 + b4 < KB ? (it.d & 15u) : (uint32_t)kDialects][0]);
     };
-    // of W the norm is taken from its codes only where K is long: with 0.5 % outlier channels x 50 on A the looser one is 2^22.5 units at
-    // K = 4096 and too much at 14336
+    // Of W the norm is taken from its codes only where K is long, where the looser one of ordinary data comes near the limit (Gaussian W, 0.5 %
+    // outlier channels x 50 on A: 2^22.5 units at K = 4096, 2^24 at 14336); the 16 instructions of 60 are the second look's otherwise.
     const bool w_codes = KB > 192;
     uint8_t* slot = &lds.x[kg][0][0] + (b4 >> 1) * 2048 + (b4 & 1) * 512;
     auto expand = [&](const Item& it, int j, uint4 tab, int buf, int kb0) {
@@ -178,12 +185,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         return ok ? v : __builtin_inff();
     };
     // the largest of a wave's values, whose quads hold equal ones (not negative: ordered like their bits); no LDS
-    auto take_norm = [&](int v, int side) {
+    auto take_norm = [&](int v, int side, int which) {
         v = max(v, quad_dpp<0x141>(v));
         v = max(v, quad_dpp<0x140>(v));
         v = max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
                 max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-        if (lane == 0) atomicMax(&lds.norm[side], v);
+        if (lane == 0) atomicMax(&lds.norm[side][which], v);
     };
     auto finish_norms = [&] {
         int most[2] = {0, 0};
@@ -210,8 +217,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
             }
         }
         if constexpr (S::KG == 1) {
-            take_norm(most[0], 0);
-            take_norm(most[1], 1);
+            take_norm(most[0], 0, 0);
+            take_norm(most[1], 1, 0);
         }
     };
     struct Operands { v8i a[TI], b[TJ]; };                             // of a pair of blocks
@@ -251,6 +258,17 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     };
     using First = std::integral_constant<int, 0>;
     using Second = std::integral_constant<int, 1>;
+    auto products_once = [&] {                                         // kOnce
+        Scales s;
+        read_scales(s, 0);
+        Operands o;
+        read(o, 0, 0);
+        multiply(o, s, First{});
+        if (KB > 2) {
+            read(o, 0, 1);
+            multiply(o, s, Second{});
+        }
+    };
     if constexpr (S::kOnce) {
         if (KB > 0) {
 #pragma unroll
@@ -258,17 +276,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         }
         finish_norms();
         __syncthreads();
-        if (KB > 0) {
-            Scales s;
-            read_scales(s, 0);
-            Operands o;
-            read(o, 0, 0);
-            multiply(o, s, First{});
-            if (KB > 2) {
-                read(o, 0, 1);
-                multiply(o, s, Second{});
-            }
-        }
+        if (KB > 0) products_once();
     } else if constexpr (S::kPrivate) {
         // one wave: its LDS operations execute in order, so lanes exchange operands without a barrier; the fences keep
         // the compiler to that order (they cost no instruction).  4 waves per SIMD hide the latencies
@@ -347,32 +355,169 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         finish_norms();
     }
     if constexpr (!S::kOnce) __syncthreads();
-    if constexpr (S::KG > 1) {
-        for (int row = tid; row < (S::kRows + 63) / 64 * 64; row += S::kThreads) {       // whole waves
-            float v = 0.0f;
-            if (row < S::kRows) {
-                uint32_t lo = 255;
-                bool ok = true;
+    // the thread's place, taken anew: nothing of it is kept in registers through the products for what follows
+    int tid_ = threadIdx.x;
+    asm volatile("" : "+v"(tid_));
+    const int lane_ = tid_ & 63, h_ = lane_ >> 5, r_ = lane_ & 31;
+    constexpr int kOut = TI * TJ * 16;
+    float* sums = lds.sums + (S::kOnce ? 0 : (kg * S::WM * S::WN + wave) * kOut * 64 + lane_);          // of this lane
+    auto put_sums = [&] {
 #pragma unroll
-                for (int g = 0; g < S::KG; ++g) {
-                    lo = min(lo, (uint32_t)lds.lo[g][row]);
-                    ok = ok && lds.ok[g][row] != 0;
-                }
-                float s = 0.0f;
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-                for (int g = 0; g < S::KG; ++g) s += lds.sq[g][row];
-                v = row_norm(s, lo, ok);
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int x = 0; x < 16; ++x) sums[((i * TJ + j) * 16 + x) * 64] = acc[i][j][x];
+    };
+    // NV values of every row from row_lo to row_hi, over the groups: the largest of A's and of W's rows
+    auto over_groups = [&](auto nv_c, int which, int row_lo, int row_hi, auto&& of_row) {
+        constexpr int NV = decltype(nv_c)::value;
+        static_assert(S::kTm % 32 == 0 && S::kTn % 32 == 0, "half a wave holds rows of one operand");
+        for (int i = tid_; i < (row_hi - row_lo + 63) / 64 * 64; i += S::kThreads) {      // whole waves
+            const int row = row_lo + i;
+            float v[NV] = {};
+            if (row < row_hi) of_row(row, v);
+#pragma unroll
+            for (int q = 0; q < NV; ++q) {
+                int b = __builtin_bit_cast(int, v[q]);
+#pragma unroll
+                for (int o = 1; o < 32; o <<= 1) b = max(b, __shfl_xor(b, o));
+                if ((lane_ & 31) == 0 && row < row_hi) atomicMax(&lds.norm[row < S::kTm ? 0 : 1][which + q], b);
             }
-            static_assert(S::kTm % 32 == 0 && S::kTn % 32 == 0, "half a wave holds rows of one operand");
-            int b = __builtin_bit_cast(int, v);
-#pragma unroll
-            for (int o = 1; o < 32; o <<= 1) b = max(b, __shfl_xor(b, o));
-            if ((lane & 31) == 0 && row < S::kRows) atomicMax(&lds.norm[row < S::kTm ? 0 : 1], b);
         }
+    };
+    constexpr bool kPutEarly = S::KG > 1 && TI * TJ == 1;              // (a barrier less; 64 registers are too much LDS traffic before it: 13.4 -> 14.0 us for 249 x 11523 x 640)
+    if constexpr (S::KG > 1) {
+        if constexpr (kPutEarly) put_sums();
+        over_groups(std::integral_constant<int, 1>{}, 0, 0, S::kRows, [&](int row, float (&v)[1]) {
+            uint32_t lo = 255;
+            bool ok = true;
+#pragma unroll
+            for (int g = 0; g < S::KG; ++g) {
+                lo = min(lo, (uint32_t)lds.lo[g][row]);
+                ok = ok && lds.ok[g][row] != 0;
+                v[0] += lds.sq[g][row];
+            }
+            v[0] = row_norm(v[0], lo, ok);
+        });
         __syncthreads();
     }
+    auto norm = [&](int side, int which) { return __builtin_bit_cast(float, lds.norm[side][which]); };
     // the same for every thread
-    if (!(sqrtf(__builtin_bit_cast(float, lds.norm[0])) * sqrtf(__builtin_bit_cast(float, lds.norm[1])) <= kExactUnits)) {
+    bool proven = sqrtf(norm(0, 0)) * sqrtf(norm(1, 0)) <= kExactUnits;
+    const bool looked = !proven && fmaxf(norm(0, 0), norm(1, 0)) < __builtin_inff();
+    if (looked) {
+        // A second look at the codes: what exact_prep_kernel keeps of a prepared operand (ExactStat), first of W, whose norm was a
+        // bound, then of A.  The sums are in LDS meanwhile (K of one iteration: the operands still are) and set no register count.
+        if constexpr (!kPutEarly && !S::kOnce) put_sums();
+        auto look = [&](auto side_c) {
+            constexpr int kSide = decltype(side_c)::value, kFirst = kSide == 0 ? 0 : S::kItemsA;
+            constexpr int kN = kSide == 0 ? S::kItemsA : S::kItems - S::kItemsA;
+            constexpr int kAhead = S::kOnce ? 1 : 2;                   // iterations whose loads are on their way
+            Item next[kAhead][kN];
+            float sq2[kN], low[kN], high[kN];                          // of this thread's blocks of the rows
+            int ref[kN], far[kN];
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {
+#pragma unroll
+                for (int d = 0; d < kAhead; ++d) load(next[d][j], kFirst + j, k_lo + 4 * d);
+                sq2[j] = low[j] = high[j] = 0.0f;
+                far[j] = 0;
+                if constexpr (S::KG == 1) {
+                    int e = (int)ends[kFirst + j].x;
+                    e = max(e, quad_dpp<0xB1>(e));
+                    ref[j] = 255 - max(e, quad_dpp<0x4E>(e));
+                } else {
+                    ref[j] = 255;
+#pragma unroll
+                    for (int g = 0; g < S::KG; ++g) ref[j] = min(ref[j], (int)lds.lo[g][(kFirst + j) * S::kItemRows + r4]);
+                }
+            }
+            const int k_hi = min(k_lo + per, KB);
+#pragma unroll 1
+            for (int k = k_lo; k < k_hi; k += 4 * kAhead) {
+#pragma unroll
+                for (int d = 0; d < kAhead; ++d) {
+                    const int kb0 = k + 4 * d;
+                    if (kb0 >= k_hi) break;
+#pragma unroll
+                    for (int j = 0; j < kN; ++j) {
+                        const uint4 tab = table(next[d][j], kb0);
+                        const uint32_t c4[4] = {next[d][j].c.x, next[d][j].c.y, next[d][j].c.z, next[d][j].c.w};
+                        const int delta = (int)next[d][j].e - ref[j];
+                        uint32_t u[8], s2 = 0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            u[2 * q] = __builtin_amdgcn_perm(tab.w, tab.z, c4[q] & 0x07070707u);
+                            u[2 * q + 1] = __builtin_amdgcn_perm(tab.w, tab.z, (c4[q] >> 4) & 0x07070707u);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) s2 = __builtin_amdgcn_udot4(u[q], u[q], s2, false);
+                        load(next[d][j], kFirst + j, kb0 + 4 * kAhead);
+                        const bool some = s2 != 0, is_high = some && delta >= 4;               // (beyond K the table is all zeros)
+                        const float v = some ? ldexpf((float)s2, 2 * delta) : 0.0f;
+                        sq2[j] += v;
+                        low[j] += is_high ? 0.0f : v;
+                        far[j] = max(far[j], some ? delta : 0);
+                        if (__ballot(is_high) != 0ull) {
+                            uint32_t s1 = 0;
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) s1 = __builtin_amdgcn_udot4(u[q], 0x01010101u, s1, false);
+                            high[j] += is_high ? ldexpf((float)s1, delta) : 0.0f;
+                        }
+                    }
+                }
+            }
+            auto over_quad = [&](float a) {
+                a += __builtin_bit_cast(float, quad_dpp<0xB1>(__builtin_bit_cast(int, a)));
+                return a + __builtin_bit_cast(float, quad_dpp<0x4E>(__builtin_bit_cast(int, a)));
+            };
+            ExactStat most{0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {
+                int f = far[j];
+                f = max(f, quad_dpp<0xB1>(f));
+                f = max(f, quad_dpp<0x4E>(f));
+                const ExactStat v{over_quad(sq2[j]), over_quad(low[j]), over_quad(high[j]), ldexpf(15.0f, f)};
+                if constexpr (S::KG == 1) most = ExactStat{fmaxf(most.sq, v.sq), fmaxf(most.sq_low, v.sq_low), fmaxf(most.sum_high, v.sum_high), fmaxf(most.top, v.top)};
+                else if (b4 == 0) lds.part[kg][(kFirst + j) * S::kItemRows + r4] = v;
+            }
+            if constexpr (S::KG == 1) {
+                take_norm(__builtin_bit_cast(int, most.sq), kSide, 1);
+                take_norm(__builtin_bit_cast(int, most.sq_low), kSide, 2);
+                take_norm(__builtin_bit_cast(int, most.sum_high), kSide, 3);
+                take_norm(__builtin_bit_cast(int, most.top), kSide, 4);
+            } else {
+                __syncthreads();
+                over_groups(std::integral_constant<int, 4>{}, 1, kSide == 0 ? 0 : S::kTm, kSide == 0 ? S::kTm : S::kRows, [&](int row, float (&o)[4]) {
+#pragma unroll
+                    for (int g = 0; g < S::KG; ++g) {
+                        const ExactStat v = lds.part[g][row];
+                        o[0] += v.sq;
+                        o[1] += v.sq_low;
+                        o[2] += v.sum_high;
+                        o[3] = fmaxf(o[3], v.top);
+                    }
+                });
+            }
+            __syncthreads();
+            return ExactStat{norm(kSide, 1), norm(kSide, 2), norm(kSide, 3), norm(kSide, 4)};
+        };
+        const ExactStat w = look(std::integral_constant<int, 1>{});
+        const float inf = __builtin_inff();
+        proven = sums_exactly(ExactStat{norm(0, 0), inf, inf, sqrtf(norm(0, 0))}, w);          // (an element is at most the norm of its row)
+        if (!proven) proven = sums_exactly(look(std::integral_constant<int, 0>{}), w);
+        if (S::KG == 1 && proven) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) acc[i][j][x] = S::kOnce ? 0.0f : sums[((i * TJ + j) * 16 + x) * 64];
+            if constexpr (S::kOnce) products_once();
+        }
+    }
+    if (!proven) {
         __syncthreads();
 #pragma unroll 1
         for (int i = 0; i < (S::kTm / F::kTm) * (S::kTn / F::kTn); ++i) {
@@ -391,25 +536,19 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     constexpr int kEsz = BF16 ? 2 : 4;
     const int row0 = m0 + wm * 32 * TI, col0 = n0 + wn * 32 * TJ;      // of this wave
     if constexpr (S::KG > 1) {
-        // the groups' exact partial sums, added through LDS; group kg finishes its share of the tile's outputs
-        constexpr int kOut = TI * TJ * 16, kShare = kOut / S::KG;
-        static_assert(sizeof(float) * S::KG * S::WM * S::WN * kOut * 64 <= sizeof(lds.x), "partial tiles reuse the operands");
-        float* red = reinterpret_cast<float*>(&lds.x[0][0][0]);
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                for (int x = 0; x < 16; ++x)
-                    red[((kg * S::WM * S::WN + wave) * kOut + (i * TJ + j) * 16 + x) * 64 + lane] = acc[i][j][x];
-        __syncthreads();
+        if constexpr (!kPutEarly) {
+            if (!looked) put_sums();
+            __syncthreads();
+        }
+        // the groups' exact partial sums are added; group kg finishes its share of the tile's outputs
+        constexpr int kShare = kOut / S::KG;
 #pragma unroll
         for (int q = 0; q < kShare; ++q) {
             const int o = kg * kShare + q, i = o / (16 * TJ), j = o / 16 % TJ, x = o % 16;
             float sum = 0.0f;
 #pragma unroll
-            for (int g = 0; g < S::KG; ++g) sum += red[((g * S::WM * S::WN + wave) * kOut + o) * 64 + lane];
-            const int lr = 32 * i + 8 * (x >> 2) + 4 * h + (x & 3), lc = 32 * j + r;
+            for (int g = 0; g < S::KG; ++g) sum += lds.sums[((g * S::WM * S::WN + wave) * kOut + o) * 64 + lane_];
+            const int lr = 32 * i + 8 * (x >> 2) + 4 * h_ + (x & 3), lc = 32 * j + r_;
             if (row0 + lr < p.M && col0 + lc < p.N) {
                 const int64_t at = bz * p.strideC + (int64_t)(row0 + lr) * p.ldc + col0 + lc;
                 if constexpr (BF16) static_cast<uint16_t*>(p.out)[at] = f32_to_bf16_rne(sum);
@@ -424,8 +563,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         // bf16: every lane stores two adjacent columns of one row (as in gemm_native_kernel)
         const bool pairs = BF16 && full && (p.ldc & 1) == 0 && ((p.strideC * kEsz) & 3) == 0 &&
                            (reinterpret_cast<uintptr_t>(p.out) & 3) == 0;
-        const uint32_t lane_off = pairs ? (uint32_t)((4 * h + (r & 1)) * row_bytes + (r & ~1) * kEsz)
-                                        : (uint32_t)(4 * h * row_bytes + r * kEsz);
+        const uint32_t lane_off = pairs ? (uint32_t)((4 * h_ + (r_ & 1)) * row_bytes + (r_ & ~1) * kEsz)
+                                        : (uint32_t)(4 * h_ * row_bytes + r_ * kEsz);
         auto store = [&](auto full_c, auto pairs_c) {
             constexpr bool kFull = decltype(full_c)::value, kPairs = decltype(pairs_c)::value;
 #pragma unroll
@@ -440,15 +579,15 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
 #pragma unroll
                             for (int x = 0; x < 4; x += 2) {
                                 const uint32_t b0 = f32_to_bf16_rne(acc[i][j][4 * q + x]), b1 = f32_to_bf16_rne(acc[i][j][4 * q + x + 1]);
-                                const uint32_t send = (r & 1) ? b0 : b1;
+                                const uint32_t send = (r_ & 1) ? b0 : b1;
                                 const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xf, 0xf, true);
-                                const uint32_t word = (r & 1) ? (recv | (b1 << 16)) : (b0 | (recv << 16));
+                                const uint32_t word = (r_ & 1) ? (recv | (b1 << 16)) : (b0 | (recv << 16));
                                 DFP4_OUT_STORE(reinterpret_cast<uint32_t*>(rowp + (int64_t)x * row_bytes + lane_off), word);
                             }
                         } else {
 #pragma unroll
                             for (int x = 0; x < 4; ++x) {
-                                if (kFull || (row0 + i * 32 + 8 * q + 4 * h + x < p.M && col0 + j * 32 + r < p.N)) {
+                                if (kFull || (row0 + i * 32 + 8 * q + 4 * h_ + x < p.M && col0 + j * 32 + r_ < p.N)) {
                                     uint8_t* dst = rowp + (int64_t)x * row_bytes + lane_off;
                                     if constexpr (BF16) DFP4_OUT_STORE(reinterpret_cast<uint16_t*>(dst), f32_to_bf16_rne(acc[i][j][4 * q + x]));
                                     else DFP4_OUT_STORE(reinterpret_cast<float*>(dst), acc[i][j][4 * q + x]);
@@ -465,12 +604,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     // Prepared operands of more than 256 rows: 512 x 128 outputs that the masks decline are counted once, by the first wave of their
     // first tile (where that tile is computed again in int32: there).  Behind the stores, where it delays nobody: before the
     // products 598 x 6742 x 288 took 15.6 us instead of 15.1.
-    if (p.ref_a && p.declined && m0 % 512 == 0 && n0 % 128 == 0 && tid < 64) {
+    if (p.ref_a && p.declined && m0 % 512 == 0 && n0 % 128 == 0 && tid_ < 64) {
         int ha = 0, hw = 0, weight = 0;
         mask_weights<64>(p, m0, n0, ha, hw, weight);
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) weight += __shfl_xor(weight, o);
-        if (tid == 0 && weight > kIntBound) atomicAdd(p.declined, 1u);
+        if (tid_ == 0 && weight > kIntBound) atomicAdd(p.declined, 1u);
     }
 }
 

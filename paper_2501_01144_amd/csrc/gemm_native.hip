@@ -44,6 +44,7 @@
 #include <type_traits>
 #include "common.h"
 #include "formatbook.h"
+#include "exact_norms.h"
 #include "fp6_pack.h"
 #include "quant_pass.h"
 #include "gemm_int8_tile.h"
@@ -111,21 +112,9 @@ __global__ __launch_bounds__(256) void native_pack_kernel(PackParams p) {
     reinterpret_cast<uint8_t*>(p.dst.sc)[(((int64_t)(tile >> 2) * p.S + s) * 64 + lane) * 4 + (tile & 3)] = (uint8_t)eb;
 }
 
-// ---- exact products: the norms of packed rows
-// Of the rows of a 32-row tile over a chunk of K, in units of the row (its reference: the smallest exponent of its
-// nonzero blocks); every entry the largest over the rows, so that sums over chunks and maxima over tiles bound every row.
-struct alignas(16) ExactStat {
-    float sq;          // sum of squares
-    float sq_low;      // sum of squares over blocks less than 4 binades above the reference
-    float sum_high;    // sum of magnitudes over the other blocks
-    float top;         // largest magnitude, at most
-};
+// ---- exact products: the norms of packed rows (ExactStat)
 constexpr int kStatChunks = 32;                       // chunks of a row, at most: [row tile][32]
 constexpr int kMaxChunkBlocks = 64;
-constexpr float kExactUnits = 16777216.0f * 0.9998f;  // the bounds' own rounding stays below 1e-4
-// Rows whose reference lies outside these exponent bytes take the int32 path: a product of two units is then at least 2^-126
-// (no partial sum is subnormal) and a sum of 2^24 of them below 2^127.
-constexpr int kMinRef = 66, kMaxRef = 178;
 
 struct ExactOperand {
     const uint8_t *codes, *dial, *expo;
@@ -390,14 +379,6 @@ __device__ __forceinline__ ExactStat reduce_stat(ExactStat (&v)[N]) {
     }
     m.top = wave_max(m.top);
     return m;
-}
-
-// Whether sum |a||w| is at most 2^24 units for all of them: Cauchy-Schwarz over all blocks; or over the low blocks of one
-// operand, and its high blocks (outlier channels) by their sum of magnitudes times the other's largest.  (Infinite norms and
-// 0 times infinity fail every comparison.)
-__device__ __forceinline__ bool sums_exactly(const ExactStat& a, const ExactStat& w) {
-    return sqrtf(a.sq) * sqrtf(w.sq) <= kExactUnits || sqrtf(a.sq_low) * sqrtf(w.sq) + a.sum_high * w.top <= kExactUnits ||
-           sqrtf(a.sq) * sqrtf(w.sq_low) + a.top * w.sum_high <= kExactUnits;
 }
 
 constexpr int kRqPitch = 136;         // bf16 per staged output row (128 + 8: rows stay 16-byte aligned)
