@@ -234,9 +234,12 @@ int dfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const voi
 int mxfp4_gemm_prepared(dfp4_tensor A, void* a_prepared, dfp4_tensor W, const void* w_prepared, void* out,
                         int out_dtype, int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
 /*
- * Diagnostic: number of output tiles whose exponents spread beyond what int32 sums take in products on this prepared A
- * ([M, K]) since it was prepared (128 x 128 in the large kernel, 512 x 128 in gemm_f8_kernel, smaller ones for at most 256
- * rows of A).  Of these the parts without a proof that their fp32 sums are exact went the per-block fp32 path.  `count` is a HOST pointer.  Synchronizes with the device.
+ * Diagnostic: number of output tiles, in products on this prepared A ([M, K]) since it was prepared, whose exponents spread
+ * beyond what int32 sums take.  `count` is a HOST pointer.  Synchronizes with the device.  Counted are
+ *   by the large kernel (dfp4_gemm_path 0)   128 x 128 outputs that were summed with one fp32 addition per block;
+ *   by gemm_f8_kernel, more than 256 rows    512 x 128 outputs, by the operands' exponents alone: those of their tiles with a proof
+ *                                            that fp32 sums are exact were summed exactly, the others block by block;
+ *   by gemm_f8_kernel, at most 256 rows      its tiles (or the pieces they are computed again in) that were summed block by block.
  */
 int dfp4_gemm_declined_tiles(const void* a_prepared, int64_t M, int64_t K, uint32_t* count);
 /*

@@ -65,9 +65,12 @@ inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
 // takes everything the large one is not for (few rows, K beyond 16384), and the products it is estimated to finish sooner:
 // those with few output tiles, and batches whose packed A would be read only once or twice (P V of attention).  K of one
 // iteration of the direct kernel (Q K^T) goes there unless it is prepared already.  fast_cost is of the int8 kernel that
-// the large one replaced, which is faster everywhere: the line lies where it lay, so that no product changed to a slower
-// kernel, and on its direct side the large kernel is not far off (with its prepass / direct: 3000 x 5000 x 992 42 / 54 us,
-// 1188 x 2211 x 9472 61 / 106).
+// the large one replaced and choose_direct's estimates of int8 operands, so the line lies where it lay between those two.  The large kernel
+// gained more than the direct one, which leaves products on the direct side that it would finish sooner, up to 1.4 times (microseconds,
+// large with its prepass / direct):
+//   2048 x 4096 x 4096  46 / 62     512 x 4096 x 14336  74 / 105     1188 x 2211 x 9472  69 / 82     3000 x 5000 x 992  39 / 47
+//    777 x 3001 x 2080  38 / 24     512 x 4096 x  4096  49 /  32     1024 x 1024 x 4096  59 / 18     P V, 128 x 2048 x 128 x 2048  324 / 153
+// and of the sizes measured none on the large side the other way (4096 x 4096 x 4096 60 / 123, 2048 x 2048 x 14336 85 / 133).
 // An A operand of fewer rows than kPreparedMinRows is not packed ahead: its products read it as it is.
 constexpr int kPreparedMinRows = 257;
 inline bool large_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
@@ -207,7 +210,8 @@ __global__ void clear_count_kernel(uint32_t* count) {
 }  // namespace
 
 // Largest operands of a single launch: larger products are cut into pieces of at most this many rows on the host, larger
-// prepared operands are refused.
+// prepared operands are refused.  The bound of A is the documented one (its operand was once int8, 49152 bytes per 512 rows and block, with 31-bit
+// offsets); what the kernels index in 32 bits, rows x K / 32 x 16 bytes of codes and 65535 tiles of 256 rows, lies beyond both.
 static int64_t max_rows_a(int64_t KB) {
     const int64_t tiles = (((int64_t)1 << 31) - 1) / ((KB + 1) * 49152);
     return (tiles < 65535 ? tiles : 65535) * 512;

@@ -373,7 +373,7 @@ def gemm_prepared(a, w, dtype=torch.float32, out=None, workspace=None):
 
 
 def gemm_declined_tiles(a):
-    """dfp4_gemm_declined_tiles: tiles of products on this prepared A that took the per-block fp32 path."""
+    """dfp4_gemm_declined_tiles: tiles of products on this prepared A whose exponents spread beyond int32 sums (include/dfp4.h)."""
     n = ctypes.c_uint32(0)
     _check(load().dfp4_gemm_declined_tiles(_ptr(a.buf), a.q.rows, a.q.K, ctypes.byref(n)), "dfp4_gemm_declined_tiles")
     return int(n.value)

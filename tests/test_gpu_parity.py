@@ -445,7 +445,7 @@ def test_gemm_few_rows_both_forms_of_the_tile(scale, K, exact):
 
 
 def test_gemm_very_long_k_is_summed_exactly():
-    # K beyond the large kernel's range (more than 512 blocks): gemm_direct_kernel, exact while the sum fits int32
+    # K beyond the large kernel's range (more than 512 blocks): gemm_f8_kernel, exact while the sum fits int32
     M, N, K = 70, 64, 32 * 520
     print(f"gemm parity: long K {M}x{N}x{K}", flush=True)
     a = synth.gaussian(M, K, 1.0, seed=71)
@@ -962,7 +962,7 @@ def test_gemm_random_edge_shapes_all_paths():
         w = (torch.randn(N, K, generator=g) * 0.02).to(torch.bfloat16)
         ref, absdot = _gemm_ref(synth.to_f64(a), synth.to_f64(w))
         qa, qw = dfp4.quantize(_dev(a)), dfp4.quantize(_dev(w))
-        _assert_gemm_close(dfp4.gemm(qa, qw), ref, absdot, f"int8 path {M}x{N}x{K}")
+        _assert_gemm_close(dfp4.gemm(qa, qw), ref, absdot, f"exact path {M}x{N}x{K}")
         _assert_gemm_close(dfp4.gemm_native(qa, qw), ref, absdot, f"native path {M}x{N}x{K}")
         if N % 32 == 0:
             rq = dfp4.gemm_requant(qa, qw)
@@ -972,7 +972,7 @@ def test_gemm_random_edge_shapes_all_paths():
             assert torch.equal(rq.exponent, want.exponent)
         refm, absm = _gemm_ref(synth.to_f64(a), synth.to_f64(w), mx=True)
         qam, qwm = dfp4.mxfp4_quantize(_dev(a)), dfp4.mxfp4_quantize(_dev(w))
-        _assert_gemm_close(dfp4.mxfp4_gemm(qam, qwm), refm, absm, f"mx int8 path {M}x{N}x{K}")
+        _assert_gemm_close(dfp4.mxfp4_gemm(qam, qwm), refm, absm, f"mx exact path {M}x{N}x{K}")
         _assert_gemm_close(dfp4.mxfp4_gemm_native(qam, qwm), refm, absm, f"mx native path {M}x{N}x{K}")
 
 
@@ -1482,13 +1482,13 @@ def _check_outputs(out, ref, absdot, exact_rows, what):
     (1500, 4000, 1120, 6), (1000, 2049, 96, 7), (300, 2049, 16416, 4)])
 def test_gemm_direct_every_shape(M, N, K, path, wide):
     assert dfp4.gemm_path(M, N, K) == dfp4.gemm_path(M, N, K, prepared=True) == path
-    print(f"gemm_direct_kernel, path {path}: {M}x{N}x{K}, declined tiles {wide}", flush=True)
+    print(f"gemm_f8_kernel, path {path}: {M}x{N}x{K}, declined tiles {wide}", flush=True)
     rows = [32, 64, 64, 128, 128, 256, 128][path - 1]
     tile_rows = torch.arange(M, device="cuda") // rows
     exact = (tile_rows != M // 3 // rows) & (tile_rows != (M - 1) // rows) if wide else torch.ones(M, dtype=torch.bool, device="cuda")
     qa, qw, ref, absdot = _path_operands(M, N, K, wide)
     pa, pw = dfp4.gemm_prepare(qa, weight=False), dfp4.gemm_prepare(qw, weight=True)
-    # prepared operands of more than 256 rows are taken or declined by 512 x 128 outputs, as in gemm_fast_kernel
+    # prepared operands of more than 256 rows are taken or declined by 512 x 128 outputs
     exact_p = exact if M <= 256 or K > 16384 or not wide else (torch.arange(M, device="cuda") // 512 != M // 3 // 512) & (torch.arange(M, device="cuda") // 512 != (M - 1) // 512)
     for dtype in (torch.float32, torch.bfloat16):
         _check_outputs(dfp4.gemm(qa, qw, dtype=dtype), ref, absdot, exact, f"plain {dtype}")
@@ -1501,10 +1501,10 @@ def test_gemm_direct_every_shape(M, N, K, path, wide):
 @pytest.mark.parametrize("M,N,K,prepared", [
     (1552, 5664, 160, True), (518, 6686, 2848, True), (1188, 2211, 9472, True), (2338, 396, 16032, True),    # K whole, in 2, 4 and 8 shares
     (2320, 5408, 448, False), (793, 4639, 4896, False), (845, 2333, 11104, False)])                          # K whole, in 2 and 4
-def test_gemm_fast_kernel_plain_outputs(M, N, K, prepared, wide):
+def test_gemm_large_kernel_outputs(M, N, K, prepared, wide):
     # ragged results of the large kernel in both types, with classes on W and with declined tiles
     assert dfp4.gemm_path(M, N, K, prepared=prepared) == 0
-    print(f"gemm_fast_kernel: {M}x{N}x{K}, prepared {prepared}, declined tiles {wide}", flush=True)
+    print(f"the large kernel: {M}x{N}x{K}, prepared {prepared}, declined tiles {wide}", flush=True)
     tile_rows = torch.arange(M, device="cuda") // 512
     exact = (tile_rows != M // 3 // 512) & (tile_rows != (M - 1) // 512) if wide else torch.ones(M, dtype=torch.bool, device="cuda")
     qa, qw, ref, absdot = _path_operands(M, N, K, wide)
