@@ -93,14 +93,14 @@ PyObject* call(Py_ssize_t given, Py_ssize_t wanted, F&& f) {
         PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
         return nullptr;
     }
-    // torch's own exceptions (an exhausted device: torch.OutOfMemoryError) as torch.empty raises them
-    HANDLE_TH_ERRORS
     try {
         return f();
     } catch (const Failure&) {
-        return nullptr;
+    } catch (...) {
+        // as torch.empty raises them: an exhausted device is a torch.OutOfMemoryError
+        torch::translate_exception_to_python(std::current_exception());
     }
-    END_HANDLE_TH_ERRORS
+    return nullptr;
 }
 
 // quantize(x, block, mx) -> codes, dialect, exponent, rows, K
