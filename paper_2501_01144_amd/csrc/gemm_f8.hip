@@ -13,7 +13,7 @@
 // kernel's register count.  Microseconds of a call, plain inputs / outlier channels on A (x 50) and W (x 20), or A alone (x 200), without a second look,
 // so that such tiles were multiplied twice / with it:
 //   32 x 4096 x 4096  9.2 / 21.2, 20.6 / 12.9, 12.8      1500 x 4000 x 1120                20.3 / 113 / 24
-//   777 x 3001 x 2080  24 /   91,   85 / 30, 30          P V, 128 x 2048 x 2048 x 128       160 / 637 / 181
+//   777 x 3001 x 2080  24 /   91,   85 / 30, 30          P V, 128 x 2048 x 128 x 2048       155 / 637 / 181
 // The second look is vector-ALU work (a third of a product's time for either operand) and lost where it finds no proof: channels x 1000 on A at
 // K = 14336, 16 rows 84 -> 104, 512 rows 616 -> 694.
 //
@@ -21,10 +21,10 @@
 // both operands cost up to four products per pair of blocks.  Microseconds of a call with int8 / with FP8 operands (A with 0.5 %
 // outlier channels x 50, scores with two outlier dimensions on both):
 //   16 x 4096 x 4096      10.7 /  9.5     777 x 3001 x 2080     28.6 / 24.1     2048 x 4096 x 4096            78.7 / 65.7
-//   16 x 14336 x 4096     17.2 / 14.6     512 x 4096 x 4096     37.2 / 30.7     scores, 128 x 2048 x 2048 x 128  487 / 382
-//   36 x 7898 x 1344      10.9 /  9.0     512 x 4096 x 14336     110 / 100      P V, 128 x 2048 x 2048 x 128     210 / 195
+//   16 x 14336 x 4096     17.2 / 14.6     512 x 4096 x 4096     37.2 / 30.7     scores, 128 x 2048 x 2048 x 128  487 / 366
+//   36 x 7898 x 1344      10.9 /  9.0     512 x 4096 x 14336     110 / 100      P V, 128 x 2048 x 128 x 2048     210 / 155
 // and, on prepared operands of more than 256 rows (where the references and classes were there already),
-//   300 x 4096 x 4096     32.7 / 26.9     777 x 3001 x 2080     30.1 / 25.4     1500 x 4000 x 1120            23.5 / 21.3
+//   300 x 4096 x 4096     32.7 / 26.9     777 x 3001 x 2080     30.1 / 25.4     1500 x 4000 x 1120            23.5 / 20.3
 // What bounds it: as before nothing alone.  An item is about 60 vector-ALU instructions, and the expansion, the LDS traffic and the
 // products of a workgroup's few waves overlap only in part.  Tried: one operand buffer and three or four waves per SIMD for the
 // 128 x 128 and 256 x 128 tiles (3 to 18 % slower); four waves per SIMD for the tiles of one iteration (scores above 369, but 16 x 700 x 1312 x
