@@ -77,7 +77,7 @@ struct F8Lds {
     uint8_t lo[S::KG][S::kRows];                                       // ... smallest exponent byte (255: all zero) ...
     uint8_t ok[S::KG][S::kRows];                                       // ... and whether all are in range
     ExactStat part[S::KG > 1 ? S::KG : 1][S::KG > 1 ? S::kRows : 1];   // of the groups, second look
-    int norm[2][5];                                                    // of A's, of W's rows in their units, the largest (bits): squared norm; ExactStat
+    int norm[2][8];                                                    // of A's, of W's rows in their units, the largest (bits): squared norm; ExactStat
 };
 
 template <int CTRL>
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         ends[j] = v2u{0, 0};
     }
     for (int i = tid; i < (kDialects + 1) * 4; i += S::kThreads) (&lds.tab[0][0])[i] = (&g_f8_book.w[0][0])[i];
-    if (tid < 10) lds.norm[tid / 5][tid % 5] = 0;
+    if (tid < 16) (&lds.norm[0][0])[tid] = 0;
     __syncthreads();
 
     const int wm = wave / S::WN, wn = wave % S::WN, h = lane >> 5, r = lane & 31;
@@ -258,25 +258,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     };
     using First = std::integral_constant<int, 0>;
     using Second = std::integral_constant<int, 1>;
-    auto products_once = [&] {                                         // kOnce
-        Scales s;
-        read_scales(s, 0);
-        Operands o;
-        read(o, 0, 0);
-        multiply(o, s, First{});
-        if (KB > 2) {
-            read(o, 0, 1);
-            multiply(o, s, Second{});
-        }
-    };
     if constexpr (S::kOnce) {
         if (KB > 0) {
 #pragma unroll
             for (int j = 0; j < S::kItems; ++j) expand(item[j], j, table(item[j], 0), 0, 0);
         }
         finish_norms();
-        __syncthreads();
-        if (KB > 0) products_once();
+        __syncthreads();                                               // (its products follow once it is known whether they are wanted)
     } else if constexpr (S::kPrivate) {
         // one wave: its LDS operations execute in order, so lanes exchange operands without a barrier; the fences keep
         // the compiler to that order (they cost no instruction).  4 waves per SIMD hide the latencies
@@ -355,9 +343,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         finish_norms();
     }
     if constexpr (!S::kOnce) __syncthreads();
-    // the thread's place, taken anew: nothing of it is kept in registers through the products for what follows
+    // the thread's place, where registers are short taken anew: nothing of it is kept through the products for what follows
     int tid_ = threadIdx.x;
-    asm volatile("" : "+v"(tid_));
+    if constexpr (S::KG > 1) asm volatile("" : "+v"(tid_));
     const int lane_ = tid_ & 63, h_ = lane_ >> 5, r_ = lane_ & 31;
     constexpr int kOut = TI * TJ * 16;
     float* sums = lds.sums + (S::kOnce ? 0 : (kg * S::WM * S::WN + wave) * kOut * 64 + lane_);          // of this lane
@@ -386,7 +374,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
             }
         }
     };
-    constexpr bool kPutEarly = S::KG > 1 && TI * TJ == 1;              // (a barrier less; 64 registers are too much LDS traffic before it: 13.4 -> 14.0 us for 249 x 11523 x 640)
+    // The groups' sums go to LDS ahead of the norms' barrier, which saves one, where they are few; 64 registers delay it (249 x 11523 x 640 13.4 -> 14.0 us)
+    constexpr bool kPutEarly = S::KG > 1 && TI * TJ == 1;
     if constexpr (S::KG > 1) {
         if constexpr (kPutEarly) put_sums();
         over_groups(std::integral_constant<int, 1>{}, 0, 0, S::kRows, [&](int row, float (&v)[1]) {
@@ -408,12 +397,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
     const bool looked = !proven && fmaxf(norm(0, 0), norm(1, 0)) < __builtin_inff();
     if (looked) {
         // A second look at the codes: what exact_prep_kernel keeps of a prepared operand (ExactStat), first of W, whose norm was a
-        // bound, then of A.  The sums are in LDS meanwhile (K of one iteration: the operands still are) and set no register count.
+        // bound, then of A.  The sums are in LDS meanwhile and set no register count (K of one iteration: there are none yet).
         if constexpr (!kPutEarly && !S::kOnce) put_sums();
         auto look = [&](auto side_c) {
             constexpr int kSide = decltype(side_c)::value, kFirst = kSide == 0 ? 0 : S::kItemsA;
             constexpr int kN = kSide == 0 ? S::kItemsA : S::kItems - S::kItemsA;
-            constexpr int kAhead = S::kOnce ? 1 : 2;                   // iterations whose loads are on their way
+            constexpr int kAhead = S::KG == 1 ? 1 : 2;                 // iterations whose loads are on their way
             Item next[kAhead][kN];
             float sq2[kN], low[kN], high[kN];                          // of this thread's blocks of the rows
             int ref[kN], far[kN];
@@ -507,14 +496,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         const float inf = __builtin_inff();
         proven = sums_exactly(ExactStat{norm(0, 0), inf, inf, sqrtf(norm(0, 0))}, w);          // (an element is at most the norm of its row)
         if (!proven) proven = sums_exactly(look(std::integral_constant<int, 0>{}), w);
-        if (S::KG == 1 && proven) {
+        if (S::KG == 1 && !S::kOnce && proven) {
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
                 for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                    for (int x = 0; x < 16; ++x) acc[i][j][x] = S::kOnce ? 0.0f : sums[((i * TJ + j) * 16 + x) * 64];
-            if constexpr (S::kOnce) products_once();
+                    for (int x = 0; x < 16; ++x) acc[i][j][x] = sums[((i * TJ + j) * 16 + x) * 64];
         }
     }
     if (!proven) {
@@ -530,6 +518,20 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
             __syncthreads();
         }
         return;
+    }
+
+    if constexpr (S::kOnce) {
+        if (KB > 0) {
+            Scales s;
+            read_scales(s, 0);
+            Operands o;
+            read(o, 0, 0);
+            multiply(o, s, First{});
+            if (KB > 2) {
+                read(o, 0, 1);
+                multiply(o, s, Second{});
+            }
+        }
     }
 
     // ---- results
