@@ -9,13 +9,14 @@
 // taken while the items are expanded: of A from its codes, of W, which has most of the rows where A has few, up to K = 6144 from its
 // exponents alone (||w||^2 <= sum over blocks of 32 15^2 4^offset: about three times the norm of Gaussian data, more with outliers) and
 // beyond from its codes.  A tile without a proof looks at the codes a second time, first W's, then A's, for the three bounds of
-// gemm_native.hip; one that passes none is computed again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the
-// kernel's register count.  Microseconds of a call, plain inputs / outlier channels on A (x 50) and W (x 20), or A alone (x 200), without a second look,
+// gemm_native.hip, over all of K or over every group's share of it (the groups' sums are added with one rounding); one that passes none is computed
+// again in int32 (gemm_int8_tile.h), in pieces small enough that they do not set the kernel's register count.  Microseconds of a call, plain inputs / outlier channels on A (x 50) and W (x 20), or A alone (x 200), without a second look,
 // so that such tiles were multiplied twice / with it:
 //   32 x 4096 x 4096  9.2 / 21.2, 20.6 / 12.9, 12.8      1500 x 4000 x 1120                20.3 / 113 / 24
 //   777 x 3001 x 2080  24 /   91,   85 / 30, 30          P V, 128 x 2048 x 128 x 2048       155 / 637 / 181
-// The second look is vector-ALU work (a third of a product's time for either operand) and lost where it finds no proof: channels x 1000 on A at
-// K = 14336, 16 rows 84 -> 104, 512 rows 616 -> 694.
+// The bound of every group's share (without it / with it): channels x 1000 on A, 16 x 4096 x 14336 104 / 46, 700 x 1024 x 8192 217 / 53; W x 100 and
+// A x 50, 250 x 4096 x 4096 120 / 29.  The second look is vector-ALU work (a third of a product's time for either operand) and lost where it finds no
+// proof: channels x 1000 on A, 512 x 4096 x 14336 616 -> 697.
 //
 // This took the place of int8 operands with classes (gemm_int8_tile.h).  There a pass over the exponents came first, and classes on
 // both operands cost up to four products per pair of blocks.  Microseconds of a call with int8 / with FP8 operands (A with 0.5 %
@@ -77,7 +78,7 @@ struct F8Lds {
     uint8_t lo[S::KG][S::kRows];                                       // ... smallest exponent byte (255: all zero) ...
     uint8_t ok[S::KG][S::kRows];                                       // ... and whether all are in range
     ExactStat part[S::KG > 1 ? S::KG : 1][S::KG > 1 ? S::kRows : 1];   // of the groups, second look
-    int norm[2][8];                                                    // of A's, of W's rows in their units, the largest (bits): squared norm; ExactStat
+    int norm[2][8];                                                    // of A's, of W's rows in their units, the largest (bits): squared norm; ExactStat; [0][5] groups without a proof
 };
 
 template <int CTRL>
@@ -496,6 +497,39 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_f8_kernel(
         const float inf = __builtin_inff();
         proven = sums_exactly(ExactStat{norm(0, 0), inf, inf, sqrtf(norm(0, 0))}, w);          // (an element is at most the norm of its row)
         if (!proven) proven = sums_exactly(look(std::integral_constant<int, 0>{}), w);
+        if constexpr (S::KG > 1) {
+            if (!proven) {
+                // It is enough that every group's sums are exact, if adding them rounds once: every wave bounds its group's
+                ExactStat a{0, 0, 0, 0}, b{0, 0, 0, 0};
+#pragma unroll
+                for (int row = 0; row < S::kRows; row += 32) {
+                    const ExactStat v = lds.part[kg][row + (lane_ & 31)];
+                    ExactStat& m = row < S::kTm ? a : b;
+                    m = ExactStat{fmaxf(m.sq, v.sq), fmaxf(m.sq_low, v.sq_low), fmaxf(m.sum_high, v.sum_high), fmaxf(m.top, v.top)};
+                }
+#pragma unroll
+                for (int o = 1; o < 32; o <<= 1) {
+                    a = ExactStat{fmaxf(a.sq, __shfl_xor(a.sq, o)), fmaxf(a.sq_low, __shfl_xor(a.sq_low, o)), fmaxf(a.sum_high, __shfl_xor(a.sum_high, o)), fmaxf(a.top, __shfl_xor(a.top, o))};
+                    b = ExactStat{fmaxf(b.sq, __shfl_xor(b.sq, o)), fmaxf(b.sq_low, __shfl_xor(b.sq_low, o)), fmaxf(b.sum_high, __shfl_xor(b.sum_high, o)), fmaxf(b.top, __shfl_xor(b.top, o))};
+                }
+                if (!sums_exactly(a, b) && lane_ == 0) atomicOr(&lds.norm[0][5], 1);
+                __syncthreads();
+                proven = lds.norm[0][5] == 0;
+                if (S::KG > 2 && proven) {
+                    // (two are: one addition.)  The outputs that this thread finishes below, at most 2^27 units: added here, zeros left for there
+#pragma unroll 1
+                    for (int o = kg * (kOut / S::KG); o < (kg + 1) * (kOut / S::KG); ++o) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int g = S::KG - 1; g >= 0; --g) {
+                            float& part = lds.sums[((g * S::WM * S::WN + wave) * kOut + o) * 64 + lane_];
+                            sum += (double)part;
+                            part = g == 0 ? (float)sum : 0.0f;
+                        }
+                    }
+                }
+            }
+        }
         if (S::KG == 1 && !S::kOnce && proven) {
 #pragma unroll
             for (int i = 0; i < TI; ++i)
