@@ -166,12 +166,12 @@ int dfp4_dequantize(dfp4_tensor in, void* y, int y_dtype, int64_t ld_elems, void
  *   out[m, n] = sum over blocks kb of 2^(ea[m,kb] + ew[n,kb] - 2) *
  *               sum over k in kb of (+-ua[m,k]) * (+-uw[n,k])
  * with u the 4-bit unsigned integers (half-units) the codes index.  The sum is exact,
- * rounded once to the output type: large products run on the block-scaled matrix instruction
- * where norms of the operands' rows show that no partial sum exceeds the 24 bits of fp32, all
- * others on the int8 matrix cores with int32 accumulation (exponent offsets folded into the
- * operands), where the block exponents of a tile span at most 12 binades per row.  Output
- * tiles whose exponents spread further than either takes are accumulated in fp32, one
- * addition per block, by the workgroup that finds them.
+ * rounded once to the output type: on the block-scaled matrix instruction for tiles of the
+ * output where norms of the operands' rows show that no partial sum exceeds the 24 bits of
+ * fp32, on the int8 matrix cores with int32 accumulation (exponent offsets folded into the
+ * operands) for others whose block exponents span at most 12 binades per row.  Tiles whose
+ * exponents spread further than either takes are accumulated in fp32, one addition per
+ * block, by the workgroup that finds them.
  *   A        quantized [M, K]; W quantized [N, K] (both blocked along K)
  *   out      device, [M, N] row-major, leading dimension ldc (elements, N <= ldc < 2^27);
  *            out_dtype DFP4_F32 or DFP4_BF16 (round to nearest even)
