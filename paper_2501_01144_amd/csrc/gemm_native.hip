@@ -37,6 +37,10 @@
 // than 2^24 of these every partial sum, in any order, is a whole number that fp32 holds.  The matrix instruction adds
 // such terms exactly (3.2 million outputs of single instructions with sums of absolute terms below 2^24 units, block
 // offsets up to 16 binades and addends up to 2^23.9 checked: none off; its alignment keeps 24 bits).
+// One exception: 0.5 is a subnormal number of both formats, and the instruction aligns a product of two of them as if it were four times as
+// large.  With blocks 23 binades up, where such a product is 2^23 units, the last bit of the sum is lost (2.4e9 outputs below 2^24 units
+// checked: none off but of these; FP8, where 0.5 is normal: none).  A dialect's largest magnitude is 8 units or more, so that the product of two
+// blocks' largest is 2^29 or more there; blocks that a quantizer has made hold a magnitude of 8 at least and have no proof then anyway.
 // exact_prep_kernel therefore computes, beside the packed form, norms of the rows in units (ExactStat), and a workgroup
 // compares three bounds of sum |a||w| with 2^24 after its main loop.  A tile that passes none is computed again in
 // int32 from the 4-bit operands by the same workgroup (gemm_int8_tile.h).  On activations with 0.5 % outlier channels
@@ -381,6 +385,7 @@ __device__ __forceinline__ ExactStat reduce_stat(ExactStat (&v)[N]) {
     return m;
 }
 
+constexpr float kSubnormalUnits = 536870912.0f;      // 2^29, see the file header
 constexpr int kRqPitch = 136;         // bf16 per staged output row (128 + 8: rows stay 16-byte aligned)
 // requantizing epilogue: quantizer tables and, per wave, 64 rows x 128 columns of bf16 results, where the operands were
 struct RequantLds {
@@ -526,7 +531,8 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         for (int i = 0; i < TA / 2; ++i) asm volatile("" : "+v"(stat_a[i].sq), "+v"(stat_a[i].sq_low), "+v"(stat_a[i].sum_high), "+v"(stat_a[i].top));
 #pragma unroll
         for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(stat_w[i].sq), "+v"(stat_w[i].sq_low), "+v"(stat_w[i].sum_high), "+v"(stat_w[i].top));
-        const bool exact = sums_exactly(reduce_stat(stat_a), reduce_stat(stat_w));
+        const ExactStat top_a = reduce_stat(stat_a), top_w = reduce_stat(stat_w);
+        const bool exact = sums_exactly(top_a, top_w) && top_a.top * top_w.top < kSubnormalUnits;
         if (lane == 0) s_ctl[wave] = exact ? 1 : 0;
         __syncthreads();                                     // and the operands in LDS are done with
         if (__builtin_amdgcn_readfirstlane(s_ctl[0] & s_ctl[1] & s_ctl[2] & s_ctl[3]) == 0) {

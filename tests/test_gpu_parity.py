@@ -1678,6 +1678,32 @@ def test_gemm_exact_sums_at_the_limit(M, N, K, prepared, path, mx, over):
     assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
 
 
+@pytest.mark.parametrize("M,N,K", [(1552, 5664, 160), (518, 6686, 2848), (2338, 396, 16032), (2304, 4096, 4096)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_gemm_exact_sums_with_a_large_product(M, N, K, mx):
+    # One product of 2^23 units beside units: below 2^24 in all, and yet the block-scaled instruction drops the last bit of its sum where
+    # both factors are the smallest magnitude (a subnormal FP6 or FP4 number) of blocks 23 binades up.
+    assert dfp4.gemm_path(M, N, K, prepared=True) == 0
+    print(f"gemm, one product of 2^23 units: {M}x{N}x{K}, mx {mx}", flush=True)
+    g, KB = torch.Generator(device="cuda").manual_seed(K + M), K // 32
+    def operand(rows, up, base):
+        idx = (torch.rand(rows, KB, 32, generator=g, device="cuda") < 0.2).long()  # u = 1 or 0
+        sign = torch.randint(0, 2, idx.shape, generator=g, device="cuda")
+        delta, kb = torch.zeros(rows, KB, dtype=torch.long, device="cuda"), KB - 2
+        idx[:, kb], idx[:, kb, 5], delta[:, kb] = 0, 1, up
+        dial = torch.randint(0, 16, (rows, KB), generator=g, device="cuda")        # index 1 is u = 1 in all
+        whole = idx * (1 - 2 * sign) << delta.unsqueeze(-1)
+        code = ((sign << 3) | idx).view(rows, K // 2, 2)
+        return dfp4.QTensor((code[..., 0] | (code[..., 1] << 4)).to(torch.uint8), None if mx else dial.to(torch.uint8),
+                            (delta + base).to(torch.uint8), rows, K), whole.view(rows, K).double()
+    (qa, a), (qw, w) = operand(M, 11, 121), operand(N, 12, 118)
+    units = a @ w.T
+    assert float((a.abs() @ w.abs().T).max()) < 2 ** 24 and bool((units.long() & 1).any())
+    out = dfp4.gemm_prepared(dfp4.gemm_prepare(qa, weight=False, mx=mx), dfp4.gemm_prepare(qw, weight=True, mx=mx))
+    torch.cuda.synchronize()
+    assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
+
+
 # --------------------------------------------------------------------------
 # Calls that allocate their result raise what torch.empty raises.
 # --------------------------------------------------------------------------
