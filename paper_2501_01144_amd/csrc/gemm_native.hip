@@ -1,6 +1,6 @@
-// Block-scaled GEMM on the CDNA4 scaled matrix instruction
-// (v_mfma_scale_f32_32x32x64_f8f6f4): out = A * W^T with one power-of-two scale per
-// 32 elements along K applied by the hardware, fp32 accumulation.
+// Block-scaled GEMM on the CDNA4 scaled matrix instructions
+// (v_mfma_scale_f32_16x16x128_f8f6f4, few rows v_mfma_scale_f32_32x32x64_f8f6f4): out = A * W^T with
+// one power-of-two scale per 32 elements along K applied by the hardware, fp32 accumulation.
 //
 // Two operand formats:
 //   FP4 (E2M1)  MXFP4 tensors are multiplied as they are: the 4-bit code (sign, 3-bit
@@ -12,11 +12,11 @@
 // (Section 3.3 of the paper builds its MAC from integer products because its values are
 // not a standard format; on this GPU a standard format covers them.)
 //
-// Operand layout of the instruction (checked on the hardware): lane l supplies row or
-// column l % 32 and the 32 consecutive K elements of block l / 32 of the pair, element j
-// in bits [w j, w j + w) of its operand registers (w = 4 or 6); the scale is the byte of
-// the scale register that op_sel names, 2^(byte - 127).  Output as the other 32x32 MFMAs:
-// register x of lane (h, c) is row 8 (x / 4) + 4 h + x % 4, column c.
+// Operand layout of the instructions (checked on the hardware): lane l supplies row or
+// column l % 32 (l % 16) and the 32 consecutive K elements of block l / 32 of the pair (l / 16 of
+// the four), element j in bits [w j, w j + w) of its operand registers (w = 4 or 6); the scale is
+// the byte of the scale register that op_sel names, 2^(byte - 127).  Output as the other
+// MFMAs: register x of lane (h, c) is row 8 (x / 4) + 4 h + x % 4, column c, of lane (q, c) row 4 q + x.
 //
 // Kernels.  native_pack_kernel rewrites an operand in the order the matrix instruction
 // wants it (per 32-row tile and step, 64 lanes x 16 bytes, for FP6 another 64 lanes x 8
@@ -24,9 +24,9 @@
 // tiles), so that the multiply kernel's loads are whole lines; weights are packed once,
 // offline, and quantize_native_kernel (quantize.hip) writes an activation in this form
 // directly.  gemm_native_kernel: 256 x 256 outputs per workgroup, four waves as 2 x 2, each
-// 128 x 128 (16 accumulator tiles = 256 registers, one wave per SIMD), or 128 x 256 per
-// workgroup when there are few tiles; operands go global -> LDS by direct loads five
-// or seven steps ahead, LDS -> registers one step ahead, one barrier per step; the
+// 128 x 128 (64 accumulator tiles = 256 registers, one wave per SIMD), or 128 x 256 per
+// workgroup when there are few tiles; operands go global -> LDS by direct loads two or three
+// iterations of K = 128 ahead, LDS -> registers one ahead, one barrier per iteration; the
 // main loop is generated assembly (gen_native_loop.py).  With very few tiles K is split
 // between workgroups and native_reduce_kernel adds their fp32 partial tiles in a fixed order.
 //
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void native_pack_kernel(PackParams p) {
         const uint32_t tlo = g_fp6_book.w[dl][0], thi = g_fp6_book.w[dl][1];
         const Fp6Lane v = pack6_lane(codes, tlo, thi);
         *reinterpret_cast<uint4*>(p.dst.bits + fp6_lo(tile, s, p.S) + lane * 16) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
-        *reinterpret_cast<uint2*>(p.dst.bits + fp6_hi(tile, s, p.S) + lane * 8) = make_uint2(v.w[4], v.w[5]);
+        *reinterpret_cast<uint2*>(p.dst.bits + fp6_hi(tile, s, p.S) + fp6_hi_lane(lane) * 8) = make_uint2(v.w[4], v.w[5]);
     }
     reinterpret_cast<uint8_t*>(p.dst.sc)[(((int64_t)(tile >> 2) * p.S + s) * 64 + lane) * 4 + (tile & 3)] = (uint8_t)eb;
 }
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) 
                     reinterpret_cast<uint4*>(dst)[((int64_t)tile * p.S + st) * 64 + lane] = lo;
                 } else {
                     *reinterpret_cast<uint4*>(dst + fp6_lo(tile, st, p.S) + lane * 16) = lo;
-                    *reinterpret_cast<uint2*>(dst + fp6_hi(tile, st, p.S) + lane * 8) =
+                    *reinterpret_cast<uint2*>(dst + fp6_hi(tile, st, p.S) + fp6_hi_lane(lane) * 8) =
                         *reinterpret_cast<const uint2*>(s_hi + half * kHiPitch + (lane & 31) * 8);
                 }
             }
@@ -386,6 +386,13 @@ __device__ __forceinline__ ExactStat reduce_stat(ExactStat (&v)[N]) {
 }
 
 constexpr float kSubnormalUnits = 536870912.0f;      // 2^29, see the file header
+// two results in bf16 (round to nearest even), the first in the low half
+__device__ __forceinline__ uint32_t bf16_pair(int a, int b) {
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)}, v2b));
+}
+
 constexpr int kRqPitch = 136;         // bf16 per staged output row (128 + 8: rows stay 16-byte aligned)
 // requantizing epilogue: quantizer tables and, per wave, 64 rows x 128 columns of bf16 results, where the operands were
 struct RequantLds {
@@ -456,7 +463,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     __shared__ int s_ctl[5];                                 // exact: per wave, whether its sums are exact; arrivals (split K)
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = lane >> 5, c = lane & 31;
+    const int q = lane >> 4, c = lane & 15;
     const int wm = (int)wave >> 1, wn = (int)wave & 1;
     // this workgroup's range of steps (split K: blockIdx.z, in exact products below the problem of a batch)
     const int per = (p.S + p.ksplit - 1) / p.ksplit;
@@ -490,17 +497,21 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         const uint64_t sb = wave < 2
             ? reinterpret_cast<uint64_t>(p.a.sc) + (TA == 4 ? (uint64_t)blockIdx.y * 2 + wave : (uint64_t)blockIdx.y) * (uint64_t)p.S * 256
             : reinterpret_cast<uint64_t>(p.w.sc) + ((uint64_t)blockIdx.x * 2 + (wave - 2)) * (uint64_t)p.S * 256;
-        const uint32_t l16 = (uint32_t)lane * 16u, l8 = (uint32_t)lane * 8u, l4 = (uint32_t)lane * 4u;
-        const uint32_t g16 = l16 + (uint32_t)s_lo * kGStride;
-        const uint32_t g4 = l4 + (uint32_t)s_lo * 256u;
+        const uint32_t l16 = (uint32_t)lane * 16u, l4 = (uint32_t)lane * 4u;
+        // LDS offsets of lane (q, c): stage q / 2 of a slot, block q % 2 of row c
+        const uint32_t q_at = (uint32_t)(q >> 1) * kStage, q_blk = (uint32_t)((q & 1) * 32 + c);
+        const uint32_t r16 = q_at + q_blk * 16u, r8 = q_at + ((uint32_t)(q & 1) * 16u + (uint32_t)c) * 8u, r4 = q_at + q_blk * 4u;
+        const uint32_t g16 = l16 + (uint32_t)s_lo * kGStride, g4 = l4 + (uint32_t)s_lo * 256u;
+        const uint32_t iters = (uint32_t)(S + 1) / 2u;
 #define DFP4_NATIVE_RUN(LOOP)                                                                                     \
         asm volatile(LOOP                                                                                           \
                      :                                                                                              \
                      : [alo] "s"((uint32_t)ab), [ahi] "s"((uint32_t)(ab >> 32)), [blo] "s"((uint32_t)bb),        \
                        [bhi] "s"((uint32_t)(bb >> 32)), [slo] "s"((uint32_t)sb), [shi] "s"((uint32_t)(sb >> 32)), \
                        [tstride] "s"(tstride), [wv] "s"(wave), [lds] "s"(lds),                                      \
-                       [ldsend] "s"(lds + (uint32_t)(kStages * kStage)), [steps] "s"((uint32_t)S),                  \
-                       [l16] "v"(l16), [l8] "v"(l8), [l4] "v"(l4), [g16] "v"(g16), [g4] "v"(g4)                   \
+                       [iters] "s"(iters),                                                                           \
+                       [half] "s"((S & 1) ? iters - 1u : 0xffffffffu),                                              \
+                       [g16] "v"(g16), [g4] "v"(g4), [r16] "v"(r16), [r8] "v"(r8), [r4] "v"(r4)                   \
                      : DFP4_NATIVE_VGPR_CLOBBERS, DFP4_NATIVE_ACC_CLOBBERS, DFP4_NATIVE_SGPR_CLOBBERS, "m0", "scc", \
                        "memory")
         if constexpr (kFp6 && TA == 4) DFP4_NATIVE_RUN(DFP4_NATIVE_LOOP_FP6);
@@ -510,9 +521,8 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
 #undef DFP4_NATIVE_RUN
     }
 
-    // epilogue: fp32 (or bf16, round to nearest even) [M, N]; accumulator tile (i, j) = 4 i + j.
-    // Register x of lane (kh, c) is row 32 i + 8 (x / 4) + 4 kh + x % 4, column 32 j + c.  Row
-    // addresses are wave-uniform (scalar registers); the lane adds a constant byte offset.
+    // epilogue: fp32 (or bf16, round to nearest even) [M, N].  Accumulator registers come in groups of 16: group G is row tile
+    // G / 2 (of 16 rows), columns 64 (G % 2) + ..; register 4 j + x of lane (q, c) is row c, column 16 j + 4 q + x of it.
     const int m0 = blockIdx.y * kRowsWg + wm * kRowsWave, n0 = blockIdx.x * 256 + wn * 128;
 #define DFP4_NATIVE_READ(G, V)                                                                      \
     asm volatile(DFP4_NATIVE_ACC_READ_##G                                                           \
@@ -592,8 +602,9 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
             __syncthreads();
         }
     }
+    if constexpr (MODE == kPlain) __syncthreads();               // the operands in LDS are done with
     if (m0 >= p.M || n0 >= p.N) return;
-    // accumulator tile G, with the other ranges' partial sums in exact products
+    // accumulator group G, with the other ranges' partial sums in exact products
     auto finish = [&](auto g_c, int (&v)[16]) {
         if constexpr (MODE != kPlain) {
             if (p.ksplit > 1) {
@@ -623,9 +634,9 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
                 int v[16];                                                                          \
                 DFP4_NATIVE_READ(G, v);                                                             \
                 finish(std::integral_constant<int, G>{}, v);                                        \
-                _Pragma("unroll") for (int x = 0; x < 16; ++x)                                      \
-                    st[(((G >> 2) & 1) * 32 + 8 * (x >> 2) + 4 * kh + (x & 3)) * kRqPitch + (G & 3) * 32 + c] = \
-                        f32_to_bf16_rne(__builtin_bit_cast(float, v[x]));                           \
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)                                       \
+                    *reinterpret_cast<uint2*>(&st[(((G >> 1) & 3) * 16 + c) * kRqPitch + (G & 1) * 64 + 16 * j + 4 * q]) = \
+                        make_uint2(bf16_pair(v[4 * j], v[4 * j + 1]), bf16_pair(v[4 * j + 2], v[4 * j + 3])); \
             }
             DFP4_NATIVE_TILES(DFP4_NATIVE_STAGE)
 #undef DFP4_NATIVE_STAGE
@@ -658,58 +669,87 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     uint8_t* wave_out = base + ((int64_t)m0 * ld + n0) * kEsz;                                 // uniform
     const int64_t row_bytes = ld * kEsz;                                                       // uniform
     const bool full = m0 + kRowsWave <= p.M && n0 + 128 <= p.N;                                // uniform
-    // bf16: lanes exchange values in pairs so that every lane stores two adjacent columns of one
-    // row (even lanes the even row of a row pair, odd lanes the odd row)
-    const bool pairs = BF16 && full && (ld & 1) == 0 && (reinterpret_cast<uintptr_t>(base) & 3) == 0;
-    const uint32_t lane_off = pairs ? (uint32_t)((4 * kh + (c & 1)) * row_bytes + (c & ~1) * kEsz)
-                                    : (uint32_t)(4 * kh * row_bytes + c * kEsz);
-    auto store_tile = [&](auto full_c, auto pairs_c, int t, int (&v)[16]) {
-        constexpr bool kFull = decltype(full_c)::value, kPairs = decltype(pairs_c)::value;
-        const int i = t >> 2, j = t & 3;
-        uint8_t* tile_out = wave_out + (int64_t)i * 32 * row_bytes + j * 32 * kEsz;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint8_t* rowp = tile_out + (int64_t)(8 * q) * row_bytes;                           // uniform
-            if constexpr (BF16 && kPairs) {
-#pragma unroll
-                for (int jj = 0; jj < 4; jj += 2) {
-                    const uint32_t b0 = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj]));
-                    const uint32_t b1 = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj + 1]));
-                    const uint32_t send = (c & 1) ? b0 : b1;
-                    const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xf, 0xf, true);
-                    const uint32_t word = (c & 1) ? (recv | (b1 << 16)) : (b0 | (recv << 16));
-                    *reinterpret_cast<uint32_t*>(rowp + (int64_t)jj * row_bytes + lane_off) = word;
-                }
-            } else {
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    if (kFull || (m0 + i * 32 + 8 * q + 4 * kh + jj < p.M && n0 + j * 32 + c < p.N)) {
-                        uint8_t* dst = rowp + (int64_t)jj * row_bytes + lane_off;
-                        if constexpr (BF16)
-                            *reinterpret_cast<uint16_t*>(dst) = f32_to_bf16_rne(__builtin_bit_cast(float, v[4 * q + jj]));
-                        else
-                            *reinterpret_cast<int*>(dst) = v[4 * q + jj];
-                    }
-                }
-            }
-        }
+    // Results go through the wave's part of LDS, a group (16 rows x 64 columns) at a time, so that neighbouring lanes store neighbouring columns: 16 bytes
+    // each where rows allow that, otherwise one element, or two of bf16.  (As the lanes hold them, 16 bytes of 16 rows to 16 neighbouring lanes,
+    // each lane's bytes were a write of their own: 7.5 us of fp32 and 3.8 of bf16 per tile of 256 x 256 instead of 5.6 and 2.4.  All compute
+    // units together store at the rate of their L2 caches, 11 TB/s; bf16 before, by integer arithmetic and two columns a lane, 4.5.)
+    constexpr int kPitch = BF16 ? 36 : 68, kLanes = BF16 ? 8 : 16;                                 // dwords of a row in LDS; lanes per row
+    constexpr int kWide = kLanes / 4;                                                              // 16-byte stores of a lane
+    uint32_t* st = reinterpret_cast<uint32_t*>(s_stage) + wave * (16 * kPitch);
+    const bool wide = full && (row_bytes & 15) == 0 && (reinterpret_cast<uintptr_t>(base) & 15) == 0;
+    const bool pairs = BF16 && (ld & 1) == 0 && (reinterpret_cast<uintptr_t>(base) & 3) == 0;
+    auto in_order = [] {                                     // a wave's LDS operations execute in order; this keeps the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    auto stage_group = [&](int (&v)[16]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (BF16)
+                *reinterpret_cast<uint2*>(st + c * kPitch + 8 * j + 2 * q) = make_uint2(bf16_pair(v[4 * j], v[4 * j + 1]), bf16_pair(v[4 * j + 2], v[4 * j + 3]));
+            else
+                *reinterpret_cast<int4*>(st + c * kPitch + 16 * j + 4 * q) = make_int4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+        }
+        in_order();
+    };
+    if (wide) {
+        const int lr = lane / kLanes, lc = lane % kLanes;
+        const int64_t lane_off = lr * row_bytes + lc * 16;
+        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+        v4u line0, line1, line2, line3;                      // of the group before: stored while the next is on its way through LDS
+        auto line_of = [&](int k) { return *reinterpret_cast<const v4u*>(st + (k * (16 / kWide) + lr) * kPitch + lc * 4); };
+        auto store_line = [&](int g, int k, v4u line) {
+            *reinterpret_cast<v4u*>(wave_out + (int64_t)((g >> 1) * 16 + k * (16 / kWide)) * row_bytes + (g & 1) * 64 * kEsz + lane_off) = line;
+        };
+#define DFP4_NATIVE_LINES(G)                                                                        \
+        store_line(G, 0, line0);                                                                    \
+        store_line(G, 1, line1);                                                                    \
+        if constexpr (!BF16) {                                                                      \
+            store_line(G, 2, line2);                                                                \
+            store_line(G, 3, line3);                                                                \
+        }
 #define DFP4_NATIVE_STORE(G)                                                                        \
-    {                                                                                               \
-        int v[16];                                                                                  \
-        DFP4_NATIVE_READ(G, v);                                                                     \
-        finish(std::integral_constant<int, G>{}, v);                                                \
-        store_tile(kFullC, kPairsC, G, v);                                                          \
-    }
-    if (pairs) {
-        constexpr std::true_type kFullC{}, kPairsC{};
+        {                                                                                           \
+            int v[16];                                                                              \
+            DFP4_NATIVE_READ(G, v);                                                                 \
+            finish(std::integral_constant<int, G>{}, v);                                            \
+            if constexpr (G > 0) { DFP4_NATIVE_LINES(G - 1) }                                       \
+            stage_group(v);                                                                         \
+            line0 = line_of(0);                                                                     \
+            line1 = line_of(1);                                                                     \
+            if constexpr (!BF16) {                                                                  \
+                line2 = line_of(2);                                                                 \
+                line3 = line_of(3);                                                                 \
+            }                                                                                       \
+            in_order();                                                                             \
+        }
         DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
-    } else if (full) {
-        constexpr std::true_type kFullC{};
-        constexpr std::false_type kPairsC{};
-        DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
+#undef DFP4_NATIVE_STORE
+        DFP4_NATIVE_LINES(4 * TA - 1)
+#undef DFP4_NATIVE_LINES
     } else {
-        constexpr std::false_type kFullC{}, kPairsC{};
+        const int lr = pairs ? lane >> 5 : 0, lc = pairs ? 2 * (lane & 31) : lane;
+        auto store_group = [&](int g) {
+            const int m = m0 + (g >> 1) * 16, n = n0 + (g & 1) * 64 + lc;
+            uint8_t* out = wave_out + (int64_t)((g >> 1) * 16) * row_bytes + ((g & 1) * 64 + lc) * kEsz;
+            for (int r = 0; r < 16; r += pairs ? 2 : 1) {
+                const int row = r + lr;
+                if (m + row >= p.M || n >= p.N) continue;
+                if (!BF16) *reinterpret_cast<uint32_t*>(out + row * row_bytes) = st[row * kPitch + lc];
+                else if (pairs && n + 1 < p.N) *reinterpret_cast<uint32_t*>(out + row * row_bytes) = st[row * kPitch + (lc >> 1)];
+                else *reinterpret_cast<uint16_t*>(out + row * row_bytes) = reinterpret_cast<const uint16_t*>(st + row * kPitch)[lc];
+            }
+            in_order();
+        };
+#define DFP4_NATIVE_STORE(G)                                                                        \
+        {                                                                                           \
+            int v[16];                                                                              \
+            DFP4_NATIVE_READ(G, v);                                                                 \
+            finish(std::integral_constant<int, G>{}, v);                                            \
+            stage_group(v);                                                                         \
+            store_group(G);                                                                         \
+        }
         DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
     }
 #undef DFP4_NATIVE_STORE
@@ -740,7 +780,7 @@ __global__ __launch_bounds__(1024, MT == 1 ? 8 : 4) void gemm_native_small_kerne
     auto load = [&](const PackedOperand& src, int tile, int s) {
         Operand o;
         o.lo = *reinterpret_cast<const uint4*>(src.bits + (kFp6 ? fp6_lo(tile, s, S) : ((size_t)tile * S + s) * 1024) + lane * 16);
-        if constexpr (kFp6) o.hi = *reinterpret_cast<const uint2*>(src.bits + fp6_hi(tile, s, S) + lane * 8);
+        if constexpr (kFp6) o.hi = *reinterpret_cast<const uint2*>(src.bits + fp6_hi(tile, s, S) + fp6_hi_lane(lane) * 8);
         o.sc = src.sc[((int64_t)(tile >> 2) * S + s) * 64 + lane];
         return o;
     };

@@ -1,47 +1,60 @@
 #!/usr/bin/env python3
 """Generator of gemm_native_asm.inc: main loop of gemm_native_kernel (block-scaled
-v_mfma_scale_f32_32x32x64_f8f6f4 on FP4 or FP6 operands, see gemm_native.hip).
+v_mfma_scale_f32_16x16x128_f8f6f4 on FP4 or FP6 operands, see gemm_native.hip).
 
-A workgroup computes 256 x 256 outputs with four waves as 2 x 2, each wave 128 x 128
-(4 x 4 tiles of 32 x 32, accumulator tile (i, j) in a[16 (4 i + j) : +15]).  One step =
-one pair of blocks (K = 64) = 16 MFMAs per wave.  A second form (suffix _H) halves the rows:
-128 x 256 per workgroup, 64 x 128 per wave, 8 MFMAs per step, for products with few tiles.  Both operands arrive pre-arranged in the
-instruction's register order (native_pack_kernel): FP4 a (tile, step) chunk of 64 lanes x 16 bytes; FP6 a
-(pair of tiles, step) chunk of 3 KiB, 64 lanes x 16 bytes (registers 0..3) of either tile, then 64 lanes x 8 bytes
-(registers 4, 5) of either.  The loop only moves data:
+A workgroup computes 256 x 256 outputs with four waves as 2 x 2, each wave 128 x 128 (8 x 8 tiles of
+16 x 16, accumulator tile (i, j) in a[4 (8 i + j) : +3]).  A second form (suffix _H) halves the rows: 128 x 256 per
+workgroup, 64 x 128 per wave, for products with few tiles.  W is the instruction's first operand and A its second, so that a
+lane holds four neighbouring columns of one row of the result.
 
-  global -> LDS  direct loads (global_load_lds_dwordx4, whole KiB), five or seven steps ahead, six or
-                 eight LDS stages in rotation;
-                 wave w fetches A tiles 2w, 2w+1, B tiles 2w, 2w+1 and scale chunk w; in the 128-row form
+One iteration = four blocks (K = 128) = two steps of the packed operands = 64 (32) instructions per wave.  The packed form
+(gemm_native.hip, fp6_pack.h) keeps (32 rows, step of two blocks) together; lane (q, c) of a 16 x 16 x 128 instruction
+wants block q of row c, which is step q / 2, block q % 2 there, so a lane's LDS address has the stage in it and nothing is laid
+out anew.  Both operands arrive
+
+  global -> LDS  direct loads (global_load_lds_dwordx4, whole KiB), two (three) iterations ahead, three (four) slots
+                 of two stages in rotation;
+                 wave w fetches A tiles 2w, 2w+1, B tiles 2w, 2w+1 (of 32 rows) and scale chunk w; in the 128-row form
                  A tile w, and of an FP6 pair's last KiB both waves of the pair write the same copy;
-  LDS -> regs    the wave's 4 A and 4 B tiles and two scale dwords of step s + 1 are read
-                 during step s (two register sets used alternately);
-  one barrier per step, in the middle of the MFMA stream: after it every wave's loads of
-  step s + 1 have landed and nobody reads the stage that this step's loads overwrite.
+  LDS -> regs    the wave's operands and scale dwords of iteration d + 1 are read during iteration d (two register sets
+                 used alternately);
+  one barrier per iteration, two multiplications in: after it every wave's loads of iteration d + 1 have landed and
+                 nobody reads the slot that this iteration's loads overwrite.
+
+From the last iteration that has something new to load on, the loads read the last iteration's steps again.  Where the number of steps is
+odd the second half of the last iteration is what lies behind (the next tile, or the slack), and A's registers of it and the scales (the
+upper 32 lanes) are cleared: FP4 and FP6 have no infinities, so it multiplies to zero.
+
+Why this instruction: the kernel is bound by power, and it takes a tenth less of it than 32 x 32 x 64 for the same products.
+Loops of either on registers with operands as they come sustain 6.3 (FP6) and 6.9 PFLOP/s (FP4) with 32 x 32 x 64 at 1.56 and 1.71 GHz,
+7.0 and 7.7 with 16 x 16 x 128 at 1.76 and 1.94; neighbouring instructions share an operand (rows of tiles forth and back), half a per cent.
+What it asks for: an instruction takes 16 clocks, and a wave, which is alone on its SIMD, gets one other short instruction into its shadow.  With two
+or three behind some and none behind others, addresses rotated between iterations and a branch taken in each, a step of K = 64 took 885
+clocks (FP6); with everything unrolled and spread evenly it takes 600 (512 without any other work), at 1.48 GHz, against 660 at 1.43 with the larger instruction.
+4096 x 4096, K = 8192, loop alone: FP6 58 -> 52 us, FP4 51.6 -> 46.6.
 
 LDS stage: the chunks of A tiles 0..7 and B tiles 0..7 as in memory (1 KiB per tile for FP4, 3 KiB per pair
-for FP6) + 4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).  The loop of the FP6 form is bound by LDS: a step
-reads 8 tiles in each of 4 waves and writes 16.  With registers 4, 5 kept at 8 bytes per lane a tile costs
-12 + 12 cycles of the 128 byte/cycle pipe; at the 16-byte stride that 12-byte direct loads leave, the
-8-byte reads cost as much as 16-byte ones (16 + 16).  MLP pass of 2048 rows, 4096 x 14336
-(3 products + 2 quantizers): 290 us with the 16-byte stride and four stages, 260 us so.
+for FP6) + 4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).  Per step FP6 moves 25 KB into LDS and 50 KB out of it, 600
+clocks at 128 byte/clock.  Registers 4, 5 are kept at 8 bytes per lane: at the 16-byte stride that 12-byte direct loads leave,
+their reads cost as much as 16-byte ones.
 
-Registers (fixed): a[0:255] accumulators; v[40:87] / v[88:135] operand sets (A tile i at
-+6 i, B tile j at +24 + 6 j); v136..v139 scale dwords (A, B of set 0; A, B of set 1);
-v144 / v145 global offsets (operands, scales), v150.. LDS read bases
-(the loop is unrolled over the stages, so a stage is a base register plus an immediate);
-s[60:69] global bases of the wave's five chunks, s70 step, s74 / s75 scratch, s77..s84 the
-wave's LDS addresses inside stage 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the 128-row form).
+With operands that the last cache does not hold a step takes as long as its bytes at 60 byte/ns and compute unit, however early they are
+asked for (FP6: 128-row form 1.28 times as long, 256 rows 1.07; FP4 1.13 and 1.01): what a compute unit can have in flight.
+
+Registers (fixed): a[0:255] accumulators; v[40:135] / v[136:231] operand sets (A tile i at +6 i, B tile j at +48 + 6 j);
+v[232:239] scale dwords, of either set A's even and odd tiles, B's; v240, v254 / v241, v255 global offsets (operands, scales) of the two
+steps; v242.. LDS read addresses; s[60:69] global bases of the wave's five chunks, s70 iteration, s71 iteration before which something is to
+be done, s72 / s73 bytes to the next iteration's operands and scales, s74 / s75 scratch, s76 shift of A's scales (128-row form), s77..s84 the
+wave's LDS addresses inside slot 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the 128-row form).
 """
 import os
 
-FR = [40, 88]
-SA = [136, 138]
-SB = [137, 139]
-VOFF, VSOFF = 144, 145
-VBASE = 150                      # LDS read bases: group q at VBASE + 6 q: operands A, B, scales A, B, registers 4, 5 of A, B
-S_BASE, S_VC = 60, 70
-S_T0, S_T1 = 74, 75
+FR = [40, 136]
+SC = [232, 236]                  # scale dwords of a set: A even, A odd tiles, B even, B odd
+VOFF, VSOFF = [240, 254], [241, 255]      # of the first and second step of a slot
+VBASE = 242                      # LDS read addresses, slots 0 and 1, then the others: operands A, B, scales A, B, registers 4, 5 of A, B
+S_BASE, S_VC, S_EVENT, S_GS, S_SS = 60, 70, 71, 72, 73
+S_T0, S_T1, S_SHIFT = 74, 75, 76
 S_RA, S_RB, S_RSA, S_RSB, S_DA, S_DB, S_DS, S_DA2 = 77, 78, 79, 80, 81, 82, 83, 84
 
 
@@ -56,115 +69,147 @@ def sr(n, cnt=1):
 class Fmt:
     def __init__(self, fp6, ta=4):
         self.fp6 = fp6
-        self.ta = ta                                 # A tiles (of 32 rows) per wave: 4 (256-row workgroup) or 2 (128)
+        self.ta = ta                                 # A tiles of 32 rows per wave: 4 (256-row workgroup) or 2 (128)
+        self.ni = 2 * ta                             # A tiles of 16 rows
         self.regs = 6 if fp6 else 4
-        self.tile = 1536 if fp6 else 1024            # LDS bytes per tile and stage
+        self.tile = 1536 if fp6 else 1024            # LDS bytes per 32-row tile and stage
         self.stage = (2 * ta + 8) * self.tile + 1024
         self.gstride = 3072 if fp6 else 1024         # global bytes per (pair of tiles, step) / (tile, step)
         self.code = 2 if fp6 else 4                  # cbsz / blgp
         # direct loads per wave and step: A, B, scales
         self.per_step = (3 if ta == 4 else 2) + 3 + 1 if fp6 else ta // 2 + 2 + 1
-        self.nst = 6 if fp6 and ta == 4 else 8       # LDS stages (FP6: 6 x 25 KiB or 8 x 19 KiB, FP4: 8 x 17 or 13 KiB)
-        self.dist = self.nst - 1                     # loads run this many steps ahead
-        # LDS reads address a stage as (base register of its group) + immediate (< 64 KiB)
-        self.per_group = (65535 - 4 * self.tile) // self.stage
-        self.groups = (self.nst + self.per_group - 1) // self.per_group
+        self.behind = []                             # code out of the loop's way
+        self.slots = 3 if fp6 and ta == 4 else 4     # of two stages (FP6: 6 x 25 KiB or 8 x 19 KiB, FP4: 8 x 17 or 13 KiB)
 
 
-def frag_reads(f, p, stage):
-    """LDS reads of the operands held in `stage` into register set p."""
-    q, off = stage // f.per_group, (stage % f.per_group) * f.stage
-    va, vb, vsa, vsb, va2, vb2 = (VBASE + 6 * q + i for i in range(6))
-    o = []
-    for side, v, v2 in ((0, va, va2), (1, vb, vb2)):
-        for t in range(f.ta if side == 0 else 4):
-            r = FR[p] + 24 * side + 6 * t
+def frag_reads(f, p, slot):
+    """LDS reads of the operands in `slot` into register set p, in the order in which they are wanted."""
+    va, vb, vsa, vsb, va2, vb2 = (VBASE + 6 * (slot >> 1) + i for i in range(6))
+    o, at = [], (slot & 1) * 2 * f.stage
+    scales = [f"ds_read_b32 {vr(SC[p] + i)}, {vr(v)} offset:{at + 64 * (i & 1)}" for i, v in ((0, vsa), (1, vsa), (2, vsb), (3, vsb))]
+    for side, v, v2 in ((1, vb, vb2), (0, va, va2)):
+        for t in range(8 if side else f.ni):
+            r = FR[p] + 48 * side + 6 * t
+            t32, half = t >> 1, t & 1
             if f.fp6:
-                pair = off + (t >> 1) * 3072
-                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{pair + (t & 1) * 1024}")
-                o.append(f"ds_read_b64 {vr(r + 4, 2)}, {vr(v2)} offset:{pair + 2048 + (t & 1) * 512}")
+                pair = (t32 >> 1) * 3072
+                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{at + pair + (t32 & 1) * 1024 + half * 256}")
+                o.append(f"ds_read_b64 {vr(r + 4, 2)}, {vr(v2)} offset:{at + pair + 2048 + (t32 & 1) * 512 + half * 256}")
             else:
-                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{off + t * f.tile}")
-    o.append(f"ds_read_b32 {vr(SA[p])}, {vr(vsa)} offset:{off}")
-    o.append(f"ds_read_b32 {vr(SB[p])}, {vr(vsb)} offset:{off}")
+                o.append(f"ds_read_b128 {vr(r, 4)}, {vr(v)} offset:{at + t32 * f.tile + half * 256}")
+        if side:
+            o += scales
     return o
 
 
-def dma_groups(f, stage):
-    """Direct loads of one step of this wave into `stage`, as groups (m0 setup, [loads that use it]).
-    An instruction offset applies to the global and to the LDS address alike, so the loads of one FP6
-    chunk share one m0."""
+def shift_scales(f, p):
+    """128-row form: both row halves of the workgroup share one scale dword, bytes 2 wm, 2 wm + 1"""
+    return [f"v_lshrrev_b32 {vr(SC[p] + i)}, {sr(S_SHIFT)}, {vr(SC[p] + i)}" for i in (0, 1)] if f.ta == 2 else []
+
+
+def dma_groups(f, slot):
+    """Direct loads of one iteration of this wave into `slot`, as groups (m0 setup, [loads that use it]).  An instruction offset
+    applies to the global and to the LDS address alike, so the loads of one FP6 chunk share one m0."""
     o = []
 
-    def group(dst, base, offsets, disp=0):
-        at = f"{vr(VOFF)}, {sr(S_BASE + 2 * base, 2)}"
-        o.append((f"s_add_u32 m0, {sr(dst)}, {stage * f.stage + disp}",
+    def group(dst, base, half, offsets, disp=0):
+        at = f"{vr(VOFF[half])}, {sr(S_BASE + 2 * base, 2)}"
+        o.append((f"s_add_u32 m0, {sr(dst)}, {(2 * slot + half) * f.stage + disp}",
                   [f"global_load_lds_dwordx4 {at}" + (f" offset:{x}" if x else "") for x in offsets]))
 
-    if f.fp6:
-        if f.ta == 4:
-            group(S_DA, 0, (0, 1024, 2048))
+    for half in (0, 1):
+        if f.fp6 and f.ta == 4:
+            group(S_DA, 0, half, (0, 1024, 2048))
+        elif f.fp6:
+            group(S_DA, 0, half, (0,))
+            group(S_DA2, 1, half, (2048,))
         else:
-            group(S_DA, 0, (0,))
-            group(S_DA2, 1, (2048,))
-        group(S_DB, 2, (0, 1024, 2048))
-    else:
-        for k in range(f.ta // 2):
-            group(S_DA, k, (0,), k * f.tile)
-        for k in range(2):
-            group(S_DB, 2 + k, (0,), k * f.tile)
-    o.append((f"s_add_u32 m0, {sr(S_DS)}, {stage * f.stage}", [f"global_load_lds_dword {vr(VSOFF)}, {sr(S_BASE + 8, 2)}"]))
+            for k in range(f.ta // 2):
+                group(S_DA, k, half, (0,), k * f.tile)
+        if f.fp6:
+            group(S_DB, 2, half, (0, 1024, 2048))
+        else:
+            for k in range(2):
+                group(S_DB, 2 + k, half, (0,), k * f.tile)
+        o.append((f"s_add_u32 m0, {sr(S_DS)}, {(2 * slot + half) * f.stage}",
+                  [f"global_load_lds_dword {vr(VSOFF[half])}, {sr(S_BASE + 8, 2)}"]))
     return o
 
 
-def advance_global(f):
-    return [f"v_add_u32 {vr(VOFF)}, {f.gstride}, {vr(VOFF)}", f"v_add_u32 {vr(VSOFF)}, 0x100, {vr(VSOFF)}"]
+def next_iteration():
+    return [f"v_add_u32 {vr(v)}, {sr(by)}, {vr(v)}" for by, vs in ((S_SS, VSOFF), (S_GS, VOFF)) for v in vs]
 
 
-def mfma(f, p, k):
-    i, j = k // 4, k % 4
-    acc = f"a[{16 * k}:{16 * k + 15}]"
+def mfma(f, p, i, j):
+    k = 8 * i + j
+    acc = f"a[{4 * k}:{4 * k + 3}]"
     a = vr(FR[p] + 6 * i, f.regs)
-    b = vr(FR[p] + 24 + 6 * j, f.regs)
-    return (f"v_mfma_scale_f32_32x32x64_f8f6f4 {acc}, {a}, {b}, {acc}, {vr(SA[p])}, {vr(SB[p])} "
-            f"op_sel:[{i & 1},{j & 1},0] op_sel_hi:[{i >> 1},{j >> 1},0] cbsz:{f.code} blgp:{f.code}")
+    b = vr(FR[p] + 48 + 6 * j, f.regs)
+    bi, bj = i >> 1, j >> 1               # bytes of the scale dwords
+    return (f"v_mfma_scale_f32_16x16x128_f8f6f4 {acc}, {b}, {a}, {acc}, {vr(SC[p] + 2 + (j & 1))}, {vr(SC[p] + (i & 1))} "
+            f"op_sel:[{bj & 1},{bi & 1},0] op_sel_hi:[{bj >> 1},{bi >> 1},0] cbsz:{f.code} blgp:{f.code}")
 
 
-def step(f, u):
-    """Step number u (mod the number of stages): multiplies register set u % 2, reads the operands of
-    the next step from stage (u + 1) % nst, loads stage (u + dist) % nst = (u - 1) % nst."""
-    p = u % 2
-    o = [f"s_cmp_lt_u32 {sr(S_VC)}, %[steps]", "s_cbranch_scc0 99f"]
-    reads = frag_reads(f, 1 - p, (u + 1) % f.nst)
-    dmas = dma_groups(f, (u + f.dist) % f.nst)
-    # after the barrier: every m0 setup is followed by an LDS read (m0 needs one instruction before its use)
-    tail = []
-    for m0, loads in dmas:
-        tail.append([m0] + ([reads.pop(0)] if reads else ["s_nop 0"]) + loads[:1])
-        for ld in loads[1:]:
-            tail.append([ld] + [reads.pop(0) for _ in range(min(2, len(reads)))])
-    while reads:
-        tail.append([reads.pop(0)] + ([reads.pop(0)] if reads else []))
-    nm = 4 * f.ta                     # MFMAs per step
-    per = (len(tail) + nm - 5) // (nm - 4)      # spread evenly: bunching the memory instructions is slower
-    for k in range(nm):
-        o.append(mfma(f, p, k))
-        if k == 2:
-            # the loads of step s + 1 have landed; those of the steps after it may be pending
-            o += [f"s_waitcnt vmcnt({(f.dist - 2) * f.per_step})", "s_barrier"]
-        if k >= 3:
-            for grp in tail[(k - 3) * per:(k - 2) * per]:
-                o += grp
-        if k == nm - 1:
-            o += advance_global(f)
-    o += [f"s_add_u32 {sr(S_VC)}, {sr(S_VC)}, 1", "s_waitcnt lgkmcnt(0)"]
-    if f.ta == 2:                     # both row halves of the workgroup share one scale dword: bytes 2 wm, 2 wm + 1
-        o.append(f"v_lshrrev_b32 {vr(SA[1 - p])}, {sr(S_T1)}, {vr(SA[1 - p])}")
-    return o
+BARRIER_AT = 2                   # multiplications before the barrier
+
+
+def iteration(f, u):
+    """Iteration u (mod the unrolled ones): multiplies register set u % 2, reads the operands of the next iteration from its slot,
+    loads this one's slot, which has been read.  One other instruction behind each multiplication: the next is issued 16 clocks
+    later, and two or more take longer than that."""
+    p, slot = u % 2, u % f.slots
+    order = [(i, j if i % 2 == 0 else 7 - j) for i in range(f.ni) for j in range(8)]
+    n = len(order)
+    reads = frag_reads(f, 1 - p, (slot + 1) % f.slots)
+    items = [((r + 0.5) / len(reads), "", text) for r, text in enumerate(reads)]
+    dma = []
+    for m0, loads in dma_groups(f, slot):
+        for ld in loads:
+            dma.append((m0, ld))
+            m0 = ""
+    dma += [("", text) for text in next_iteration()]
+    items += [(d / len(dma), m0, text) for d, (m0, text) in enumerate(dma)]
+    items.sort(key=lambda x: x[0])
+    before, behind = [[] for _ in order], [[] for _ in order]           # of the multiplications
+    for x, (_, m0, text) in enumerate(items):
+        k = BARRIER_AT + x * (n - BARRIER_AT) // len(items)
+        if m0:
+            (before[k] if not behind[k] else behind[k]).append(m0)
+            if behind[k]:
+                behind[k].append("s_nop 0")                             # (m0 needs one instruction before its use)
+        behind[k].append(text)
+    behind[1].append(f"s_add_u32 {sr(S_VC)}, {sr(S_VC)}, 1")
+    # B, the scales and A's first tile are there; A's others may be on their way until the barrier
+    o = []
+    for k, (i, j) in enumerate(order):
+        if k == BARRIER_AT:
+            # the loads of the next iteration have landed; those of the iterations after it may be pending
+            o += [f"s_waitcnt vmcnt({(f.slots - 2) * 2 * f.per_step}) lgkmcnt(0)", "s_barrier"]
+        o += before[k] + [mfma(f, p, i, j)] + behind[k]
+    return o + next_operands(f, 1 - p, 20 + u)
+
+
+def next_operands(f, p, label):
+    """The operands of register set p, as far as the first row of tiles needs them, and what is to be done in few iterations, out of the loop's
+    way (a branch that is taken costs 40 clocks): leave it, stop the loads, clear what is not there."""
+    f.behind += [f"{label}:", f"s_cmp_eq_u32 {sr(S_VC)}, %[iters]", "s_cbranch_scc1 99f",
+                 # from here on the last step that was loaded is loaded again
+                 f"s_cmp_eq_u32 {sr(S_GS)}, 0", f"s_cbranch_scc1 {label + 20}f",
+                 *(f"v_subrev_u32 {vr(v)}, {sr(by)}, {vr(v)}" for by, vs in ((S_SS, VSOFF), (S_GS, VOFF)) for v in vs),
+                 f"s_mov_b32 {sr(S_GS)}, 0", f"s_mov_b32 {sr(S_SS)}, 0",
+                 f"{label + 20}:", f"s_min_u32 {sr(S_EVENT)}, %[half], %[iters]",
+                 f"s_cmp_eq_u32 {sr(S_VC)}, %[half]", f"s_cbranch_scc0 {label + 40}b",
+                 # the last iteration of an odd number of steps: there is no second step
+                 f"s_mov_b32 {sr(S_EVENT)}, %[iters]", "s_waitcnt lgkmcnt(0)", "s_mov_b32 exec_lo, 0"]
+    f.behind += [f"v_mov_b32 {vr(FR[p] + 6 * t + r)}, 0" for t in range(f.ni) for r in range(f.regs)]
+    f.behind += [f"v_mov_b32 {vr(SC[p] + i)}, 0x7f7f7f7f" for i in range(4)]
+    f.behind += ["s_mov_b32 exec_lo, -1", f"s_branch {label + 40}b"]
+    return [f"s_waitcnt lgkmcnt({(f.ni - 1) * (2 if f.fp6 else 1)})"] + shift_scales(f, p) + \
+           [f"s_cmp_eq_u32 {sr(S_VC)}, {sr(S_EVENT)}", f"s_cbranch_scc1 {label}f", f"{label + 40}:"]
 
 
 def entry(f):
-    o = [f"v_accvgpr_write_b32 a{n}, 0" for n in range(256)]
+    o = [f"v_accvgpr_write_b32 a{n}, 0" for n in range(64 * f.ta)]
     # global bases: FP4 A tiles 2w, 2w+1 and B tiles 2w, 2w+1 (each tile holds `tstride` bytes); FP6 A pair w and B
     # pair w, or in the 128-row form A tile w and (second base) its pair; scale chunk
     o += [f"s_mov_b32 {sr(S_BASE)}, %[alo]", f"s_mov_b32 {sr(S_BASE + 1)}, %[ahi]",
@@ -172,7 +217,7 @@ def entry(f):
           f"s_mov_b32 {sr(S_BASE + 4)}, %[blo]", f"s_mov_b32 {sr(S_BASE + 5)}, %[bhi]",
           f"s_add_u32 {sr(S_BASE + 6)}, %[blo], %[tstride]", f"s_addc_u32 {sr(S_BASE + 7)}, %[bhi], 0",
           f"s_mov_b32 {sr(S_BASE + 8)}, %[slo]", f"s_mov_b32 {sr(S_BASE + 9)}, %[shi]"]
-    # the wave's LDS addresses inside stage 0: wm = wv >> 1, wn = wv & 1
+    # the wave's LDS addresses inside slot 0: wm = wv >> 1, wn = wv & 1
     offb, offs = 2 * f.ta * f.tile, (2 * f.ta + 8) * f.tile
     o += [f"s_lshr_b32 {sr(S_T0)}, %[wv], 1", f"s_and_b32 {sr(S_T1)}, %[wv], 1",
           f"s_mul_i32 {sr(S_RA)}, {sr(S_T0)}, {f.ta * f.tile}", f"s_add_u32 {sr(S_RA)}, {sr(S_RA)}, %[lds]",
@@ -189,45 +234,43 @@ def entry(f):
           f"s_mul_i32 {sr(S_DB)}, %[wv], {2 * f.tile}", f"s_add_u32 {sr(S_DB)}, {sr(S_DB)}, {offb}",
           f"s_add_u32 {sr(S_DB)}, {sr(S_DB)}, %[lds]"]
     if f.fp6 and f.ta == 2:           # A tile w inside pair w / 2: 1 KiB apart, in memory and in LDS
-        o += [f"s_lshl_b32 {sr(S_RSA)}, {sr(S_T1)}, 10",
-              f"s_sub_u32 {sr(S_BASE + 2)}, %[alo], {sr(S_RSA)}", f"s_subb_u32 {sr(S_BASE + 3)}, %[ahi], 0",
+        o += [f"s_lshl_b32 {sr(S_DS)}, {sr(S_T1)}, 10",
+              f"s_sub_u32 {sr(S_BASE + 2)}, %[alo], {sr(S_DS)}", f"s_subb_u32 {sr(S_BASE + 3)}, %[ahi], 0",
               f"s_mul_i32 {sr(S_DA2)}, {sr(S_T0)}, 3072", f"s_add_u32 {sr(S_DA2)}, {sr(S_DA2)}, %[lds]",
-              f"s_add_u32 {sr(S_DA)}, {sr(S_DA2)}, {sr(S_RSA)}",
-              f"s_mov_b32 {sr(S_RSA)}, {offs}", f"s_add_u32 {sr(S_RSA)}, {sr(S_RSA)}, %[lds]"]
+              f"s_add_u32 {sr(S_DA)}, {sr(S_DA2)}, {sr(S_DS)}"]
     if f.ta == 4:
         o += [f"s_lshl_b32 {sr(S_DS)}, %[wv], 8"]
     else:                             # scale chunks: wave 0 and 1 -> the A group (slot 0), waves 2, 3 -> B groups (slots 2, 3)
         o += [f"s_cmp_lt_u32 %[wv], 2", f"s_cselect_b32 {sr(S_DS)}, 0, %[wv]", f"s_lshl_b32 {sr(S_DS)}, {sr(S_DS)}, 8"]
-    o += [f"s_add_u32 {sr(S_DS)}, {sr(S_DS)}, {offs}", f"s_add_u32 {sr(S_DS)}, {sr(S_DS)}, %[lds]",
-          f"s_lshl_b32 {sr(S_T1)}, {sr(S_T0)}, 4"]              # S_T1 = 16 wm: shift of the A scale dword (128-row form)
-    for q in range(f.groups):
-        goff = q * f.per_group * f.stage
-        bases = [(S_RA, "%[l16]"), (S_RB, "%[l16]"), (S_RSA, "%[l4]"), (S_RSB, "%[l4]")]
-        if f.fp6:
-            bases += [(S_RA, "%[l8]"), (S_RB, "%[l8]")]
-        for i, (s, lane) in enumerate(bases):
-            o += [f"s_add_u32 {sr(S_T0)}, {sr(s)}, {goff}", f"v_add_u32 {vr(VBASE + 6 * q + i)}, {sr(S_T0)}, {lane}"]
-    o += [f"s_mov_b32 {sr(S_VC)}, 0",
-          f"v_mov_b32 {vr(VOFF)}, %[g16]", f"v_mov_b32 {vr(VSOFF)}, %[g4]"]
-    # pipeline fill: steps 0 .. dist-1 into stages 0 .. dist-1
-    for st in range(f.dist):
-        for m0, loads in dma_groups(f, st):
+    o += [f"s_add_u32 {sr(S_DS)}, {sr(S_DS)}, {offs}", f"s_add_u32 {sr(S_DS)}, {sr(S_DS)}, %[lds]"]
+    # lane (q, c): block q % 2 of row c in stage q / 2 of the slot
+    bases = [(S_RA, "%[r16]"), (S_RB, "%[r16]"), (S_RSA, "%[r4]"), (S_RSB, "%[r4]")]
+    if f.fp6:
+        bases += [(S_RA, "%[r8]"), (S_RB, "%[r8]")]
+    for i, (s, lane) in enumerate(bases):
+        o += [f"v_add_u32 {vr(VBASE + i)}, {sr(s)}, {lane}", f"v_add_u32 {vr(VBASE + 6 + i)}, {4 * f.stage}, {vr(VBASE + i)}"]
+    o += [f"s_mov_b32 {sr(S_VC)}, 0", f"s_mov_b32 {sr(S_GS)}, {2 * f.gstride}", f"s_movk_i32 {sr(S_SS)}, 0x200",
+          f"s_lshl_b32 {sr(S_SHIFT)}, %[wv], 3", f"s_and_b32 {sr(S_SHIFT)}, {sr(S_SHIFT)}, 16",          # 16 wm
+          # the first iteration that loads nothing new
+          f"s_max_u32 {sr(S_EVENT)}, %[iters], {f.slots}", f"s_sub_u32 {sr(S_EVENT)}, {sr(S_EVENT)}, {f.slots}",
+          f"v_mov_b32 {vr(VOFF[0])}, %[g16]", f"v_mov_b32 {vr(VSOFF[0])}, %[g4]",
+          f"v_add_u32 {vr(VOFF[1])}, {f.gstride}, {vr(VOFF[0])}", f"v_add_u32 {vr(VSOFF[1])}, 0x100, {vr(VSOFF[0])}"]
+    # pipeline fill: all slots
+    for slot in range(f.slots):
+        for m0, loads in dma_groups(f, slot):
             o += [m0, "s_nop 0"] + loads
-        o += advance_global(f)
-    # step 0's operands into set 0
-    o += [f"s_waitcnt vmcnt({(f.dist - 1) * f.per_step})", "s_barrier"]
-    o += frag_reads(f, 0, 0) + ["s_waitcnt lgkmcnt(0)"]
-    if f.ta == 2:
-        o.append(f"v_lshrrev_b32 {vr(SA[0])}, {sr(S_T1)}, {vr(SA[0])}")
-    return o
+        o += next_iteration()
+    # the first iteration's operands into set 0
+    o += [f"s_waitcnt vmcnt({(f.slots - 1) * 2 * f.per_step})", "s_barrier"]
+    return o + frag_reads(f, 0, 0) + next_operands(f, 0, 19)
 
 
 def main_loop(f):
     o = entry(f)
     o.append("80:")
-    for u in range(f.nst):
-        o += step(f, u)
-    o.append("s_branch 80b")
+    for u in range(6 if f.slots == 3 else 4):        # both register sets and all slots
+        o += iteration(f, u)
+    o += ["s_branch 80b"] + f.behind
     o += ["99:", "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_nop 15", "s_nop 15", "s_nop 15", "s_nop 15"]
     return o
 
@@ -246,7 +289,7 @@ def main():
     for g in range(16):
         rd = [f"v_accvgpr_read_b32 %{i}, a{16 * g + i}" for i in range(16)]
         parts.append(f"#define DFP4_NATIVE_ACC_READ_{g} \\\n" + c_string(rd) + "\n")
-    vclob = ", ".join(f'"v{n}"' for n in range(40, 170))
+    vclob = ", ".join(f'"v{n}"' for n in range(40, 256))
     aclob = ", ".join(f'"a{n}"' for n in range(256))
     sclob = ", ".join(f'"s{n}"' for n in range(S_BASE, S_DA2 + 1))
     parts.append(f"#define DFP4_NATIVE_VGPR_CLOBBERS {vclob}\n")

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kThreads) void quantize_native_kernel(
                 scales[(((size_t)(tile >> 2) * S + step) * 64u + slot) * 4u + (tile & 3u)] = on[p] ? (uint8_t)eb : (uint8_t)0;
             }
             if (step_ok && sub == 2) {
-                *reinterpret_cast<uint2*>(bits + fp6_hi(tile, step, S) + slot * 8u) =
+                *reinterpret_cast<uint2*>(bits + fp6_hi(tile, step, S) + fp6_hi_lane(slot) * 8u) =
                     on[p] ? make_uint2(hi16 | (next_lo << 16), next_mid) : make_uint2(0, 0);
             }
         }
