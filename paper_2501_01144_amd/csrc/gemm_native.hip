@@ -461,9 +461,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     static_assert(MODE == kPlain || (kPieceAt + sizeof(TileLds<PieceShape>) <= sizeof(s_stage) && kPieceAt % 16 == 0));
     static_assert(MODE != kRequant || sizeof(RequantLds) <= sizeof(s_stage));
     __shared__ int s_ctl[5];                                 // exact: per wave, whether its sums are exact; arrivals (split K)
-    const int tid = threadIdx.x, lane = tid & 63;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    const int q = lane >> 4, c = lane & 15;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = (int)wave >> 1, wn = (int)wave & 1;
     // this workgroup's range of steps (split K: blockIdx.z, in exact products below the problem of a batch)
     const int per = (p.S + p.ksplit - 1) / p.ksplit;
@@ -480,9 +478,9 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         const uint8_t* sa = reinterpret_cast<const uint8_t*>(p.a_stat + ((int64_t)blockIdx.y * (2 * TA) + wm * TA) * kStatChunks) + bz * p.a_stride;
         const uint8_t* sw = reinterpret_cast<const uint8_t*>(p.w_stat + ((int64_t)blockIdx.x * 8 + wn * 4) * kStatChunks) + bz * p.w_stride;
 #pragma unroll
-        for (int i = 0; i < TA / 2; ++i) stat_a[i] = reinterpret_cast<const ExactStat*>(sa)[i * 64 + lane];
+        for (int i = 0; i < TA / 2; ++i) stat_a[i] = reinterpret_cast<const ExactStat*>(sa)[i * 64 + (threadIdx.x & 63)];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) stat_w[i] = reinterpret_cast<const ExactStat*>(sw)[i * 64 + lane];
+        for (int i = 0; i < 2; ++i) stat_w[i] = reinterpret_cast<const ExactStat*>(sw)[i * 64 + (threadIdx.x & 63)];
     }
     {
         const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -497,10 +495,12 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         const uint64_t sb = wave < 2
             ? reinterpret_cast<uint64_t>(p.a.sc) + (TA == 4 ? (uint64_t)blockIdx.y * 2 + wave : (uint64_t)blockIdx.y) * (uint64_t)p.S * 256
             : reinterpret_cast<uint64_t>(p.w.sc) + ((uint64_t)blockIdx.x * 2 + (wave - 2)) * (uint64_t)p.S * 256;
-        const uint32_t l16 = (uint32_t)lane * 16u, l4 = (uint32_t)lane * 4u;
+        uint32_t lane = threadIdx.x & 63u;
+        asm volatile("" : "+v"(lane));                       // nothing of it is kept through the loop for what follows, registers are short
+        const uint32_t l16 = lane * 16u, l4 = lane * 4u;
         // LDS offsets of lane (q, c): stage q / 2 of a slot, block q % 2 of row c
-        const uint32_t q_at = (uint32_t)(q >> 1) * kStage, q_blk = (uint32_t)((q & 1) * 32 + c);
-        const uint32_t r16 = q_at + q_blk * 16u, r8 = q_at + ((uint32_t)(q & 1) * 16u + (uint32_t)c) * 8u, r4 = q_at + q_blk * 4u;
+        const uint32_t q = lane >> 4, c = lane & 15u, q_at = (q >> 1) * kStage, q_blk = (q & 1u) * 32u + c;
+        const uint32_t r16 = q_at + q_blk * 16u, r8 = q_at + ((q & 1u) * 16u + c) * 8u, r4 = q_at + q_blk * 4u;
         const uint32_t g16 = l16 + (uint32_t)s_lo * kGStride, g4 = l4 + (uint32_t)s_lo * 256u;
         const uint32_t iters = (uint32_t)(S + 1) / 2u;
 #define DFP4_NATIVE_RUN(LOOP)                                                                                     \
@@ -523,6 +523,9 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
 
     // epilogue: fp32 (or bf16, round to nearest even) [M, N].  Accumulator registers come in groups of 16: group G is row tile
     // G / 2 (of 16 rows), columns 64 (G % 2) + ..; register 4 j + x of lane (q, c) is row c, column 16 j + 4 q + x of it.
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                            // (anew, see above)
+    const int lane = tid & 63, q = lane >> 4, c = lane & 15;
     const int m0 = blockIdx.y * kRowsWg + wm * kRowsWave, n0 = blockIdx.x * 256 + wn * 128;
 #define DFP4_NATIVE_READ(G, V)                                                                      \
     asm volatile(DFP4_NATIVE_ACC_READ_##G                                                           \
@@ -669,15 +672,12 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     uint8_t* wave_out = base + ((int64_t)m0 * ld + n0) * kEsz;                                 // uniform
     const int64_t row_bytes = ld * kEsz;                                                       // uniform
     const bool full = m0 + kRowsWave <= p.M && n0 + 128 <= p.N;                                // uniform
-    // Results go through the wave's part of LDS, a group (16 rows x 64 columns) at a time, so that neighbouring lanes store neighbouring columns: 16 bytes
-    // each where rows allow that, otherwise one element, or two of bf16.  (As the lanes hold them, 16 bytes of 16 rows to 16 neighbouring lanes,
+    // Results go through the wave's part of LDS, a group (16 rows x 64 columns) at a time, so that neighbouring lanes store neighbouring columns.  (As the lanes hold them, 16 bytes of 16 rows to 16 neighbouring lanes,
     // each lane's bytes were a write of their own: 7.5 us of fp32 and 3.8 of bf16 per tile of 256 x 256 instead of 5.6 and 2.4.  All compute
     // units together store at the rate of their L2 caches, 11 TB/s; bf16 before, by integer arithmetic and two columns a lane, 4.5.)
-    constexpr int kPitch = BF16 ? 36 : 68, kLanes = BF16 ? 8 : 16;                                 // dwords of a row in LDS; lanes per row
-    constexpr int kWide = kLanes / 4;                                                              // 16-byte stores of a lane
+    typedef uint32_t v16u __attribute__((ext_vector_type(16)));
+    constexpr int kPitch = BF16 ? 36 : 68;                                                         // dwords of a row in LDS
     uint32_t* st = reinterpret_cast<uint32_t*>(s_stage) + wave * (16 * kPitch);
-    const bool wide = full && (row_bytes & 15) == 0 && (reinterpret_cast<uintptr_t>(base) & 15) == 0;
-    const bool pairs = BF16 && (ld & 1) == 0 && (reinterpret_cast<uintptr_t>(base) & 3) == 0;
     auto in_order = [] {                                     // a wave's LDS operations execute in order; this keeps the compiler to it
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -693,66 +693,76 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         }
         in_order();
     };
-    if (wide) {
-        const int lr = lane / kLanes, lc = lane % kLanes;
-        const int64_t lane_off = lr * row_bytes + lc * 16;
-        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-        v4u line0, line1, line2, line3;                      // of the group before: stored while the next is on its way through LDS
-        auto line_of = [&](int k) { return *reinterpret_cast<const v4u*>(st + (k * (16 / kWide) + lr) * kPitch + lc * 4); };
-        auto store_line = [&](int g, int k, v4u line) {
-            *reinterpret_cast<v4u*>(wave_out + (int64_t)((g >> 1) * 16 + k * (16 / kWide)) * row_bytes + (g & 1) * 64 * kEsz + lane_off) = line;
-        };
-#define DFP4_NATIVE_LINES(G)                                                                        \
-        store_line(G, 0, line0);                                                                    \
-        store_line(G, 1, line1);                                                                    \
-        if constexpr (!BF16) {                                                                      \
-            store_line(G, 2, line2);                                                                \
-            store_line(G, 3, line3);                                                                \
-        }
-#define DFP4_NATIVE_STORE(G)                                                                        \
-        {                                                                                           \
-            int v[16];                                                                              \
-            DFP4_NATIVE_READ(G, v);                                                                 \
-            finish(std::integral_constant<int, G>{}, v);                                            \
-            if constexpr (G > 0) { DFP4_NATIVE_LINES(G - 1) }                                       \
-            stage_group(v);                                                                         \
-            line0 = line_of(0);                                                                     \
-            line1 = line_of(1);                                                                     \
-            if constexpr (!BF16) {                                                                  \
-                line2 = line_of(2);                                                                 \
-                line3 = line_of(3);                                                                 \
-            }                                                                                       \
-            in_order();                                                                             \
-        }
-        DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
-#undef DFP4_NATIVE_STORE
-        DFP4_NATIVE_LINES(4 * TA - 1)
-#undef DFP4_NATIVE_LINES
-    } else {
-        const int lr = pairs ? lane >> 5 : 0, lc = pairs ? 2 * (lane & 31) : lane;
-        auto store_group = [&](int g) {
-            const int m = m0 + (g >> 1) * 16, n = n0 + (g & 1) * 64 + lc;
-            uint8_t* out = wave_out + (int64_t)((g >> 1) * 16) * row_bytes + ((g & 1) * 64 + lc) * kEsz;
-            for (int r = 0; r < 16; r += pairs ? 2 : 1) {
-                const int row = r + lr;
-                if (m + row >= p.M || n >= p.N) continue;
-                if (!BF16) *reinterpret_cast<uint32_t*>(out + row * row_bytes) = st[row * kPitch + lc];
-                else if (pairs && n + 1 < p.N) *reinterpret_cast<uint32_t*>(out + row * row_bytes) = st[row * kPitch + (lc >> 1)];
-                else *reinterpret_cast<uint16_t*>(out + row * row_bytes) = reinterpret_cast<const uint16_t*>(st + row * kPitch)[lc];
+    // A lane reads and stores kElems elements of each of kRows rows, every row by kLanes lanes: 16 bytes, two bf16 (where rows are an even
+    // number of them), or one element.  A group is stored while the next is on its way through LDS.
+    auto store_all = [&](auto elems_c, auto full_c) {
+        constexpr int kElems = decltype(elems_c)::value, kLanes = 64 / kElems, kBy = 64 / kLanes, kRows = 16 / kBy;
+        constexpr bool kFull = decltype(full_c)::value;      // no edge
+        constexpr int kBytes = kElems * kEsz, kDwords = kBytes < 4 ? 1 : kBytes / 4;
+        const int lr = lane / kLanes, lc = lane % kLanes * kElems;
+        const int64_t lane_off = lr * row_bytes + lc * kEsz;
+        auto read_lines = [&] {
+            v16u x = {};
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const uint8_t* src = reinterpret_cast<const uint8_t*>(st + (k * kBy + lr) * kPitch) + lc * kEsz;
+                if constexpr (kBytes == 2) x[k] = *reinterpret_cast<const uint16_t*>(src);
+                else if constexpr (kBytes == 4) x[k] = *reinterpret_cast<const uint32_t*>(src);
+                else {
+                    const uint4 y = *reinterpret_cast<const uint4*>(src);
+                    x[4 * k] = y.x;
+                    x[4 * k + 1] = y.y;
+                    x[4 * k + 2] = y.z;
+                    x[4 * k + 3] = y.w;
+                }
             }
             in_order();
+            return x;
         };
+        auto store_lines = [&](int g, v16u x) {
+            const int m = m0 + (g >> 1) * 16, left = p.N - (n0 + (g & 1) * 64 + lc);              // columns from the lane's first on
+            uint8_t* out = wave_out + (int64_t)((g >> 1) * 16) * row_bytes + (g & 1) * 64 * kEsz;
+            if (!kFull && left <= 0) return;
+            auto store_rows = [&](auto all_c) {
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) {
+                    if (!decltype(all_c)::value && m + k * kBy + lr >= p.M) continue;
+                    uint8_t* dst = out + (int64_t)(k * kBy) * row_bytes + lane_off;
+                    if constexpr (kBytes == 2) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)x[k];
+                    else if constexpr (kDwords == 1) {
+                        if (kElems == 1 || kFull || left > 1) *reinterpret_cast<uint32_t*>(dst) = x[k];
+                        else *reinterpret_cast<uint16_t*>(dst) = (uint16_t)x[k];
+                    } else *reinterpret_cast<uint4*>(dst) = make_uint4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+                }
+            };
+            if (kFull || m + 16 <= p.M) store_rows(std::true_type{});        // (a branch before every store: 3 us of fp32 a tile)
+            else store_rows(std::false_type{});
+        };
+        v16u line = {};
 #define DFP4_NATIVE_STORE(G)                                                                        \
         {                                                                                           \
             int v[16];                                                                              \
             DFP4_NATIVE_READ(G, v);                                                                 \
             finish(std::integral_constant<int, G>{}, v);                                            \
             stage_group(v);                                                                         \
-            store_group(G);                                                                         \
+            const v16u next = read_lines();                                                         \
+            if constexpr (G > 0) store_lines(G - 1, line);                                          \
+            line = next;                                                                            \
         }
         DFP4_NATIVE_TILES(DFP4_NATIVE_STORE)
-    }
 #undef DFP4_NATIVE_STORE
+        store_lines(4 * TA - 1, line);
+    };
+    const uintptr_t at = reinterpret_cast<uintptr_t>(base);
+    constexpr int kWide = 16 / kEsz;
+    using Wide = std::integral_constant<int, kWide>;
+    using Pair = std::integral_constant<int, BF16 ? 2 : 1>;
+    using One = std::integral_constant<int, 1>;
+    const bool wide = (row_bytes & 15) == 0 && (at & 15) == 0 && (n0 + 128 <= p.N || p.N % kWide == 0);
+    if (wide && full) store_all(Wide{}, std::true_type{});
+    else if (wide) store_all(Wide{}, std::false_type{});
+    else if (BF16 && (ld & 1) == 0 && (at & 3) == 0) store_all(Pair{}, std::false_type{});
+    else store_all(One{}, std::false_type{});
 #undef DFP4_NATIVE_TILES
 #undef DFP4_NATIVE_READ
 }
@@ -861,13 +871,20 @@ __global__ __launch_bounds__(256) void native_reduce_kernel(const float* __restr
 }
 
 inline int64_t up256(int64_t x) { return (x + 255) & ~(int64_t)255; }
-// Workgroups per output tile: with at most a quarter as many tiles as compute units K is split in 2
-// or 4 ranges (at half as many the partial tiles and the extra kernel cost what the split gains)
+// Workgroups per output tile.  With at most a quarter as many tiles as compute units K can be split in 2 or 4 ranges of at least 8 steps; it is
+// where the steps saved (0.15 us each in the 128-row form; FP6 0.17, FP4 0.13) cost more than the partial tiles and the kernel that adds them:
+// 3 us and 0.45 us per megabyte of partials.  Microseconds, split / whole (FP6):
+//   256 x 1024 x 4096  11.4 / 14.7      512 x 4096 x 4096   22.4 / 15.4      1024 x 4096 x  8192  35.3 / 29.7
+//   256 x 4096 x 4096  16.0 / 15.0      512 x 4096 x 14336  32.2 / 44.9      1024 x 4096 x 14336  46.3 / 46.7
 inline int native_ksplit(int64_t M, int64_t N, int64_t KB) {
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), S = (KB + 1) / 2, cu = device_cu_count();
-    int s = 1;
-    while (s < 4 && tiles * s * 4 <= cu && S / (2 * s) >= 8) s *= 2;
-    return s;
+    int best = 1;
+    float least = 0.15f * (float)S;
+    for (int s = 2; s <= 4 && tiles * s * 2 <= cu && S / s >= 8; s *= 2) {
+        const float us = 0.15f * (float)S / (float)s + 3.0f + 0.45f * (float)s * (float)M * (float)N * 4e-6f;
+        if (us < least) least = us, best = s;
+    }
+    return best;
 }
 // One packed operand: [bits | scales], rows padded to 256, eight steps of slack behind each array.
 struct OperandLayout { int64_t sc, total; };
@@ -951,9 +968,10 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
     p.ksplit = native_ksplit(M, N, KB);
     if (p.ksplit > 1 && (!splitk || splitk_bytes < native_splitk_bytes(M, N, K))) p.ksplit = 1;
     p.part = static_cast<float*>(splitk);
-    // 256-row workgroups unless they would leave half of the compute units idle
+    // 256-row workgroups unless they would leave half of the compute units idle, or there are no more than 128 rows (128 x 4096 x 2048
+    // 13.2 us with 256-row workgroups, 9.8 so)
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
-    const bool half = tiles256 * p.ksplit * 2 <= device_cu_count() && M > 128;
+    const bool half = tiles256 * p.ksplit * 2 <= device_cu_count() || M <= 128;
     dim3 grid((unsigned)((N + 255) / 256), (unsigned)((M + (half ? 127 : 255)) / (half ? 128 : 256)), (unsigned)p.ksplit);
     if (grid.y > 65535) return DFP4_ERR_SHAPE;
     const bool bf16 = out_dtype == DFP4_BF16 && p.ksplit == 1;     // partial tiles are fp32

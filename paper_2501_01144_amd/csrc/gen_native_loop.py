@@ -21,7 +21,7 @@ out anew.  Both operands arrive
   one barrier per iteration, two multiplications in: after it every wave's loads of iteration d + 1 have landed and
                  nobody reads the slot that this iteration's loads overwrite.
 
-From the last iteration that has something new to load on, the loads read the last iteration's steps again.  Where the number of steps is
+Where there is nothing new to load any more, the loads read the last step again.  Where the number of steps is
 odd the second half of the last iteration is what lies behind (the next tile, or the slack), and A's registers of it and the scales (the
 upper 32 lanes) are cleared: FP4 and FP6 have no infinities, so it multiplies to zero.
 
@@ -42,16 +42,15 @@ With operands that the last cache does not hold a step takes as long as its byte
 asked for (FP6: 128-row form 1.28 times as long, 256 rows 1.07; FP4 1.13 and 1.01): what a compute unit can have in flight.
 
 Registers (fixed): a[0:255] accumulators; v[40:135] / v[136:231] operand sets (A tile i at +6 i, B tile j at +48 + 6 j);
-v[232:239] scale dwords, of either set A's even and odd tiles, B's; v240, v254 / v241, v255 global offsets (operands, scales) of the two
-steps; v242.. LDS read addresses; s[60:69] global bases of the wave's five chunks, s70 iteration, s71 iteration before which something is to
-be done, s72 / s73 bytes to the next iteration's operands and scales, s74 / s75 scratch, s76 shift of A's scales (128-row form), s77..s84 the
+v[232:239] scale dwords, of either set A's even and odd tiles, B's; v240 / v241 global offsets (operands, scales); v242.. LDS read addresses; s[60:69] global bases of the wave's five chunks, s70 iteration, s71 iteration before which something is to
+be done, s72 / s73 bytes to the next step's operands and scales, s74 / s75 scratch, s76 shift of A's scales (128-row form), s77..s84 the
 wave's LDS addresses inside slot 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the 128-row form).
 """
 import os
 
 FR = [40, 136]
 SC = [232, 236]                  # scale dwords of a set: A even, A odd tiles, B even, B odd
-VOFF, VSOFF = [240, 254], [241, 255]      # of the first and second step of a slot
+VOFF, VSOFF = 240, 241
 VBASE = 242                      # LDS read addresses, slots 0 and 1, then the others: operands A, B, scales A, B, registers 4, 5 of A, B
 S_BASE, S_VC, S_EVENT, S_GS, S_SS = 60, 70, 71, 72, 73
 S_T0, S_T1, S_SHIFT = 74, 75, 76
@@ -107,37 +106,34 @@ def shift_scales(f, p):
     return [f"v_lshrrev_b32 {vr(SC[p] + i)}, {sr(S_SHIFT)}, {vr(SC[p] + i)}" for i in (0, 1)] if f.ta == 2 else []
 
 
-def dma_groups(f, slot):
-    """Direct loads of one iteration of this wave into `slot`, as groups (m0 setup, [loads that use it]).  An instruction offset
+def dma_groups(f, stage):
+    """Direct loads of one step of this wave into `stage`, as groups (m0 setup, [loads that use it]).  An instruction offset
     applies to the global and to the LDS address alike, so the loads of one FP6 chunk share one m0."""
     o = []
 
-    def group(dst, base, half, offsets, disp=0):
-        at = f"{vr(VOFF[half])}, {sr(S_BASE + 2 * base, 2)}"
-        o.append((f"s_add_u32 m0, {sr(dst)}, {(2 * slot + half) * f.stage + disp}",
+    def group(dst, base, offsets, disp=0):
+        at = f"{vr(VOFF)}, {sr(S_BASE + 2 * base, 2)}"
+        o.append((f"s_add_u32 m0, {sr(dst)}, {stage * f.stage + disp}",
                   [f"global_load_lds_dwordx4 {at}" + (f" offset:{x}" if x else "") for x in offsets]))
 
-    for half in (0, 1):
-        if f.fp6 and f.ta == 4:
-            group(S_DA, 0, half, (0, 1024, 2048))
-        elif f.fp6:
-            group(S_DA, 0, half, (0,))
-            group(S_DA2, 1, half, (2048,))
+    if f.fp6:
+        if f.ta == 4:
+            group(S_DA, 0, (0, 1024, 2048))
         else:
-            for k in range(f.ta // 2):
-                group(S_DA, k, half, (0,), k * f.tile)
-        if f.fp6:
-            group(S_DB, 2, half, (0, 1024, 2048))
-        else:
-            for k in range(2):
-                group(S_DB, 2 + k, half, (0,), k * f.tile)
-        o.append((f"s_add_u32 m0, {sr(S_DS)}, {(2 * slot + half) * f.stage}",
-                  [f"global_load_lds_dword {vr(VSOFF[half])}, {sr(S_BASE + 8, 2)}"]))
+            group(S_DA, 0, (0,))
+            group(S_DA2, 1, (2048,))
+        group(S_DB, 2, (0, 1024, 2048))
+    else:
+        for k in range(f.ta // 2):
+            group(S_DA, k, (0,), k * f.tile)
+        for k in range(2):
+            group(S_DB, 2 + k, (0,), k * f.tile)
+    o.append((f"s_add_u32 m0, {sr(S_DS)}, {stage * f.stage}", [f"global_load_lds_dword {vr(VSOFF)}, {sr(S_BASE + 8, 2)}"]))
     return o
 
 
-def next_iteration():
-    return [f"v_add_u32 {vr(v)}, {sr(by)}, {vr(v)}" for by, vs in ((S_SS, VSOFF), (S_GS, VOFF)) for v in vs]
+def next_step():
+    return [f"v_add_u32 {vr(VOFF)}, {sr(S_GS)}, {vr(VOFF)}", f"v_add_u32 {vr(VSOFF)}, {sr(S_SS)}, {vr(VSOFF)}"]
 
 
 def mfma(f, p, i, j):
@@ -163,11 +159,12 @@ def iteration(f, u):
     reads = frag_reads(f, 1 - p, (slot + 1) % f.slots)
     items = [((r + 0.5) / len(reads), "", text) for r, text in enumerate(reads)]
     dma = []
-    for m0, loads in dma_groups(f, slot):
-        for ld in loads:
-            dma.append((m0, ld))
-            m0 = ""
-    dma += [("", text) for text in next_iteration()]
+    for half in (0, 1):
+        for m0, loads in dma_groups(f, 2 * slot + half):
+            for ld in loads:
+                dma.append((m0, ld))
+                m0 = ""
+        dma += [("", text) for text in next_step()]
     items += [(d / len(dma), m0, text) for d, (m0, text) in enumerate(dma)]
     items.sort(key=lambda x: x[0])
     before, behind = [[] for _ in order], [[] for _ in order]           # of the multiplications
@@ -195,7 +192,7 @@ def next_operands(f, p, label):
     f.behind += [f"{label}:", f"s_cmp_eq_u32 {sr(S_VC)}, %[iters]", "s_cbranch_scc1 99f",
                  # from here on the last step that was loaded is loaded again
                  f"s_cmp_eq_u32 {sr(S_GS)}, 0", f"s_cbranch_scc1 {label + 20}f",
-                 *(f"v_subrev_u32 {vr(v)}, {sr(by)}, {vr(v)}" for by, vs in ((S_SS, VSOFF), (S_GS, VOFF)) for v in vs),
+                 f"v_subrev_u32 {vr(VOFF)}, {sr(S_GS)}, {vr(VOFF)}", f"v_subrev_u32 {vr(VSOFF)}, {sr(S_SS)}, {vr(VSOFF)}",
                  f"s_mov_b32 {sr(S_GS)}, 0", f"s_mov_b32 {sr(S_SS)}, 0",
                  f"{label + 20}:", f"s_min_u32 {sr(S_EVENT)}, %[half], %[iters]",
                  f"s_cmp_eq_u32 {sr(S_VC)}, %[half]", f"s_cbranch_scc0 {label + 40}b",
@@ -249,17 +246,16 @@ def entry(f):
         bases += [(S_RA, "%[r8]"), (S_RB, "%[r8]")]
     for i, (s, lane) in enumerate(bases):
         o += [f"v_add_u32 {vr(VBASE + i)}, {sr(s)}, {lane}", f"v_add_u32 {vr(VBASE + 6 + i)}, {4 * f.stage}, {vr(VBASE + i)}"]
-    o += [f"s_mov_b32 {sr(S_VC)}, 0", f"s_mov_b32 {sr(S_GS)}, {2 * f.gstride}", f"s_movk_i32 {sr(S_SS)}, 0x200",
+    o += [f"s_mov_b32 {sr(S_VC)}, 0", f"s_mov_b32 {sr(S_GS)}, {f.gstride}", f"s_movk_i32 {sr(S_SS)}, 0x100",
           f"s_lshl_b32 {sr(S_SHIFT)}, %[wv], 3", f"s_and_b32 {sr(S_SHIFT)}, {sr(S_SHIFT)}, 16",          # 16 wm
           # the first iteration that loads nothing new
           f"s_max_u32 {sr(S_EVENT)}, %[iters], {f.slots}", f"s_sub_u32 {sr(S_EVENT)}, {sr(S_EVENT)}, {f.slots}",
-          f"v_mov_b32 {vr(VOFF[0])}, %[g16]", f"v_mov_b32 {vr(VSOFF[0])}, %[g4]",
-          f"v_add_u32 {vr(VOFF[1])}, {f.gstride}, {vr(VOFF[0])}", f"v_add_u32 {vr(VSOFF[1])}, 0x100, {vr(VSOFF[0])}"]
+          f"v_mov_b32 {vr(VOFF)}, %[g16]", f"v_mov_b32 {vr(VSOFF)}, %[g4]"]
     # pipeline fill: all slots
-    for slot in range(f.slots):
-        for m0, loads in dma_groups(f, slot):
+    for stage in range(2 * f.slots):
+        for m0, loads in dma_groups(f, stage):
             o += [m0, "s_nop 0"] + loads
-        o += next_iteration()
+        o += next_step()
     # the first iteration's operands into set 0
     o += [f"s_waitcnt vmcnt({(f.slots - 1) * 2 * f.per_step})", "s_barrier"]
     return o + frag_reads(f, 0, 0) + next_operands(f, 0, 19)
@@ -289,7 +285,7 @@ def main():
     for g in range(16):
         rd = [f"v_accvgpr_read_b32 %{i}, a{16 * g + i}" for i in range(16)]
         parts.append(f"#define DFP4_NATIVE_ACC_READ_{g} \\\n" + c_string(rd) + "\n")
-    vclob = ", ".join(f'"v{n}"' for n in range(40, 256))
+    vclob = ", ".join(f'"v{n}"' for n in range(40, 254))
     aclob = ", ".join(f'"a{n}"' for n in range(256))
     sclob = ", ".join(f'"s{n}"' for n in range(S_BASE, S_DA2 + 1))
     parts.append(f"#define DFP4_NATIVE_VGPR_CLOBBERS {vclob}\n")
