@@ -1704,6 +1704,31 @@ def test_gemm_exact_sums_with_a_large_product(M, N, K, mx):
     assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
 
 
+# Fewer iterations than the loop of gemm_native_kernel keeps on their way, odd numbers of steps, both tile heights, K split, tiles of an XCD in
+# rectangles (2048 x 1024), and results at every alignment of their rows (`first` columns into rows of N + `more`): nothing beside them is written.
+@pytest.mark.parametrize("M,N,K", [(65, 257, 32), (128, 300, 64), (129, 256, 96), (200, 513, 160), (257, 264, 192), (300, 1024, 224), (256, 256, 256),
+                                   (400, 700, 288), (1030, 520, 416), (2048, 1024, 544), (100, 1000, 8224), (4096, 2048, 96)])
+@pytest.mark.parametrize("first,more", [(0, 0), (8, 8), (2, 4), (1, 3)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_gemm_native_loop_and_results(M, N, K, first, more, mx):
+    print(f"gemm native: {M}x{N}x{K}, {first} columns into rows of {N + more}, mx {mx}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    x, w = (torch.randn(r, K, generator=g, device="cuda").to(torch.bfloat16) for r in (M, N))
+    quant, back = (dfp4.mxfp4_quantize, dfp4.mxfp4_dequantize) if mx else (dfp4.quantize, dfp4.dequantize)
+    qa, qw = quant(x), quant(w)
+    a, b = dfp4.native_pack(qa, mx=mx), dfp4.native_pack(qw, mx=mx)
+    da, dw = back(qa).double(), back(qw).double()
+    ref, absdot = da @ dw.T, da.abs() @ dw.abs().T
+    for dtype in (torch.float32, torch.bfloat16):
+        rows = torch.full((M, N + more), 12345.0, dtype=dtype, device="cuda")
+        out = dfp4.gemm_native_packed(a, b, out=rows[:, first:first + N])
+        torch.cuda.synchronize()
+        err = (out.double() - ref).abs()
+        assert bool((err <= GEMM_RTOL * absdot + (ref.abs() * 2.0 ** -8 if dtype == torch.bfloat16 else 0)).all())
+        rows[:, first:first + N] = 12345.0
+        assert bool((rows == torch.full((), 12345.0, dtype=dtype, device="cuda")).all())
+
+
 # --------------------------------------------------------------------------
 # Calls that allocate their result raise what torch.empty raises.
 # --------------------------------------------------------------------------
