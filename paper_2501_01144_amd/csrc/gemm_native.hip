@@ -139,6 +139,27 @@ struct ExactPrepParams {
     int KB, S, chunks, chunk_blocks, wgs_a;
 };
 
+// the value DPP control CTRL brings to a lane
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+// the largest value of 64 lanes; of every eighth lane's (no LDS: a chain of cross-lane reads there costs a workgroup a microsecond)
+__device__ __forceinline__ float rows_max(float v) {
+    v = fmaxf(v, dpp<0x128>(v));                      // 8 lanes on, within 16
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp<0xB1>(v));
+    v = fmaxf(v, dpp<0x4E>(v));
+    v = fmaxf(v, dpp<0x141>(v));
+    v = fmaxf(v, dpp<0x140>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+
 __device__ __forceinline__ float quad_pair_sum(float v) {     // over 8 neighbouring lanes, in all of them
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
@@ -163,7 +184,8 @@ __device__ const ExactBook g_exact_book = make_exact_book();
 // (q, tile) takes rows 8 q .. of row tile `tile` of the four, a lane one block at a time.  Bound by latency: exponents of
 // the whole rows (which every chunk reads again, 1/16 of the codes' bytes each time), then codes, tables, stores; so there are 16
 // waves to a workgroup, 8 threads look through a row's exponents, and the codes are on their way meanwhile (with 4 waves of 4
-// blocks per lane: 2048 x 4096 10.0 us, 2048 x 14336 21.7; so 8.3 and 15.5).  8 lanes read the 128 bytes of 8 blocks of a
+// blocks per lane: 2048 x 4096 10.0 us, 2048 x 14336 21.7; so 8.3 and 15.5).  Maxima over lanes by DPP and lane reads instead of chains through LDS (2800
+// of 17000 clocks), and no exponents read twice: 2048 x 4096 9.0 -> 7.3 us, 4096 x 4096 14.1 -> 11.4, 2048 x 14336 17.9 -> 17.2 over eight sets of buffers.  8 lanes read the 128 bytes of 8 blocks of a
 // row, so that loads are whole lines, and the 8 rows of a wave are 128 contiguous bytes of a step's 16-byte parts.
 template <int FMT>
 __global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) {
@@ -220,9 +242,11 @@ __global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) 
             for (int i0 = part; i0 < n16; i0 += 32) {
                 uint4 v[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], e + 16 * min(i0 + 8 * q, n16 - 1), 16);   // no alignment assumed
+                for (int q = 0; q < 4; ++q)
+                    if (8 * q < n16) __builtin_memcpy(&v[q], e + 16 * min(i0 + 8 * q, n16 - 1), 16);          // no alignment assumed
 #pragma unroll
-                for (int q = 0; q < 4; ++q) { scan(v[q].x); scan(v[q].y); scan(v[q].z); scan(v[q].w); }
+                for (int q = 0; q < 4; ++q)
+                    if (8 * q < n16) { scan(v[q].x); scan(v[q].y); scan(v[q].z); scan(v[q].w); }
             }
             for (int i = n16 * 16 + part; i < KB; i += 8) scan(e[i] * 0x01010101u);
         }
@@ -279,9 +303,8 @@ __global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) 
         }
         if (o.mask) {
             uint32_t cls = on ? 1u << min(((int)e - lowest) >> 2, kMaxClass + 1) : 0u;
-#pragma unroll
-            for (int x = 8; x < 64; x <<= 1) cls |= (uint32_t)__shfl_xor((int)cls, x);
-            if (lane < 8) atomicOr(&s_mask[sub + k8], cls);
+            cls |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cls, 0x128, 0xf, 0xf, true);      // 8 lanes on: another row of the same blocks
+            if ((lane & 8) == 0) atomicOr(&s_mask[sub + k8], cls);
         }
         __syncthreads();
         {
@@ -313,14 +336,10 @@ __global__ __launch_bounds__(1024, 8) void exact_prep_kernel(ExactPrepParams p) 
     m.sq = quad_pair_sum(m.sq);
     m.sq_low = quad_pair_sum(m.sq_low);
     m.sum_high = quad_pair_sum(m.sum_high);
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-        m.top = fmaxf(m.top, __shfl_xor(m.top, x));
-        if (x < 8) continue;
-        m.sq = fmaxf(m.sq, __shfl_xor(m.sq, x));
-        m.sq_low = fmaxf(m.sq_low, __shfl_xor(m.sq_low, x));
-        m.sum_high = fmaxf(m.sum_high, __shfl_xor(m.sum_high, x));
-    }
+    m.top = wave_max(m.top);
+    m.sq = rows_max(m.sq);
+    m.sq_low = rows_max(m.sq_low);
+    m.sum_high = rows_max(m.sum_high);
     if (lane == 0) s_stat[wave >> 2][t4] = m;
     __syncthreads();
     if (wave < 4) {
@@ -349,29 +368,12 @@ struct ExactParams : NativeParams {
     int64_t cnt_stride;               // dwords
 };
 
-// the value DPP control CTRL brings to a lane
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-// the larger of the sums over lanes 0..31 and 32..63; the largest value of 64 lanes (no LDS: a chain of cross-lane reads there
-// costs a workgroup a microsecond)
+// the larger of the sums over lanes 0..31 and 32..63
 __device__ __forceinline__ float half_sum_max(float v) {
     v = quad_pair_sum(v);
     v += dpp<0x140>(v);                               // mirrored within 16 lanes
     return fmaxf(lane_value(v, 0) + lane_value(v, 16), lane_value(v, 32) + lane_value(v, 48));
 }
-__device__ __forceinline__ float wave_max(float v) {
-    v = fmaxf(v, dpp<0xB1>(v));
-    v = fmaxf(v, dpp<0x4E>(v));
-    v = fmaxf(v, dpp<0x141>(v));
-    v = fmaxf(v, dpp<0x140>(v));
-    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
-}
-
 // The largest norms of a wave's rows (lane: chunk lane % 32 of tile lane / 32 of each pair of tiles), in all lanes
 template <int N>
 __device__ __forceinline__ ExactStat reduce_stat(ExactStat (&v)[N]) {
