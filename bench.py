@@ -450,7 +450,7 @@ def main():
         n_gemm_ms = sum(nk[n] for n in gemm_ops)
         n_tops = total_ops / (n_gemm_ms * 1e-3) / 1e12
         out["native_fp6_step"] = {
-            "what": "same step with dfp4_quantize_native + dfp4_gemm_native_packed (v_mfma_scale_f32_32x32x64_f8f6f4, "
+            "what": "same step with dfp4_quantize_native + dfp4_gemm_native_packed (v_mfma_scale_f32_16x16x128_f8f6f4, "
                     "FP6 E2M3 operands, fp32 accumulation in the matrix core); weights packed beforehand, each "
                     "activation quantized online straight into the packed form",
             "ms_per_step": round(ms_n, 4), "TOPs": round(total_ops / (ms_n * 1e-3) / 1e12, 1), "steps": nside,
@@ -689,9 +689,9 @@ def main():
         out.update({"value": n["TOPs"], "ms_per_step": n["ms_per_step"], "kernel_ms": n["kernel_ms"], "dtype": "fp6",
                     "roofline": n["roofline"], "steps": n["steps"],
                     "pct_int8_peak_step": round(100.0 * n["TOPs"] / INT8_PEAK_TOPS, 2)})
-        out["config"]["gemm"] = "native (v_mfma_scale_f32_32x32x64_f8f6f4, FP6 E2M3 operands)"
+        out["config"]["gemm"] = "native (v_mfma_scale_f32_16x16x128_f8f6f4, FP6 E2M3 operands)"
     else:
-        out["config"]["gemm"] = "exact (v_mfma_scale_f32_32x32x64_f8f6f4, FP6 E2M3 operands; tiles whose fp32 sums are not proven exact: v_mfma_i32_32x32x32_i8)"
+        out["config"]["gemm"] = "exact (v_mfma_scale_f32_16x16x128_f8f6f4, FP6 E2M3 operands; tiles whose fp32 sums are not proven exact: v_mfma_i32_32x32x32_i8)"
     print(json.dumps(out))
 
 

@@ -269,7 +269,7 @@ int dfp4_gemm_noalloc(dfp4_tensor A, dfp4_tensor W, void* out, int out_dtype, in
 
 /*
  * Matrix multiply on the block-scaled matrix instruction of the GPU
- * (v_mfma_scale_f32_32x32x64_f8f6f4): out = A * W^T as dfp4_gemm / mxfp4_gemm, but
+ * (v_mfma_scale_f32_16x16x128_f8f6f4 and 32x32x64): out = A * W^T as dfp4_gemm / mxfp4_gemm, but
  * with the power-of-two block scales applied and the sum accumulated in fp32 by
  * the hardware.  dfp4_gemm_native repacks the DialectFP4 operands to FP6 E2M3,
  * in which every DialectFP4 value is exact; mxfp4_gemm_native uses the MXFP4

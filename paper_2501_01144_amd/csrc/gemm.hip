@@ -67,7 +67,7 @@ inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
 // iteration of the direct kernel (Q K^T) goes there unless it is prepared already.  fast_cost is of the int8 kernel that
 // the large one replaced and choose_direct's estimates of int8 operands, so the line lies where it lay between those two.  The large kernel
 // gained more than the direct one, which leaves products on the direct side that it would finish sooner, up to 1.4 times (microseconds,
-// large with its prepass / direct):
+// large with its prepass, in the loop before the present one, / direct):
 //   2048 x 4096 x 4096  46 / 62     512 x 4096 x 14336  74 / 105     1188 x 2211 x 9472  69 / 82     3000 x 5000 x 992  39 / 47
 //    777 x 3001 x 2080  38 / 24     512 x 4096 x  4096  49 /  32     1024 x 1024 x 4096  59 / 18     P V, 128 x 2048 x 128 x 2048  324 / 153
 // and of the sizes measured none on the large side the other way (4096 x 4096 x 4096 60 / 123, 2048 x 2048 x 14336 85 / 133).
