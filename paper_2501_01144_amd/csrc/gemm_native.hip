@@ -634,6 +634,12 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
             }
         }
     };
+    // Results pass between the lanes of a wave through its part of LDS.  A wave's LDS operations execute in order; this keeps the compiler to it
+    auto in_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
     if constexpr (MODE == kRequant) {
         // Section 3.3: results are quantized again for the next multiplication.  Each value is rounded to bf16 as the bf16 output
         // would be; the wave stages 64 rows x 128 columns in LDS and re-reads them in the quantizer's layout (4 lanes per
@@ -654,6 +660,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
             }
             DFP4_NATIVE_TILES(DFP4_NATIVE_STAGE)
 #undef DFP4_NATIVE_STAGE
+            in_order();
             for (int pass = 0; pass < 16; ++pass) {
                 const int b = pass * 16 + (lane >> 2), row = b >> 2, cb = b & 3, sub = lane & 3;
                 const uint4 wv = *reinterpret_cast<const uint4*>(&st[row * kRqPitch + cb * 32 + sub * 8]);
@@ -670,6 +677,7 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
                     }
                 }
             }
+            in_order();
         }
         return;
     }
@@ -689,11 +697,6 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     typedef uint32_t v16u __attribute__((ext_vector_type(16)));
     constexpr int kPitch = BF16 ? 36 : 68;                                                         // dwords of a row in LDS
     uint32_t* st = reinterpret_cast<uint32_t*>(s_stage) + wave * (16 * kPitch);
-    auto in_order = [] {                                     // a wave's LDS operations execute in order; this keeps the compiler to it
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     auto stage_group = [&](int (&v)[16]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

@@ -765,6 +765,22 @@ def test_gemm_requant_split_k_bit_exact():
     _assert_quant_equal(q, _requant_ref(a, w), "requant split K")
 
 
+# Both tile heights (3000 x 3296: 156 tiles of 256 x 256), whose waves stage their rows in two halves or at once, edges in both directions.
+@pytest.mark.parametrize("M,N,K", [(3000, 3296, 256), (1000, 1120, 192)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_gemm_requant_equals_the_quantized_product(M, N, K, mx):
+    print(f"gemm_requant against quantize(gemm): {M}x{N}x{K}, mx {mx}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    quant = dfp4.mxfp4_quantize if mx else dfp4.quantize
+    qa, qw = (quant(torch.randn(r, K, generator=g, device="cuda").to(torch.bfloat16)) for r in (M, N))
+    # sums of such blocks are exact, so that both round the same number
+    want = quant((dfp4.mxfp4_gemm if mx else dfp4.gemm)(qa, qw, dtype=torch.bfloat16))
+    q = (dfp4.mxfp4_gemm_requant if mx else dfp4.gemm_requant)(qa, qw)
+    torch.cuda.synchronize()
+    assert torch.equal(q.codes, want.codes) and torch.equal(q.exponent, want.exponent)
+    assert mx or torch.equal(q.dialect, want.dialect)
+
+
 @pytest.mark.parametrize("B,M,N,K", [(3, 600, 352, 128), (5, 40, 64, 256), (2, 2048, 2048, 128)])
 def test_gemm_requant_batched(B, M, N, K):
     # attention-like batches: every problem's quantized scores against the oracle, bit for bit where the
