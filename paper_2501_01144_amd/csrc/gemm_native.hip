@@ -691,9 +691,10 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
     uint8_t* wave_out = base + ((int64_t)m0 * ld + n0) * kEsz;                                 // uniform
     const int64_t row_bytes = ld * kEsz;                                                       // uniform
     const bool full = m0 + kRowsWave <= p.M && n0 + 128 <= p.N;                                // uniform
-    // Results go through the wave's part of LDS, a group (16 rows x 64 columns) at a time, so that neighbouring lanes store neighbouring columns.  (As the lanes hold them, 16 bytes of 16 rows to 16 neighbouring lanes,
-    // each lane's bytes were a write of their own: 7.5 us of fp32 and 3.8 of bf16 per tile of 256 x 256 instead of 5.6 and 2.4.  All compute
-    // units together store at the rate of their L2 caches, 11 TB/s; bf16 before, by integer arithmetic and two columns a lane, 4.5.)
+    // Results go through the wave's part of LDS, a group (16 rows x 64 columns) at a time, so that neighbouring lanes store neighbouring
+    // columns.  (As the lanes hold them, 16 bytes of 16 rows to 16 neighbouring lanes, each lane's bytes were a write of their own: 7.5 us of fp32
+    // and 3.8 of bf16 per tile of 256 x 256 instead of 5.6 and 2.4.  All compute units together store at the rate of their L2 caches, 11 TB/s;
+    // bf16 before, by integer arithmetic and two columns a lane, 4.5.)
     typedef uint32_t v16u __attribute__((ext_vector_type(16)));
     constexpr int kPitch = BF16 ? 36 : 68;                                                         // dwords of a row in LDS
     uint32_t* st = reinterpret_cast<uint32_t*>(s_stage) + wave * (16 * kPitch);
@@ -707,28 +708,24 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         }
         in_order();
     };
-    // A lane reads and stores kElems elements of each of kRows rows, every row by kLanes lanes: 16 bytes, two bf16 (where rows are an even
-    // number of them), or one element.  A group is stored while the next is on its way through LDS.
-    auto store_all = [&](auto elems_c, auto full_c) {
-        constexpr int kElems = decltype(elems_c)::value, kLanes = 64 / kElems, kBy = 64 / kLanes, kRows = 16 / kBy;
+    // A lane reads and stores 16 bytes of each of kRows rows, every row by kLanes lanes.  Rows may begin anywhere, memory takes 16 bytes at any
+    // address (one element a lane where rows were no multiple of 16 bytes: 4992 x 4878 x 32 bf16 23.2 us, 6720 x 256 x 192 into rows of 257
+    // 8.0).  A group is stored while the next is on its way through LDS.
+    constexpr int kElems = 16 / kEsz, kLanes = 64 / kElems, kBy = 64 / kLanes, kRows = 16 / kBy;
+    auto store_all = [&](auto full_c, auto cut_c) {
         constexpr bool kFull = decltype(full_c)::value;      // no edge
-        constexpr int kBytes = kElems * kEsz, kDwords = kBytes < 4 ? 1 : kBytes / 4;
+        constexpr bool kCut = decltype(cut_c)::value;        // the last column lies inside a lane's 16 bytes
         const int lr = lane / kLanes, lc = lane % kLanes * kElems;
         const int64_t lane_off = lr * row_bytes + lc * kEsz;
         auto read_lines = [&] {
             v16u x = {};
 #pragma unroll
             for (int k = 0; k < kRows; ++k) {
-                const uint8_t* src = reinterpret_cast<const uint8_t*>(st + (k * kBy + lr) * kPitch) + lc * kEsz;
-                if constexpr (kBytes == 2) x[k] = *reinterpret_cast<const uint16_t*>(src);
-                else if constexpr (kBytes == 4) x[k] = *reinterpret_cast<const uint32_t*>(src);
-                else {
-                    const uint4 y = *reinterpret_cast<const uint4*>(src);
-                    x[4 * k] = y.x;
-                    x[4 * k + 1] = y.y;
-                    x[4 * k + 2] = y.z;
-                    x[4 * k + 3] = y.w;
-                }
+                const uint4 y = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(st + (k * kBy + lr) * kPitch) + lc * kEsz);
+                x[4 * k] = y.x;
+                x[4 * k + 1] = y.y;
+                x[4 * k + 2] = y.z;
+                x[4 * k + 3] = y.w;
             }
             in_order();
             return x;
@@ -738,16 +735,33 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
             uint8_t* out = wave_out + (int64_t)((g >> 1) * 16) * row_bytes + (g & 1) * 64 * kEsz;
             if (!kFull && left <= 0) return;
             auto store_rows = [&](auto all_c) {
+                auto put = [&](int64_t at, auto bytes_c) {   // so many bytes of every row
 #pragma unroll
-                for (int k = 0; k < kRows; ++k) {
-                    if (!decltype(all_c)::value && m + k * kBy + lr >= p.M) continue;
-                    uint8_t* dst = out + (int64_t)(k * kBy) * row_bytes + lane_off;
-                    if constexpr (kBytes == 2) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)x[k];
-                    else if constexpr (kDwords == 1) {
-                        if (kElems == 1 || kFull || left > 1) *reinterpret_cast<uint32_t*>(dst) = x[k];
-                        else *reinterpret_cast<uint16_t*>(dst) = (uint16_t)x[k];
-                    } else *reinterpret_cast<uint4*>(dst) = make_uint4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+                    for (int k = 0; k < kRows; ++k) {
+                        if (!decltype(all_c)::value && m + k * kBy + lr >= p.M) continue;
+                        const uint32_t v[4] = {x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]};
+                        __builtin_memcpy(out + (int64_t)(k * kBy) * row_bytes + at, v, decltype(bytes_c)::value);
+                    }
+                };
+                if (!kCut || left >= kElems) {
+                    put(lane_off, std::integral_constant<int, 16>{});
+                    return;
                 }
+                const int bytes = left * kEsz;               // the last columns: 8 bytes, 4, 2 (by scalar branches on N no faster; 4 bytes a lane for all slower)
+                int64_t at = lane_off;
+                if (bytes & 8) {
+                    put(at, std::integral_constant<int, 8>{});
+                    at += 8;
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) x[4 * k] = x[4 * k + 2], x[4 * k + 1] = x[4 * k + 3];
+                }
+                if (bytes & 4) {
+                    put(at, std::integral_constant<int, 4>{});
+                    at += 4;
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) x[4 * k] = x[4 * k + 1];
+                }
+                if (bytes & 2) put(at, std::integral_constant<int, 2>{});
             };
             if (kFull || m + 16 <= p.M) store_rows(std::true_type{});        // (a branch before every store: 3 us of fp32 a tile)
             else store_rows(std::false_type{});
@@ -767,16 +781,9 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
 #undef DFP4_NATIVE_STORE
         store_lines(4 * TA - 1, line);
     };
-    const uintptr_t at = reinterpret_cast<uintptr_t>(base);
-    constexpr int kWide = 16 / kEsz;
-    using Wide = std::integral_constant<int, kWide>;
-    using Pair = std::integral_constant<int, BF16 ? 2 : 1>;
-    using One = std::integral_constant<int, 1>;
-    const bool wide = (row_bytes & 15) == 0 && (at & 15) == 0 && (n0 + 128 <= p.N || p.N % kWide == 0);
-    if (wide && full) store_all(Wide{}, std::true_type{});
-    else if (wide) store_all(Wide{}, std::false_type{});
-    else if (BF16 && (ld & 1) == 0 && (at & 3) == 0) store_all(Pair{}, std::false_type{});
-    else store_all(One{}, std::false_type{});
+    if (full) store_all(std::true_type{}, std::false_type{});
+    else if (n0 + 128 <= p.N || p.N % kElems == 0) store_all(std::false_type{}, std::false_type{});
+    else store_all(std::false_type{}, std::true_type{});
 #undef DFP4_NATIVE_TILES
 #undef DFP4_NATIVE_READ
 }
