@@ -49,7 +49,7 @@ __device__ __forceinline__ Fp6Lane pack6_lane(uint4 c, uint32_t tlo, uint32_t th
 // rows at once, which would meet on the same LDS banks otherwise.  Every KiB is one direct load of a wave into LDS, and both parts are
 // read back at their own width (see gen_native_loop.py).
 constexpr int kFp6PairBytes = 3072;
-constexpr int kSlackSteps = 8;         // behind the bits and behind the scales: the multiply loop first loads up to 8 steps, however few there are
+constexpr int kSlackSteps = 8;         // behind the bits and behind the scales: the multiply loop takes two steps at a time and reads one behind an odd number
 __host__ __device__ inline size_t fp6_lo(size_t tile, size_t step, size_t S) {
     return ((tile >> 1) * S + step) * kFp6PairBytes + (tile & 1) * 1024;
 }

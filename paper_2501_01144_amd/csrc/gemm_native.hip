@@ -67,7 +67,7 @@ constexpr int kFmtFp6 = 2, kFmtFp4 = 4;      // format codes of the instruction 
 //   bits [row tile of 32][step][64 lanes x 16 bytes]                    FP4: registers 0..3 of the lane
 //        [pair of row tiles][step][3 KiB]                              FP6: see fp6_pack.h
 //   sc   [group of 4 row tiles][step][lane] dword: byte t = scale byte of row tile 4 g + t
-// Both arrays end with eight steps of slack: the loop first loads up to eight steps, however few there are.
+// Both arrays end with eight steps of slack: the loop takes two steps at a time and reads one behind an odd number of them.
 struct PackedOperand {
     uint8_t* bits;
     uint32_t* sc;

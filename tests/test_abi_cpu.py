@@ -2,6 +2,7 @@
 every function include/dfp4.h declares, reports the formatbook the oracle
 uses, and rejects bad arguments before touching the device."""
 import ctypes
+import importlib.util
 import os
 import re
 
@@ -227,3 +228,35 @@ def test_a_native_module_that_does_not_load_says_why(monkeypatch):
     monkeypatch.setitem(sys.modules, "paper_2501_01144_amd._binding", None)
     with pytest.raises(dfp4.Dfp4Error, match="halted"):                # the import system's own words
         dfp4.load()
+
+
+# --------------------------------------------------------------------------
+# Main loop of gemm_native_kernel, from its generator: what its entry executes for a number of iterations.
+# --------------------------------------------------------------------------
+@pytest.mark.parametrize("fp6,ta", [(False, 4), (True, 4), (False, 2), (True, 2)])
+@pytest.mark.parametrize("iters", [1, 2, 3, 4, 5, 64])
+def test_native_loop_first_loads_no_more_than_there_is(fp6, ta, iters):
+    spec = importlib.util.spec_from_file_location("gen_native_loop", os.path.join(os.path.dirname(dfp4.__file__), "csrc", "gen_native_loop.py"))
+    gen = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(gen)
+    f = gen.Fmt(fp6, ta)
+    lines = gen.main_loop(f)
+    loads, steps, pending, scc, at = 0, 0, None, False, 0
+    while "s_barrier" not in lines[at]:
+        op, *args = lines[at].replace(",", " ").split()
+        at += 1
+        if op.startswith("global_load_lds"):
+            loads += 1
+        elif op == "v_add_u32" and args[0] == args[2] == gen.vr(gen.VOFF):
+            steps += 1                                       # to the next step's operands
+        elif op == "s_waitcnt":
+            pending = int(re.search(r"vmcnt\((\d+)\)", args[0]).group(1))
+        elif op == "s_cmp_eq_u32" and args[0] == "%[iters]":
+            scc = iters == int(args[1])
+        elif op == "s_branch" or op == "s_cbranch_scc1" and scc:
+            at = lines.index(args[0][:-1] + ":", at if args[0][-1] == "f" else 0)
+    slots = min(iters, f.slots)
+    assert loads == 2 * slots * f.per_step and steps == 2 * slots
+    # the first iteration's loads, of two steps, have landed at the barrier; where the fill was cut short all have, since the loop counts
+    # on f.slots iterations of them
+    assert pending == (0 if iters < f.slots else (f.slots - 1) * 2 * f.per_step)
