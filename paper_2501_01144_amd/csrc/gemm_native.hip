@@ -911,6 +911,9 @@ inline int native_ksplit(int64_t M, int64_t N, int64_t KB) {
 // rather than every eighth column: of those that divide the grid in eight, the one that reads the fewest rows.  2048 x 4096 x 14336
 // (FP6, 128-row tiles) reads 200 MB from beyond the XCDs' caches instead of 246: 60.7 -> 60.4 us with operands in the last cache, 77.5 -> 75.4 with
 // weights from memory; 2048 x 4096 x 4096 27.3 -> 26.9 (FP4 21.4 -> 19.6), 4096 x 4096 x 4096 34.9 -> 33.6 and 37.4 -> 36.5.
+// Not for native products with K split, whose partial tiles cost more so (rectangles / columns: 128 x 4096 x 4096 FP6 in 4 ranges 14.8 / 11.8,
+// 256 x 4096 x 4096 FP4 in 4 19.4 / 13.4, 512 x 4096 x 14336 the same); exact ones, which keep a tile's sums together, gain (2048 x 2048 x 8192
+// 33.3 / 34.2, 1024 x 2048 x 14336 40.4 / 41.4) or do not care.
 inline void choose_rect(NativeParams& p, dim3 grid, int tile_rows) {
     const int64_t gx = grid.x, gy = grid.y;
     p.rect_w = p.rects_x = p.rect_h = 0;
@@ -1015,7 +1018,7 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
     const bool half = tiles256 * p.ksplit * 2 <= device_cu_count() || M <= 128;
     dim3 grid((unsigned)((N + 255) / 256), (unsigned)((M + (half ? 127 : 255)) / (half ? 128 : 256)), (unsigned)p.ksplit);
     if (grid.y > 65535) return DFP4_ERR_SHAPE;
-    choose_rect(p, grid, half ? 128 : 256);
+    if (p.ksplit == 1) choose_rect(p, grid, half ? 128 : 256);
     const bool bf16 = out_dtype == DFP4_BF16 && p.ksplit == 1;     // partial tiles are fp32
 #define DFP4_NATIVE_LAUNCH(F, B)                                                                         \
     do {                                                                                                 \

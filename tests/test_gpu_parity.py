@@ -1745,6 +1745,31 @@ def test_gemm_native_loop_and_results(M, N, K, first, more, mx):
         assert bool((rows == torch.full((), 12345.0, dtype=dtype, device="cuda")).all())
 
 
+# K is split where that pays: 128 x 4096 x 4096 took as long in four ranges as whole.
+@pytest.mark.parametrize("M,N,K", [(128, 4096, 4096), (256, 1024, 4096), (512, 4096, 14336)])
+def test_gemm_native_split_k_pays(M, N, K):
+    lib = dfp4.load()
+    a, b = (dfp4.native_pack(dfp4.quantize(torch.randn(r, K, device="cuda").to(torch.bfloat16))) for r in (M, N))
+    need = int(lib.dfp4_gemm_native_splitk_bytes(M, N, K))
+    assert need > 0
+    room = torch.empty(need, dtype=torch.uint8, device="cuda")
+    out = torch.empty(M, N, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    times = {"split": [], "whole": []}
+    for rep in range(12):
+        for k, (ptr, size) in {"split": (room.data_ptr(), need), "whole": (None, 0)}.items():
+            first, last = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            first.record()
+            for _ in range(20):
+                assert lib.dfp4_gemm_native_packed(a.buf.data_ptr(), M, b.buf.data_ptr(), N, K, out.data_ptr(), 0, N, ptr, size, stream) == 0
+            last.record()
+            last.synchronize()
+            times[k].append(first.elapsed_time(last) * 50)
+    us = {k: float(np.median(v[2:])) for k, v in times.items()}
+    print(f"gemm native {M}x{N}x{K} fp32, us: {us}", flush=True)
+    assert us["split"] < 0.88 * us["whole"], us
+
+
 # Results into rows of any alignment go out 16 bytes a lane: they took 1.3 times as long as aligned ones where a lane stored one or two elements.
 def test_gemm_native_results_of_any_alignment_take_as_long():
     M, N, K = 4992, 4864, 32
