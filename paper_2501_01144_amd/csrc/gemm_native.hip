@@ -893,25 +893,33 @@ __global__ __launch_bounds__(256) void native_reduce_kernel(const float* __restr
 
 inline int64_t up256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // Workgroups per output tile.  With at most a quarter as many tiles as compute units K can be split in 2 or 4 ranges of at least 8 steps; it is
-// where the steps saved (0.15 us each in the 128-row form; FP6 0.17, FP4 0.13) cost more than the partial tiles and the kernel that adds them:
-// 3 us and 0.45 us per megabyte of partials.  Microseconds, split / whole (FP6):
-//   256 x 1024 x 4096  11.4 / 14.7      512 x 4096 x 4096   22.4 / 15.4      1024 x 4096 x  8192  35.3 / 29.7
-//   256 x 4096 x 4096  16.0 / 15.0      512 x 4096 x 14336  32.2 / 44.9      1024 x 4096 x 14336  46.3 / 46.7
-inline int native_ksplit(int64_t M, int64_t N, int64_t KB) {
-    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), S = (KB + 1) / 2, cu = device_cu_count();
+// where the steps saved cost more than the partial tiles and the kernel that adds them, which depends on the format (FP6 has the longer
+// steps) and on the type of the results (a whole product's fp32 results take longer to leave).  Where N is a multiple of 2048, eight columns of
+// tiles, that kernel's workgroups run on the XCD whose cache holds their partial tiles, until these are too large for the caches.  The constants
+// (us a step, us, us per MB) choose best over 950 drawn sizes, both formats and types, each measured whole and in every number of ranges: 0.23 %
+// slower than the best choice in the mean; with one 0.15 us a step for both, 3 us and 0.45 us per MB 0.51 %.  Whole / 2 / 4 ranges (fp32):
+//   FP6  256 x 1024 x 4096  15.8 / 13.0 / 11.6     1024 x 1216 x 6176  25.4 / 22.2 / 23.5   65 x 4096 x 2560  11.9 / 11.1 / 10.0
+//        512 x 4096 x 4096  17.4 / 20.4 / 22.8     512 x 4096 x 14336  46.7 / 36.1 / 33.9
+//   FP4  256 x 1024 x 4096  13.3 / 11.5 / 10.5     5920 x 117 x 4736   15.4 / 16.5 / 17.3     195 x 15369 x 13568  38.6 / 46.6
+//        512 x 4096 x 4096  14.6 / 17.8 / 22.0     512 x 4096 x 14336  37.6 / 31.5 / 30.2
+inline int native_ksplit(int64_t M, int64_t N, int64_t KB, bool fp6, bool bf16, int64_t cu) {
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), S = (KB + 1) / 2;
+    const float steps = (fp6 ? 0.18f : 0.14f) * (float)S;
     int best = 1;
-    float least = 0.15f * (float)S;
+    float least = steps + (bf16 ? 0.0f : 0.5f);
     for (int s = 2; s <= 4 && tiles * s * 2 <= cu && S / s >= 8; s *= 2) {
-        const float us = 0.15f * (float)S / (float)s + 3.0f + 0.45f * (float)s * (float)M * (float)N * 4e-6f;
+        const float mb = 4e-6f * (float)s * (float)M * (float)N, per_mb = N % 2048 == 0 ? fminf(0.44f, 0.15f + 0.016f * mb) : 0.5f;
+        const float us = steps / (float)s + 3.5f + per_mb * mb;
         if (us < least) least = us, best = s;
     }
     return best;
 }
+inline int64_t native_part_bytes(int64_t M, int64_t N, int ksplit) { return ksplit > 1 ? up256((int64_t)ksplit * M * N * 4) : 0; }
 // Workgroups go to the 8 XCDs in turn, and each XCD has a cache of its own.  Where all tiles run at once the tiles of an XCD form a rectangle
 // rather than every eighth column: of those that divide the grid in eight, the one that reads the fewest rows.  2048 x 4096 x 14336
 // (FP6, 128-row tiles) reads 200 MB from beyond the XCDs' caches instead of 246: 60.7 -> 60.4 us with operands in the last cache, 77.5 -> 75.4 with
 // weights from memory; 2048 x 4096 x 4096 27.3 -> 26.9 (FP4 21.4 -> 19.6), 4096 x 4096 x 4096 34.9 -> 33.6 and 37.4 -> 36.5.
-// Not for native products with K split, whose partial tiles cost more so (rectangles / columns: 128 x 4096 x 4096 FP6 in 4 ranges 14.8 / 11.8,
+// Not for native products with K split, whose partial tiles cost more where their column does not name their XCD (native_ksplit; rectangles / columns: 128 x 4096 x 4096 FP6 in 4 ranges 14.8 / 11.8,
 // 256 x 4096 x 4096 FP4 in 4 19.4 / 13.4, 512 x 4096 x 14336 the same); exact ones, which keep a tile's sums together, gain (2048 x 2048 x 8192
 // 33.3 / 34.2, 1024 x 2048 x 14336 40.4 / 41.4) or do not care.
 inline void choose_rect(NativeParams& p, dim3 grid, int tile_rows) {
@@ -951,10 +959,16 @@ size_t native_scale_offset(int64_t rows, int64_t K, bool fp6) {
     return (size_t)operand_layout(rows, K / kBlock, fp6).sc;
 }
 
+// enough for either format and type of the results
 size_t native_splitk_bytes(int64_t M, int64_t N, int64_t K) {
     if (M == 0 || N == 0) return 0;
-    const int s = native_ksplit(M, N, K / kBlock);
-    return s > 1 ? (size_t)up256((int64_t)s * M * N * 4) : 0;
+    const int64_t cu = device_cu_count();
+    int most = 1;
+    for (int form = 0; form < 4; ++form) {
+        const int s = native_ksplit(M, N, K / kBlock, (form & 1) != 0, (form & 2) != 0, cu);
+        if (s > most) most = s;
+    }
+    return (size_t)native_part_bytes(M, N, most);
 }
 
 size_t gemm_native_workspace_bytes(int64_t M, int64_t N, int64_t K, bool fp6) {
@@ -1009,13 +1023,14 @@ int launch_gemm_native_packed(bool fp6, const void* a_packed, const void* w_pack
         });
         return check_launch();
     }
-    p.ksplit = native_ksplit(M, N, KB);
-    if (p.ksplit > 1 && (!splitk || splitk_bytes < native_splitk_bytes(M, N, K))) p.ksplit = 1;
+    const int64_t cu = device_cu_count();
+    p.ksplit = native_ksplit(M, N, KB, fp6, out_dtype == DFP4_BF16, cu);
+    if (p.ksplit > 1 && (!splitk || (int64_t)splitk_bytes < native_part_bytes(M, N, p.ksplit))) p.ksplit = 1;
     p.part = static_cast<float*>(splitk);
     // 256-row workgroups unless they would leave half of the compute units idle, or there are no more than 128 rows (128 x 4096 x 2048
     // 13.2 us with 256-row workgroups, 9.8 so)
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
-    const bool half = tiles256 * p.ksplit * 2 <= device_cu_count() || M <= 128;
+    const bool half = tiles256 * p.ksplit * 2 <= cu || M <= 128;
     dim3 grid((unsigned)((N + 255) / 256), (unsigned)((M + (half ? 127 : 255)) / (half ? 128 : 256)), (unsigned)p.ksplit);
     if (grid.y > 65535) return DFP4_ERR_SHAPE;
     if (p.ksplit == 1) choose_rect(p, grid, half ? 128 : 256);

@@ -260,3 +260,22 @@ def test_native_loop_first_loads_no_more_than_there_is(fp6, ta, iters):
     # the first iteration's loads, of two steps, have landed at the barrier; where the fill was cut short all have, since the loop counts
     # on f.slots iterations of them
     assert pending == (0 if iters < f.slots else (f.slots - 1) * 2 * f.per_step)
+
+
+@pytest.mark.parametrize("M,N,K,ranges", [
+    # microseconds (FP6, fp32) whole / in 2 ranges of K / in 4
+    (231, 5376, 6048, 2),         # 24.1, 21.2
+    (1024, 1216, 6176, 2),        # 25.4, 22.2, 23.5
+    (361, 2048, 3936, 4),         # 15.7, 14.3, 13.1
+    (65, 4096, 2560, 4),          # 11.9, 11.1, 10.0
+    (512, 4096, 14336, 4),        # 46.7, 36.1, 33.9
+    (256, 1024, 4096, 4),         # 15.8, 13.0, 11.6
+    (512, 4096, 4096, 1),         # 17.4, 20.4, 22.8
+    (461, 4940, 2368, 1),         # 13.4, 19.1
+    (3136, 767, 1280, 1),         # 10.9, 20.9
+    (2048, 14336, 4096, 1), (64, 64, 480, 1)])
+def test_native_k_is_split_where_it_pays(lib, M, N, K, ranges):
+    # the room asked for is enough for either format and type of the results; these sizes are FP6's to choose
+    lib.dfp4_gemm_native_splitk_bytes.restype = ctypes.c_size_t
+    need = lib.dfp4_gemm_native_splitk_bytes(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K))
+    assert need == (-(-ranges * M * N * 4 // 256) * 256 if ranges > 1 else 0)
