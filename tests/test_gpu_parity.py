@@ -1720,13 +1720,36 @@ def test_gemm_exact_sums_with_a_large_product(M, N, K, mx):
     assert torch.equal(out, (units * 2.0 ** (118 + 121 - 256)).float())
 
 
-# Fewer iterations than the loop of gemm_native_kernel keeps on their way, odd numbers of steps, both tile heights, K split, tiles of an XCD in
-# rectangles (2048 x 1024), and results at every alignment of their rows (`first` columns into rows of N + `more`): nothing beside them is written.
-@pytest.mark.parametrize("M,N,K", [(65, 257, 32), (128, 300, 64), (129, 256, 96), (200, 513, 160), (257, 264, 192), (300, 1024, 224), (256, 256, 256),
-                                   (400, 700, 288), (1030, 520, 416), (2048, 1024, 544), (100, 1000, 8224), (4096, 2048, 96)])
+def _rows_of_any_alignment(M, N, first, more, dtype):
+    """[M, N] inside a larger buffer, `first` columns into rows of N + more, and what is true of the buffer when nothing beside it was written"""
+    buf = torch.full((M + 512, N + more), 12345.0, dtype=dtype, device="cuda")
+    out = buf[256:256 + M, first:first + N]
+
+    def untouched():
+        out.fill_(12345.0)
+        return bool((buf == torch.full((), 12345.0, dtype=dtype, device="cuda")).all())
+    return out, untouched
+
+
+def _native_rows(M, N, ranges):
+    """rows of a workgroup's tile in gemm_native_kernel"""
+    tiles = -(-M // 256) * -(-N // 256)
+    return 128 if tiles * ranges * 2 <= torch.cuda.get_device_properties(0).multi_processor_count or M <= 128 else 256
+
+
+# Fewer iterations than the loop of gemm_native_kernel keeps on their way, odd numbers of steps, both tile heights, K in two and four ranges,
+# tiles of an XCD in rectangles (2048 x 1024, 4000 x 4096), edges, and results at every alignment of their rows: nothing beside them is written.
+@pytest.mark.parametrize("M,N,K,rows,ranges", [
+    (65, 257, 32, 128, 1), (128, 300, 64, 128, 1), (129, 256, 96, 128, 1), (200, 513, 160, 128, 1), (257, 264, 192, 128, 1), (300, 1024, 224, 128, 1),
+    (256, 256, 256, 128, 1), (400, 700, 288, 128, 1), (1030, 520, 416, 128, 1), (2048, 1024, 544, 128, 1), (4096, 2048, 96, 128, 1),
+    (100, 1000, 8224, 128, 4), (300, 5000, 12064, 128, 2),
+    (1552, 5664, 32, 256, 1), (4000, 4096, 96, 256, 1), (1552, 5664, 160, 256, 1), (2338, 4001, 224, 256, 1), (2304, 3849, 416, 256, 1),
+    (4100, 2055, 544, 256, 1)])
 @pytest.mark.parametrize("first,more", [(0, 0), (8, 8), (2, 4), (1, 3)])
 @pytest.mark.parametrize("mx", [False, True])
-def test_gemm_native_loop_and_results(M, N, K, first, more, mx):
+def test_gemm_native_loop_and_results(M, N, K, rows, ranges, first, more, mx):
+    need = int(dfp4.load().dfp4_gemm_native_splitk_bytes(M, N, K))
+    assert need == (-(-ranges * M * N * 4 // 256) * 256 if ranges > 1 else 0) and _native_rows(M, N, ranges) == rows
     print(f"gemm native: {M}x{N}x{K}, {first} columns into rows of {N + more}, mx {mx}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(K + M)
     x, w = (torch.randn(r, K, generator=g, device="cuda").to(torch.bfloat16) for r in (M, N))
@@ -1736,13 +1759,40 @@ def test_gemm_native_loop_and_results(M, N, K, first, more, mx):
     da, dw = back(qa).double(), back(qw).double()
     ref, absdot = da @ dw.T, da.abs() @ dw.abs().T
     for dtype in (torch.float32, torch.bfloat16):
-        rows = torch.full((M, N + more), 12345.0, dtype=dtype, device="cuda")
-        out = dfp4.gemm_native_packed(a, b, out=rows[:, first:first + N])
+        out, untouched = _rows_of_any_alignment(M, N, first, more, dtype)
+        dfp4.gemm_native_packed(a, b, out=out)
         torch.cuda.synchronize()
         err = (out.double() - ref).abs()
         assert bool((err <= GEMM_RTOL * absdot + (ref.abs() * 2.0 ** -8 if dtype == torch.bfloat16 else 0)).all())
-        rows[:, first:first + N] = 12345.0
-        assert bool((rows == torch.full((), 12345.0, dtype=dtype, device="cuda")).all())
+        assert untouched()
+
+
+# The same epilogue after exact sums: both tile heights, whole and with K split, there with the tiles of an XCD in rectangles.
+@pytest.mark.parametrize("M,N,K,rows,split", [(1552, 5664, 160, 256, False), (2338, 4001, 544, 256, False), (3968, 4096, 96, 256, False),
+                                              (1000, 2000, 14336, 128, True), (2000, 2041, 8192, 128, True), (2048, 4096, 8224, 128, False)])
+@pytest.mark.parametrize("first,more", [(0, 0), (2, 4), (1, 3)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_gemm_exact_results_of_any_alignment(M, N, K, rows, split, first, more, mx):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    across, down = -(-N // 256), -(-M // rows)
+    assert dfp4.gemm_path(M, N, K, prepared=True) == 0 and _native_rows(M, N, 1) == rows
+    assert (int(dfp4.load().dfp4_gemm_prepared_workspace_bytes(M, N, K)) > 0) == split
+    if split:                                                # a power of two of columns, eight rectangles, all workgroups at once
+        assert across & (across - 1) == 0 and down % 8 == 0 and across * down * 2 <= cus
+    print(f"gemm, exact: {M}x{N}x{K}, {first} columns into rows of {N + more}, mx {mx}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    quant, back = (dfp4.mxfp4_quantize, dfp4.mxfp4_dequantize) if mx else (dfp4.quantize, dfp4.dequantize)
+    qa, qw = (quant(torch.randn(r, K, generator=g, device="cuda").to(torch.bfloat16)) for r in (M, N))
+    a, b = dfp4.gemm_prepare(qa, weight=False, mx=mx), dfp4.gemm_prepare(qw, weight=True, mx=mx)
+    ref = back(qa).double() @ back(qw).double().T            # exact: whole numbers of units below 2^24, as fp32 holds them
+    assert dfp4.gemm_declined_tiles(a) == 0
+    for dtype in (torch.float32, torch.bfloat16):
+        out, untouched = _rows_of_any_alignment(M, N, first, more, dtype)
+        dfp4.gemm_prepared(a, b, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref.float().to(dtype)) and torch.equal(ref.float().double(), ref)
+        assert untouched()
+    assert dfp4.gemm_declined_tiles(a) == 0
 
 
 # K is split where that pays: 128 x 4096 x 4096 took as long in four ranges as whole.
