@@ -44,12 +44,14 @@ __device__ __forceinline__ Fp6Lane pack6_lane(uint4 c, uint32_t tlo, uint32_t th
 }
 
 // Packed FP6 operand: per (pair of 32-row tiles, step) 3072 bytes = 64 lanes x 16 bytes (registers 0..3) of the even
-// tile, the same of the odd tile, then 64 x 8 bytes (registers 4, 5) of the even and of the odd tile; lane = 32 * (block % 2) + row % 32.
-// The 8-byte parts lie in the order [half of the tile's rows][block % 2][row % 16] (fp6_hi_lane): the multiply loop reads both blocks of 16
-// rows at once, which would meet on the same LDS banks otherwise.  Every KiB is one direct load of a wave into LDS, and both parts are
-// read back at their own width (see gen_native_loop.py).
+// tile, the same of the odd tile, then 64 x 8 bytes (registers 4, 5) of the even and of the odd tile;
+// lane = 32 * (block % 2) + row % 32.  The 8-byte parts lie in the order [half of the tile's rows][block % 2][row % 16]
+// (fp6_hi_lane): the multiply loop reads both blocks of 16 rows at once, which would meet on the same LDS banks otherwise
+// (the scales' dwords do, see gen_native_loop.py).  Every KiB is one direct load of a wave into LDS, and both parts are
+// read back at their own width.
 constexpr int kFp6PairBytes = 3072;
-constexpr int kSlackSteps = 8;         // behind the bits and behind the scales: the multiply loop takes two steps at a time and reads one behind an odd number
+// behind the bits and behind the scales: the multiply loop takes two steps at a time and reads one behind an odd number
+constexpr int kSlackSteps = 8;
 __host__ __device__ inline size_t fp6_lo(size_t tile, size_t step, size_t S) {
     return ((tile >> 1) * S + step) * kFp6PairBytes + (tile & 1) * 1024;
 }

@@ -65,17 +65,19 @@ inline int choose_ksplit(int64_t tiles, int64_t KB, int64_t cu) {
 // takes everything the large one is not for (few rows, K beyond 16384), and the products it is estimated to finish sooner:
 // those with few output tiles, and batches whose packed A would be read only once or twice (P V of attention).  K of one
 // iteration of the direct kernel (Q K^T) goes there unless it is prepared already.  fast_cost is of the int8 kernel that
-// the large one replaced and choose_direct's estimates of int8 operands, so the line lies where it lay between those two.  The large kernel
-// gained more than the direct one, which leaves products on the direct side that it would finish sooner, up to 1.4 times (microseconds,
-// large with its prepass, in the loop before the present one, / direct):
-//   2048 x 4096 x 4096  46 / 62     512 x 4096 x 14336  74 / 105     1188 x 2211 x 9472  69 / 82     3000 x 5000 x 992  39 / 47
-//    777 x 3001 x 2080  38 / 24     512 x 4096 x  4096  49 /  32     1024 x 1024 x 4096  59 / 18     P V, 128 x 2048 x 128 x 2048  324 / 153
-// and of the sizes measured none on the large side the other way (4096 x 4096 x 4096 60 / 123, 2048 x 2048 x 14336 85 / 133).
+// the large one replaced and choose_direct's estimates of int8 operands, so the line lies where it lay between those two.  The
+// large kernel gained more than the direct one, which leaves products on the direct side that it would finish sooner, up to
+// 1.7 times (microseconds, large with its prepass / direct):
+//   2048 x 4096 x 4096  40 / 59     512 x 4096 x 14336  70 / 101     1188 x 2211 x 9472  63 / 81     3000 x 5000 x 992  32 / 44
+//    777 x 3001 x 2080  33 / 24     512 x 4096 x  4096  45 /  29     1024 x 1024 x 4096  56 / 18     P V, 128 x 2048 x 128 x 2048  308 / 153
+//   prepared: 1024 x 4096 x 4096  25 / 43     400 x 2759 x 6592  34 / 44     512 x 4096 x 4096  30 / 29     300 x 4096 x 4096  28 / 27
+// and of the sizes measured none on the large side the other way (4096 x 4096 x 4096 55 / 114, 2048 x 2048 x 14336 72 / 124).
 // An A operand of fewer rows than kPreparedMinRows is not packed ahead: its products read it as it is.
 constexpr int kPreparedMinRows = 257;
 inline bool large_kernel_can(int64_t M, int64_t KB) { return M > 64 && KB > 0 && KB <= kMaxKB; }
-// Estimated microseconds of that int8 kernel (512 x 128 outputs per workgroup), fitted like those of the direct shapes: per round of workgroups a fixed
-// part, and per block of a workgroup's share of K more where the chip is full, growing beyond 128 blocks; the results; the exchange of partial tiles between s workgroups; the prepass unless the operands are prepared
+// Estimated microseconds of that int8 kernel (512 x 128 outputs per workgroup), fitted like those of the direct shapes: per
+// round of workgroups a fixed part, and per block of a workgroup's share of K more where the chip is full, growing beyond 128
+// blocks; the results; the exchange of partial tiles between s workgroups; the prepass unless the operands are prepared
 inline float fast_cost(int64_t M, int64_t N, int64_t KB, int64_t batch, bool prepared, int64_t cu) {
     const int64_t tiles = ((M + kTileM - 1) / kTileM) * ((N + kTileN - 1) / kTileN) * batch;
     const int s = choose_ksplit(tiles, KB, cu);

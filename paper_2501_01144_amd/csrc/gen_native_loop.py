@@ -26,25 +26,31 @@ odd the second half of the last iteration is what lies behind (the next tile, or
 upper 32 lanes) are cleared: FP4 and FP6 have no infinities, so it multiplies to zero.
 
 Why this instruction: the kernel is bound by power, and it takes a tenth less of it than 32 x 32 x 64 for the same products.
-Loops of either on registers with operands as they come sustain 6.3 (FP6) and 6.9 PFLOP/s (FP4) with 32 x 32 x 64 at 1.56 and 1.71 GHz,
-7.0 and 7.7 with 16 x 16 x 128 at 1.76 and 1.94; neighbouring instructions share an operand (rows of tiles forth and back), half a per cent.
-What it asks for: an instruction takes 16 clocks, and a wave, which is alone on its SIMD, gets one other short instruction into its shadow.  With two
-or three behind some and none behind others, addresses rotated between iterations and a branch taken in each, a step of K = 64 took 885
-clocks (FP6); with everything unrolled and spread evenly it takes 600 (512 without any other work), at 1.48 GHz, against 660 at 1.43 with the larger instruction.
-4096 x 4096, K = 8192, loop alone: FP6 58 -> 52 us, FP4 51.6 -> 46.6.
+Loops of either on registers with operands as they come sustain 6.3 (FP6) and 6.9 PFLOP/s (FP4) with 32 x 32 x 64 at 1.56 and
+1.71 GHz, 7.0 and 7.7 with 16 x 16 x 128 at 1.76 and 1.94; neighbouring instructions share an operand (rows of tiles forth and
+back), half a per cent.  What it asks for: an instruction takes 16 clocks, and a wave, which is alone on its SIMD, gets one
+other short instruction into its shadow.  With two or three behind some and none behind others, addresses rotated between
+iterations and a branch taken in each, a step of K = 64 took 885 clocks (FP6); with everything unrolled and spread evenly it
+takes 600 (512 without any other work), at 1.48 GHz, against 660 at 1.43 with the larger instruction.  4096 x 4096, K = 8192,
+loop alone: FP6 58 -> 52 us, FP4 51.6 -> 46.6.  On operands that are all zero the same loop runs at the full clock, 2.4 GHz.
 
-LDS stage: the chunks of A tiles 0..7 and B tiles 0..7 as in memory (1 KiB per tile for FP4, 3 KiB per pair
-for FP6) + 4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).  Per step FP6 moves 25 KB into LDS and 50 KB out of it, 600
-clocks at 128 byte/clock.  Registers 4, 5 are kept at 8 bytes per lane: at the 16-byte stride that 12-byte direct loads leave,
-their reads cost as much as 16-byte ones.
+LDS stage: the chunks of A tiles 0..7 and B tiles 0..7 as in memory (1 KiB per tile for FP4, 3 KiB per pair for FP6) +
+4 x 256 bytes of scales (A groups 0, 1, B groups 0, 1).  Per step FP6 moves 25 KB into LDS and 50 KB out of it, 600 clocks at
+128 byte/clock: as long as a step takes, so that a clock spared elsewhere in the loop gains nothing.  Registers 4, 5 are kept at
+8 bytes per lane: at the 16-byte stride that 12-byte direct loads leave, their reads cost as much as 16-byte ones.  The reads of
+scales conflict, two clocks each, four an iteration and wave: the blocks of lanes q and q + 2 lie a stage apart, a multiple
+of 256 bytes (that and 16 clocks a group of fp32 results are all conflicts that the counters see).
 
-With operands that the last cache does not hold a step takes as long as its bytes at 60 byte/ns and compute unit, however early they are
-asked for (FP6: 128-row form 1.28 times as long, 256 rows 1.07; FP4 1.13 and 1.01): what a compute unit can have in flight.
+With operands that the last cache does not hold a step takes as long as its bytes at 60 byte/ns and compute unit, however
+early they are asked for (FP6: 128-row form 1.28 times as long, 256 rows 1.07; FP4 1.13 and 1.01): what a compute unit can
+have in flight.
 
 Registers (fixed): a[0:255] accumulators; v[40:135] / v[136:231] operand sets (A tile i at +6 i, B tile j at +48 + 6 j);
-v[232:239] scale dwords, of either set A's even and odd tiles, B's; v240 / v241 global offsets (operands, scales); v242.. LDS read addresses; s[60:69] global bases of the wave's five chunks, s70 iteration, s71 iteration before which something is to
-be done, s72 / s73 bytes to the next step's operands and scales, s74 / s75 scratch, s76 shift of A's scales (128-row form), s77..s84 the
-wave's LDS addresses inside slot 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the 128-row form).
+v[232:239] scale dwords, of either set A's even and odd tiles, B's; v240 / v241 global offsets (operands, scales); v242.. LDS
+read addresses; s[60:69] global bases of the wave's five chunks, s70 iteration, s71 iteration before which something is to be
+done, s72 / s73 bytes to the next step's operands and scales, s74 / s75 scratch, s76 shift of A's scales (128-row form),
+s77..s84 the wave's LDS addresses inside slot 0 (reads: A, B, scales A, B; loads: A, B, scales, the FP6 pair of A in the
+128-row form).
 """
 import os
 

@@ -189,21 +189,21 @@ def test_gemm_prepared_refuses_a_weight_beyond_its_limit(lib):
 @pytest.mark.parametrize("M,N,K,batch,prepared,large", [
     # microseconds of the large kernel (with its prepass unless prepared) and of the best shape of gemm_f8_kernel; the line is that of the int8
     # kernels before them, and the large kernel is the faster one of three that it does not get
-    (2048, 4096, 14336, 1, 0, True),       # 111, 308
-    (1536, 4096, 14336, 1, 0, True),       # 90, 174
-    (2048, 2048, 14336, 1, 0, True),       # 85, 133
-    (2048, 4096, 11008, 1, 0, True),       # 88, 149
-    (1024, 14336, 4096, 1, 0, True),       # 67, 115
-    (3067, 1281, 14464, 1, 0, True),       # 87, 198
-    (4096, 4096, 4096, 1, 0, True),        # 60, 123
-    (512, 14336, 4096, 1, 1, True),        # 25, 58
-    (2048, 4096, 4096, 1, 0, False),       # 46, 62
-    (777, 3001, 2080, 1, 0, False),        # 38, 24
-    (512, 4096, 14336, 1, 0, False),       # 74, 105
-    (1024, 1024, 4096, 1, 0, False),       # 59, 18
-    (2048, 128, 2048, 128, 0, False),      # 324, 153
-    (2048, 2048, 128, 128, 0, False),      # 665, 361
-    (400, 2759, 6592, 1, 1, False),        # 38, 45
+    (2048, 4096, 14336, 1, 0, True),       # 101, 190
+    (1536, 4096, 14336, 1, 0, True),       # 84, 174
+    (2048, 2048, 14336, 1, 0, True),       # 72, 124
+    (2048, 4096, 11008, 1, 0, True),       # 81, 146
+    (1024, 14336, 4096, 1, 0, True),       # 61, 109
+    (3067, 1281, 14464, 1, 0, True),       # 83, 198
+    (4096, 4096, 4096, 1, 0, True),        # 55, 114
+    (512, 14336, 4096, 1, 1, True),        # 23, 57
+    (2048, 4096, 4096, 1, 0, False),       # 40, 59
+    (777, 3001, 2080, 1, 0, False),        # 33, 24
+    (512, 4096, 14336, 1, 0, False),       # 70, 101
+    (1024, 1024, 4096, 1, 0, False),       # 56, 18
+    (2048, 128, 2048, 128, 0, False),      # 308, 153
+    (2048, 2048, 128, 128, 0, False),      # 567, 360
+    (400, 2759, 6592, 1, 1, False),        # 34, 44
     (64, 28672, 16384, 1, 0, False), (1, 32, 32, 1, 0, False), (700, 700, 16416, 1, 1, False)])     # the only kernel
 def test_gemm_path_of_sizes(lib, M, N, K, batch, prepared, large):
     path = lib.dfp4_gemm_path(M, N, K, batch, prepared)
