@@ -712,9 +712,10 @@ __global__ __launch_bounds__(256, 1) void gemm_native_kernel(std::conditional_t<
         }
         in_order();
     };
-    // A lane reads and stores 16 bytes of each of kRows rows, every row by kLanes lanes.  Rows may begin anywhere, memory takes 16 bytes at any
-    // address (one element a lane where rows were no multiple of 16 bytes: 4992 x 4878 x 32 bf16 23.2 us, 6720 x 256 x 192 into rows of 257
-    // 8.0).  A group is stored while the next is on its way through LDS.
+    // A lane reads and stores 16 bytes of each of kRows rows, every row by kLanes lanes.  Rows may begin anywhere, memory takes 16
+    // bytes at any address (with one element a lane where rows were no multiple of 16 bytes 4992 x 4864 x 32 in bf16 into rows
+    // of 4867 took 23.1 us, so 16.6).  A group is stored while the next is on its way through LDS (two and four groups at once: 1 and
+    // 3 % slower in fp32).
     constexpr int kElems = 16 / kEsz, kLanes = 64 / kElems, kBy = 64 / kLanes, kRows = 16 / kBy;
     auto store_all = [&](auto full_c, auto cut_c) {
         constexpr bool kFull = decltype(full_c)::value;      // no edge
@@ -902,7 +903,8 @@ inline int64_t up256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // leave).  Where N is a multiple of 2048, eight columns of tiles, that kernel's workgroups run on the XCD whose cache holds
 // their partial tiles, until these are too large for the caches.  The constants (us a step, us, us per MB) choose best over
 // 950 drawn sizes, both formats and types, each measured whole and in every number of ranges: 0.23 % slower than the best
-// choice in the mean; with one 0.15 us a step for both, 3 us and 0.45 us per MB 0.51 %.  Whole / 2 / 4 ranges (fp32):
+// choice in the mean, one in fifty by more than 5 % (up to 17); with one 0.15 us a step for both, 3 us and 0.45 us per MB
+// 0.51 %, one in 23.  Whole / 2 / 4 ranges (fp32):
 //   FP6  256 x 1024 x 4096  15.8 / 13.0 / 11.6     1024 x 1216 x 6176  25.4 / 22.2 / 23.5   65 x 4096 x 2560  11.9 / 11.1 / 10.0
 //        512 x 4096 x 4096  17.4 / 20.4 / 22.8     512 x 4096 x 14336  46.7 / 36.1 / 33.9
 //   FP4  256 x 1024 x 4096  13.3 / 11.5 / 10.5     5920 x 117 x 4736   15.4 / 16.5 / 17.3     195 x 15369 x 13568  38.6 / 46.6
